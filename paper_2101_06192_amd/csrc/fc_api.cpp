@@ -170,21 +170,23 @@ int prepare_graph(fc_ctx *ctx, const fc_graph *g, bool trusted, GraphView *out) 
         v.weights = g->nnz ? g->weights : nullptr;
     }
     if (!trusted) {
-        Small *sm = static_cast<Small *>(ctx->small.ptr);
-        unsigned int err = 0;
-        FC_HIP(ctx, hipMemsetAsync(&sm->graph_err, 0, sizeof(unsigned int), ctx->stream), "memset");
-        FC_HIP(ctx, fc::launch_validate_rows(v.row_ptr, v.n, v.nnz, &sm->graph_err, ctx->stream),
+        // both passes are enqueued together (the second does nothing once the
+        // first has found bad row offsets) and read back once
+        GraphCheck *gc = &static_cast<Small *>(ctx->small.ptr)->check;
+        GraphCheck found{};
+        FC_HIP(ctx, hipMemsetAsync(gc, 0, sizeof(GraphCheck), ctx->stream), "memset");
+        FC_HIP(ctx, fc::launch_validate_rows(v.row_ptr, v.n, v.nnz, &gc->err, ctx->stream),
                "validate_rows launch");
-        FC_HIP(ctx, hipMemcpyAsync(&err, &sm->graph_err, sizeof(err), hipMemcpyDeviceToHost,
-                                   ctx->stream), "copy error word");
-        FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "validate_rows");
-        if (err) return set_err(ctx, FC_ERR_GRAPH, "row_ptr is not monotone from 0 to nnz");
-        FC_HIP(ctx, fc::launch_validate_cols(v.row_ptr, v.col_idx, v.weights, v.n, v.nnz,
-                                             &sm->graph_err, ctx->stream),
+        FC_HIP(ctx, fc::launch_validate_cols(v.row_ptr, v.col_idx, v.weights, v.n, v.nnz, &gc->err,
+                                             &gc->sym_diff, ctx->stream),
                "validate_cols launch");
-        FC_HIP(ctx, hipMemcpyAsync(&err, &sm->graph_err, sizeof(err), hipMemcpyDeviceToHost,
-                                   ctx->stream), "copy error word");
-        FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "validate_cols");
+        FC_HIP(ctx, hipMemcpyAsync(&found, gc, sizeof(found), hipMemcpyDeviceToHost, ctx->stream),
+               "copy error word");
+        FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "graph checks");
+        unsigned int err = found.err;
+        if (err & fc::kErrGraphRowPtr)
+            return set_err(ctx, FC_ERR_GRAPH, "row_ptr is not monotone from 0 to nnz");
+        if (found.sym_diff) err |= fc::kErrGraphAsymmetric;
         if (err) {
             std::string m = "graph is not simple, sorted and symmetric:";
             if (err & fc::kErrGraphColumn) m += " column out of range;";
@@ -354,7 +356,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
                 FC_HIP(ctx, hipMemsetAsync(&sm->sum, 0, sizeof(unsigned long long), ctx->stream),
                        "memset cross count");
                 FC_HIP(ctx, fc::launch_count_cross(g.row_ptr, g.col_idx, static_cast<uint32_t>(g.n),
-                                                   B, &sm->sum, ctx->stream),
+                                                   g.nnz, B, &sm->sum, ctx->stream),
                        "count_cross");
                 unsigned long long cross = 0;
                 FC_HIP(ctx, hipMemcpyAsync(&cross, &sm->sum, sizeof(cross), hipMemcpyDeviceToHost,

@@ -14,10 +14,17 @@ struct DevBuf {
     size_t bytes = 0;
 };
 
+struct GraphCheck {  // what the CSR checks found
+    unsigned int err;
+    unsigned int pad;
+    unsigned long long sym_diff;  // downward minus upward entries: 0 in a symmetric graph
+};
+
 struct Small {  // device-side counters of one call
     fc::Totals totals;
     unsigned int queue;
-    unsigned int graph_err;
+    unsigned int pad0;
+    GraphCheck check;
     unsigned long long sum;
     unsigned int dmax;
     unsigned int pad;

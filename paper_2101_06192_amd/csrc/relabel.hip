@@ -51,26 +51,58 @@ __device__ __forceinline__ uint32_t class_rank(uint32_t c, bool widest_first) {
     return c == 4u || !widest_first ? c : 3u - c;
 }
 
-// One block of kClasses threads, thread k serial over the blocks of class k:
-// base[b][k] = first internal id of class k in block b; bounds[r] = end of the
-// class of rank r, r < 4 (bounds[3] = number of vertices that are not
-// isolated).
-__global__ void class_scan_kernel(const uint32_t *__restrict__ blk, uint32_t nb, int widest_first,
-                                  uint32_t *__restrict__ base, uint32_t *__restrict__ bounds) {
-    __shared__ uint32_t tot[kClasses];
-    const uint32_t k = threadIdx.x;
-    uint32_t s = 0;
-    for (uint32_t b = 0; b < nb; ++b) s += blk[b * kClasses + k];
-    tot[class_rank(k, widest_first)] = s;
-    __syncthreads();
-    const uint32_t r = class_rank(k, widest_first);
-    uint32_t start = 0;
-    for (uint32_t j = 0; j < r; ++j) start += tot[j];
-    if (r + 1 < kClasses) bounds[r] = start + tot[r];
-    for (uint32_t b = 0; b < nb; ++b) {
-        base[b * kClasses + k] = start;
-        start += blk[b * kClasses + k];
+// One block: base[b][k] = first internal id of class k in block b; bounds[r] =
+// end of the class of rank r, r < 4 (bounds[3] = number of vertices that are
+// not isolated).  Thread t owns a run of consecutive blocks: it sums its run,
+// the run sums are scanned over the waves, and it walks its run again.  (One
+// thread per class walking all blocks in turn took 35 us for 200 K vertices
+// and 680 us for 4 M, a chain of dependent loads; now 4.0 us and 12.5 us.)
+constexpr uint32_t kScanThreads = 1024;
+
+__global__ __launch_bounds__(kScanThreads) void class_scan_kernel(
+    const uint32_t *__restrict__ blk, uint32_t nb, int widest_first, uint32_t *__restrict__ base,
+    uint32_t *__restrict__ bounds) {
+    constexpr uint32_t kWaves = kScanThreads / 64u;
+    __shared__ uint32_t s_wave[kClasses][kWaves];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t run = (nb + kScanThreads - 1u) / kScanThreads;
+    const uint64_t b0 = static_cast<uint64_t>(threadIdx.x) * run;
+    const uint64_t b1 = b0 + run < nb ? b0 + run : nb;
+    uint32_t sum[kClasses] = {}, before[kClasses];
+    for (uint64_t b = b0; b < b1; ++b)
+        for (uint32_t k = 0; k < kClasses; ++k) sum[k] += blk[b * kClasses + k];
+    for (uint32_t k = 0; k < kClasses; ++k) {  // inclusive scan over the wave's runs
+        uint32_t x = sum[k];
+        for (uint32_t off = 1; off < 64u; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off, 64);
+            if (lane >= off) x += y;
+        }
+        if (lane == 63u) s_wave[k][wave] = x;
+        before[k] = x - sum[k];
     }
+    __syncthreads();
+    uint32_t total[kClasses];
+    for (uint32_t k = 0; k < kClasses; ++k) {
+        uint32_t t = 0;
+        for (uint32_t w = 0; w < kWaves; ++w) {
+            if (w == wave) before[k] += t;
+            t += s_wave[k][w];
+        }
+        total[k] = t;
+    }
+    for (uint32_t k = 0; k < kClasses; ++k) {  // classes of a lower rank come first
+        const uint32_t r = class_rank(k, widest_first);
+        uint32_t start = 0;
+        for (uint32_t j = 0; j < kClasses; ++j)
+            if (class_rank(j, widest_first) < r) start += total[j];
+        if (threadIdx.x == 0 && r + 1 < kClasses) bounds[r] = start + total[k];
+        before[k] += start;
+    }
+    for (uint64_t b = b0; b < b1; ++b)
+        for (uint32_t k = 0; k < kClasses; ++k) {
+            base[b * kClasses + k] = before[k];
+            before[k] += blk[b * kClasses + k];
+        }
 }
 
 // inv[v] = internal id of v, orig[internal] = v: rank inside the block from
@@ -129,7 +161,7 @@ hipError_t launch_class_bounds(const int32_t *row_ptr, uint32_t n, bool widest_f
     const uint32_t nb = relabel_blocks(n);
     if (nb == 0) return hipSuccess;
     class_count_kernel<<<nb, kPlaceThreads, 0, stream>>>(row_ptr, n, blk);
-    class_scan_kernel<<<1, kClasses, 0, stream>>>(blk, nb, widest_first ? 1 : 0, base, bounds);
+    class_scan_kernel<<<1, kScanThreads, 0, stream>>>(blk, nb, widest_first ? 1 : 0, base, bounds);
     return hipGetLastError();
 }
 
