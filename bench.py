@@ -499,7 +499,7 @@ def leg_solve(fc, inputs, dev, steps, warmup) -> dict:
         # n x k arrays per iteration: apply, update, direction) over the whole leg,
         # residuals and refinement included in the time: a lower bound on the rate
         es = 8 if prec == "fp64" else 4
-        alg = out["iters"] * (2 * g.m * k * es + 12 * g.n * k * es)
+        alg = out["iters"] * (2 * g.m * k * es + 10 * g.n * k * es)
         ach = alg / dt / 1e9
         legs[prec] = {"ms": 1000 * dt, "inner_iters": out["iters"],
                       "max_relres": float(out["relres"].max()),

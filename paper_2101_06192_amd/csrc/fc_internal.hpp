@@ -38,7 +38,8 @@ struct fc_ctx {
     hipStream_t stream = nullptr;
     std::string last_error;
     DevBuf state, vrec, row_ptr, col_idx, small, rtmp, thr, cword, ckk, clists, clevels, cbits;
-    DevBuf s_r64, s_r, s_z, s_p, s_q, s_d, s_pa, s_pb, s_small, s_wdeg;  // solver workspace
+    DevBuf s_r64, s_r, s_p, s_q, s_d, s_pa, s_pb, s_small, s_wdeg;  // solver workspace
+    DevBuf s_minv, s_segbase, s_seg, s_segsum;  // solver: preconditioner, long rows' segments
     DevBuf rl_blk, rl_base, rl_inv, rl_orig, rl_vrec, rl_adj;     // degree-class relabelling
     DevBuf iso;                                                   // isolated-vertex bitmap
     DevBuf corigt;                                                // hybrid: target ids per slot

@@ -302,30 +302,51 @@ hipError_t launch_estimate(const uint32_t *R, int32_t n, uint32_t tau, int liter
                            double *closeness, hipStream_t stream);
 
 // Block CG on (alpha L + I) X = B, row-major n x k, k <= 64.
+// Rows of more than kCgLongRow neighbours are summed in segments of kCgSegment
+// entries first.
+constexpr uint32_t kCgLongRow = 128, kCgSegment = 128;
+struct CgRows {
+    uint32_t *seg_base;  // n: first segment of a long row (unset elsewhere)
+    int2 *seg;           // {first entry, end} of every segment
+    uint32_t *count;     // segments in all
+};
 struct CgWork {
     const int32_t *row_ptr;
     const int32_t *col_idx;
     const double *weights;  // edge weights (weighted Laplacian), or null
     const double *wdeg;     // weighted degrees (with weights), or null
     uint32_t n, k;
+    uint32_t kp;            // columns of the inner vectors (cg_padded)
     double alpha;
     uint32_t max_blocks;
+    CgRows rows;
+    uint32_t segments;      // segments in all, once the host has read *rows.count
+    void *seg_sum;          // segments x kp sums (room for binary64)
     const double *B;        // n x k right-hand sides
     double *X;              // n x k solution (binary64)
     double *R64;            // n x k binary64 residual B - A X
-    void *r, *z, *p, *q, *d;  // n x k inner vectors in the inner precision
-    double *partial_a, *partial_b;  // max_blocks x 64 partial sums
-    double *scalars;        // 8 x 64: rz, rz_new, pq, rr, tol2, step, beta, active
+    void *r, *p, *q, *d;    // n x kp inner vectors in the inner precision
+    void *minv;             // n: Jacobi preconditioner in the inner precision
+    double *partial_a, *partial_b;  // 64 x max_blocks partial sums, column by column
+    double *scalars;        // rz, -, -, -, tol2, step, beta, active (64 each), iterations done
     double *scale;          // 64: residual norms the inner solve is scaled by
     double *res_rr, *res_bb;  // 64: |R_j|^2 and |B_j|^2
-    unsigned int *any;      // device flag: some column still active
+    unsigned int *nonzero;  // whether X held anything but zeros when cg_prepare ran
 };
+// Columns the inner vectors are padded to: whole loads of 16 bytes where k is
+// wide enough.
+uint32_t cg_padded(uint32_t k, bool fp32);
+// Long rows' segments (*rows.count zero before), the preconditioner, and
+// *nonzero (zero before) from X.
+hipError_t cg_prepare(const CgWork &w, bool fp32, hipStream_t stream);
 // Inner Jacobi-preconditioned CG on A d = R64 / scale (per column), then
-// X += scale * d.  Stops a column when |r_j|^2 <= tol2_j (scalars[256 + j]).
+// X += scale * d.  Stops a column when |r_j|^2 <= tol2_j (scalars[256 + j]);
+// *iters = iterations that had an active column.
 template <typename T>
 hipError_t cg_inner(const CgWork &w, uint32_t max_iters, uint32_t poll, uint32_t *iters,
                     hipStream_t stream);
-// R64 = B - A X and |R_j|^2 into res_rr (and |B_j|^2 into res_bb).
-hipError_t cg_residual(const CgWork &w, bool with_b, hipStream_t stream);
+// R64 = B - A X (B when gather is false: X known to be zero) and |R_j|^2 into
+// res_rr (and |B_j|^2 into res_bb).
+hipError_t cg_residual(const CgWork &w, bool with_b, bool gather, hipStream_t stream);
 
 }  // namespace fc

@@ -36,17 +36,25 @@ extern "C" int fc_solve(fc_ctx *ctx, const fc_graph *g, double alpha, const doub
     const size_t nk = static_cast<size_t>(n) * k;
     const size_t tb = fp32 ? 4 : 8;
     const uint32_t max_blocks = std::max<uint32_t>(64, ctx->cu_count * 8);
+    const uint32_t kp = fc::cg_padded(k, fp32);
+    const size_t nkp = static_cast<size_t>(n) * kp;
+    // no more segments than this: every long row adds at most one that is not full
+    const size_t seg_bound = static_cast<size_t>(gv.nnz) / fc::kCgSegment +
+                             static_cast<size_t>(gv.nnz) / fc::kCgLongRow + 1;
     // workspace is cached in the context (grow-only), like the sampler scratch
     struct {
-        DevBuf &r64, &r, &z, &p, &q, &d, &pa, &pb, &small;
-    } sb{ctx->s_r64, ctx->s_r, ctx->s_z, ctx->s_p, ctx->s_q, ctx->s_d, ctx->s_pa, ctx->s_pb, ctx->s_small};
+        DevBuf &r64, &r, &p, &q, &d, &pa, &pb, &small;
+    } sb{ctx->s_r64, ctx->s_r, ctx->s_p, ctx->s_q, ctx->s_d, ctx->s_pa, ctx->s_pb, ctx->s_small};
     auto fail = [&](int code) { return code; };
-    if ((rc = ensure(ctx, sb.r64, 8 * nk, "residual")) || (rc = ensure(ctx, sb.r, tb * nk, "r")) ||
-        (rc = ensure(ctx, sb.z, tb * nk, "z")) || (rc = ensure(ctx, sb.p, tb * nk, "p")) ||
-        (rc = ensure(ctx, sb.q, tb * nk, "q")) || (rc = ensure(ctx, sb.d, tb * nk, "d")) ||
+    if ((rc = ensure(ctx, sb.r64, 8 * nk, "residual")) || (rc = ensure(ctx, sb.r, tb * nkp, "r")) ||
+        (rc = ensure(ctx, sb.p, tb * nkp, "p")) || (rc = ensure(ctx, sb.q, tb * nkp, "q")) ||
+        (rc = ensure(ctx, sb.d, tb * nkp, "d")) ||
+        (rc = ensure(ctx, ctx->s_minv, tb * static_cast<size_t>(n), "preconditioner")) ||
+        (rc = ensure(ctx, ctx->s_segbase, 4 * static_cast<size_t>(n), "long rows")) ||
+        (rc = ensure(ctx, ctx->s_seg, 8 * seg_bound, "row segments")) ||
         (rc = ensure(ctx, sb.pa, 8 * 64 * static_cast<size_t>(max_blocks), "partials")) ||
         (rc = ensure(ctx, sb.pb, 8 * 64 * static_cast<size_t>(max_blocks), "partials")) ||
-        (rc = ensure(ctx, sb.small, 8 * (512 + 64 + 64 + 64) + 64, "solver scalars")))
+        (rc = ensure(ctx, sb.small, 8 * (576 + 64 + 64 + 64) + 64, "solver scalars")))
         return fail(rc);
     double *small = static_cast<double *>(sb.small.ptr);
     fc::CgWork w{};
@@ -63,29 +71,47 @@ extern "C" int fc_solve(fc_ctx *ctx, const fc_graph *g, double alpha, const doub
     }
     w.n = n;
     w.k = k;
+    w.kp = kp;
     w.alpha = alpha;
     w.max_blocks = max_blocks;
     w.B = B;
     w.X = X;
     w.R64 = static_cast<double *>(sb.r64.ptr);
     w.r = sb.r.ptr;
-    w.z = sb.z.ptr;
     w.p = sb.p.ptr;
     w.q = sb.q.ptr;
     w.d = sb.d.ptr;
+    w.minv = ctx->s_minv.ptr;
     w.partial_a = static_cast<double *>(sb.pa.ptr);
     w.partial_b = static_cast<double *>(sb.pb.ptr);
     w.scalars = small;
-    w.scale = small + 512;
-    w.res_rr = small + 576;
-    w.res_bb = small + 640;
-    w.any = reinterpret_cast<unsigned int *>(small + 704);
+    w.scale = small + 576;
+    w.res_rr = small + 640;
+    w.res_bb = small + 704;
+    w.nonzero = reinterpret_cast<unsigned int *>(small + 768);
+    w.rows.count = w.nonzero + 1;
+    w.rows.seg_base = static_cast<uint32_t *>(ctx->s_segbase.ptr);
+    w.rows.seg = static_cast<int2 *>(ctx->s_seg.ptr);
+    // long rows, preconditioner, and whether there is an initial guess at all
+    unsigned int found[2] = {0, 0};
+    FC_HIP(ctx, hipMemsetAsync(w.nonzero, 0, sizeof(found), ctx->stream), "memset");
+    FC_HIP(ctx, fc::cg_prepare(w, fp32, ctx->stream), "solver preparation");
+    FC_HIP(ctx, hipMemcpyAsync(found, w.nonzero, sizeof(found), hipMemcpyDeviceToHost, ctx->stream),
+           "copy");
+    FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "solver preparation");
+    bool gather = found[0] != 0;  // X = 0: the first residual is B
+    w.segments = found[1];
+    if (w.segments) {
+        if ((rc = ensure(ctx, ctx->s_segsum, 8 * static_cast<size_t>(w.segments) * kp, "segment sums")))
+            return fail(rc);
+        w.seg_sum = ctx->s_segsum.ptr;
+    }
 
     std::vector<double> rr(k), bb(k), scale(k), tol2(64, 0.0);
     uint32_t total = 0;
     bool first = true, converged = false;
     for (int sweep = 0; sweep < 64; ++sweep) {
-        FC_HIP(ctx, fc::cg_residual(w, first, ctx->stream), "residual");
+        FC_HIP(ctx, fc::cg_residual(w, first, gather, ctx->stream), "residual");
         FC_HIP(ctx, hipMemcpyAsync(rr.data(), w.res_rr, 8 * k, hipMemcpyDeviceToHost, ctx->stream), "copy");
         if (first)
             FC_HIP(ctx, hipMemcpyAsync(bb.data(), w.res_bb, 8 * k, hipMemcpyDeviceToHost, ctx->stream),
@@ -117,6 +143,7 @@ extern "C" int fc_solve(fc_ctx *ctx, const fc_graph *g, double alpha, const doub
                             : fc::cg_inner<double>(w, budget, 8, &it, ctx->stream);
         if (e != hipSuccess) return fail(hip_fail(ctx, e, "inner CG"));
         total += it;
+        gather = true;
     }
     FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "solve");
     if (iters_out) *iters_out = static_cast<int32_t>(total);
