@@ -73,81 +73,108 @@ __device__ __forceinline__ Quad quad() {
     return {32u * (w >> 1), 32u * (w & 1u), threadIdx.x & 63u};
 }
 
-// Pivot block inverse: D = A[p0.., p0..] (64 x 64, SPD) inverted by
-// Gauss-Jordan without pivoting, written to Dinv (64 x 64, row-major).  The
-// 256 threads hold the block in registers, a 4 x 4 sub-block each (thread
-// (ty, tx) = rows 4 ty.., columns 4 tx..); step p publishes row p and column p
-// (the multipliers, read before any row changes them) through LDS, double
-// buffered by the step's parity so that one barrier per step suffices, and row
-// p is scaled by the pivot's reciprocal.
-__global__ __launch_bounds__(kThreads) void gj_pivot_kernel(const double *__restrict__ A, uint32_t N,
-                                                            uint32_t p0, double *__restrict__ Dinv) {
-    __shared__ double rowp[2][kT], colp[2][kT];
+// Inverse of the 64 x 64 SPD block at (p0, p0) of A by Gauss-Jordan without
+// pivoting, left in registers.  The 256 threads hold a 4 x 4 sub-block each
+// (thread (ty, tx) = rows 4 ty.., columns 4 tx..); step p publishes row p and
+// column p (the multipliers, read before any row changes them) through LDS,
+// double buffered by the step's parity so that one barrier per step suffices,
+// and row p is scaled by the pivot's reciprocal.
+__device__ __forceinline__ void pivot_inverse(const double *__restrict__ A, uint32_t N, uint32_t p0,
+                                              double (*rowp)[kT], double (*colp)[kT],
+                                              double (&d)[4][4]) {
     const uint32_t tx = threadIdx.x & 15u, ty = threadIdx.x >> 4;
-    double d[4][4];
 #pragma unroll
     for (uint32_t r = 0; r < 4; ++r)
 #pragma unroll
         for (uint32_t c = 0; c < 4; ++c)
             d[r][c] = A[static_cast<size_t>(p0 + 4u * ty + r) * N + p0 + 4u * tx + c];
-    for (uint32_t p = 0; p < kT; ++p) {
-        const uint32_t b = p & 1u, band = p >> 2, lp = p & 3u;
-        if (tx == band)
+    for (uint32_t band = 0; band < kT / 4u; ++band)
 #pragma unroll
-            for (uint32_t r = 0; r < 4; ++r) colp[b][4u * ty + r] = d[r][lp];
-        if (ty == band)
+        for (uint32_t lp = 0; lp < 4; ++lp) {  // register indexes stay constants
+            const uint32_t p = 4u * band + lp, b = lp & 1u;
+            if (tx == band)
 #pragma unroll
-            for (uint32_t c = 0; c < 4; ++c) rowp[b][4u * tx + c] = d[lp][c];
-        __syncthreads();
-        const double inv = 1.0 / rowp[b][p];
-        double rp[4];
+                for (uint32_t r = 0; r < 4; ++r) colp[b][4u * ty + r] = d[r][lp];
+            if (ty == band)
 #pragma unroll
-        for (uint32_t c = 0; c < 4; ++c) {
-            const uint32_t j = 4u * tx + c;
-            rp[c] = (j == p ? 1.0 : rowp[b][j]) * inv;  // row p of the result
-        }
-#pragma unroll
-        for (uint32_t r = 0; r < 4; ++r) {
-            const uint32_t i = 4u * ty + r;
-            const double f = colp[b][i];
+                for (uint32_t c = 0; c < 4; ++c) rowp[b][4u * tx + c] = d[lp][c];
+            __syncthreads();
+            const double inv = 1.0 / rowp[b][p];
+            double rp[4];
 #pragma unroll
             for (uint32_t c = 0; c < 4; ++c) {
                 const uint32_t j = 4u * tx + c;
-                // column p of row i becomes -f / piv; the others subtract f * row p
-                d[r][c] = i == p ? rp[c] : (j == p ? 0.0 : d[r][c]) - f * rp[c];
+                rp[c] = (j == p ? 1.0 : rowp[b][j]) * inv;  // row p of the result
+            }
+#pragma unroll
+            for (uint32_t r = 0; r < 4; ++r) {
+                const uint32_t i = 4u * ty + r;
+                const double f = colp[b][i];
+#pragma unroll
+                for (uint32_t c = 0; c < 4; ++c) {
+                    const uint32_t j = 4u * tx + c;
+                    // column p of row i becomes -f / piv; the others subtract f * row p
+                    d[r][c] = i == p ? rp[c] : (j == p ? 0.0 : d[r][c]) - f * rp[c];
+                }
             }
         }
+}
+
+// One 64-wide Gauss-Jordan step on a small matrix (the 256 x 256 pivot block),
+// out of place: with D = A[p, p]^{-1},
+//   out[p, p] = D               out[p, j] = D A[p, j]
+//   out[i, p] = -A[i, p] D      out[i, j] = A[i, j] - A[i, p] (D A[p, j])
+// One workgroup per tile, each of which inverts the pivot block for itself: the
+// chain of 64 pivots sets the time (36 us), and doing it in every workgroup
+// spares the launches between pivot, row panel, update, column panel and
+// write-back (five, 77 us a step in all; 44 steps were 3.4 of the 5.0 ms that
+// the inverse of a 2816 x 2816 matrix took; now kStep us a step).
+__global__ __launch_bounds__(kThreads) void gj_step_kernel(const double *__restrict__ A, uint32_t N,
+                                                           uint32_t pt, double *__restrict__ out) {
+    __shared__ double X[kT * kPad], Y[kT * kPad], rowp[2][kT], colp[2][kT];
+    const uint32_t ti = blockIdx.y, tj = blockIdx.x;
+    const uint32_t p0 = pt * kT, i0 = ti * kT, j0 = tj * kT;
+    const uint32_t tx = threadIdx.x & 15u, ty = threadIdx.x >> 4;
+    double d[4][4];
+    pivot_inverse(A, N, p0, rowp, colp, d);
+    if (ti == pt && tj == pt) {
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r)
+#pragma unroll
+            for (uint32_t c = 0; c < 4; ++c)
+                out[static_cast<size_t>(p0 + 4u * ty + r) * N + p0 + 4u * tx + c] = d[r][c];
+        return;
     }
+    // the panel product: D A[p, j] with D on the left, or (column panel) -A[i, p] D
+    const bool column = tj == pt;
+    double *D = column ? Y : X;
 #pragma unroll
     for (uint32_t r = 0; r < 4; ++r)
 #pragma unroll
-        for (uint32_t c = 0; c < 4; ++c) Dinv[(4u * ty + r) * kT + 4u * tx + c] = d[r][c];
-}
-
-// Row panel: A[p-rows, j-tile] <- Dinv A[p-rows, j-tile] (j-tile != p);
-// column panel: A[i-tile, p-cols] <- -A[i-tile, p-cols] Dinv (i-tile != p).
-__global__ __launch_bounds__(kThreads) void gj_panel_kernel(double *__restrict__ A, uint32_t N,
-                                                            uint32_t pt,
-                                                            const double *__restrict__ Dinv,
-                                                            uint32_t column) {
-    const uint32_t t = blockIdx.x;
-    if (t == pt) return;
-    __shared__ double X[kT * kPad], Y[kT * kPad];
-    const uint32_t p0 = pt * kT, t0 = t * kT;
-    if (!column) {
-        for (uint32_t e = threadIdx.x; e < kT * kT; e += kThreads)
-            X[(e / kT) * kPad + e % kT] = Dinv[e];
-        stage(A, N, p0, t0, Y, false);
-    } else {
-        stage(A, N, t0, p0, X, true);
-        for (uint32_t e = threadIdx.x; e < kT * kT; e += kThreads)
-            Y[(e / kT) * kPad + e % kT] = Dinv[e];
-    }
+        for (uint32_t c = 0; c < 4; ++c) D[(4u * ty + r) * kPad + 4u * tx + c] = d[r][c];
+    if (column) stage(A, N, i0, p0, X, true);
+    else stage(A, N, p0, j0, Y, false);
     __syncthreads();
     const Quad q = quad();
     double4_t acc[2][2] = {};
     tile_mma(X, Y, q.qr, q.qc, q.lane, acc);
-    const uint32_t r0 = column ? t0 : p0, c0 = column ? p0 : t0;
+    if (ti != pt && tj != pt) {  // then the trailing tile, from that product
+        __syncthreads();
+#pragma unroll
+        for (uint32_t s = 0; s < 2; ++s)
+#pragma unroll
+            for (uint32_t u = 0; u < 2; ++u)
+#pragma unroll
+                for (uint32_t r = 0; r < 4; ++r) {
+                    const uint32_t row = q.qr + 16u * s + d_row(q.lane, r);
+                    const uint32_t col = q.qc + 16u * u + d_col(q.lane);
+                    Y[row * kPad + col] = acc[s][u][r];
+                    acc[s][u][r] = A[static_cast<size_t>(i0 + row) * N + j0 + col];
+                }
+        stage(A, N, i0, p0, X, true);  // -A[i, p]
+        __syncthreads();
+        tile_mma(X, Y, q.qr, q.qc, q.lane, acc);
+    }
 #pragma unroll
     for (uint32_t s = 0; s < 2; ++s)
 #pragma unroll
@@ -156,40 +183,8 @@ __global__ __launch_bounds__(kThreads) void gj_panel_kernel(double *__restrict__
             for (uint32_t r = 0; r < 4; ++r) {
                 const uint32_t row = q.qr + 16u * s + d_row(q.lane, r);
                 const uint32_t col = q.qc + 16u * u + d_col(q.lane);
-                A[static_cast<size_t>(r0 + row) * N + c0 + col] = acc[s][u][r];
+                out[static_cast<size_t>(i0 + row) * N + j0 + col] = acc[s][u][r];
             }
-}
-
-// Trailing update: A[i, j] -= A[i, p] A[p, j] for tiles i, j != p (A[i, p]
-// still the old column panel, A[p, j] the new row panel).
-__global__ __launch_bounds__(kThreads) void gj_update_kernel(double *__restrict__ A, uint32_t N,
-                                                             uint32_t pt) {
-    const uint32_t ti = blockIdx.y, tj = blockIdx.x;
-    if (ti == pt || tj == pt) return;
-    __shared__ double X[kT * kPad], Y[kT * kPad];
-    const uint32_t p0 = pt * kT, i0 = ti * kT, j0 = tj * kT;
-    stage(A, N, i0, p0, X, true);  // -A[i, p]
-    stage(A, N, p0, j0, Y, false);
-    __syncthreads();
-    const Quad q = quad();
-    double4_t acc[2][2];
-#pragma unroll
-    for (uint32_t s = 0; s < 2; ++s)
-#pragma unroll
-        for (uint32_t u = 0; u < 2; ++u)
-#pragma unroll
-            for (uint32_t r = 0; r < 4; ++r)
-                acc[s][u][r] = A[static_cast<size_t>(i0 + q.qr + 16u * s + d_row(q.lane, r)) * N + j0 +
-                                 q.qc + 16u * u + d_col(q.lane)];
-    tile_mma(X, Y, q.qr, q.qc, q.lane, acc);
-#pragma unroll
-    for (uint32_t s = 0; s < 2; ++s)
-#pragma unroll
-        for (uint32_t u = 0; u < 2; ++u)
-#pragma unroll
-            for (uint32_t r = 0; r < 4; ++r)
-                A[static_cast<size_t>(i0 + q.qr + 16u * s + d_row(q.lane, r)) * N + j0 + q.qc +
-                  16u * u + d_col(q.lane)] = acc[s][u][r];
 }
 
 // Tile product over K = kchunks x kK: out[ti, tj] = (load_c ? out[ti, tj] : 0)
@@ -208,8 +203,13 @@ struct GemmArgs {
     uint32_t load_c, negate_x;
 };
 
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_kernel(GemmArgs g) {
-    const uint32_t ti = blockIdx.y, tj = blockIdx.x;
+// One product (grid = its column tiles x row tiles), or two independent ones by
+// blockIdx.z, the second with the grid's sides exchanged (a row and a column
+// panel).
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_kernel(
+    GemmArgs g0, GemmArgs g1) {
+    const GemmArgs &g = blockIdx.z ? g1 : g0;
+    const uint32_t ti = blockIdx.z ? blockIdx.x : blockIdx.y, tj = blockIdx.z ? blockIdx.y : blockIdx.x;
     if ((ti >= g.si0 && ti < g.si1) || (tj >= g.sj0 && tj < g.sj1)) return;
     __shared__ double X[kT * kPadK], Y[kK * kPad];
     const Quad q = quad();
@@ -269,12 +269,26 @@ __global__ __launch_bounds__(kThreads) void copy_block_kernel(const double *__re
         dst[static_cast<size_t>(r) * ldd + c] = src[static_cast<size_t>(r) * lds + c];
 }
 
-__global__ __launch_bounds__(kThreads) void gj_put_kernel(double *__restrict__ A, uint32_t N,
-                                                          uint32_t pt,
-                                                          const double *__restrict__ Dinv) {
-    const uint32_t p0 = pt * kT;
-    for (uint32_t e = threadIdx.x; e < kT * kT; e += kThreads)
-        A[static_cast<size_t>(p0 + e / kT) * N + p0 + e % kT] = Dinv[e];
+// The pivot step's new rows and columns written back, one row of A per block:
+// rows [p0, p0 + kB) from R outside the pivot columns and W inside them, every
+// other row's pivot columns from C.
+__global__ __launch_bounds__(kThreads) void put_panels_kernel(const double *__restrict__ W,
+                                                              const double *__restrict__ R,
+                                                              const double *__restrict__ C,
+                                                              uint32_t N, uint32_t p0,
+                                                              double *__restrict__ A) {
+    static_assert(kB == kThreads, "one pivot column per thread");
+    const uint32_t r = blockIdx.x, t = threadIdx.x;
+    double *row = A + static_cast<size_t>(r) * N;
+    if (r < p0 || r >= p0 + kB) {
+        row[p0 + t] = C[static_cast<size_t>(r) * kB + t];
+        return;
+    }
+    const double *Rr = R + static_cast<size_t>(r - p0) * N, *Wr = W + static_cast<size_t>(r - p0) * kB;
+    for (uint32_t c = t; c < N; c += kThreads) {
+        const uint32_t d = c - p0;  // wraps below p0
+        row[c] = d < kB ? Wr[d] : Rr[c];
+    }
 }
 
 // alpha L + I of the first n rows (weighted when w is not null), identity on
@@ -362,7 +376,29 @@ __global__ __launch_bounds__(kThreads) void copy_col_kernel(const double *__rest
 // Column sums of squares over row chunks of kChunk rows (part[chunk * N + j]),
 // optionally after the downdate M[i][j] -= cv[i] rv[j] / piv of vertex v,
 // whose row and column become zero.
-constexpr uint32_t kChunk = 64;
+//
+// Bound by the matrix's traffic (n^2 read and written).  The rows of a chunk go
+// kRows at a time, all of them loaded before the first is stored: with one load
+// in flight per lane (a store between any two) a step on n = 2708 took 25 us,
+// 4.7 TB/s; now 21.9 us, 5.4 TB/s, the rate of a large copy (32 rows at a time: 23.2).
+constexpr uint32_t kChunk = 64, kRows = 16;
+template <bool kDown>
+__device__ __forceinline__ double colsq_rows(double *__restrict__ p, uint32_t N, uint32_t i,
+                                             uint32_t rows, uint32_t v, bool jv, double f,
+                                             const double *__restrict__ cv, double s) {
+    double x[kRows];
+#pragma unroll
+    for (uint32_t q = 0; q < kRows; ++q) x[q] = q < rows ? p[static_cast<size_t>(q) * N] : 0.0;
+#pragma unroll
+    for (uint32_t q = 0; q < kRows; ++q) {
+        if (kDown && q < rows) {
+            x[q] = (i + q == v || jv) ? 0.0 : x[q] - cv[i + q] * f;
+            p[static_cast<size_t>(q) * N] = x[q];
+        }
+        s += x[q] * x[q];  // adding the zeros past the end changes nothing
+    }
+    return s;
+}
 __global__ __launch_bounds__(kThreads) void colsq_kernel(double *__restrict__ A, uint32_t n, uint32_t N,
                                                          uint32_t v0, const unsigned long long *vsel,
                                                          const double *__restrict__ cv,
@@ -376,19 +412,14 @@ __global__ __launch_bounds__(kThreads) void colsq_kernel(double *__restrict__ A,
     const uint32_t i0 = c * kChunk, i1 = min(n, i0 + kChunk);
     double s = 0.0;
     if (cv && v < n) {
-        const double piv = *pivp;
-        const double f = rv[j] / piv;
-        for (uint32_t i = i0; i < i1; ++i) {
-            double *p = A + static_cast<size_t>(i) * N + j;
-            const double x = (i == v || j == v) ? 0.0 : *p - cv[i] * f;
-            *p = x;
-            s += x * x;
-        }
+        const double f = rv[j] / *pivp;
+        for (uint32_t i = i0; i < i1; i += kRows)
+            s = colsq_rows<true>(A + static_cast<size_t>(i) * N + j, N, i, min(kRows, i1 - i), v,
+                                 j == v, f, cv, s);
     } else {
-        for (uint32_t i = i0; i < i1; ++i) {
-            const double x = A[static_cast<size_t>(i) * N + j];
-            s += x * x;
-        }
+        for (uint32_t i = i0; i < i1; i += kRows)
+            s = colsq_rows<false>(A + static_cast<size_t>(i) * N + j, N, i, min(kRows, i1 - i), v,
+                                  false, 0.0, cv, s);
     }
     part[static_cast<size_t>(c) * N + j] = s;
 }
@@ -415,46 +446,62 @@ __global__ __launch_bounds__(kThreads) void gain_kernel(const double *__restrict
                                                         unsigned long long *__restrict__ bmax,
                                                         uint32_t *__restrict__ bid,
                                                         double *__restrict__ bdiag, uint32_t *bad) {
-    __shared__ unsigned long long sk[kThreads];
-    __shared__ uint32_t si[kThreads];
+    constexpr uint32_t kWaves = kThreads / 64u;
+    __shared__ unsigned long long sk[kWaves];
+    __shared__ uint32_t si[kWaves];
     __shared__ double sd[kThreads];
     const uint32_t t = threadIdx.x, j = blockIdx.x * kThreads + t;
+    const uint32_t lane = t & 63u, wave = t >> 6;
     unsigned long long key = 0ull;
-    bool ok = false;
+    uint32_t id = ~0u;
     const double djj = j < n ? A[static_cast<size_t>(j) * N + j] : 0.0;
+    sd[t] = djj;
     if (j < n && !taken[j]) {
+        // the chunk sums in order, sixteen loads in flight (one at a time: 14 us
+        // a step on n = 2708, 43 chunks; now 4.9)
         double sum = 0.0;
-        for (uint32_t c = 0; c < chunks; ++c) sum += part[static_cast<size_t>(c) * N + j];
+        for (uint32_t c = 0; c < chunks; c += 16u) {
+            double x[16];
+#pragma unroll
+            for (uint32_t q = 0; q < 16u; ++q)
+                x[q] = c + q < chunks ? part[static_cast<size_t>(c + q) * N + j] : 0.0;
+#pragma unroll
+            for (uint32_t q = 0; q < 16u; ++q) sum += x[q];
+        }
         const double g = sum / djj;
         if (g == g) {
             key = gain_key(g);
-            ok = true;
+            id = j;
         } else {
             atomicOr(bad, 2u);
         }
     }
-    sk[t] = key;
-    sd[t] = djj;
-    __syncthreads();
-    for (uint32_t h = kThreads / 2; h > 0; h >>= 1) {
-        if (t < h) {
-            sk[t] = max(sk[t], sk[t + h]);
-            sd[t] += sd[t + h];
+    // the largest key and its smallest id: in the wave, then over the waves
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long k2 = __shfl_xor(key, off, 64);
+        const uint32_t i2 = __shfl_xor(id, off, 64);
+        if (k2 > key || (k2 == key && i2 < id)) {
+            key = k2;
+            id = i2;
         }
-        __syncthreads();
     }
-    const unsigned long long top = sk[0];
-    si[t] = ok && key == top ? j : ~0u;
+    if (lane == 0) {
+        sk[wave] = key;
+        si[wave] = id;
+    }
     __syncthreads();
-    for (uint32_t h = kThreads / 2; h > 0; h >>= 1) {
-        if (t < h) si[t] = min(si[t], si[t + h]);
-        __syncthreads();
-    }
-    if (t == 0) {
-        bmax[blockIdx.x] = top;
-        bid[blockIdx.x] = si[0];
-        bdiag[blockIdx.x] = sd[0];
-    }
+    if (wave != 0) return;
+    double tr = (sd[lane] + sd[lane + 128u]) + (sd[lane + 64u] + sd[lane + 192u]);
+    for (int off = 32; off > 0; off >>= 1) tr += __shfl_down(tr, off, 64);
+    if (lane != 0) return;
+    for (uint32_t w = 1; w < kWaves; ++w)
+        if (sk[w] > key || (sk[w] == key && si[w] < id)) {
+            key = sk[w];
+            id = si[w];
+        }
+    bmax[blockIdx.x] = key;
+    bid[blockIdx.x] = id;
+    bdiag[blockIdx.x] = tr;
 }
 
 // The step's vertex from the gain blocks' results (every block of the next
@@ -462,30 +509,26 @@ __global__ __launch_bounds__(kThreads) void gain_kernel(const double *__restrict
 // pattern, or n when there is none.
 __device__ uint32_t reduce_choice(const unsigned long long *__restrict__ bmax,
                                   const uint32_t *__restrict__ bid, uint32_t nb, uint32_t n) {
-    __shared__ unsigned long long sk[kThreads];
-    __shared__ uint32_t si[kThreads];
-    const uint32_t t = threadIdx.x;
-    unsigned long long k = 0ull;
-    for (uint32_t b = t; b < nb; b += kThreads) k = max(k, bmax[b]);
-    sk[t] = k;
-    __syncthreads();
-    for (uint32_t h = kThreads / 2; h > 0; h >>= 1) {
-        if (t < h) sk[t] = max(sk[t], sk[t + h]);
-        __syncthreads();
-    }
-    const unsigned long long top = sk[0];
+    const uint32_t lane = threadIdx.x & 63u;  // every wave for itself: no barrier
+    unsigned long long key = 0ull;
     uint32_t id = ~0u;
-    for (uint32_t b = t; b < nb; b += kThreads)
-        if (bmax[b] == top) id = min(id, bid[b]);
-    si[t] = id;
-    __syncthreads();
-    for (uint32_t h = kThreads / 2; h > 0; h >>= 1) {
-        if (t < h) si[t] = min(si[t], si[t + h]);
-        __syncthreads();
+    for (uint32_t b = lane; b < nb; b += 64u) {
+        const unsigned long long k2 = bmax[b];
+        const uint32_t i2 = bid[b];
+        if (k2 > key || (k2 == key && i2 < id)) {
+            key = k2;
+            id = i2;
+        }
     }
-    const uint32_t v = si[0];
-    __syncthreads();  // the arrays are reused by a later call
-    return v < n ? v : n;
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long k2 = __shfl_xor(key, off, 64);
+        const uint32_t i2 = __shfl_xor(id, off, 64);
+        if (k2 > key || (k2 == key && i2 < id)) {
+            key = k2;
+            id = i2;
+        }
+    }
+    return id < n ? id : n;
 }
 
 // Column v of the chosen vertex (and its row) copied out before the downdate,
@@ -550,7 +593,7 @@ inline unsigned int blocks_for(uint32_t items) { return (items + kThreads - 1) /
 
 uint32_t group_dim(uint32_t n) { return (n + kB - 1) / kB * kB; }
 size_t group_scratch_doubles(uint32_t N) {
-    return static_cast<size_t>(kB) * kB + 2 * static_cast<size_t>(kB) * N + kT * kT;
+    return 2 * static_cast<size_t>(kB) * kB + 2 * static_cast<size_t>(kB) * N;
 }
 uint32_t group_chunks(uint32_t n) { return (n + kChunk - 1) / kChunk; }
 
@@ -565,15 +608,13 @@ hipError_t launch_group_build(const int32_t *row_ptr, const int32_t *col_idx, co
 
 namespace {
 
-// In-place Gauss-Jordan inverse with 64-wide pivot blocks (N a multiple of 64).
-void invert_64(double *A, uint32_t N, double *Dinv, hipStream_t stream) {
-    const uint32_t nt = N / kT;
+// Gauss-Jordan inverse of the kB x kB matrix at W with 64-wide pivot blocks: an
+// even number of out-of-place steps between W and T, so the result is at W.
+void invert_64(double *W, double *T, hipStream_t stream) {
+    constexpr uint32_t nt = kB / kT;
+    static_assert(nt % 2 == 0, "the last step writes W");
     for (uint32_t pt = 0; pt < nt; ++pt) {
-        gj_pivot_kernel<<<1, kThreads, 0, stream>>>(A, N, pt * kT, Dinv);
-        gj_panel_kernel<<<nt, kThreads, 0, stream>>>(A, N, pt, Dinv, 0u);
-        gj_update_kernel<<<dim3(nt, nt), kThreads, 0, stream>>>(A, N, pt);
-        gj_panel_kernel<<<nt, kThreads, 0, stream>>>(A, N, pt, Dinv, 1u);
-        gj_put_kernel<<<1, kThreads, 0, stream>>>(A, N, pt, Dinv);
+        gj_step_kernel<<<dim3(nt, nt), kThreads, 0, stream>>>(pt % 2 ? T : W, kB, pt, pt % 2 ? W : T);
     }
 }
 
@@ -585,38 +626,25 @@ void invert_64(double *A, uint32_t N, double *Dinv, hipStream_t stream) {
 //   A[i, j] -= A[i, P] R[:, j]          (i, j outside P; A[i, P] still the old panel)
 //   C = -A[:, P] W                      (column panel, out of place: N x 256)
 //   A[P, :] = R, A[:, P] = C, A[P, P] = W
-// Scratch: W (256 x 256), R (256 x N), C (N x 256), then a 64 x 64 block.
+// Scratch: W (256 x 256), R (256 x N), C (N x 256), then another 256 x 256.
 hipError_t launch_group_invert(double *A, uint32_t N, double *scratch, hipStream_t stream) {
     double *W = scratch, *R = W + kB * kB, *C = R + static_cast<size_t>(kB) * N;
-    double *D64 = C + static_cast<size_t>(N) * kB;
+    double *T = C + static_cast<size_t>(N) * kB;
     const uint32_t nt = N / kT, pb = kB / kT;
     for (uint32_t p0 = 0; p0 < N; p0 += kB) {
         const uint32_t pt0 = p0 / kT, pt1 = pt0 + pb;
         copy_block_kernel<<<dim3(1, kB), kThreads, 0, stream>>>(A + static_cast<size_t>(p0) * N + p0, N,
                                                                 W, kB, kB);
-        invert_64(W, kB, D64, stream);
-        GemmArgs row{W, A + static_cast<size_t>(p0) * N, R, kB, N, N, kB / kK, 0u, 0u, pt0, pt1, 0u, 0u};
-        gemm_kernel<<<dim3(nt, pb), kThreads, 0, stream>>>(row);
-        GemmArgs upd{A + p0, R, A, N, N, N, kB / kK, pt0, pt1, pt0, pt1, 1u, 1u};
-        gemm_kernel<<<dim3(nt, nt), kThreads, 0, stream>>>(upd);
+        invert_64(W, T, stream);
+        // both panels at once (the column panel does not need the new rows), then
+        // the trailing update
+        GemmArgs row{W, A + static_cast<size_t>(p0) * N, R, kB, N, N, kB / kK,
+                     0u, 0u, pt0, pt1, 0u, 0u};
         GemmArgs col{A + p0, W, C, N, kB, kB, kB / kK, pt0, pt1, 0u, 0u, 0u, 1u};
-        gemm_kernel<<<dim3(pb, nt), kThreads, 0, stream>>>(col);
-        // write back: rows of P from R (outside P's columns), columns of P from C
-        // (outside P's rows), and W on the diagonal block
-        if (p0 > 0)
-            copy_block_kernel<<<dim3(4, kB), kThreads, 0, stream>>>(R, N, A + static_cast<size_t>(p0) * N,
-                                                                    N, p0);
-        if (p0 + kB < N)
-            copy_block_kernel<<<dim3(4, kB), kThreads, 0, stream>>>(
-                R + p0 + kB, N, A + static_cast<size_t>(p0) * N + p0 + kB, N, N - p0 - kB);
-        if (p0 > 0)
-            copy_block_kernel<<<dim3(1, p0), kThreads, 0, stream>>>(C, kB, A + p0, N, kB);
-        if (p0 + kB < N)
-            copy_block_kernel<<<dim3(1, N - p0 - kB), kThreads, 0, stream>>>(
-                C + static_cast<size_t>(p0 + kB) * kB, kB, A + static_cast<size_t>(p0 + kB) * N + p0, N,
-                kB);
-        copy_block_kernel<<<dim3(1, kB), kThreads, 0, stream>>>(W, kB, A + static_cast<size_t>(p0) * N + p0,
-                                                                N, kB);
+        gemm_kernel<<<dim3(nt, pb, 2), kThreads, 0, stream>>>(row, col);
+        GemmArgs upd{A + p0, R, A, N, N, N, kB / kK, pt0, pt1, pt0, pt1, 1u, 1u};
+        gemm_kernel<<<dim3(nt, nt), kThreads, 0, stream>>>(upd, upd);
+        put_panels_kernel<<<N, kThreads, 0, stream>>>(W, R, C, N, p0, A);
     }
     return hipGetLastError();
 }
