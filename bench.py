@@ -495,7 +495,7 @@ def leg_solve(fc, inputs, dev, steps, warmup) -> dict:
         dt, out = _timed(lambda: fc.solve(dg, 1.0, B, rtol=1e-9, precision=prec, device=dev,
                                           trusted=True, as_torch=True), steps, warmup)
         sols[prec] = out["X"]
-        # bytes of the inner iterations alone (gathered neighbour rows + 12 streamed
+        # bytes of the inner iterations alone (gathered neighbour rows + 10 streamed
         # n x k arrays per iteration: apply, update, direction) over the whole leg,
         # residuals and refinement included in the time: a lower bound on the rate
         es = 8 if prec == "fp64" else 4

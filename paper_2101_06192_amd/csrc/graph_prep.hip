@@ -39,9 +39,13 @@ __global__ void validate_rows_kernel(const int32_t *__restrict__ row_ptr, int32_
 //
 // Bound by the random lines of row_ptr[u] and u's row: R-MAT with 2^22
 // vertices, 65 M entries: 9.70 ms (16 entries per thread, every entry
-// searched) before, 2.96 ms now; 10 K entries of a small graph: 26 us
-// (a chain of 16 searches per thread) before, 4.8 us now.
-constexpr uint32_t kColThreads = 256;
+// searched) before, 2.99 ms now; 10 K entries of a small graph: 26 us
+// (a chain of 16 searches per thread) before, 5.0 us now.
+// Wide blocks of several steps: each block ends in one atomic on sym_diff, and
+// 7800 of them on that one word took 94 us (2 M entries: 106 us a call, now
+// 76); more blocks than fit at once, so that the ones with hub rows, which
+// search for nearly every entry, even out.
+constexpr uint32_t kColThreads = 512, kColBlocks = 1024;
 
 __global__ __launch_bounds__(kColThreads) void validate_cols_kernel(
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx,
@@ -187,8 +191,8 @@ __global__ void row_wdeg_kernel(const int32_t *__restrict__ row_ptr,
 // degree and the weighted volume are reduced per block (kVrecBlocks blocks at
 // most, each walking the vertices in strides) before they touch their one
 // global word: with an atomic per wave, 15.6 K atomics on one address took
-// 182 us of a pass that streams 24 MB (10^6 vertices); now 20 us.
-constexpr uint32_t kVrecThreads = 256, kVrecBlocks = 1024;
+// 182 us of a pass that streams 24 MB (10^6 vertices); now 10 us.
+constexpr uint32_t kVrecThreads = 1024, kVrecBlocks = 256;
 
 __global__ __launch_bounds__(kVrecThreads) void build_vrec_kernel(
     const int32_t *__restrict__ row_ptr, const double *__restrict__ S, int32_t n, double alpha,
@@ -270,8 +274,8 @@ hipError_t launch_validate_cols(const int32_t *row_ptr, const int32_t *col_idx,
                                 const double *weights, int32_t n, int64_t nnz, unsigned int *err,
                                 unsigned long long *sym_diff, hipStream_t stream) {
     if (n == 0 || nnz == 0) return hipSuccess;
-    // up to 8 entries per lane once that still leaves thousands of blocks
-    const int64_t want = nnz / (static_cast<int64_t>(kColThreads) * 4096);
+    // up to 8 steps per wave once there are kColBlocks blocks
+    const int64_t want = nnz / (static_cast<int64_t>(kColThreads) * kColBlocks);
     const uint32_t steps = static_cast<uint32_t>(want < 1 ? 1 : want > 8 ? 8 : want);
     validate_cols_kernel<<<blocks_for(nnz, static_cast<int>(kColThreads * steps)), kColThreads, 0,
                            stream>>>(row_ptr, col_idx, weights, n, nnz, steps, err, sym_diff);

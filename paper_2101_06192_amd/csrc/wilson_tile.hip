@@ -882,7 +882,9 @@ __global__ __launch_bounds__(kPreThreads) void tile_predraw_kernel(TileArgs a, u
 // Entries that join ids of different tiles, one CSR entry per lane and step.
 // (One row per thread left the hub rows to one lane each: 10.8 ms on R-MAT
 // with 2^22 vertices, 65 M entries; now 0.19 ms.)
-__global__ __launch_bounds__(256) void count_cross_kernel(const int32_t *__restrict__ row_ptr,
+constexpr uint32_t kCrossThreads = 1024, kCrossBlocks = 512;
+
+__global__ __launch_bounds__(kCrossThreads) void count_cross_kernel(const int32_t *__restrict__ row_ptr,
                                                           const int32_t *__restrict__ col_idx,
                                                           int32_t n, int64_t nnz, uint32_t B,
                                                           uint32_t steps, unsigned long long *out) {
@@ -891,7 +893,8 @@ __global__ __launch_bounds__(256) void count_cross_kernel(const int32_t *__restr
     __syncthreads();
     RowFinder rows;
     uint32_t c = 0;
-    const int64_t first = (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * 64 * steps;
+    const int64_t first =
+        (static_cast<int64_t>(blockIdx.x) * (kCrossThreads / 64u) + (threadIdx.x >> 6)) * 64 * steps;
     for (uint32_t t = 0; t < steps; ++t) {
         const int64_t j0 = first + static_cast<int64_t>(t) * 64;
         if (j0 >= nnz) break;
@@ -912,13 +915,11 @@ hipError_t launch_count_cross(const int32_t *row_ptr, const int32_t *col_idx, ui
                               int64_t nnz, uint32_t B, unsigned long long *out,
                               hipStream_t stream) {
     if (n == 0 || nnz == 0) return hipSuccess;
-    // up to 32 entries per lane once that still leaves a few blocks per CU: each
-    // block ends in an atomic on the one total
-    const int64_t want = nnz / (256 * 2048);
-    const uint32_t steps = static_cast<uint32_t>(want < 1 ? 1 : want > 32 ? 32 : want);
-    const int64_t per = 256 * static_cast<int64_t>(steps);
-    count_cross_kernel<<<static_cast<unsigned int>((nnz + per - 1) / per), 256, 0, stream>>>(
-        row_ptr, col_idx, static_cast<int32_t>(n), nnz, B, steps, out);
+    const int64_t per_step = static_cast<int64_t>(kCrossThreads) * kCrossBlocks;
+    const uint32_t steps = static_cast<uint32_t>((nnz + per_step - 1) / per_step);
+    const int64_t per = static_cast<int64_t>(kCrossThreads) * steps;
+    count_cross_kernel<<<static_cast<unsigned int>((nnz + per - 1) / per), kCrossThreads, 0,
+                         stream>>>(row_ptr, col_idx, static_cast<int32_t>(n), nnz, B, steps, out);
     return hipGetLastError();
 }
 
