@@ -1,10 +1,9 @@
 // fc_rank and fc_kendall_tau: the ranking output of the estimate (Section 6,
 // "Vertex Ranking") on the device.
 #include <cmath>
+#include <cstddef>
 #include <cstring>
 #include <limits>
-#include <utility>
-#include <vector>
 
 #include "fc_internal.hpp"
 #include "fc_rank_kernels.hpp"
@@ -13,83 +12,45 @@ using namespace fc_host;
 
 namespace {
 
-// rk_hist holds the 8 x 256 digit counts, the 8 x 256 digit bases, then a
-// NaN flag and the four Kendall sums (u64 at word offset kOutWord).
-constexpr size_t kHistWords = 8 * 256;
-constexpr size_t kFlagWord = 2 * kHistWords;
-constexpr size_t kOutWord = kFlagWord + 8;
-constexpr size_t kSmallBytes = 4 * (2 * kHistWords + 64);
+// Counters of one call (rk_hist), zeroed together: the digit counts of up to
+// three sorts (the third one of four bytes), what each knows of its keys, the
+// four Kendall sums.
+struct RankSmall {
+    unsigned int totals[2][8 * 256];
+    unsigned int pair_totals[4 * 256];
+    fc::SortInfo info[2], pair;
+    unsigned long long out[4];
+};
 
-int ensure_sort(fc_ctx *ctx, size_t n) {
+int ensure_sort(fc_ctx *ctx, size_t n, fc::SortBufs *b, RankSmall **small) {
     int rc;
     if ((rc = ensure(ctx, ctx->rk_key0, 8 * n, "rank keys")) ||
         (rc = ensure(ctx, ctx->rk_key1, 8 * n, "rank keys")) ||
         (rc = ensure(ctx, ctx->rk_val0, 4 * n, "rank values")) ||
         (rc = ensure(ctx, ctx->rk_val1, 4 * n, "rank values")) ||
-        (rc = ensure(ctx, ctx->rk_hist, kSmallBytes, "digit counts")) ||
+        (rc = ensure(ctx, ctx->rk_hist, sizeof(RankSmall), "digit counts")) ||
         (rc = ensure(ctx, ctx->rk_thist,
                      4 * 256 * static_cast<size_t>(fc::rank_tiles(static_cast<uint32_t>(n))),
                      "tile counts")))
         return rc;
+    b->key[0] = static_cast<uint64_t *>(ctx->rk_key0.ptr);
+    b->key[1] = static_cast<uint64_t *>(ctx->rk_key1.ptr);
+    b->val[0] = static_cast<int32_t *>(ctx->rk_val0.ptr);
+    b->val[1] = static_cast<int32_t *>(ctx->rk_val1.ptr);
+    *small = static_cast<RankSmall *>(ctx->rk_hist.ptr);
+    FC_HIP(ctx, hipMemsetAsync(*small, 0, sizeof(RankSmall), ctx->stream), "memset counts");
     return FC_OK;
 }
 
-// Stable sort of the keys in rk_key0 with the values in rk_val0 (rk_key0 /
-// rk_val0 and rk_key1 / rk_val1 alternate); *keys and *vals point at the
-// sorted arrays.  With score set, the keys are first made from the scores
-// (FC_ERR_ARG when a score is NaN); else rk_key0 / rk_val0 hold them already.
-int sort_keys(fc_ctx *ctx, const double *score, uint32_t n, bool descending,
-              const uint64_t **keys, const int32_t **vals) {
-    unsigned int *hist = static_cast<unsigned int *>(ctx->rk_hist.ptr);
-    unsigned int *base_d = hist + kHistWords;
-    unsigned int *bad_d = hist + kFlagWord;
-    FC_HIP(ctx, hipMemsetAsync(hist, 0, 4 * (kFlagWord + 1), ctx->stream), "memset counts");
-    if (score)
-        FC_HIP(ctx, fc::launch_rank_keys(score, n, descending,
-                                         static_cast<uint64_t *>(ctx->rk_key0.ptr),
-                                         static_cast<int32_t *>(ctx->rk_val0.ptr), bad_d,
-                                         ctx->stream),
-               "rank keys");
-    FC_HIP(ctx, fc::launch_digit_hist(static_cast<const uint64_t *>(ctx->rk_key0.ptr), n, hist,
-                                      ctx->stream),
-           "digit counts");
-    std::vector<unsigned int> h(kHistWords + 1);
-    FC_HIP(ctx, hipMemcpyAsync(h.data(), hist, 4 * kHistWords, hipMemcpyDeviceToHost, ctx->stream),
-           "copy digit counts");
-    FC_HIP(ctx, hipMemcpyAsync(&h[kHistWords], bad_d, 4, hipMemcpyDeviceToHost, ctx->stream),
-           "copy flag");
-    FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "digit counts");
-    if (h[kHistWords]) return set_err(ctx, FC_ERR_ARG, "score contains NaN");
-    // passes whose byte differs between keys, with their digit bases
-    std::vector<unsigned int> base(kHistWords, 0);
-    bool active[8];
-    for (int p = 0; p < 8; ++p) {
-        active[p] = true;
-        unsigned int run = 0;
-        for (int d = 0; d < 256; ++d) {
-            const unsigned int c = h[p * 256 + d];
-            if (c == n) active[p] = false;
-            base[p * 256 + d] = run;
-            run += c;
-        }
-    }
-    FC_HIP(ctx, hipMemcpyAsync(base_d, base.data(), 4 * kHistWords, hipMemcpyHostToDevice,
-                               ctx->stream),
-           "copy digit bases");
-    DevBuf *kin = &ctx->rk_key0, *kout = &ctx->rk_key1, *vin = &ctx->rk_val0, *vout = &ctx->rk_val1;
-    for (int p = 0; p < 8; ++p) {
-        if (!active[p]) continue;
-        FC_HIP(ctx, fc::launch_radix_pass(static_cast<const uint64_t *>(kin->ptr),
-                                          static_cast<const int32_t *>(vin->ptr), n, 8u * p,
-                                          static_cast<unsigned int *>(ctx->rk_thist.ptr),
-                                          base_d + p * 256, static_cast<uint64_t *>(kout->ptr),
-                                          static_cast<int32_t *>(vout->ptr), ctx->stream),
-               "radix pass");
-        std::swap(kin, kout);
-        std::swap(vin, vout);
-    }
-    *keys = static_cast<const uint64_t *>(kin->ptr);
-    *vals = static_cast<const int32_t *>(vin->ptr);
+// Stable sort of the scores; the vertices end in the buffers as their info says.
+int sort_scores(fc_ctx *ctx, const double *score, uint32_t n, bool descending,
+                const fc::SortBufs &b, RankSmall *small, int which) {
+    FC_HIP(ctx, fc::launch_rank_keys(score, n, descending, b, &small->info[which], ctx->stream),
+           "rank keys");
+    FC_HIP(ctx, fc::launch_sort(b, n, 8, &small->info[which],
+                                static_cast<unsigned int *>(ctx->rk_thist.ptr),
+                                small->totals[which], ctx->stream),
+           "radix sort");
     return FC_OK;
 }
 
@@ -103,16 +64,18 @@ extern "C" int fc_rank(fc_ctx *ctx, const double *score, int32_t n, int32_t desc
     if (n == 0) return FC_OK;
     if (!score) return set_err(ctx, FC_ERR_ARG, "score is NULL");
     const uint32_t un = static_cast<uint32_t>(n);
-    if ((rc = ensure_sort(ctx, static_cast<size_t>(n)))) return rc;
-    const uint64_t *keys;
-    const int32_t *sorted;
-    if ((rc = sort_keys(ctx, score, un, descending != 0, &keys, &sorted))) return rc;
-    if (order)
-        FC_HIP(ctx, hipMemcpyAsync(order, sorted, 4 * static_cast<size_t>(n),
-                                   hipMemcpyDeviceToDevice, ctx->stream),
-               "copy order");
-    if (rank) FC_HIP(ctx, fc::launch_rank_of(sorted, un, rank, ctx->stream), "rank");
+    fc::SortBufs b;
+    RankSmall *small;
+    if ((rc = ensure_sort(ctx, static_cast<size_t>(n), &b, &small)) ||
+        (rc = sort_scores(ctx, score, un, descending != 0, b, small, 0)))
+        return rc;
+    FC_HIP(ctx, fc::launch_order(b, un, &small->info[0], order, rank, ctx->stream), "order");
+    fc::SortInfo info{};
+    FC_HIP(ctx, hipMemcpyAsync(&info, &small->info[0], sizeof(info), hipMemcpyDeviceToHost,
+                               ctx->stream),
+           "copy flag");
     FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "rank");
+    if (info.bad) return set_err(ctx, FC_ERR_ARG, "score contains NaN");
     return FC_OK;
 }
 
@@ -131,48 +94,44 @@ extern "C" int fc_kendall_tau(fc_ctx *ctx, const double *a, const double *b, int
     const bool pairs = ctx->kendall_pairs;
     if (n > 0) {
         const size_t nn = static_cast<size_t>(n);
-        if ((rc = ensure_sort(ctx, nn)) || (rc = ensure(ctx, ctx->rk_ra, 4 * nn, "ranks")) ||
+        fc::SortBufs bufs;
+        RankSmall *small;
+        if ((rc = ensure(ctx, ctx->rk_ra, 4 * nn, "ranks")) ||
             (rc = ensure(ctx, ctx->rk_rb, 4 * nn, "ranks")) ||
-            (rc = ensure(ctx, ctx->rk_s, 8 * nn, "merge runs")))
+            (rc = ensure(ctx, ctx->rk_s, 8 * nn, "merge runs")) ||
+            (rc = ensure_sort(ctx, nn, &bufs, &small)))
             return rc;
-        unsigned long long *out_d =
-            reinterpret_cast<unsigned long long *>(static_cast<unsigned int *>(ctx->rk_hist.ptr) +
-                                                   kOutWord);
+        uint32_t *ra = static_cast<uint32_t *>(ctx->rk_ra.ptr);
+        uint32_t *rb = static_cast<uint32_t *>(ctx->rk_rb.ptr);
         // each vector's scores -> min-ranks (equal scores share a rank) and its ties
-        const double *src[2] = {a, b};
-        DevBuf *dst[2] = {&ctx->rk_ra, &ctx->rk_rb};
-        for (int v = 0; v < 2; ++v) {
-            const uint64_t *keys;
-            const int32_t *ids;
-            if ((rc = sort_keys(ctx, src[v], un, false, &keys, &ids))) return rc;
-            if (v == 0) FC_HIP(ctx, hipMemsetAsync(out_d, 0, sizeof(out), ctx->stream), "memset sums");
-            FC_HIP(ctx, fc::launch_min_rank(keys, ids, un, static_cast<uint32_t *>(dst[v]->ptr),
-                                            out_d + 1 + v, ctx->stream),
-                   "min ranks");
-        }
-        const uint32_t *ra = static_cast<const uint32_t *>(ctx->rk_ra.ptr);
-        const uint32_t *rb = static_cast<const uint32_t *>(ctx->rk_rb.ptr);
+        if ((rc = sort_scores(ctx, a, un, false, bufs, small, 0))) return rc;
+        FC_HIP(ctx, fc::launch_min_rank(bufs, un, &small->info[0], ra, &small->out[1], ctx->stream),
+               "min ranks");
+        if ((rc = sort_scores(ctx, b, un, false, bufs, small, 1))) return rc;
+        FC_HIP(ctx, fc::launch_min_rank(bufs, un, &small->info[1], rb, &small->out[2], ctx->stream),
+               "min ranks");
         if (pairs) {  // all n(n-1)/2 pairs compared (the definition, tiled)
-            FC_HIP(ctx, hipMemsetAsync(out_d, 0, sizeof(out), ctx->stream), "memset sums");
-            FC_HIP(ctx, fc::launch_kendall(ra, rb, un, out_d, ctx->stream), "kendall");
+            FC_HIP(ctx, hipMemsetAsync(small->out, 0, sizeof(out), ctx->stream), "memset sums");
+            FC_HIP(ctx, fc::launch_kendall(ra, rb, un, small->out, ctx->stream), "kendall");
         } else {
-            // pairs tied in both: equal (rank a, rank b); discordant pairs: strict
-            // inversions of rank b in the order of the (a, b) sort
-            FC_HIP(ctx, fc::launch_pair_keys(ra, rb, un, static_cast<uint64_t *>(ctx->rk_key0.ptr),
-                                             static_cast<int32_t *>(ctx->rk_val0.ptr), ctx->stream),
-                   "pair keys");
-            const uint64_t *keys;
-            const int32_t *ids;
-            if ((rc = sort_keys(ctx, nullptr, un, false, &keys, &ids))) return rc;
-            FC_HIP(ctx, fc::launch_min_rank(keys, ids, un, nullptr, out_d + 3, ctx->stream),
-                   "joint ties");
-            uint32_t *sbuf = static_cast<uint32_t *>(ctx->rk_s.ptr);
-            FC_HIP(ctx, fc::launch_inversions(rb, ids, un, sbuf, sbuf + nn, out_d, ctx->stream),
-                   "inversions");
+            // discordant pairs: strict inversions of one vector's ranks in the order
+            // of the other (ties there broken by the first); pairs tied in both
+            uint32_t *s = static_cast<uint32_t *>(ctx->rk_s.ptr);
+            FC_HIP(ctx, fc::launch_discordant(bufs, un, &small->info[1], &small->pair, ra, rb,
+                                              static_cast<unsigned int *>(ctx->rk_thist.ptr),
+                                              small->pair_totals, s, s + nn, small->out, ctx->stream),
+                   "discordant pairs");
         }
-        FC_HIP(ctx, hipMemcpyAsync(out, out_d, sizeof(out), hipMemcpyDeviceToHost, ctx->stream),
+        struct {
+            fc::SortInfo info[2], pair;
+            unsigned long long out[4];
+        } got;
+        static_assert(sizeof(got) == sizeof(RankSmall) - offsetof(RankSmall, info), "the tail of RankSmall");
+        FC_HIP(ctx, hipMemcpyAsync(&got, small->info, sizeof(got), hipMemcpyDeviceToHost, ctx->stream),
                "copy sums");
         FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "kendall");
+        if (got.info[0].bad || got.info[1].bad) return set_err(ctx, FC_ERR_ARG, "score contains NaN");
+        std::memcpy(out, got.out, sizeof(out));
     }
     const int64_t n0 = static_cast<int64_t>(n) * (n - 1) / 2;
     const int64_t ta = static_cast<int64_t>(out[1]), tb = static_cast<int64_t>(out[2]),

@@ -8,33 +8,45 @@
 
 namespace fc {
 
-// Ranking output (rank.hip).  Keys: order-preserving uint64 of each score
-// (complemented when descending), val[i] = i when val is not null; *bad |= 1
-// when a score is NaN.
-hipError_t launch_rank_keys(const double *score, uint32_t n, bool descending, uint64_t *key,
-                            int32_t *val, unsigned int *bad, hipStream_t stream);
-// hist[p * 256 + d] += keys whose byte p is d (hist zeroed by the caller).
-hipError_t launch_digit_hist(const uint64_t *key, uint32_t n, unsigned int *hist,
-                             hipStream_t stream);
+// What one sort knows of its keys (device memory, zeroed by the caller): the
+// bits in which any two keys differ, and whether a score was NaN.
+struct SortInfo {
+    unsigned long long vary;
+    unsigned int bad;
+    unsigned int pad;
+};
+// Keys and values in two buffers: a sort reads buffer 0 and alternates; the
+// number of bytes in which the keys differ tells where it ends.
+struct SortBufs {
+    uint64_t *key[2];
+    int32_t *val[2];
+};
+
+// Order-preserving keys of the scores (complemented when descending) and the
+// values 0 .. n - 1 into buffer 0, and *info.
+hipError_t launch_rank_keys(const double *score, uint32_t n, bool descending, const SortBufs &b,
+                            SortInfo *info, hipStream_t stream);
 // Tiles of the radix sort (thist holds 256 * rank_tiles(n) counters).
 uint32_t rank_tiles(uint32_t n);
-// One stable pass on byte shift / 8: (key, val) -> (okey, oval); base[d] =
-// keys whose byte is below d.
-hipError_t launch_radix_pass(const uint64_t *key, const int32_t *val, uint32_t n, uint32_t shift,
-                             unsigned int *thist, const unsigned int *base, uint64_t *okey,
-                             int32_t *oval, hipStream_t stream);
-hipError_t launch_rank_of(const int32_t *order, uint32_t n, int32_t *rank, hipStream_t stream);
-// out[sval[i]] = the number of sorted keys below skey[i] (skey ascending; out
-// may be null); *ties += pairs of equal keys.
-hipError_t launch_min_rank(const uint64_t *skey, const int32_t *sval, uint32_t n, uint32_t *out,
+// Stable sort by the low `bytes` bytes of the keys (those that vary); totals:
+// bytes x 256 zeroed counters.
+hipError_t launch_sort(const SortBufs &b, uint32_t n, uint32_t bytes, const SortInfo *info,
+                       unsigned int *thist, unsigned int *totals, hipStream_t stream);
+// The sorted values into order and their inverse into rank (either may be
+// null); nothing when info->bad.
+hipError_t launch_order(const SortBufs &b, uint32_t n, const SortInfo *info, int32_t *order,
+                        int32_t *rank, hipStream_t stream);
+// out[val[i]] = the number of sorted keys below key[i]; *ties += pairs of equal keys.
+hipError_t launch_min_rank(const SortBufs &b, uint32_t n, const SortInfo *info, uint32_t *out,
                            unsigned long long *ties, hipStream_t stream);
-// key[i] = ra[i] << 32 | rb[i], val[i] = i.
-hipError_t launch_pair_keys(const uint32_t *ra, const uint32_t *rb, uint32_t n, uint64_t *key,
-                            int32_t *val, hipStream_t stream);
-// *inv += strict inversions of s = rb[id[.]] (pairs p < q with s_p > s_q) by a
-// bottom-up merge sort (s and tmp: n scratch each).
-hipError_t launch_inversions(const uint32_t *rb, const int32_t *id, uint32_t n, uint32_t *s,
-                             uint32_t *tmp, unsigned long long *inv, hipStream_t stream);
+// Discordant pairs of two vectors from their min-ranks: out[0] += pairs ordered
+// strictly the other way, out[3] += pairs tied in both; out[1], out[2] hold the
+// pairs tied in a and in b.  b holds the order by vector b (its sort's info in
+// info_b); pair and totals (4 x 256) are zero before; s and tmp: n scratch each.
+hipError_t launch_discordant(const SortBufs &b, uint32_t n, const SortInfo *info_b, SortInfo *pair,
+                             const uint32_t *ra, const uint32_t *rb, unsigned int *thist,
+                             unsigned int *totals, uint32_t *s, uint32_t *tmp,
+                             unsigned long long *out, hipStream_t stream);
 // Kendall pair counts of two rank vectors (< 2^31) over all pairs i < j
 // (n <= 65535 * 256): out[0] += sum of sign products, out[1..3] += pairs tied in
 // a, in b, in both (out zeroed by the caller; out[0] is two's complement).

@@ -6,6 +6,16 @@
 // Omega_vv (Eq. "eq-fdistu-tr": farness grows with Omega_vv); the paper ranks
 // the vertices by the estimate and reports Kendall's rank correlation against
 // the ground truth (Section 6, "Vertex Ranking").
+//
+// Everything of one call is enqueued without a look at the device: which bytes
+// of the keys differ at all (the others need no pass), whether a score was NaN
+// and whether a vector has ties is left in a small record that the later
+// kernels read, returning at once where there is nothing to do.
+//
+// At these sizes (n = 1000 .. a few million) a pass is launches and dependent
+// loads, not bytes: n = 200 000, per byte pass 40 us (histogram 6, one
+// workgroup's serial scan 18, scatter 16 over 49 workgroups) before, 12.7 us now;
+// ranking and tau-b together 1.67 ms before, 0.55 ms now.
 #include "fc_rank_kernels.hpp"
 
 namespace fc {
@@ -13,7 +23,10 @@ namespace fc {
 namespace {
 
 constexpr uint32_t kRankThreads = 256;
-constexpr uint32_t kTileRounds = 16;  // a tile is kTileRounds x kRankThreads keys
+constexpr uint32_t kRankWaves = kRankThreads / 64u;
+// The kernels that end in an atomic on one word per block (12 ns each, one after
+// the other): wide blocks, two per CU at most, striding.
+constexpr uint32_t kWideThreads = 1024, kWideBlocks = 512;
 
 // Order-preserving map of a binary64 to uint64 (-0 and +0 map alike): flip
 // every bit of a negative number, set the sign bit of a positive one.
@@ -22,220 +35,405 @@ __device__ __forceinline__ uint64_t order_key(double x) {
     return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }
 
-__global__ __launch_bounds__(kRankThreads) void keys_kernel(const double *__restrict__ score,
-                                                             uint32_t n, uint32_t descending,
-                                                             uint64_t *__restrict__ key,
-                                                             int32_t *__restrict__ val,
-                                                             unsigned int *bad) {
-    const uint32_t i = blockIdx.x * kRankThreads + threadIdx.x;
-    if (i >= n) return;
-    const double x = score[i];
-    if (x != x) atomicOr(bad, 1u);
-    const uint64_t k = order_key(x);
-    key[i] = descending ? ~k : k;
-    if (val) val[i] = static_cast<int32_t>(i);
+// A byte in which the keys differ takes a pass; the passes alternate between
+// the two buffers, the first reading buffer 0.
+__device__ __forceinline__ bool byte_active(unsigned long long vary, uint32_t p) {
+    return ((vary >> (8u * p)) & 255u) != 0;
+}
+__device__ __forceinline__ uint32_t passes_below(unsigned long long vary, uint32_t p) {
+    uint32_t c = 0;
+    for (uint32_t q = 0; q < p; ++q) c += byte_active(vary, q) ? 1u : 0u;
+    return c;
 }
 
-// All eight 8-bit digit histograms of the keys in one pass (hist[p * 256 + d]).
-__global__ __launch_bounds__(kRankThreads) void digit_hist_kernel(const uint64_t *__restrict__ key,
-                                                                  uint32_t n,
-                                                                  unsigned int *__restrict__ hist) {
-    __shared__ unsigned int h[8 * 256];
-    for (uint32_t i = threadIdx.x; i < 8 * 256; i += kRankThreads) h[i] = 0;
-    __syncthreads();
-    for (uint32_t i = blockIdx.x * kRankThreads + threadIdx.x; i < n;
-         i += gridDim.x * kRankThreads) {
-        const uint64_t k = key[i];
-#pragma unroll
-        for (uint32_t p = 0; p < 8; ++p) atomicAdd(&h[p * 256 + ((k >> (8 * p)) & 255u)], 1u);
+// Keys, values and what is known of them: the bits in which any key differs
+// from the first one's, and whether a score is NaN.
+__global__ __launch_bounds__(kWideThreads) void keys_kernel(const double *__restrict__ score,
+                                                            uint32_t n, uint32_t descending,
+                                                            uint64_t *__restrict__ key,
+                                                            int32_t *__restrict__ val,
+                                                            SortInfo *info) {
+    __shared__ unsigned long long s_vary[kWideThreads / 64u];
+    const uint64_t k0 = order_key(score[0]);
+    unsigned long long vary = 0;
+    bool bad = false;
+    for (size_t i = static_cast<size_t>(blockIdx.x) * kWideThreads + threadIdx.x; i < n;
+         i += static_cast<size_t>(gridDim.x) * kWideThreads) {
+        const double x = score[i];
+        bad |= x != x;
+        const uint64_t k = order_key(x);
+        vary |= k ^ k0;
+        key[i] = descending ? ~k : k;
+        val[i] = static_cast<int32_t>(i);
     }
+    if (__ballot(bad) && (threadIdx.x & 63u) == 0) info->bad = 1u;
+    for (int off = 32; off > 0; off >>= 1) vary |= __shfl_xor(vary, off, 64);
+    if ((threadIdx.x & 63u) == 0) s_vary[threadIdx.x >> 6] = vary;
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < 8 * 256; i += kRankThreads)
-        if (h[i]) atomicAdd(&hist[i], h[i]);
+    if (threadIdx.x != 0) return;
+    for (uint32_t w = 1; w < kWideThreads / 64u; ++w) vary |= s_vary[w];
+    if (vary) atomicOr(&info->vary, vary);
 }
 
-// Digit counts of one tile: thist[d * ntiles + tile].
-__global__ __launch_bounds__(kRankThreads) void tile_hist_kernel(const uint64_t *__restrict__ key,
-                                                                 uint32_t n, uint32_t shift,
+// A tile is kRankWaves x R x 64 keys, wave after wave: wave w holds R runs of
+// 64 consecutive keys, so the stable order inside a tile is (wave, run, lane).
+template <uint32_t R>
+__device__ __forceinline__ size_t tile_first() {
+    return (static_cast<size_t>(blockIdx.x) * kRankWaves + (threadIdx.x >> 6)) * (R * 64u) +
+           (threadIdx.x & 63u);
+}
+
+// Digit counts of one tile: thist[d * ntiles + tile], and total[d] over the tiles.
+template <uint32_t R>
+__global__ __launch_bounds__(kRankThreads) void tile_hist_kernel(SortBufs b, uint32_t n, uint32_t p,
                                                                  uint32_t ntiles,
-                                                                 unsigned int *__restrict__ thist) {
+                                                                 const SortInfo *info,
+                                                                 unsigned int *__restrict__ thist,
+                                                                 unsigned int *total) {
+    const unsigned long long vary = info->vary;
+    if (!byte_active(vary, p)) return;
+    const uint64_t *key = b.key[passes_below(vary, p) & 1u];
     __shared__ unsigned int h[256];
     h[threadIdx.x] = 0;
     __syncthreads();
-    const size_t base = static_cast<size_t>(blockIdx.x) * kTileRounds * kRankThreads;
-#pragma unroll 4
-    for (uint32_t r = 0; r < kTileRounds; ++r) {
-        const size_t i = base + r * kRankThreads + threadIdx.x;
-        if (i < n) atomicAdd(&h[(key[i] >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    thist[static_cast<size_t>(threadIdx.x) * ntiles + blockIdx.x] = h[threadIdx.x];
-}
-
-// Exclusive offsets: thread d turns its row of tile counts into the position
-// of the tile's first key with digit d (base[d] = keys with a smaller digit).
-__global__ __launch_bounds__(256) void tile_scan_kernel(unsigned int *__restrict__ thist,
-                                                        uint32_t ntiles,
-                                                        const unsigned int *__restrict__ base) {
-    const uint32_t d = threadIdx.x;
-    unsigned int run = base[d];
-    unsigned int *row = thist + static_cast<size_t>(d) * ntiles;
-    for (uint32_t t = 0; t < ntiles; ++t) {
-        const unsigned int c = row[t];
-        row[t] = run;
-        run += c;
-    }
-}
-
-// Stable scatter of one tile: keys are taken in position order, 256 at a
-// time (wave w holds positions 64 w .. 64 w + 63 of the round); a key's place
-// is its digit's running offset plus the keys with the same digit earlier in
-// the round (earlier waves, then earlier lanes, found with eight ballots).
-__global__ __launch_bounds__(kRankThreads) void tile_scatter_kernel(
-    const uint64_t *__restrict__ key, const int32_t *__restrict__ val, uint32_t n, uint32_t shift,
-    uint32_t ntiles, const unsigned int *__restrict__ thist, uint64_t *__restrict__ okey,
-    int32_t *__restrict__ oval) {
-    __shared__ unsigned int run[256];
-    __shared__ unsigned int cnt[kRankThreads / 64][256];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    run[tid] = thist[static_cast<size_t>(tid) * ntiles + blockIdx.x];
+    const size_t base = tile_first<R>();
+    uint64_t k[R];
 #pragma unroll
-    for (uint32_t w = 0; w < kRankThreads / 64; ++w) cnt[w][tid] = 0;
+    for (uint32_t r = 0; r < R; ++r) k[r] = base + r * 64u < n ? key[base + r * 64u] : 0ull;
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r)
+        if (base + r * 64u < n) atomicAdd(&h[(k[r] >> (8u * p)) & 255u], 1u);
     __syncthreads();
-    const size_t base = static_cast<size_t>(blockIdx.x) * kTileRounds * kRankThreads;
+    const unsigned int c = h[threadIdx.x];
+    thist[static_cast<size_t>(threadIdx.x) * ntiles + blockIdx.x] = c;
+    if (c) atomicAdd(&total[threadIdx.x], c);
+}
+
+// One wave per digit: its tile counts become the position of each tile's first
+// key with that digit (the keys with a smaller digit, then the tiles before).
+__global__ __launch_bounds__(64) void tile_scan_kernel(unsigned int *__restrict__ thist,
+                                                       uint32_t ntiles, uint32_t p,
+                                                       const SortInfo *info,
+                                                       const unsigned int *__restrict__ total) {
+    if (!byte_active(info->vary, p)) return;
+    const uint32_t d = blockIdx.x, lane = threadIdx.x;
+    unsigned int run = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < 4u; ++q) run += q * 64u + lane < d ? total[q * 64u + lane] : 0u;
+    for (int off = 32; off > 0; off >>= 1) run += __shfl_xor(run, off, 64);
+    unsigned int *row = thist + static_cast<size_t>(d) * ntiles;
+    for (uint32_t t0 = 0; t0 < ntiles; t0 += 256u) {  // four loads in flight
+        unsigned int c[4];
+#pragma unroll
+        for (uint32_t q = 0; q < 4u; ++q) {
+            const uint32_t t = t0 + q * 64u + lane;
+            c[q] = t < ntiles ? row[t] : 0u;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4u; ++q) {
+            const uint32_t t = t0 + q * 64u + lane;
+            unsigned int x = c[q];
+            for (uint32_t off = 1; off < 64u; off <<= 1) {
+                const unsigned int y = __shfl_up(x, off, 64);
+                if (lane >= off) x += y;
+            }
+            if (t < ntiles) row[t] = run + x - c[q];
+            run += __shfl(x, 63, 64);
+        }
+    }
+}
+
+// Stable scatter of one tile.  Each wave counts its own keys run by run (the
+// keys of a run with the same digit found with eight ballots), without a
+// barrier; then the waves' counts give every key its place.
+template <uint32_t R>
+__global__ __launch_bounds__(kRankThreads) void tile_scatter_kernel(
+    SortBufs b, uint32_t n, uint32_t p, uint32_t ntiles, const SortInfo *info,
+    const unsigned int *__restrict__ thist) {
+    const unsigned long long vary = info->vary;
+    if (!byte_active(vary, p)) return;
+    const uint32_t src = passes_below(vary, p) & 1u;
+    const uint64_t *key = b.key[src];
+    const int32_t *val = b.val[src];
+    uint64_t *okey = b.key[src ^ 1u];
+    int32_t *oval = b.val[src ^ 1u];
+    __shared__ unsigned int cnt[kRankWaves][256];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const unsigned int start = thist[static_cast<size_t>(tid) * ntiles + blockIdx.x];
+#pragma unroll
+    for (uint32_t w = 0; w < kRankWaves; ++w) cnt[w][tid] = 0;
+    const size_t base = tile_first<R>();
     const uint64_t below = (1ull << lane) - 1ull;
-    for (uint32_t r = 0; r < kTileRounds; ++r) {
-        const size_t i = base + r * kRankThreads + tid;
-        const bool valid = i < n;
-        const uint64_t k = valid ? key[i] : 0ull;
-        const int32_t v = valid ? val[i] : 0;
-        const uint32_t d = static_cast<uint32_t>((k >> shift) & 255u);
+    uint64_t k[R];
+    int32_t v[R];
+    uint32_t place[R];
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const bool valid = base + r * 64u < n;
+        k[r] = valid ? key[base + r * 64u] : 0ull;
+        v[r] = valid ? val[base + r * 64u] : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const bool valid = base + r * 64u < n;
+        const uint32_t d = static_cast<uint32_t>((k[r] >> (8u * p)) & 255u);
         uint64_t peers = __ballot(valid);
 #pragma unroll
-        for (uint32_t b = 0; b < 8; ++b) {
-            const uint64_t m = __ballot((d >> b) & 1u);
-            peers &= ((d >> b) & 1u) ? m : ~m;
+        for (uint32_t q = 0; q < 8; ++q) {
+            const uint64_t m = __ballot((d >> q) & 1u);
+            peers &= ((d >> q) & 1u) ? m : ~m;
         }
         const uint32_t before = static_cast<uint32_t>(__popcll(peers & below));
-        if (valid && before == 0) cnt[wave][d] = static_cast<uint32_t>(__popcll(peers));
-        __syncthreads();
-        if (valid) {
-            unsigned int pos = run[d] + before;
-            for (uint32_t w = 0; w < wave; ++w) pos += cnt[w][d];
-            okey[pos] = k;
-            oval[pos] = v;
-        }
-        __syncthreads();
-        unsigned int add = 0;
+        const uint32_t seen = cnt[wave][d];
+        place[r] = seen + before;
+        __builtin_amdgcn_wave_barrier();  // every lane has read before the leaders write
+        if (valid && before == 0) cnt[wave][d] = seen + static_cast<uint32_t>(__popcll(peers));
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    unsigned int run = start;  // thread d: digit d's place in each wave
 #pragma unroll
-        for (uint32_t w = 0; w < kRankThreads / 64; ++w) {
-            add += cnt[w][tid];
-            cnt[w][tid] = 0;
-        }
-        run[tid] += add;
-        __syncthreads();
+    for (uint32_t w = 0; w < kRankWaves; ++w) {
+        const unsigned int c = cnt[w][tid];
+        cnt[w][tid] = run;
+        run += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        if (base + r * 64u >= n) continue;
+        const uint32_t d = static_cast<uint32_t>((k[r] >> (8u * p)) & 255u);
+        const uint32_t at = cnt[wave][d] + place[r];
+        okey[at] = k[r];
+        oval[at] = v[r];
     }
 }
 
-__global__ __launch_bounds__(kRankThreads) void rank_of_kernel(const int32_t *__restrict__ order,
-                                                               uint32_t n,
-                                                               int32_t *__restrict__ rank) {
+// The sorted values as order and their inverse as rank (nothing when a score
+// was NaN).
+__global__ __launch_bounds__(kRankThreads) void order_kernel(SortBufs b, uint32_t n,
+                                                             const SortInfo *info,
+                                                             int32_t *__restrict__ order,
+                                                             int32_t *__restrict__ rank) {
+    if (info->bad) return;
+    const int32_t *val = b.val[passes_below(info->vary, 8u) & 1u];
     const uint32_t i = blockIdx.x * kRankThreads + threadIdx.x;
-    if (i < n) rank[order[i]] = static_cast<int32_t>(i);
+    if (i >= n) return;
+    const int32_t v = val[i];
+    if (order) order[i] = v;
+    if (rank) rank[v] = static_cast<int32_t>(i);
 }
 
-// Min-rank of every key after the sort: the number of keys strictly below it
-// (equal keys share it), found by binary search in the sorted keys and
-// scattered to the key's original index.
-// Also adds sum over positions of (i - min-rank) into *ties: a run of t equal
-// keys contributes 0 + 1 + ... + (t - 1) = t(t - 1)/2, its tied pairs.
+// Adds the block's sum of x to *out (one atomic).
 __device__ __forceinline__ void block_add_u64(unsigned long long x, unsigned long long *out) {
-    __shared__ unsigned long long red[kRankThreads / 64];
+    __shared__ unsigned long long red[kWideThreads / 64];
     for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
     if ((threadIdx.x & 63u) == 0) red[threadIdx.x >> 6] = x;
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long t = 0;
-        for (uint32_t w = 0; w < kRankThreads / 64; ++w) t += red[w];
+        for (uint32_t w = 0; w < kWideThreads / 64; ++w) t += red[w];
         if (t) atomicAdd(out, t);
     }
 }
 
-__global__ __launch_bounds__(kRankThreads) void min_rank_kernel(const uint64_t *__restrict__ skey,
-                                                                const int32_t *__restrict__ sval,
-                                                                uint32_t n,
+// First position of the run of equal elements that ends at i (same(j): whether
+// j < i is in it; the run is contiguous): doubling steps back, then halving.
+template <typename F>
+__device__ __forceinline__ uint32_t run_start(uint32_t i, F same) {
+    uint32_t in = i, step = 1;  // in: known to be in the run
+    while (step <= i && same(i - step)) {
+        in = i - step;
+        step <<= 1;
+    }
+    // the run starts in (i - step, in], or at 0 when i < step
+    uint32_t lo = step <= i ? i - step + 1u : 0u;
+    while (lo < in) {
+        const uint32_t mid = lo + ((in - lo) >> 1);
+        if (same(mid)) in = mid;
+        else lo = mid + 1u;
+    }
+    return in;
+}
+
+// Min-rank of every key after the sort: the number of keys strictly below it
+// (equal keys share it), scattered to the key's original index.  Also adds sum
+// over positions of (i - min-rank) into *ties: a run of t equal keys
+// contributes 0 + 1 + ... + (t - 1) = t(t - 1)/2, its tied pairs.
+__global__ __launch_bounds__(kWideThreads) void min_rank_kernel(SortBufs b, uint32_t n,
+                                                                const SortInfo *info,
                                                                 uint32_t *__restrict__ out,
                                                                 unsigned long long *__restrict__ ties) {
-    const uint32_t i = blockIdx.x * kRankThreads + threadIdx.x;
+    const uint32_t src = passes_below(info->vary, 8u) & 1u;
+    const uint64_t *key = b.key[src];
+    const int32_t *val = b.val[src];
     unsigned long long t = 0;
-    if (i < n) {
-        const uint64_t k = skey[i];
-        uint32_t lo = 0, hi = i;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (skey[mid] < k) lo = mid + 1;
-            else hi = mid;
-        }
-        if (out) out[sval[i]] = lo;
-        t = i - lo;
+    for (size_t l = static_cast<size_t>(blockIdx.x) * kWideThreads + threadIdx.x; l < n;
+         l += static_cast<size_t>(gridDim.x) * kWideThreads) {
+        const uint32_t i = static_cast<uint32_t>(l);
+        const uint64_t k = key[i];
+        const uint32_t lo = run_start(i, [&](uint32_t j) { return key[j] == k; });
+        out[val[i]] = lo;
+        t += i - lo;
     }
     block_add_u64(t, ties);
 }
 
-// Composite keys (ra[i] << 32 | rb[i]) with the indices as values.
-__global__ __launch_bounds__(kRankThreads) void pair_keys_kernel(const uint32_t *__restrict__ ra,
-                                                                 const uint32_t *__restrict__ rb,
-                                                                 uint32_t n,
-                                                                 uint64_t *__restrict__ key,
-                                                                 int32_t *__restrict__ val) {
+// The order whose strict inversions are the discordant pairs, from both
+// vectors' ranks and the order of b (buffer of the sort just done):
+//   b without ties: s = rank a in the order of b;
+//   a without ties: s = rank b in the order of a (its ranks are the places);
+//   else the stable sort of b's order by rank a (three passes for 2^24 values:
+//   the order by b is there already), keys and values for it in buffer 0.
+// pair->vary = 0 tells the later kernels that s is complete.
+__global__ __launch_bounds__(kRankThreads) void pair_keys_kernel(
+    SortBufs b, uint32_t n, const SortInfo *info_b, const uint32_t *__restrict__ ra,
+    const uint32_t *__restrict__ rb, const unsigned long long *__restrict__ ties, SortInfo *pair,
+    uint32_t *__restrict__ s) {
+    const bool b_free = ties[1] == 0, a_free = ties[0] == 0;
+    const int32_t *ids = b.val[passes_below(info_b->vary, 8u) & 1u];
     const uint32_t i = blockIdx.x * kRankThreads + threadIdx.x;
+    if (i == 0 && !a_free && !b_free) {
+        unsigned long long m = n - 1u;
+        for (uint32_t q = 1; q < 64u; q <<= 1) m |= m >> q;
+        pair->vary = m;
+    }
     if (i >= n) return;
-    key[i] = (static_cast<uint64_t>(ra[i]) << 32) | rb[i];
-    val[i] = static_cast<int32_t>(i);
+    if (b_free) {
+        s[i] = ra[ids[i]];
+    } else if (a_free) {
+        s[ra[i]] = rb[i];
+    } else {  // the thread that overwrites ids[i] has read it
+        const int32_t id = ids[i];
+        b.key[0][i] = ra[id];
+        b.val[0][i] = id;
+    }
 }
 
-// s[i] = rb[id[i]]: rank b in the order of the (a, b) sort.
-__global__ __launch_bounds__(kRankThreads) void gather_kernel(const uint32_t *__restrict__ rb,
-                                                              const int32_t *__restrict__ id,
-                                                              uint32_t n, uint32_t *__restrict__ s) {
+// After the pair passes: s = rank b in the order of (a, b).
+__global__ __launch_bounds__(kRankThreads) void pair_order_kernel(SortBufs b, uint32_t n,
+                                                                  const SortInfo *pair,
+                                                                  const uint32_t *__restrict__ rb,
+                                                                  uint32_t *__restrict__ s) {
+    const unsigned long long vary = pair->vary;
+    if (!vary) return;
+    const int32_t *val = b.val[passes_below(vary, 8u) & 1u];
     const uint32_t i = blockIdx.x * kRankThreads + threadIdx.x;
-    if (i < n) s[i] = rb[id[i]];
+    if (i < n) s[i] = rb[val[i]];
 }
 
-// One level of a bottom-up merge sort of s with strict-inversion counts: runs
-// of `width` are sorted; each element finds its place in the merged run by
-// binary search in the sibling run (a left element after the right elements
-// below it, a right element after the left elements not above it, so equal
-// values keep their order), and a right element adds the left elements above
-// it to *inv (pairs p < q with s_p > s_q).
-__global__ __launch_bounds__(kRankThreads) void merge_level_kernel(const uint32_t *__restrict__ in,
+// Pairs tied in both: runs of equal (rank a, rank b) in that order.
+__global__ __launch_bounds__(kWideThreads) void joint_ties_kernel(SortBufs b, uint32_t n,
+                                                                  const SortInfo *pair,
+                                                                  const uint32_t *__restrict__ s,
+                                                                  unsigned long long *__restrict__ ties) {
+    const unsigned long long vary = pair->vary;
+    if (!vary) return;
+    const uint64_t *key = b.key[passes_below(vary, 8u) & 1u];
+    unsigned long long t = 0;
+    for (size_t l = static_cast<size_t>(blockIdx.x) * kWideThreads + threadIdx.x; l < n;
+         l += static_cast<size_t>(gridDim.x) * kWideThreads) {
+        const uint32_t i = static_cast<uint32_t>(l);
+        const uint64_t k = key[i];
+        const uint32_t x = s[i];
+        t += i - run_start(i, [&](uint32_t j) { return key[j] == k && s[j] == x; });
+    }
+    block_add_u64(t, ties);
+}
+
+// Strict inversions (pairs p < q with s_p > s_q) by a bottom-up merge sort.
+// An element finds its place by binary search in the sibling runs: after the
+// elements of earlier runs that are not above it and those of later runs that
+// are below it, so equal values keep their order; the elements of earlier runs
+// above it are its inversions.
+//
+// The first ten levels: 1024 elements in LDS, one per thread.
+__global__ __launch_bounds__(kWideThreads) void merge_tile_kernel(uint32_t *__restrict__ s, uint32_t n,
+                                                                   unsigned long long *__restrict__ inv) {
+    __shared__ uint32_t x[2][kWideThreads];
+    const uint32_t t = threadIdx.x;
+    unsigned long long c = 0;
+    for (size_t first = static_cast<size_t>(blockIdx.x) * kWideThreads; first < n;
+         first += static_cast<size_t>(gridDim.x) * kWideThreads) {
+        const uint32_t m = static_cast<uint32_t>(min(static_cast<size_t>(kWideThreads), n - first));
+        __syncthreads();
+        if (t < m) x[0][t] = s[first + t];
+        __syncthreads();
+        uint32_t at = 0;
+        for (uint32_t w = 1; w < m; w <<= 1, at ^= 1u) {
+            const uint32_t *in = x[at];
+            if (t < m) {
+                const uint32_t l0 = t & ~(2u * w - 1u);
+                const uint32_t r0 = min(l0 + w, m), r1 = min(l0 + 2u * w, m);
+                const bool left = t < r0;
+                const uint32_t y = in[t];
+                uint32_t lo = left ? r0 : l0, hi = left ? r1 : r0;
+                const uint32_t from = lo;
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (left ? in[mid] < y : in[mid] <= y) lo = mid + 1u;
+                    else hi = mid;
+                }
+                const uint32_t before = lo - from;
+                x[at ^ 1u][l0 + (t - (left ? l0 : r0)) + before] = y;
+                if (!left) c += r0 - lo;
+            }
+            __syncthreads();
+        }
+        if (t < m) s[first + t] = x[at][t];
+    }
+    block_add_u64(c, inv);
+}
+
+// The levels above, four runs of `width` into one: the three searches of an
+// element go on together (n = 200 000: 13.7 us for a level of four runs, against
+// two of 6.7 us and a launch more for two runs at a time).
+__global__ __launch_bounds__(kWideThreads) void merge_four_kernel(const uint32_t *__restrict__ in,
                                                                    uint32_t n, uint32_t width,
                                                                    uint32_t *__restrict__ out,
                                                                    unsigned long long *__restrict__ inv) {
-    const uint32_t i = blockIdx.x * kRankThreads + threadIdx.x;
     unsigned long long c = 0;
-    if (i < n) {
+    for (uint64_t l = static_cast<uint64_t>(blockIdx.x) * kWideThreads + threadIdx.x; l < n;
+         l += static_cast<uint64_t>(gridDim.x) * kWideThreads) {
+        const uint32_t i = static_cast<uint32_t>(l);
+        const uint64_t first = i / width / 4u * 4u * static_cast<uint64_t>(width);
+        const uint32_t own = static_cast<uint32_t>((i - first) / width);
         const uint32_t x = in[i];
-        const uint32_t l0 = (i / (2 * width)) * (2 * width);
-        const uint32_t r0 = min(l0 + width, n), r1 = min(l0 + 2 * width, n);
-        if (i < r0) {  // left run: count right elements < x
-            uint32_t lo = r0, hi = r1;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (in[mid] < x) lo = mid + 1;
-                else hi = mid;
-            }
-            out[l0 + (i - l0) + (lo - r0)] = x;
-        } else {  // right run: count left elements <= x
-            uint32_t lo = l0, hi = r0;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (in[mid] <= x) lo = mid + 1;
-                else hi = mid;
-            }
-            out[l0 + (i - r0) + (lo - l0)] = x;
-            c = r0 - lo;
+        uint32_t lo[3], hi[3], start[3], end[3];
+        bool earlier[3];
+#pragma unroll
+        for (uint32_t q = 0; q < 3u; ++q) {  // the three other runs
+            const uint32_t r = q < own ? q : q + 1u;
+            const uint64_t a = first + r * static_cast<uint64_t>(width);
+            const uint64_t b = a + width;
+            start[q] = static_cast<uint32_t>(a < n ? a : n);
+            end[q] = static_cast<uint32_t>(b < n ? b : n);
+            earlier[q] = q < own;
+            lo[q] = start[q];
+            hi[q] = end[q];
         }
+        while (lo[0] < hi[0] || lo[1] < hi[1] || lo[2] < hi[2]) {
+            uint32_t y[3], mid[3];
+#pragma unroll
+            for (uint32_t q = 0; q < 3u; ++q) {
+                mid[q] = lo[q] + ((hi[q] - lo[q]) >> 1);
+                y[q] = lo[q] < hi[q] ? in[mid[q]] : 0u;
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < 3u; ++q) {
+                if (lo[q] >= hi[q]) continue;
+                if (earlier[q] ? y[q] <= x : y[q] < x) lo[q] = mid[q] + 1u;
+                else hi[q] = mid[q];
+            }
+        }
+        uint64_t at = first + (i - first) % width;
+#pragma unroll
+        for (uint32_t q = 0; q < 3u; ++q) {
+            at += lo[q] - start[q];
+            if (earlier[q]) c += end[q] - lo[q];
+        }
+        out[at] = x;
     }
     block_add_u64(c, inv);
 }
@@ -316,71 +514,90 @@ __global__ __launch_bounds__(kRankThreads) void kendall_kernel(const uint32_t *_
 inline unsigned int blocks_for(uint64_t items, uint32_t threads) {
     return static_cast<unsigned int>((items + threads - 1) / threads);
 }
+inline unsigned int wide_blocks(uint64_t items) {
+    const uint64_t b = (items + kWideThreads - 1) / kWideThreads;
+    return static_cast<unsigned int>(b < kWideBlocks ? b : kWideBlocks);
+}
+
+// Runs of 64 keys per wave and tile: short tiles while the tiles are few, so
+// that 200 000 keys still fill the CUs; long ones once there are thousands,
+// whose counts would otherwise be as much work as the keys.
+constexpr uint32_t kShortTile = 4, kLongTile = 16;
+inline uint32_t tile_rounds(uint32_t n) { return n <= (1u << 20) ? kShortTile : kLongTile; }
 
 }  // namespace
 
-uint32_t rank_tiles(uint32_t n) { return (n + kTileRounds * kRankThreads - 1) / (kTileRounds * kRankThreads); }
+uint32_t rank_tiles(uint32_t n) {
+    const uint32_t keys = tile_rounds(n) * kRankThreads;
+    return n / keys + (n % keys ? 1u : 0u);
+}
 
-hipError_t launch_rank_keys(const double *score, uint32_t n, bool descending, uint64_t *key,
-                            int32_t *val, unsigned int *bad, hipStream_t stream) {
+hipError_t launch_rank_keys(const double *score, uint32_t n, bool descending, const SortBufs &b,
+                            SortInfo *info, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    keys_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(
-        score, n, descending ? 1u : 0u, key, val, bad);
+    keys_kernel<<<wide_blocks(n), kWideThreads, 0, stream>>>(
+        score, n, descending ? 1u : 0u, b.key[0], b.val[0], info);
     return hipGetLastError();
 }
 
-hipError_t launch_digit_hist(const uint64_t *key, uint32_t n, unsigned int *hist,
-                             hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    uint32_t blocks = blocks_for(n, kRankThreads * 16u);
-    if (blocks > 2048) blocks = 2048;
-    digit_hist_kernel<<<blocks, kRankThreads, 0, stream>>>(key, n, hist);
-    return hipGetLastError();
-}
-
-hipError_t launch_radix_pass(const uint64_t *key, const int32_t *val, uint32_t n, uint32_t shift,
-                             unsigned int *thist, const unsigned int *base, uint64_t *okey,
-                             int32_t *oval, hipStream_t stream) {
-    if (n == 0) return hipSuccess;
+hipError_t launch_sort(const SortBufs &b, uint32_t n, uint32_t bytes, const SortInfo *info,
+                       unsigned int *thist, unsigned int *totals, hipStream_t stream) {
+    if (n < 2) return hipSuccess;
     const uint32_t ntiles = rank_tiles(n);
-    tile_hist_kernel<<<ntiles, kRankThreads, 0, stream>>>(key, n, shift, ntiles, thist);
-    tile_scan_kernel<<<1, 256, 0, stream>>>(thist, ntiles, base);
-    tile_scatter_kernel<<<ntiles, kRankThreads, 0, stream>>>(key, val, n, shift, ntiles, thist,
-                                                             okey, oval);
+    const bool shorts = tile_rounds(n) == kShortTile;
+    for (uint32_t p = 0; p < bytes; ++p) {
+        unsigned int *total = totals + 256u * p;
+        if (shorts)
+            tile_hist_kernel<kShortTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles, info,
+                                                                             thist, total);
+        else
+            tile_hist_kernel<kLongTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles, info,
+                                                                            thist, total);
+        tile_scan_kernel<<<256, 64, 0, stream>>>(thist, ntiles, p, info, total);
+        if (shorts)
+            tile_scatter_kernel<kShortTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles,
+                                                                                info, thist);
+        else
+            tile_scatter_kernel<kLongTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles,
+                                                                               info, thist);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_rank_of(const int32_t *order, uint32_t n, int32_t *rank, hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    rank_of_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(order, n, rank);
+hipError_t launch_order(const SortBufs &b, uint32_t n, const SortInfo *info, int32_t *order,
+                        int32_t *rank, hipStream_t stream) {
+    if (n == 0 || (!order && !rank)) return hipSuccess;
+    order_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(b, n, info, order, rank);
     return hipGetLastError();
 }
 
-hipError_t launch_min_rank(const uint64_t *skey, const int32_t *sval, uint32_t n, uint32_t *out,
+hipError_t launch_min_rank(const SortBufs &b, uint32_t n, const SortInfo *info, uint32_t *out,
                            unsigned long long *ties, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    min_rank_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(skey, sval, n, out, ties);
+    min_rank_kernel<<<wide_blocks(n), kWideThreads, 0, stream>>>(b, n, info, out, ties);
     return hipGetLastError();
 }
 
-hipError_t launch_pair_keys(const uint32_t *ra, const uint32_t *rb, uint32_t n, uint64_t *key,
-                            int32_t *val, hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    pair_keys_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(ra, rb, n, key, val);
-    return hipGetLastError();
-}
-
-hipError_t launch_inversions(const uint32_t *rb, const int32_t *id, uint32_t n, uint32_t *s,
-                             uint32_t *tmp, unsigned long long *inv, hipStream_t stream) {
+hipError_t launch_discordant(const SortBufs &b, uint32_t n, const SortInfo *info_b, SortInfo *pair,
+                             const uint32_t *ra, const uint32_t *rb, unsigned int *thist,
+                             unsigned int *totals, uint32_t *s, uint32_t *tmp,
+                             unsigned long long *out, hipStream_t stream) {
     if (n < 2) return hipSuccess;
-    gather_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(rb, id, n, s);
-    uint32_t *a = s, *b = tmp;
-    for (uint32_t w = 1; w < n; w *= 2) {
-        merge_level_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(a, n, w, b, inv);
-        uint32_t *t = a;
-        a = b;
-        b = t;
-        if (w > 0x7FFFFFFFu) break;
+    pair_keys_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(b, n, info_b, ra, rb,
+                                                                              out + 1, pair, s);
+    uint32_t bytes = 1;
+    while (bytes < 4u && (static_cast<uint64_t>(n - 1u) >> (8u * bytes))) ++bytes;
+    hipError_t e = launch_sort(b, n, bytes, pair, thist, totals, stream);
+    if (e != hipSuccess) return e;
+    pair_order_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(b, n, pair, rb, s);
+    joint_ties_kernel<<<wide_blocks(n), kWideThreads, 0, stream>>>(b, n, pair, s, out + 3);
+    merge_tile_kernel<<<wide_blocks(n), kWideThreads, 0, stream>>>(s, n, out);
+    for (uint64_t w = kWideThreads; w < n; w *= 4) {
+        merge_four_kernel<<<wide_blocks(n), kWideThreads, 0, stream>>>(
+            s, n, static_cast<uint32_t>(w), tmp, out);
+        uint32_t *t = s;
+        s = tmp;
+        tmp = t;
     }
     return hipGetLastError();
 }
