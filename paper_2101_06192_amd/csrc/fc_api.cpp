@@ -301,13 +301,59 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     bool lds_bits = false, in_bits = false, word32 = false;
     uint32_t repop_words = 0;  // global-counter sampler: re-pop filter words (0: off)
     bool use_lds = false, use_hyb = false, use_tile = false;
+    size_t jump_lds = 0;  // LDS of one tree of the small-graph variant (0: not used)
     fc::TileArgs ta{};
     uint32_t tile_threads = 1024;
     uint32_t lds_words = 0, lds_threads = 1024, hot = 0;
     bool lds_lean = false;  // LDS-counter sampler: the lean register shape
     uint32_t tshift = 32;
     unsigned int dmax = 0;
-    if (use_coop) {
+    // small graphs: the whole tree in LDS (reported as wilson_lds, whose place it
+    // takes in the automatic choice)
+    if (mode == 0 && ctx->coop_lds_counts && !ctx->phase_timing &&
+        static_cast<uint32_t>(g.n) <= fc::kJumpMax &&
+        fc::jump_lds_bytes(static_cast<uint32_t>(g.n)) + kLdsStaticBytes <= ctx->max_lds)
+        jump_lds = fc::jump_lds_bytes(static_cast<uint32_t>(g.n));
+    if (jump_lds) {
+        kname = "wilson_lds";
+        const uint32_t n = static_cast<uint32_t>(g.n);
+        lds_threads = jump_threads_for(ctx, n, tree_count);
+        const int fit = fc::jump_max_active(lds_threads, jump_lds, weighted);
+        slots = std::max<size_t>(1, state_budget_now(ctx) / (4u * static_cast<size_t>(n)));
+        slots = std::min<size_t>(slots, tree_count);
+        slots = std::min<size_t>(slots, static_cast<size_t>(ctx->cu_count) *
+                                            static_cast<size_t>(std::max(1, fit)));
+        if (ctx->max_slots) slots = std::min<size_t>(slots, ctx->max_slots);
+        if ((rc = ensure(ctx, ctx->cword, 4u * static_cast<size_t>(n) * slots, "draw counts"))) return rc;
+        c.word = ctx->cword.ptr;
+        c.n_max = n;
+        c.slots = static_cast<uint32_t>(slots);
+        c.item_count = tree_count;
+        c.key0 = static_cast<uint32_t>(p->seed);
+        c.key1 = static_cast<uint32_t>(p->seed >> 32);
+        c.max_rounds = 0x40000000u;
+        // the limit of the tree words that the LDS-counter variant keeps counts in
+        c.k_limit = ctx->max_draws ? std::min(ctx->max_draws, 0x0FFFFFFFu) : 0x0FFFFFFFu;
+        c.queue = &sm->queue;
+        c.totals = &sm->totals;
+        fc::CoopJob &j = c.single;
+        j.vrec = vrec;
+        j.col_idx = g.col_idx;
+        j.wsum = wsum;
+        j.wthr = wthr;
+        j.n = n;
+        j.tree_count = tree_count;
+        j.stream_id = p->stream_id;
+        j.tree_begin = tree_begin;
+        j.step_cap = step_cap;
+        j.root_counts = root_counts;
+        j.visit_counts = reinterpret_cast<unsigned long long *>(visit_counts);
+        j.tree_digests = reinterpret_cast<unsigned long long *>(tree_digests);
+        j.tree_steps = reinterpret_cast<unsigned long long *>(tree_steps);
+        j.parents = parents;
+        j.tree_visits = tree_visits;
+    }
+    if (use_coop && !jump_lds) {
         // LDS-counter variant when the degree-class count fields and the settled
         // bitmap of one tree fit in LDS (at least 4 + 1 bits per vertex)
         // (isolated vertices need no LDS, so only the id width bounds n here)
@@ -657,7 +703,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         ta.parents = parents;
         ta.tree_visits = tree_visits;
     }
-    if (use_coop && !use_lds && !use_hyb && !use_tile) {
+    if (use_coop && !jump_lds && !use_lds && !use_hyb && !use_tile) {
         // 32-bit tree words when target and in-arrow count both fit (the count of
         // a vertex never exceeds its degree)
         word_layout(static_cast<uint32_t>(g.n), dmax, ctx->coop_word32, &tshift, &word32);
@@ -766,7 +812,10 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     }
 
     FC_HIP(ctx, hipEventRecord(ctx->ev0, ctx->stream), "event");
-    if (use_tile) {
+    if (jump_lds) {
+        FC_HIP(ctx, fc::launch_wilson_jump(c, lds_threads, jump_lds, weighted, ctx->stream),
+               "wilson_jump launch");
+    } else if (use_tile) {
         if (ta.pre) {
             FC_HIP(ctx, fc::launch_tile_predraw(ta, ctx->stream), "tile_predraw launch");
             FC_HIP(ctx, hipEventRecord(ctx->evm, ctx->stream), "event");
@@ -800,7 +849,8 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     if (tot.error & fc::kErrVisitOverflow)
         return set_err(ctx, FC_ERR_OVERFLOW,
                        ctx->max_draws ? "a per-vertex draw count exceeded option max_draws"
-                       : use_lds ? "a per-vertex draw count exceeded 2^28 - 1 (the LDS-counter "
+                       : use_lds || jump_lds
+                           ? "a per-vertex draw count exceeded 2^28 - 1 (the LDS-counter "
                                    "sampler's limit; option coop_lds_counts = 0 allows 2^31 - 1)"
                                  : "a per-vertex visit counter exceeded 2^31 - 1");
     if (stats) {
@@ -880,6 +930,16 @@ uint32_t lds_threads_for(const fc_ctx *ctx, uint64_t trees, uint32_t lds_words) 
     return t;
 }
 
+uint32_t jump_threads_for(const fc_ctx *ctx, uint32_t n, uint64_t trees) {
+    const uint32_t least = std::max<uint32_t>(64u, (n + fc::kJumpOwn - 1) / fc::kJumpOwn);
+    uint32_t t = 1024u;
+    if (ctx->lds_threads >= least) return ctx->lds_threads;
+    const uint64_t fit_lds = ctx->max_lds / (fc::jump_lds_bytes(n) + kLdsStaticBytes);
+    const uint64_t per_cu = std::min<uint64_t>((trees + ctx->cu_count - 1) / ctx->cu_count, fit_lds);
+    while (t / 2 >= least && 2048u / t < per_cu) t /= 2;
+    return t;
+}
+
 int begin(fc_ctx *ctx) {
     if (!ctx) return FC_ERR_ARG;
     ctx->last_error.clear();
@@ -942,7 +1002,8 @@ int fc_create(fc_ctx **out, int hip_device, void *hip_stream) {
     if (fc::coop_set_lds_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess ||
         fc::lds_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess ||
         fc::hyb_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess ||
-        fc::tile_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess) {
+        fc::tile_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess ||
+        fc::jump_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess) {
         (void)hipGetLastError();
         fc_destroy(ctx);
         return FC_ERR_HIP;

@@ -134,6 +134,8 @@ int begin(fc_ctx *ctx);
 // Threads per workgroup of the LDS-counter sampler for `trees` trees whose
 // counters and bitmap take lds_words words of LDS.
 uint32_t lds_threads_for(const fc_ctx *ctx, uint64_t trees, uint32_t lds_words);
+// Threads per workgroup of the small-graph sampler for `trees` trees of n vertices.
+uint32_t jump_threads_for(const fc_ctx *ctx, uint32_t n, uint64_t trees);
 // Bits of the target field so that n < 2^tshift, and whether a 32-bit tree
 // word also holds an in-arrow count up to dmax.
 void word_layout(uint32_t n, uint32_t dmax, bool allow32, uint32_t *tshift, bool *word32);

@@ -168,6 +168,17 @@ hipError_t lds_set_limit(size_t bytes);  // as coop_set_lds_limit, for the LDS-c
 hipError_t launch_lds_predraw(const CoopArgs &a, hipStream_t stream);
 int lds_max_active(uint32_t threads, uint32_t lds_words, bool weighted, bool repop, bool lean);
 
+// Small-graph variant: the whole tree in LDS, paths followed by pointer jumping.
+// On the caller's ids (vrec, col_idx of the job; no relabelling); n_max at most
+// kJumpMax and kJumpOwn vertices per thread; a.word: slots * n_max u32, the high
+// parts of draw counts (unset between uses); no lists, levels or bits.
+constexpr uint32_t kJumpMax = 32766, kJumpOwn = 32;
+size_t jump_lds_bytes(uint32_t n);
+hipError_t jump_set_limit(size_t bytes);  // as coop_set_lds_limit
+int jump_max_active(uint32_t threads, size_t lds, bool weighted);
+hipError_t launch_wilson_jump(const CoopArgs &a, uint32_t threads, size_t lds, bool weighted,
+                              hipStream_t stream);
+
 // Hybrid variant (ids widest class first: 32-bit fields end at e3, 16-bit at
 // e2, 8-bit at e1, then 4-bit): LDS fields and settled bits of ids [0, hot).
 hipError_t launch_wilson_hyb(const CoopArgs &a, uint32_t threads, uint32_t lds_words,
