@@ -931,11 +931,17 @@ uint32_t lds_threads_for(const fc_ctx *ctx, uint64_t trees, uint32_t lds_words) 
 }
 
 uint32_t jump_threads_for(const fc_ctx *ctx, uint32_t n, uint64_t trees) {
-    const uint32_t least = std::max<uint32_t>(64u, (n + fc::kJumpOwn - 1) / fc::kJumpOwn);
-    uint32_t t = 1024u;
-    if (ctx->lds_threads >= least) return ctx->lds_threads;
+    const uint32_t own = std::max<uint32_t>(64u, (n + fc::kJumpOwn - 1) / fc::kJumpOwn);
+    if (ctx->lds_threads >= own) return ctx->lds_threads;
+    // The widest workgroup while a tree has a CU (or half of one) to itself: its
+    // latency is what counts (n = 3000, 64 trees: 40 us with 1024 threads, 50 with
+    // 256).  Narrower ones, down to four vertices a thread or four waves, as more
+    // trees share a CU: 4096 trees of n = 1000 take 129 us with 256 threads, 172
+    // with 128, 156 with 512, 276 with 1024.
+    const uint32_t least = std::max(own, std::min<uint32_t>(256u, ((n + 3u) / 4u + 63u) & ~63u));
     const uint64_t fit_lds = ctx->max_lds / (fc::jump_lds_bytes(n) + kLdsStaticBytes);
     const uint64_t per_cu = std::min<uint64_t>((trees + ctx->cu_count - 1) / ctx->cu_count, fit_lds);
+    uint32_t t = 1024u;
     while (t / 2 >= least && 2048u / t < per_cu) t /= 2;
     return t;
 }

@@ -20,20 +20,31 @@
 //            nobody left can reach u*: if v still could, some vertex on its
 //            chain of jumps would be next to one that reached
 //   cycles   the others stand on a cycle or hang off one.  Each marks J of
-//            itself; a marked vertex follows the arrows, and if it comes back
-//            to itself before meeting a marked vertex of a smaller id, that
-//            cycle is popped.  (A mark that is not on a cycle yet, after few
-//            jumps on a long path, finds no cycle; a round that pops nothing
-//            is followed by one with enough jumps and no bound on the walk.)
+//            itself, and every marked vertex follows the arrows to the next
+//            marked one.  If that map takes the marks onto all of themselves,
+//            they all stand on cycles, and the paths walked are the cycles
+//            whole: all of them are popped.  A mark that nobody walked to is
+//            still on its way to a cycle (few jumps, long path): then a few
+//            more jumps, and marks and walks again.  (Every cycle holds marks:
+//            its own vertices' jumps stay on it.)
 // and back to the 2-cycles with the vertices that drew, until all are settled.
 //
-// LDS (n vertices on the caller's ids, u* = n; 6.25 bytes a vertex):
+// The jumps go over all unsettled vertices once.  After that every unsettled
+// vertex that has drawn only once hangs, over others of its kind, off one that
+// has drawn again: a cycle that forms later passes through one of those.  So the
+// later rounds jump among the vertices that have drawn again alone, from the
+// first of their kind that their arrows lead to (found by walking there), and
+// the tree is finished when these are settled.  Where such a walk would be long
+// (deep forests), the round jumps over all unsettled vertices again.
+//
+// LDS (n vertices on the caller's ids, u* = n; 6.4 bytes a vertex):
 //   mark   bitmap: marks, or the vertices of the 2-cycle check under way
-//   spill  bitmap: draw counts that left 16 bits (their high parts are in
+//   hit    bitmap: marks that a walk ended at
+//   spill  bitmap: draw counts that left 15 bits (their high parts are in
 //          global memory, set when the bit is)
 //   T      u16 target | settled << 15
 //   J      u16 jump; between the jumps the list of vertices that draw again
-//   K      u16 low half of the draw count
+//   K      u16 low 15 bits of the draw count | drawn again << 15
 // A thread owns the vertices tid, tid + T, ...: at most 32, with a bit each in
 // a register for "not settled yet".
 #include "fc_kernels.hpp"
@@ -45,10 +56,12 @@ namespace {
 
 constexpr uint32_t kSettled = 0x8000u;
 constexpr uint32_t kIdMask = 0x7FFFu;
-constexpr uint32_t kMinJumps = 5;    // passes before marks are worth following
-constexpr uint32_t kFullJumps = 16;  // passes that cover any path (n < 2^15)
-constexpr uint32_t kWalk = 64;       // arrows a mark follows in an ordinary round
-constexpr uint32_t kU = 4;           // vertices a thread keeps in flight
+constexpr uint32_t kMinJumps = 4;   // passes before marks are tried
+constexpr uint32_t kMoreJumps = 3;  // and after some were not on a cycle
+constexpr uint32_t kU = 4, kD = 2;  // vertices a thread keeps in flight: jumping, drawing
+constexpr uint32_t kWalk = 96;      // arrows a walk to the next vertex that drew again may take
+constexpr uint32_t kAgain = 0x8000u;
+constexpr uint32_t kLowBits = 15;
 
 // Offsets in LDS words / u16s for n vertices.
 struct JumpLayout {
@@ -66,10 +79,15 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
 
     const uint32_t T = blockDim.x, tid = threadIdx.x, lane = tid & 63u;
     unsigned int err = 0;
+    // The totals and the queue are one line of memory for all workgroups, 12 ns an
+    // addition: thread 0 keeps the totals and adds them once at the end, the first
+    // tree is the workgroup's own number, and the next one is asked for while the
+    // outputs are written.  (Four additions a tree took 200 of the 217 us of 4096
+    // trees of 1000 vertices.)
+    unsigned long long all_draws = 0, all_roots = 0, all_digests = 0;
+    if (tid == 0) s_item = blockIdx.x;
 
     for (;;) {
-        __syncthreads();
-        if (tid == 0) s_item = atomicAdd(a.queue, 1u);
         __syncthreads();
         const uint32_t item = uniform(s_item);
         if (item >= a.item_count) break;
@@ -79,33 +97,38 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
         const uint32_t n = job.n;
         const JumpLayout L = jump_layout(n);
         uint32_t *__restrict__ mark = s_dyn;
-        uint32_t *__restrict__ spill = s_dyn + L.nb;
-        uint16_t *arrow = reinterpret_cast<uint16_t *>(s_dyn + 2u * L.nb);
+        uint32_t *__restrict__ hit = s_dyn + L.nb;
+        uint32_t *__restrict__ spill = s_dyn + 2u * L.nb;
+        uint16_t *arrow = reinterpret_cast<uint16_t *>(s_dyn + 3u * L.nb);
         uint16_t *jump = arrow + L.half;
         uint16_t *list = jump;
         uint16_t *drawn = jump + L.half;
         uint32_t *__restrict__ high = static_cast<uint32_t *>(a.word) + static_cast<size_t>(blockIdx.x) * a.n_max;
 
         auto marked = [&](uint32_t v) { return (mark[v >> 5] >> (v & 31u)) & 1u; };
+        auto draws_of = [&](uint32_t v) {
+            uint32_t k = drawn[v] & (kAgain - 1u);
+            if ((spill[v >> 5] >> (v & 31u)) & 1u) k |= high[v] << kLowBits;
+            return k;
+        };
         // Arrow of v from its next draw; the draw count goes up by one.
         auto redraw = [&](uint32_t v) {
-            uint32_t k = drawn[v];
-            if ((spill[v >> 5] >> (v & 31u)) & 1u) k |= high[v] << 16;
-            VRec r = load_vrec(job.vrec, v);
+            const uint32_t k = draws_of(v);
+            VRec r = load_vrec(job.vrec, v);  // on its way during the Philox rounds
+            const Philox4 x = philox4x32_10(v, k, t, job.stream_id, a.key0, a.key1);
             hold_vrec(r);
             if (k >= a.k_limit) {  // the error ends the tree here: as if v were a root
                 err |= kErrVisitOverflow;
                 arrow[v] = static_cast<uint16_t>(n | kSettled);
                 return;
             }
-            const Philox4 x = philox4x32_10(v, k, t, job.stream_id, a.key0, a.key1);
             const uint32_t tg = arrow_target<kWeighted>(r, x.x0, x.x1, job.col_idx, job.wsum, job.wthr, n);
             // a target seen settled settles v: its path to u* is final
             const bool done = tg == n || (arrow[tg] & kSettled);
             arrow[v] = static_cast<uint16_t>(tg | (done ? kSettled : 0u));
-            drawn[v] = static_cast<uint16_t>(k + 1u);
-            if (((k + 1u) & 0xFFFFu) == 0u) {
-                high[v] = (k + 1u) >> 16;
+            drawn[v] = static_cast<uint16_t>(((k + 1u) & (kAgain - 1u)) | kAgain);
+            if (((k + 1u) & (kAgain - 1u)) == 0u) {
+                high[v] = (k + 1u) >> kLowBits;
                 atomicOr(&spill[v >> 5], 1u << (v & 31u));
             }
         };
@@ -121,7 +144,7 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
                     static_cast<uint16_t>(v);
         };
 
-        for (uint32_t i = tid; i < 2u * L.nb; i += T) s_dyn[i] = 0u;
+        for (uint32_t i = tid; i < 3u * L.nb; i += T) s_dyn[i] = 0u;
         if (tid == 0) {
             s_cnt = 0;
             s_digest = 0;
@@ -130,16 +153,16 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
         }
         // first arrows
         uint32_t open = 0;  // bit i: vertex i T + tid is not settled
-        for (uint32_t i0 = 0; i0 * T < n; i0 += kU) {
-            VRec r[kU] = {};
-            uint32_t tg[kU];
+        for (uint32_t i0 = 0; i0 * T < n; i0 += kD) {
+            VRec r[kD] = {};
+            uint32_t tg[kD];
 #pragma unroll
-            for (uint32_t q = 0; q < kU; ++q) {
+            for (uint32_t q = 0; q < kD; ++q) {
                 const uint32_t v = (i0 + q) * T + tid;
                 if (v < n) r[q] = load_vrec(job.vrec, v);
             }
 #pragma unroll
-            for (uint32_t q = 0; q < kU; ++q) {
+            for (uint32_t q = 0; q < kD; ++q) {
                 const uint32_t v = (i0 + q) * T + tid;
                 tg[q] = n;
                 if (v < n) {
@@ -148,7 +171,7 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
                 }
             }
 #pragma unroll
-            for (uint32_t q = 0; q < kU; ++q) {
+            for (uint32_t q = 0; q < kD; ++q) {
                 const uint32_t v = (i0 + q) * T + tid;
                 if (v >= n) continue;
                 arrow[v] = static_cast<uint16_t>(tg[q] | (tg[q] == n ? kSettled : 0u));
@@ -174,7 +197,7 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
         __syncthreads();
         unsigned long long draws = n;
         uint32_t rounds = 0;
-        bool full = false;
+        bool wide = true;  // this round's jumps go over all unsettled vertices
         uint32_t cur = 0, ccur = uniform(s_cnt);  // the list's vertices that draw: [cur, cur + ccur)
         bool done = false;
         for (;;) {
@@ -229,109 +252,169 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
                 err |= kErrStepCap;
                 break;
             }
-            // jumps; settled vertices are never anybody's jump
-            for (uint32_t todo = open; todo; todo &= todo - 1u) {
-                const uint32_t b = static_cast<uint32_t>(__builtin_ctz(todo));
-                const uint32_t v = b * T + tid;
-                const uint32_t w = arrow[v];
-                bool reached = (w & kSettled) != 0u;
-                uint32_t to = w & kIdMask;
-                if (!reached && (arrow[to] & kSettled)) {
-                    reached = true;
-                    arrow[v] = static_cast<uint16_t>(w | kSettled);
+            // where each vertex's jumps start; settled vertices are never anybody's jump
+            uint32_t work;  // the vertices of this round
+            for (;;) {
+                work = open;
+                if (!wide)
+                    for (uint32_t todo = open; todo; todo &= todo - 1u) {
+                        const uint32_t b = static_cast<uint32_t>(__builtin_ctz(todo));
+                        if (!(drawn[b * T + tid] & kAgain)) work &= ~(1u << b);
+                    }
+                bool deep = false;
+                for (uint32_t todo = work; todo; todo &= todo - 1u) {
+                    const uint32_t b = static_cast<uint32_t>(__builtin_ctz(todo));
+                    const uint32_t v = b * T + tid;
+                    const uint32_t w = arrow[v];
+                    bool reached = (w & kSettled) != 0u;
+                    uint32_t to = w & kIdMask;
+                    if (!reached) {
+                        uint32_t x = arrow[to];
+                        if (!wide) {
+                            uint32_t steps = 0;
+                            for (uint32_t d = drawn[to]; !(x & kSettled) && !(d & kAgain);) {
+                                if (++steps > kWalk) break;
+                                to = x & kIdMask;
+                                x = arrow[to];
+                                d = drawn[to];
+                            }
+                            deep |= steps > kWalk;
+                        }
+                        reached = (x & kSettled) != 0u;
+                        if (reached) arrow[v] = static_cast<uint16_t>(w | kSettled);
+                    }
+                    if (reached) {  // others may jump here before they see it settled
+                        to = n;
+                        open &= ~(1u << b);
+                        work &= ~(1u << b);
+                    }
+                    jump[v] = static_cast<uint16_t>(to);
                 }
-                if (reached) {  // others may jump here before they see it settled
-                    to = n;
-                    open &= ~(1u << b);
-                }
-                jump[v] = static_cast<uint16_t>(to);
+                if (wide) break;
+                if (__ballot(deep) && lane == 0) s_flags[3] = 1u;
+                __syncthreads();
+                wide = uniform(s_flags[3]) != 0u;
+                if (!wide) break;
+                __syncthreads();
+                if (tid == 0) s_flags[3] = 0;
             }
             __syncthreads();
-            for (uint32_t p = 0;; ++p) {
-                bool settled = false;
-                for (uint32_t todo = open; todo;) {
-                    uint32_t b[kU], j[kU];
-                    uint32_t have = 0;
+            // jumps until a pass settles nobody, marks, walks to the next mark; where
+            // some mark turns out not to be on a cycle, a few more jumps
+            uint32_t least = kMinJumps;
+            for (;;) {
+                for (uint32_t p = 0;; ++p) {
+                    bool settled = false;
+                    for (uint32_t todo = work; todo;) {
+                        uint32_t b[kU], j[kU];
+                        uint32_t have = 0;
 #pragma unroll
-                    for (uint32_t q = 0; q < kU; ++q) {
-                        b[q] = 0;
-                        j[q] = n;
-                        if (todo) {
-                            b[q] = static_cast<uint32_t>(__builtin_ctz(todo));
-                            todo &= todo - 1u;
-                            have |= 1u << q;
-                            j[q] = jump[b[q] * T + tid];
-                        }
-                    }
-#pragma unroll
-                    for (uint32_t q = 0; q < kU; ++q)
-                        if (have & (1u << q)) j[q] = jump[j[q]];
-#pragma unroll
-                    for (uint32_t q = 0; q < kU; ++q)
-                        if (have & (1u << q)) {
-                            const uint32_t v = b[q] * T + tid;
-                            jump[v] = static_cast<uint16_t>(j[q]);
-                            if (j[q] == n) {
-                                arrow[v] = static_cast<uint16_t>(arrow[v] | kSettled);
-                                open &= ~(1u << b[q]);
-                                settled = true;
+                        for (uint32_t q = 0; q < kU; ++q) {
+                            b[q] = 0;
+                            j[q] = n;
+                            if (todo) {
+                                b[q] = static_cast<uint32_t>(__builtin_ctz(todo));
+                                todo &= todo - 1u;
+                                have |= 1u << q;
+                                j[q] = jump[b[q] * T + tid];
                             }
                         }
+#pragma unroll
+                        for (uint32_t q = 0; q < kU; ++q)
+                            if (have & (1u << q)) j[q] = jump[j[q]];
+#pragma unroll
+                        for (uint32_t q = 0; q < kU; ++q)
+                            if (have & (1u << q)) {
+                                const uint32_t v = b[q] * T + tid;
+                                jump[v] = static_cast<uint16_t>(j[q]);
+                                if (j[q] == n) {
+                                    arrow[v] = static_cast<uint16_t>(arrow[v] | kSettled);
+                                    open &= ~(1u << b[q]);
+                                    work &= ~(1u << b[q]);
+                                    settled = true;
+                                }
+                            }
+                    }
+                    // bit 0: somebody is left, bit 1: somebody was settled in this pass
+                    const uint32_t f = (__ballot(work != 0u) ? 1u : 0u) | (__ballot(settled) ? 2u : 0u);
+                    if (lane == 0 && f) atomicOr(&s_flags[p & 3u], f);
+                    __syncthreads();
+                    const uint32_t all = uniform(s_flags[p & 3u]);
+                    if (tid == 0) s_flags[(p + 2u) & 3u] = 0;
+                    if (!(all & 1u)) {
+                        done = true;
+                        break;
+                    }
+                    if (!(all & 2u) && p + 1u >= least) break;
                 }
-                // bit 0: somebody is open, bit 1: somebody was settled in this pass
-                const uint32_t f = (__ballot(open != 0u) ? 1u : 0u) | (__ballot(settled) ? 2u : 0u);
-                if (lane == 0 && f) atomicOr(&s_flags[p & 3u], f);
                 __syncthreads();
-                const uint32_t all = uniform(s_flags[p & 3u]);
-                if (tid == 0) s_flags[(p + 2u) & 3u] = 0;
-                if (!(all & 1u)) {
-                    done = true;
-                    break;
+                if (tid < 4u) s_flags[tid] = 0;
+                if (done) break;
+                for (uint32_t todo = work; todo; todo &= todo - 1u) {
+                    const uint32_t b = static_cast<uint32_t>(__builtin_ctz(todo));
+                    const uint32_t c = jump[b * T + tid];
+                    atomicOr(&mark[c >> 5], 1u << (c & 31u));
                 }
-                if (!(all & 2u) && p + 1u >= (full ? kFullJumps : kMinJumps)) break;
+                __syncthreads();
+                uint32_t mine = 0;  // the vertices of this thread that are marked
+                for (uint32_t todo = work; todo; todo &= todo - 1u) {
+                    const uint32_t b = static_cast<uint32_t>(__builtin_ctz(todo));
+                    if (marked(b * T + tid)) mine |= 1u << b;
+                }
+                for (uint32_t todo = mine; todo; todo &= todo - 1u) {
+                    uint32_t x = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                    do {  // ends: the arrows lead to a cycle, which holds a mark
+                        x = arrow[x] & kIdMask;
+                    } while (!marked(x));
+                    atomicOr(&hit[x >> 5], 1u << (x & 31u));
+                }
+                __syncthreads();
+                bool stray = false;
+                for (uint32_t todo = mine; todo; todo &= todo - 1u) {
+                    const uint32_t c = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                    stray |= !((hit[c >> 5] >> (c & 31u)) & 1u);
+                }
+                if (__ballot(stray) && lane == 0) s_flags[3] = 1u;
+                if (tid == 0) s_cnt = 0;
+                __syncthreads();
+                const bool again = uniform(s_flags[3]) != 0u;
+                if (!again)  // the jumps are not needed any more: list the cycles there
+                    for (uint32_t todo = mine; todo; todo &= todo - 1u) {
+                        const uint32_t c = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                        uint32_t x = c, len = 0;
+                        do {
+                            x = arrow[x] & kIdMask;
+                            ++len;
+                        } while (!marked(x));
+                        uint32_t at = atomicAdd(&s_cnt, len);
+                        x = c;
+                        do {
+                            list[at++] = static_cast<uint16_t>(x);
+                            x = arrow[x] & kIdMask;
+                        } while (--len);
+                    }
+                __syncthreads();
+                for (uint32_t i = tid; i < 2u * L.nb; i += T) mark[i] = 0u;  // and hit
+                if (tid == 0) s_flags[3] = 0;
+                if (!again) break;
+                least = kMoreJumps;
+                __syncthreads();
             }
-            __syncthreads();
-            if (tid < 4u) s_flags[tid] = 0;
             if (done) break;
-            // marks, then walks
-            for (uint32_t todo = open; todo; todo &= todo - 1u) {
-                const uint32_t b = static_cast<uint32_t>(__builtin_ctz(todo));
-                const uint32_t c = jump[b * T + tid];
-                atomicOr(&mark[c >> 5], 1u << (c & 31u));
-            }
-            if (tid == 0) s_cnt = 0;
-            __syncthreads();
-            const uint32_t bound = full ? n + 1u : kWalk;
-            for (uint32_t todo = open; todo; todo &= todo - 1u) {
-                const uint32_t b = static_cast<uint32_t>(__builtin_ctz(todo));
-                const uint32_t c = b * T + tid;
-                if (!marked(c)) continue;
-                uint32_t x = arrow[c] & kIdMask, len = 1;
-                while (x != c && len < bound && !(x < c && marked(x))) {
-                    x = arrow[x] & kIdMask;
-                    ++len;
-                }
-                if (x != c) continue;
-                uint32_t at = atomicAdd(&s_cnt, len);
-                do {
-                    list[at++] = static_cast<uint16_t>(x);
-                    x = arrow[x] & kIdMask;
-                } while (x != c);
-            }
-            __syncthreads();
-            for (uint32_t i = tid; i < L.nb; i += T) mark[i] = 0u;
             cur = 0;
             ccur = uniform(s_cnt);
-            if (full && ccur == 0u) {  // cannot be: some cycle is left and its marks close it
+            if (ccur == 0u) {  // cannot be: somebody is left, so is a cycle
                 err |= kErrStepCap;
                 break;
             }
-            full = ccur == 0u;
             __syncthreads();
+            wide = false;
         }
         __syncthreads();
         if (err & kErrStepCap) break;
 
+        uint32_t next = a.item_count;
+        if (tid == 0 && a.item_count > gridDim.x) next = gridDim.x + atomicAdd(a.queue, 1u);
         unsigned long long my_digest = 0, my_roots = 0;
         for (uint32_t v = tid; v < n; v += T) {
             const uint32_t to = arrow[v] & kIdMask;
@@ -343,8 +426,7 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
             const size_t at = static_cast<size_t>(ti) * n + v;
             if (job.parents) job.parents[at] = static_cast<int32_t>(to);
             if (job.visit_counts || job.tree_visits) {
-                uint32_t k = drawn[v];
-                if ((spill[v >> 5] >> (v & 31u)) & 1u) k |= high[v] << 16;
+                const uint32_t k = draws_of(v);
                 if (job.visit_counts)
                     atomicAdd(&job.visit_counts[v], static_cast<unsigned long long>(k));
                 if (job.tree_visits) job.tree_visits[at] = k;
@@ -362,10 +444,16 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
         if (tid == 0) {
             if (job.tree_digests) job.tree_digests[ti] = s_digest;
             if (job.tree_steps) job.tree_steps[ti] = draws;
-            atomicAdd(&a.totals->walk_steps, draws);
-            atomicAdd(&a.totals->roots, s_roots);
-            atomicAdd(&a.totals->digest_sum, s_digest);
+            all_draws += draws;
+            all_roots += s_roots;
+            all_digests += s_digest;
+            s_item = next;
         }
+    }
+    if (tid == 0 && all_draws) {
+        atomicAdd(&a.totals->walk_steps, all_draws);
+        atomicAdd(&a.totals->roots, all_roots);
+        atomicAdd(&a.totals->digest_sum, all_digests);
     }
     if (err) atomicOr(&a.totals->error, err);
 }
@@ -379,7 +467,7 @@ const void *jump_kernel_of(bool weighted) {
 
 size_t jump_lds_bytes(uint32_t n) {
     const JumpLayout L = jump_layout(n);
-    return 8u * static_cast<size_t>(L.nb) + 2u * (2u * static_cast<size_t>(L.half) + n);
+    return 12u * static_cast<size_t>(L.nb) + 2u * (2u * static_cast<size_t>(L.half) + n);
 }
 
 hipError_t jump_set_limit(size_t bytes) {

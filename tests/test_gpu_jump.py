@@ -55,9 +55,9 @@ def test_families(gpu_lib, make, alpha):
 
 
 def test_largest_that_fits_and_the_next(gpu_lib):
-    """The widest graphs of this sampler (32 vertices a thread at 1024 threads is
+    """The widest graphs of this sampler (25500 or so; 32 vertices a thread at 1024 threads is
     never reached: 160 KB of LDS end it first) and ones beyond it."""
-    for n in (25_600, 25_999, 26_040, 26_060, 27_000):
+    for n in (25_000, 25_500, 25_520, 25_600, 26_000, 27_000):
         g = inputs.barabasi_albert(n, 2, n)
         _compare(gpu_lib, g, 1.5, n, 0, 6)
 
