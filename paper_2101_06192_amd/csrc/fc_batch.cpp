@@ -4,10 +4,11 @@
 // (trees), ordered largest graph first so that the longest trees start early,
 // and samples each list with a workgroup-per-tree kernel in one persistent
 // launch whose workgroups pull items from a device queue.  With LDS counters
-// the jobs fall into up to two launch groups: graphs whose counter fields take
-// at most a quarter of a CU's LDS ("narrow": several trees per CU, narrower
-// workgroups) and the rest ("wide": one or two trees per CU).  Each group's
-// per-slot scratch is sized for its largest graph.  Everything that does not
+// the jobs fall into launch groups: graphs whose trees fit LDS whole (the
+// small-graph variant, in three groups by how many of them a CU holds), graphs
+// whose counter fields take at most a third of a CU's LDS ("narrow": several
+// trees per CU, narrower workgroups) and the rest ("wide": one or two trees per
+// CU).  Each group's per-slot scratch is sized for its largest graph.  Everything that does not
 // change between runs (validation, vertex records, relabelling, item order,
 // scratch, launch shapes) happens once in fc_batch_create; a run replays one
 // captured HIP graph: per group, fill kernels (counters, draw-count epochs)
@@ -44,9 +45,15 @@ struct Group {
     bool weighted = false;   // some job's graph carries edge weights
     bool repop = false;      // re-formed 2-cycles popped within their round (LDS kernel)
     bool lean = false;       // LDS kernel: the lean register shape (at most 512 threads)
+    bool jump = false;       // small-graph kernel (whole trees in LDS); use_lds is false
+    size_t jump_lds = 0;     // its dynamic LDS (largest graph)
     uint32_t repop_words = 0;  // the same, global-counter kernel: its LDS filter (set with the shape)
     uint32_t lds_words = 0;  // dynamic LDS of the LDS-counter kernel (largest graph)
 };
+
+// wide, narrow, and the small graphs by the trees of the largest that a CU holds:
+// up to three, up to eight, more
+constexpr int kMaxGroups = 5;
 
 }  // namespace
 
@@ -58,7 +65,7 @@ struct fc_batch {
     DevBuf vrec, dmax, iso, wsum, wthr, wtot;  // weighted graphs' running row sums and step
                                                // thresholds, each job's weighted volume
     DevBuf rl_blk, rl_base, rl_bounds, rl_inv, rl_orig, rl_adj, rl_vrec;  // degree-class relabelling
-    Group grp[2];
+    Group grp[kMaxGroups];
     int ngroups = 0;
     uint32_t item_count = 0;
     hipStream_t stream = nullptr;
@@ -95,6 +102,7 @@ hipError_t enqueue_group(const Group &g, const fc::CoopArgs &a, uint32_t threads
     hipError_t e = fc::launch_fill_u64(static_cast<unsigned long long *>(g.small.ptr),
                                        sizeof(Small) / 8, 0ull, stream);
     if (e != hipSuccess) return e;
+    if (g.jump) return fc::launch_wilson_jump(a, threads, g.jump_lds, g.weighted, stream);
     if (g.use_lds)
         return fc::launch_wilson_lds(a, threads, g.lds_words, g.weighted, g.repop, g.lean, stream);
     e = fc::launch_fill_u64(static_cast<unsigned long long *>(g.kk.ptr), g.kk_words, 0ull, stream);
@@ -107,6 +115,13 @@ hipError_t enqueue_group(const Group &g, const fc::CoopArgs &a, uint32_t threads
 int size_scratch(fc_ctx *ctx, Group &g, uint32_t slots) {
     int rc;
     const size_t n = g.n_max, nwords = (n + 31) / 32;
+    if (g.jump) {
+        if ((rc = ensure(ctx, g.word, 4 * n * slots, "batch draw counts"))) return rc;
+        g.slots = slots;
+        g.args.word = g.word.ptr;
+        g.args.slots = slots;
+        return FC_OK;
+    }
     const size_t wbytes = g.word32 && !g.use_lds ? 4 : 8;
     if ((rc = ensure(ctx, g.word, wbytes * n * slots, "batch tree words"))) return rc;
     if (!g.use_lds && (rc = ensure(ctx, g.kk, 8 * n * slots, "batch draw counts"))) return rc;
@@ -129,14 +144,17 @@ int size_scratch(fc_ctx *ctx, Group &g, uint32_t slots) {
 // (also picks the re-pop filter of a global-counter group for this shape)
 uint32_t slots_for(const fc_ctx *ctx, Group &g, uint32_t threads, uint32_t wg_per_cu) {
     const size_t n = g.n_max;
-    const int fit = g.use_lds ? fc::lds_max_active(threads, g.lds_words, g.weighted, g.repop, g.lean)
+    const int fit = g.jump      ? fc::jump_max_active(threads, g.jump_lds, g.weighted)
+                    : g.use_lds ? fc::lds_max_active(threads, g.lds_words, g.weighted, g.repop, g.lean)
                               : fc::coop_max_active(threads, g.lds_bits, g.in_bits, g.word32,
                                                     g.n_max, g.weighted, 0u);
     if (fit > 0) wg_per_cu = std::min<uint32_t>(wg_per_cu, static_cast<uint32_t>(fit));
-    g.repop_words = g.use_lds ? 0u
-                              : coop_repop_words(ctx, threads, wg_per_cu, g.lds_bits, g.in_bits,
+    g.repop_words = g.use_lds || g.jump
+                        ? 0u
+                        : coop_repop_words(ctx, threads, wg_per_cu, g.lds_bits, g.in_bits,
                                                  g.word32, g.n_max, g.weighted);
-    const size_t per_slot = g.use_lds ? (8 + 24 + 4) * n + 8
+    const size_t per_slot = g.jump      ? 4 * n
+                            : g.use_lds ? (8 + 24 + 4) * n + 8
                                       : ((g.word32 ? 4 : 8) + 8 + 24 + 4) * n + 8 +
                                             (g.lds_bits ? 0 : 4 * ((n + 31) / 32));
     size_t slots = std::max<size_t>(1, ctx->state_budget / per_slot);
@@ -193,7 +211,7 @@ void disk_store(const fc_ctx *ctx, const TuneKey &k, const std::array<uint32_t, 
 
 TuneKey tune_key(const fc_batch *b, const Group &g) {
     const fc_ctx *ctx = b->ctx;
-    TuneKey k = {static_cast<uint64_t>(ctx->device), g.use_lds, g.n_max, g.lds_words, g.weighted,
+    TuneKey k = {static_cast<uint64_t>(ctx->device), g.jump ? 2u : g.use_lds ? 1u : 0u, g.n_max, g.lds_words, g.weighted,
                  g.word32, g.lds_bits, g.in_bits, ctx->lds_repop, ctx->coop_repop,
                  ctx->state_budget, ctx->max_draws};
     for (int32_t j : g.jobs) {
@@ -242,7 +260,10 @@ int autotune(fc_batch *b, Group &g) {
     // R-MAT batches); 0, 1 and 2 keep the re-pops as the option says
     std::vector<std::array<uint32_t, 4>> cand;
     const bool tune_repop = g.use_lds && ctx->lds_repop == 3;
-    if (g.use_lds) {
+    if (g.jump) {
+        for (uint32_t t : {128u, 256u, 512u, 1024u})
+            if (t * fc::kJumpOwn >= g.n_max) cand.push_back({t, 64u, g.repop ? 1u : 0u, 0u});
+    } else if (g.use_lds) {
         for (const auto &c : cand_lds) {
             cand.push_back({c[0], c[1], g.repop ? 1u : 0u, c[2]});
             if (tune_repop) cand.push_back({c[0], c[1], g.repop ? 0u : 1u, c[2]});
@@ -353,7 +374,6 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         return set_err(ctx, FC_ERR_ARG, "need out != NULL and a job array");
     *out = nullptr;
     uint64_t items = 0;
-    uint32_t n_max = 0;
     for (int32_t i = 0; i < n_jobs; ++i) {
         const fc_job &j = jobs[i];
         if ((rc = check_graph_args(ctx, &j.graph))) return rc;
@@ -364,10 +384,7 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
             return set_err(ctx, FC_ERR_ARG, "job root_counts is NULL");
         if (static_cast<uint64_t>(j.tree_begin) + j.tree_count > 0x100000000ull)
             return set_err(ctx, FC_ERR_ARG, "job tree ids must stay below 2^32");
-        if (j.graph.n > 0) {
-            items += j.tree_count;
-            n_max = std::max<uint32_t>(n_max, static_cast<uint32_t>(j.graph.n));
-        }
+        if (j.graph.n > 0) items += j.tree_count;
     }
     if (items >= 0xFFFFFFFFull) return set_err(ctx, FC_ERR_ARG, "more than 2^32 - 1 trees in a batch");
 
@@ -494,8 +511,15 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
                                      dmax_d + k, iso + ioff[k], wtot_d + k, b->stream),
                "build_vrec");
     }
-    const bool try_lds = ctx->coop_lds_counts && !order.empty() &&
-                         n_max < (1u << fc::kRelabelIdBits);
+    // graphs whose trees fit LDS whole need no relabelling
+    auto small = [&](uint32_t n) {
+        return ctx->coop_lds_counts && n <= fc::kJumpMax &&
+               fc::jump_lds_bytes(n) + kLdsStaticBytes <= ctx->max_lds;
+    };
+    uint32_t n_rest = 0;  // the largest of the others
+    for (const GInfo &gi : gs)
+        if (!small(gi.n)) n_rest = std::max(n_rest, gi.n);
+    const bool try_lds = ctx->coop_lds_counts && n_rest > 0 && n_rest < (1u << fc::kRelabelIdBits);
     std::vector<unsigned int> bounds(4 * gs.size(), 0u);
     if (try_lds) {
         if ((rc = ensure(ctx, b->rl_blk, 4 * fc::kRelabelClasses * tb, "class counts")) ||
@@ -506,11 +530,12 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         uint32_t *base = static_cast<uint32_t *>(b->rl_base.ptr);
         uint32_t *bnd = static_cast<uint32_t *>(b->rl_bounds.ptr);
         for (size_t f = 0; f < gs.size(); ++f)
-            FB_HIP(fc::launch_class_bounds(gs[f].rp, gs[f].n, false,
-                                           blk + fc::kRelabelClasses * gs[f].off_b,
-                                           base + fc::kRelabelClasses * gs[f].off_b, bnd + 4 * f,
-                                           b->stream),
-                   "class bounds");
+            if (!small(gs[f].n))
+                FB_HIP(fc::launch_class_bounds(gs[f].rp, gs[f].n, false,
+                                               blk + fc::kRelabelClasses * gs[f].off_b,
+                                               base + fc::kRelabelClasses * gs[f].off_b, bnd + 4 * f,
+                                               b->stream),
+                       "class bounds");
         FB_HIP(hipMemcpyAsync(bounds.data(), bnd, 16 * gs.size(), hipMemcpyDeviceToHost, b->stream),
                "copy class bounds");
     }
@@ -526,6 +551,7 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
     if (try_lds) {
         uint32_t words = 0;
         for (size_t f = 0; f < gs.size(); ++f) {
+            if (small(gs[f].n)) continue;
             gwords[f] = fc::count_layout(bounds[4 * f + 3], bounds[4 * f], bounds[4 * f + 1],
                                          bounds[4 * f + 2]).words;
             words = std::max(words, gwords[f]);
@@ -543,47 +569,64 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         uint32_t *orig = static_cast<uint32_t *>(b->rl_orig.ptr);
         unsigned long long *adj = static_cast<unsigned long long *>(b->rl_adj.ptr);
         for (const GInfo &gi : gs)
-            FB_HIP(fc::launch_relabel_graph(gi.rp, gi.ci, gi.n, gi.nnz,
-                                            base + fc::kRelabelClasses * gi.off_b, fc::kRelabelIdBits,
-                                            inv + gi.off_n, orig + gi.off_n, adj + gi.off_e,
-                                            b->stream), "relabel");
+            if (!small(gi.n))
+                FB_HIP(fc::launch_relabel_graph(gi.rp, gi.ci, gi.n, gi.nnz,
+                                                base + fc::kRelabelClasses * gi.off_b,
+                                                fc::kRelabelIdBits, inv + gi.off_n, orig + gi.off_n,
+                                                adj + gi.off_e, b->stream), "relabel");
         fc::VRec *vr = static_cast<fc::VRec *>(b->rl_vrec.ptr);
         for (size_t k = 0; k < order.size(); ++k)
-            FB_HIP(fc::launch_relabel_vrec(vrec + voff[k], inv + gs[gof[k]].off_n,
-                                           static_cast<uint32_t>(b->jobs[order[k]].graph.n),
-                                           vr + voff[k], b->stream), "relabel records");
+            if (!small(gs[gof[k]].n))
+                FB_HIP(fc::launch_relabel_vrec(vrec + voff[k], inv + gs[gof[k]].off_n,
+                                               static_cast<uint32_t>(b->jobs[order[k]].graph.n),
+                                               vr + voff[k], b->stream), "relabel records");
     }
 
-    // launch groups: with LDS counters, jobs whose fields take at most a third
-    // of the LDS form the narrow group (three workgroups per CU fit, as many as
-    // the lean shape's registers allow at 512 threads); everything else is one
-    // group
+    // launch groups.  Small graphs by how many trees of theirs fit a CU's LDS (a
+    // group's workgroups all take what its largest graph needs; kBatchOne with one
+    // group for all of them, kBatchThree with three).  With LDS counters, jobs whose
+    // fields take at most a third of the LDS form the narrow group (three workgroups
+    // per CU fit, as many as the lean shape's registers allow at 512 threads);
+    // everything else is one group.
+    std::vector<int32_t> parts[kMaxGroups];
     for (size_t k = 0; k < order.size(); ++k) {
-        const bool narrow = use_lds && 4u * static_cast<size_t>(gwords[gof[k]]) + kLdsStaticBytes <=
-                                           ctx->max_lds / 3;
-        b->grp[narrow ? 1 : 0].jobs.push_back(order[k]);
+        const uint32_t n = gs[gof[k]].n;
+        int part = 0;
+        if (small(n)) {
+            const size_t per_cu = ctx->max_lds / (fc::jump_lds_bytes(n) + kLdsStaticBytes);
+            part = per_cu <= 3 ? 2 : per_cu <= 8 ? 3 : 4;
+        } else if (use_lds && 4u * static_cast<size_t>(gwords[gof[k]]) + kLdsStaticBytes <=
+                                  ctx->max_lds / 3) {
+            part = 1;
+        }
+        parts[part].push_back(order[k]);
     }
-    if (b->grp[0].jobs.empty()) std::swap(b->grp[0].jobs, b->grp[1].jobs);
-    b->ngroups = b->grp[1].jobs.empty() ? 1 : 2;
+    for (int part = 0; part < kMaxGroups; ++part) {
+        if (parts[part].empty()) continue;
+        Group &g = b->grp[b->ngroups++];
+        g.jobs = std::move(parts[part]);
+        g.jump = part >= 2;
+        g.use_lds = use_lds && !g.jump;
+    }
 
     for (int gi = 0; gi < b->ngroups; ++gi) {
         Group &g = b->grp[gi];
         if ((rc = ensure(ctx, g.small, sizeof(Small), "batch counters"))) return fail(rc);
-        g.use_lds = use_lds;
         g.word32 = ctx->coop_word32;
         for (int32_t j : g.jobs) {
             const size_t k = pos[j];
             g.n_max = std::max<uint32_t>(g.n_max, static_cast<uint32_t>(b->jobs[j].graph.n));
             g.item_count += b->jobs[j].tree_count;
             g.weighted = g.weighted || wsum_of(k) != nullptr;
-            if (use_lds) g.lds_words = std::max(g.lds_words, gwords[gof[k]]);
+            if (g.use_lds) g.lds_words = std::max(g.lds_words, gwords[gof[k]]);
             uint32_t ts;
             bool w32;
             word_layout(static_cast<uint32_t>(b->jobs[j].graph.n), dmax[k], true, &ts, &w32);
             g.word32 = g.word32 && w32;
         }
         g.repop = ctx->lds_repop >= 2 || (ctx->lds_repop == 1 && g.weighted);
-        g.lds_bits = !use_lds && ctx->coop_lds_bits &&
+        if (g.jump) g.jump_lds = fc::jump_lds_bytes(g.n_max);
+        g.lds_bits = !g.use_lds && !g.jump && ctx->coop_lds_bits &&
                      fc::coop_lds_bytes(g.n_max) + 1024u <= ctx->max_lds;
         g.in_bits = g.lds_bits && ctx->coop_in_bits &&
                     2 * fc::coop_lds_bytes(g.n_max) + 1024u <= ctx->max_lds;
@@ -603,8 +646,8 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
             c.wthr = wthr_of(k);
             c.n = static_cast<uint32_t>(j.graph.n);
             c.tree_count = j.tree_count;
-            c.iso = use_lds ? nullptr : iso + ioff[k];
-            if (use_lds) {
+            c.iso = g.use_lds ? nullptr : iso + ioff[k];
+            if (g.use_lds) {
                 const GInfo &gf = gs[gof[k]];
                 c.vrec = static_cast<const fc::VRec *>(b->rl_vrec.ptr) + voff[k];
                 c.adj = static_cast<const unsigned long long *>(b->rl_adj.ptr) + gf.off_e;
@@ -644,14 +687,19 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         a.key0 = static_cast<uint32_t>(seed);
         a.key1 = static_cast<uint32_t>(seed >> 32);
         a.max_rounds = 0x40000000u;
-        a.k_limit = ctx->max_draws ? ctx->max_draws : use_lds ? 0xFFFFFFFFu : 0x7FFFFFFFu;
+        a.k_limit = ctx->max_draws ? ctx->max_draws : g.use_lds ? 0xFFFFFFFFu : 0x7FFFFFFFu;
+        // the limit of the tree words that the LDS-counter variant keeps counts in
+        if (g.jump) a.k_limit = std::min(a.k_limit, 0x0FFFFFFFu);
         Small *sm = static_cast<Small *>(g.small.ptr);
         a.queue = &sm->queue;
         a.totals = &sm->totals;
         a.phase_ticks = nullptr;
         a.jobs = static_cast<const fc::CoopJob *>(g.jobtab.ptr);
         a.item_job = static_cast<const uint32_t *>(g.item_job.ptr);
-        if (use_lds) {
+        if (g.jump) {
+            g.threads = jump_threads_for(ctx, g.n_max, g.item_count);
+            g.wg_per_cu = 64u;
+        } else if (g.use_lds) {
             g.threads = lds_threads_for(ctx, g.item_count, g.lds_words);
             g.wg_per_cu = ctx->lds_wg_per_cu ? ctx->lds_wg_per_cu : 64u;
             g.lean = ctx->lds_lean && g.threads <= 512u;
@@ -687,12 +735,12 @@ int fc_batch_run(fc_batch *b, fc_stats *stats) {
         std::memset(stats, 0, sizeof(*stats));
         stats->tau = b->item_count;
         const Group &g = b->grp[0];
-        if (b->ngroups == 2)
+        if (b->ngroups >= 2)  // the first two groups (the field holds no more)
             std::snprintf(stats->sampler, sizeof(stats->sampler), "%s:%u+%u",
-                          g.use_lds ? "lbatch" : "batch", g.threads, b->grp[1].threads);
+                          g.use_lds || g.jump ? "lbatch" : "batch", g.threads, b->grp[1].threads);
         else
             std::snprintf(stats->sampler, sizeof(stats->sampler), "%s:%ux%u",
-                          g.use_lds ? "lbatch" : "batch", g.threads, g.wg_per_cu);
+                          g.use_lds || g.jump ? "lbatch" : "batch", g.threads, g.wg_per_cu);
     }
     if (b->item_count == 0) return FC_OK;
     // order after the caller's earlier work on the context stream, and make the
@@ -702,7 +750,7 @@ int fc_batch_run(fc_batch *b, fc_stats *stats) {
     FC_HIP(ctx, hipEventRecord(b->ev0, b->stream), "event");
     FC_HIP(ctx, hipGraphLaunch(b->exec, b->stream), "graph launch");
     FC_HIP(ctx, hipEventRecord(b->ev1, b->stream), "event");
-    Small sm[2];
+    Small sm[kMaxGroups];
     for (int gi = 0; gi < b->ngroups; ++gi)
         FC_HIP(ctx, hipMemcpyAsync(&sm[gi], b->grp[gi].small.ptr, sizeof(Small),
                                    hipMemcpyDeviceToHost, b->stream), "copy counters");
@@ -720,12 +768,14 @@ int fc_batch_run(fc_batch *b, fc_stats *stats) {
         return set_err(ctx, FC_ERR_HIP, "a tree exceeded the step bound (internal fault)");
     if (error & fc::kErrVisitOverflow)
         return set_err(ctx, FC_ERR_OVERFLOW,
-                       b->grp[0].use_lds ? "a per-vertex draw count exceeded 2^28 - 1 (LDS counters)"
+                       b->grp[0].use_lds || b->grp[0].jump
+                           ? "a per-vertex draw count exceeded 2^28 - 1 (LDS counters)"
                                          : "a per-vertex visit counter exceeded 2^31 - 1");
     if (stats) {
         float ms = 0.f;
         (void)hipEventElapsedTime(&ms, b->ev0, b->ev1);
-        stats->trees_in_flight = b->grp[0].slots + (b->ngroups == 2 ? b->grp[1].slots : 0u);
+        stats->trees_in_flight = 0;
+        for (int gi = 0; gi < b->ngroups; ++gi) stats->trees_in_flight += b->grp[gi].slots;
         stats->walk_steps = steps;
         stats->roots = roots;
         stats->digest_sum = digests;
