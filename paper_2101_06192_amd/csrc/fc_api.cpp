@@ -135,7 +135,23 @@ int check_graph_args(fc_ctx *ctx, const fc_graph *g) {
     return FC_OK;
 }
 
-int prepare_graph(fc_ctx *ctx, const fc_graph *g, bool trusted, GraphView *out) {
+int check_outcome(fc_ctx *ctx, const fc::GraphCheck &found) {
+    unsigned int err = found.err;
+    if (err & fc::kErrGraphRowPtr)
+        return set_err(ctx, FC_ERR_GRAPH, "row_ptr is not monotone from 0 to nnz");
+    if (found.sym_diff) err |= fc::kErrGraphAsymmetric;
+    if (!err) return FC_OK;
+    std::string m = "graph is not simple, sorted and symmetric:";
+    if (err & fc::kErrGraphColumn) m += " column out of range;";
+    if (err & fc::kErrGraphSelfLoop) m += " self-loop;";
+    if (err & fc::kErrGraphOrder) m += " row not strictly ascending;";
+    if (err & fc::kErrGraphAsymmetric) m += " missing reverse edge;";
+    if (err & fc::kErrGraphWeight) m += " weight not 0 or in [2^-64, 2^64];";
+    if (err & fc::kErrGraphWeightAsym) m += " weight differs from its reverse entry's;";
+    return set_err(ctx, FC_ERR_GRAPH, m);
+}
+
+int prepare_graph(fc_ctx *ctx, const fc_graph *g, bool trusted, GraphView *out, bool defer) {
     int rc = check_graph_args(ctx, g);
     if (rc) return rc;
     GraphView v;
@@ -172,30 +188,23 @@ int prepare_graph(fc_ctx *ctx, const fc_graph *g, bool trusted, GraphView *out) 
     if (!trusted) {
         // both passes are enqueued together (the second does nothing once the
         // first has found bad row offsets) and read back once
-        GraphCheck *gc = &static_cast<Small *>(ctx->small.ptr)->check;
-        GraphCheck found{};
-        FC_HIP(ctx, hipMemsetAsync(gc, 0, sizeof(GraphCheck), ctx->stream), "memset");
+        Small *sm = static_cast<Small *>(ctx->small.ptr);
+        fc::GraphCheck *gc = &sm->check;
+        if (defer) FC_HIP(ctx, hipMemsetAsync(sm, 0, sizeof(Small), ctx->stream), "memset counters");
+        else FC_HIP(ctx, hipMemsetAsync(gc, 0, sizeof(*gc), ctx->stream), "memset");
         FC_HIP(ctx, fc::launch_validate_rows(v.row_ptr, v.n, v.nnz, &gc->err, ctx->stream),
                "validate_rows launch");
         FC_HIP(ctx, fc::launch_validate_cols(v.row_ptr, v.col_idx, v.weights, v.n, v.nnz, &gc->err,
                                              &gc->sym_diff, ctx->stream),
                "validate_cols launch");
-        FC_HIP(ctx, hipMemcpyAsync(&found, gc, sizeof(found), hipMemcpyDeviceToHost, ctx->stream),
-               "copy error word");
-        FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "graph checks");
-        unsigned int err = found.err;
-        if (err & fc::kErrGraphRowPtr)
-            return set_err(ctx, FC_ERR_GRAPH, "row_ptr is not monotone from 0 to nnz");
-        if (found.sym_diff) err |= fc::kErrGraphAsymmetric;
-        if (err) {
-            std::string m = "graph is not simple, sorted and symmetric:";
-            if (err & fc::kErrGraphColumn) m += " column out of range;";
-            if (err & fc::kErrGraphSelfLoop) m += " self-loop;";
-            if (err & fc::kErrGraphOrder) m += " row not strictly ascending;";
-            if (err & fc::kErrGraphAsymmetric) m += " missing reverse edge;";
-            if (err & fc::kErrGraphWeight) m += " weight not 0 or in [2^-64, 2^64];";
-            if (err & fc::kErrGraphWeightAsym) m += " weight differs from its reverse entry's;";
-            return set_err(ctx, FC_ERR_GRAPH, m);
+        if (defer) {
+            v.pending = true;
+        } else {
+            FC_HIP(ctx, hipMemcpyAsync(&ctx->host_small->check, gc, sizeof(*gc),
+                                       hipMemcpyDeviceToHost, ctx->stream),
+                   "copy error word");
+            FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "graph checks");
+            if ((rc = check_outcome(ctx, ctx->host_small->check))) return rc;
         }
     }
     *out = v;
@@ -238,14 +247,51 @@ int tau_for(fc_ctx *ctx, const fc_params *p, const GraphView &g, uint32_t *tau) 
     return FC_OK;
 }
 
-// Runs the sampler over [tree_begin, tree_begin + tree_count).
+// The sampler that the call's flags or the environment ask for: 0 automatic, 1
+// lane, 2 workgroup with global counters, 3 with LDS counters, 4 hybrid, 5 tiles.
+uint32_t sampler_mode(const fc_ctx *ctx, const fc_params *p) {
+    if (p->flags & FC_FLAG_SAMPLER_LANE) return 1;
+    if (p->flags & FC_FLAG_SAMPLER_COOP) return 2;
+    if (p->flags & FC_FLAG_SAMPLER_LDS) return 3;
+    if (p->flags & FC_FLAG_SAMPLER_HYB) return 4;
+    if (p->flags & FC_FLAG_SAMPLER_TILE) return 5;
+    return ctx->force_sampler;
+}
+
+// Whether n vertices are sampled by the small-graph variant: the whole tree in
+// LDS (reported as wilson_lds, whose place it takes in the automatic choice).
+// Faster than the LDS-counter one wherever it fits: 1.4 to 3 times over BA, R-MAT
+// and grid graphs of 1000 to 25900 vertices, alpha 1 to 10, 64 to 4096 trees.
+bool jump_applies(const fc_ctx *ctx, const fc_params *p, int32_t n) {
+    return sampler_mode(ctx, p) == 0 && ctx->coop_lds_counts && !ctx->phase_timing && n > 0 &&
+           static_cast<uint32_t>(n) <= fc::kJumpMax &&
+           fc::jump_lds_bytes(static_cast<uint32_t>(n)) + kLdsStaticBytes <= ctx->max_lds;
+}
+
+// Whether the graph's checks may stay on the device until the call's results are
+// read: every kernel that follows the unchecked graph looks at their outcome (row
+// sums of weights and the other samplers do not).
+bool deferrable(const fc_ctx *ctx, const fc_params *p, const fc_graph *g) {
+    return g && !(g->weights && g->nnz) && jump_applies(ctx, p, g->n);
+}
+
+// Estimators to compute from the root counts once the trees are sampled.
+struct Estimate {
+    double *diag, *farness, *closeness;
+    bool literal;
+};
+
+// Runs the sampler over [tree_begin, tree_begin + tree_count).  With est, the
+// root counts start from zero here and the estimators follow.
 int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tree_begin,
                 uint32_t tree_count, uint32_t *root_counts, uint64_t *visit_counts,
                 uint64_t *tree_digests, uint64_t *tree_steps, int32_t *parents,
-                uint32_t *tree_visits, fc_stats *stats) {
+                uint32_t *tree_visits, fc_stats *stats, const Estimate *est) {
     int rc;
     Small *sm = static_cast<Small *>(ctx->small.ptr);
-    FC_HIP(ctx, hipMemsetAsync(sm, 0, sizeof(Small), ctx->stream), "memset counters");
+    const fc::GraphCheck *check = g.pending ? &sm->check : nullptr;
+    if (!g.pending)
+        FC_HIP(ctx, hipMemsetAsync(sm, 0, sizeof(Small), ctx->stream), "memset counters");
     if (stats) {
         stats->tau = tree_count;
         stats->trees_in_flight = 0;
@@ -253,7 +299,13 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         stats->ms_sample = 0.0;
         stats->sampler[0] = 0;
     }
-    if (g.n == 0 || tree_count == 0) return FC_OK;
+    if (g.n == 0 || tree_count == 0) {
+        if (!g.pending) return FC_OK;
+        FC_HIP(ctx, hipMemcpyAsync(&ctx->host_small->check, check, sizeof(*check),
+                                   hipMemcpyDeviceToHost, ctx->stream), "copy error word");
+        FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "graph checks");
+        return check_outcome(ctx, ctx->host_small->check);
+    }
     if ((rc = ensure(ctx, ctx->vrec, sizeof(fc::VRec) * static_cast<size_t>(g.n), "vertex records")))
         return rc;
     fc::VRec *vrec = static_cast<fc::VRec *>(ctx->vrec.ptr);
@@ -265,8 +317,8 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     const bool weighted = wsum != nullptr;
     const bool repop = ctx->lds_repop >= 2 || (ctx->lds_repop == 1 && weighted);
     FC_HIP(ctx, fc::launch_build_vrec(g.row_ptr, wsum, g.n, p->alpha, vrec, &sm->dmax,
-                                      static_cast<uint32_t *>(ctx->iso.ptr), &sm->wtotal,
-                                      ctx->stream),
+                                      static_cast<uint32_t *>(ctx->iso.ptr), &sm->wtotal, check,
+                                      est ? root_counts : nullptr, ctx->stream),
            "build_vrec");
     double vol = static_cast<double>(g.nnz);  // sum of the (weighted) degrees
     if (weighted) {
@@ -278,13 +330,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     // which sampler: the lane sampler needs many trees to fill the GPU; the
     // workgroup sampler parallelises inside each tree
     // mode: 1 lane, 2 workgroup with global counters, 3 workgroup with LDS counters
-    uint32_t mode = 0;
-    if (p->flags & FC_FLAG_SAMPLER_LANE) mode = 1;
-    else if (p->flags & FC_FLAG_SAMPLER_COOP) mode = 2;
-    else if (p->flags & FC_FLAG_SAMPLER_LDS) mode = 3;
-    else if (p->flags & FC_FLAG_SAMPLER_HYB) mode = 4;
-    else if (p->flags & FC_FLAG_SAMPLER_TILE) mode = 5;
-    else mode = ctx->force_sampler;
+    const uint32_t mode = sampler_mode(ctx, p);
     // automatically always a workgroup sampler: measured, the LDS-counter one beats
     // the lane-per-tree walk even with 2^18 trees of a 1000-vertex graph
     const bool use_coop = mode == 0 || mode >= 2;
@@ -308,12 +354,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     bool lds_lean = false;  // LDS-counter sampler: the lean register shape
     uint32_t tshift = 32;
     unsigned int dmax = 0;
-    // small graphs: the whole tree in LDS (reported as wilson_lds, whose place it
-    // takes in the automatic choice)
-    if (mode == 0 && ctx->coop_lds_counts && !ctx->phase_timing &&
-        static_cast<uint32_t>(g.n) <= fc::kJumpMax &&
-        fc::jump_lds_bytes(static_cast<uint32_t>(g.n)) + kLdsStaticBytes <= ctx->max_lds)
-        jump_lds = fc::jump_lds_bytes(static_cast<uint32_t>(g.n));
+    if (jump_applies(ctx, p, g.n)) jump_lds = fc::jump_lds_bytes(static_cast<uint32_t>(g.n));
     if (jump_lds) {
         kname = "wilson_lds";
         const uint32_t n = static_cast<uint32_t>(g.n);
@@ -336,6 +377,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         c.k_limit = ctx->max_draws ? std::min(ctx->max_draws, 0x0FFFFFFFu) : 0x0FFFFFFFu;
         c.queue = &sm->queue;
         c.totals = &sm->totals;
+        c.check = check;
         fc::CoopJob &j = c.single;
         j.vrec = vrec;
         j.col_idx = g.col_idx;
@@ -399,13 +441,13 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
             bool fits = fc::tile_lds_bytes(B) + kLdsStaticBytes <= ctx->max_lds;
             bool local = mode == 5;
             if (fits && !local && g.nnz > 0) {
-                FC_HIP(ctx, hipMemsetAsync(&sm->sum, 0, sizeof(unsigned long long), ctx->stream),
+                FC_HIP(ctx, hipMemsetAsync(&sm->cross, 0, sizeof(unsigned long long), ctx->stream),
                        "memset cross count");
                 FC_HIP(ctx, fc::launch_count_cross(g.row_ptr, g.col_idx, static_cast<uint32_t>(g.n),
-                                                   g.nnz, B, &sm->sum, ctx->stream),
+                                                   g.nnz, B, &sm->cross, ctx->stream),
                        "count_cross");
                 unsigned long long cross = 0;
-                FC_HIP(ctx, hipMemcpyAsync(&cross, &sm->sum, sizeof(cross), hipMemcpyDeviceToHost,
+                FC_HIP(ctx, hipMemcpyAsync(&cross, &sm->cross, sizeof(cross), hipMemcpyDeviceToHost,
                                            ctx->stream), "copy cross count");
                 FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "count_cross");
                 local = static_cast<double>(cross) * 1000.0 <=
@@ -840,10 +882,16 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     } else
         FC_HIP(ctx, fc::launch_wilson_lane(a, ctx->stream), "wilson_lane launch");
     FC_HIP(ctx, hipEventRecord(ctx->ev1, ctx->stream), "event");
-    fc::Totals tot;
-    FC_HIP(ctx, hipMemcpyAsync(&tot, &sm->totals, sizeof(tot), hipMemcpyDeviceToHost, ctx->stream),
-           "copy totals");
+    if (est)
+        FC_HIP(ctx, fc::launch_estimate(root_counts, g.n, tree_count, est->literal, &sm->totals, check,
+                                        est->diag, est->farness, est->closeness, ctx->stream),
+               "estimate launch");
+    // everything the host wants to know, read back once
+    FC_HIP(ctx, hipMemcpyAsync(ctx->host_small, sm, sizeof(Small), hipMemcpyDeviceToHost, ctx->stream),
+           "copy counters");
     FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "sampler");
+    if (g.pending && (rc = check_outcome(ctx, ctx->host_small->check))) return rc;
+    const fc::Totals tot = ctx->host_small->totals;
     if (tot.error & fc::kErrStepCap)
         return set_err(ctx, FC_ERR_HIP, "a tree exceeded the step bound (internal fault)");
     if (tot.error & fc::kErrVisitOverflow)
@@ -870,9 +918,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         }
         for (int i = 0; i < 8; ++i) stats->phase_ms[i] = 0.0;
         if ((use_coop || use_tile) && ctx->phase_timing) {
-            unsigned long long ticks[8];
-            FC_HIP(ctx, hipMemcpy(ticks, sm->phase_ticks, sizeof(ticks), hipMemcpyDeviceToHost),
-                   "copy phase ticks");
+            const unsigned long long *ticks = ctx->host_small->phase_ticks;
             // per-workgroup average in milliseconds
             for (int i = 0; i < 8; ++i)
                 stats->phase_ms[i] = static_cast<double>(ticks[i]) / ctx->wall_khz / static_cast<double>(slots);
@@ -980,6 +1026,8 @@ int fc_create(fc_ctx **out, int hip_device, void *hip_stream) {
     ctx->stream = static_cast<hipStream_t>(hip_stream);
     if (hipEventCreate(&ctx->ev0) != hipSuccess || hipEventCreate(&ctx->ev1) != hipSuccess ||
         hipEventCreate(&ctx->evm) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void **>(&ctx->host_small), sizeof(Small),
+                      hipHostMallocDefault) != hipSuccess ||
         ensure(ctx, ctx->small, sizeof(Small), "counters") != FC_OK) {
         fc_destroy(ctx);
         return FC_ERR_HIP;
@@ -1054,6 +1102,7 @@ int fc_destroy(fc_ctx *ctx) {
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
     if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
     if (ctx->evm) (void)hipEventDestroy(ctx->evm);
+    if (ctx->host_small) (void)hipHostFree(ctx->host_small);
     delete ctx;
     return FC_OK;
 }
@@ -1186,9 +1235,11 @@ int fc_sample(fc_ctx *ctx, const fc_graph *g, const fc_params *params, uint32_t 
     if (static_cast<uint64_t>(tree_begin) + tree_count > 0x100000000ull)
         return set_err(ctx, FC_ERR_ARG, "tree ids must stay below 2^32");
     GraphView gv;
-    if ((rc = prepare_graph(ctx, g, params->flags & FC_FLAG_TRUSTED_GRAPH, &gv))) return rc;
+    if ((rc = prepare_graph(ctx, g, params->flags & FC_FLAG_TRUSTED_GRAPH, &gv,
+                            deferrable(ctx, params, g))))
+        return rc;
     rc = run_sampler(ctx, gv, params, tree_begin, tree_count, root_counts, visit_counts,
-                     tree_digests, tree_steps, parents, tree_visits, stats);
+                     tree_digests, tree_steps, parents, tree_visits, stats, nullptr);
     if (stats) stats->ms_total = now_ms() - t0;
     return rc;
 }
@@ -1221,6 +1272,7 @@ int fc_sample_noalloc(fc_ctx *ctx, const fc_graph *g, const fc_params *params,
     sh.ev0 = ctx->ev0;
     sh.ev1 = ctx->ev1;
     sh.evm = ctx->evm;
+    sh.host_small = ctx->host_small;
     sh.lanes_per_wave = ctx->lanes_per_wave;
     sh.max_slots = ctx->max_slots;
     sh.cu_count = ctx->cu_count;
@@ -1253,9 +1305,10 @@ int fc_sample_noalloc(fc_ctx *ctx, const fc_graph *g, const fc_params *params,
     sh.arena_off = 0;
     GraphView gv;
     if ((rc = ensure(&sh, sh.small, sizeof(Small), "counters")) ||
-        (rc = prepare_graph(&sh, g, params->flags & FC_FLAG_TRUSTED_GRAPH, &gv)) ||
+        (rc = prepare_graph(&sh, g, params->flags & FC_FLAG_TRUSTED_GRAPH, &gv,
+                            deferrable(&sh, params, g))) ||
         (rc = run_sampler(&sh, gv, params, tree_begin, tree_count, root_counts, visit_counts,
-                          tree_digests, tree_steps, parents, tree_visits, stats))) {
+                          tree_digests, tree_steps, parents, tree_visits, stats, nullptr))) {
         ctx->last_error = "fc_sample_noalloc: " + sh.last_error;
         return rc;
     }
@@ -1285,25 +1338,19 @@ static int estimate_common(fc_ctx *ctx, const fc_graph *g, const fc_params *para
         tmp.nnz = g->nnz;
         if ((rc = tau_for(ctx, params, tmp, &tau))) return rc;
     }
-    if ((rc = prepare_graph(ctx, g, params->flags & FC_FLAG_TRUSTED_GRAPH, &gv))) return rc;
+    if ((rc = prepare_graph(ctx, g, params->flags & FC_FLAG_TRUSTED_GRAPH, &gv,
+                            deferrable(ctx, params, g))))
+        return rc;
     uint32_t *R = root_counts_out;
     if (!R) {
         if ((rc = ensure(ctx, ctx->rtmp, sizeof(uint32_t) * static_cast<size_t>(gv.n), "root counts")))
             return rc;
         R = static_cast<uint32_t *>(ctx->rtmp.ptr);
     }
-    if (gv.n)
-        FC_HIP(ctx, hipMemsetAsync(R, 0, sizeof(uint32_t) * static_cast<size_t>(gv.n), ctx->stream),
-               "memset R");
+    const Estimate est{diag, farness, closeness, params->estimator == FC_EST_ALG1_LITERAL};
     if ((rc = run_sampler(ctx, gv, params, 0, tau, R, nullptr, nullptr, nullptr, nullptr, nullptr,
-                          stats)))
+                          stats, &est)))
         return rc;
-    Small *sm = static_cast<Small *>(ctx->small.ptr);
-    FC_HIP(ctx, hipMemsetAsync(&sm->sum, 0, sizeof(unsigned long long), ctx->stream), "memset sum");
-    FC_HIP(ctx, fc::launch_sum_u32(R, gv.n, &sm->sum, ctx->stream), "sum launch");
-    FC_HIP(ctx, fc::launch_estimate(R, gv.n, tau, params->estimator == FC_EST_ALG1_LITERAL, &sm->sum,
-                                    diag, farness, closeness, ctx->stream), "estimate launch");
-    FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "estimate");
     if (stats) stats->ms_total = now_ms() - t0;
     return FC_OK;
 }

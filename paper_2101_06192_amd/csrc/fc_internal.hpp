@@ -14,18 +14,12 @@ struct DevBuf {
     size_t bytes = 0;
 };
 
-struct GraphCheck {  // what the CSR checks found
-    unsigned int err;
-    unsigned int pad;
-    unsigned long long sym_diff;  // downward minus upward entries: 0 in a symmetric graph
-};
-
 struct Small {  // device-side counters of one call
     fc::Totals totals;
     unsigned int queue;
     unsigned int pad0;
-    GraphCheck check;
-    unsigned long long sum;
+    fc::GraphCheck check;
+    unsigned long long cross;  // CSR entries that join different tiles
     unsigned int dmax;
     unsigned int pad;
     unsigned long long phase_ticks[8];
@@ -50,6 +44,7 @@ struct fc_ctx {
     DevBuf g_mat, g_vec, g_part, g_taken, g_scr;  // group closeness: matrix, vectors, sums, flags, scratch
     DevBuf t_ex, t_exl, t_ecnt, t_pc, t_sc, t_bl, t_xb;  // tile sampler (exits, counts, lists)
     hipEvent_t ev0 = nullptr, ev1 = nullptr, evm = nullptr;
+    Small *host_small = nullptr;  // pinned: where a call's counters are read back
     size_t state_budget = 0;      // bytes of per-tree state the sampler may use
     uint32_t lanes_per_wave = 64; // active lanes per wave in the lane sampler
     uint32_t max_slots = 0;       // 0 = as many trees in flight as memory allows
@@ -120,11 +115,16 @@ struct GraphView {
     const int32_t *row_ptr = nullptr;
     const int32_t *col_idx = nullptr;
     const double *weights = nullptr;  // device edge weights, or null (unit weights)
+    bool pending = false;  // the checks are enqueued (into Small::check, the rest of Small
+                           // zeroed) but not read: kernels that follow the graph must look
 };
 
 int check_graph_args(fc_ctx *ctx, const fc_graph *g);
 // Stage (if on the host) and validate the CSR (and weights) on the device.
-int prepare_graph(fc_ctx *ctx, const fc_graph *g, bool trusted, GraphView *out);
+// defer: leave the outcome of the checks on the device (out->pending).
+int prepare_graph(fc_ctx *ctx, const fc_graph *g, bool trusted, GraphView *out, bool defer = false);
+// The error for what the checks found (FC_OK: a valid graph).
+int check_outcome(fc_ctx *ctx, const fc::GraphCheck &found);
 // Running row weight sums and step thresholds of a weighted graph into the two
 // buffers (both null for an unweighted graph).
 int weight_tables(fc_ctx *ctx, const GraphView &g, DevBuf &sbuf, DevBuf &tbuf, const double **S,

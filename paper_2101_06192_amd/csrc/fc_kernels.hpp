@@ -44,7 +44,7 @@ hipError_t launch_row_wdeg(const int32_t *row_ptr, const double *weights, int32_
 // and the W_v are added into *wtotal (when not null; any order).
 hipError_t launch_build_vrec(const int32_t *row_ptr, const double *S, int32_t n, double alpha,
                              VRec *vrec, unsigned int *dmax, uint32_t *iso, double *wtotal,
-                             hipStream_t stream);
+                             const GraphCheck *check, uint32_t *zero, hipStream_t stream);
 
 // thr(d), d = 0..d_max, as the device computes it (uint64, 2^32 for "always").
 hipError_t launch_thresholds(double alpha, int32_t d_max, unsigned long long *out,
@@ -128,6 +128,7 @@ struct CoopArgs {
     uint32_t k_limit;         // largest per-vertex draw count in one tree; beyond it is an error
     unsigned int *queue;
     Totals *totals;
+    const GraphCheck *check;          // small-graph variant: checks not read by the host yet, or null
     unsigned long long *phase_ticks;  // 7 wall-clock tick sums per phase, or null
     CoopJob single;           // the job of a single-graph launch (jobs == null)
     const CoopJob *jobs;      // batch: device job table
@@ -304,13 +305,10 @@ hipError_t launch_random_access(uint32_t *data, uint32_t words_pow2, uint32_t it
                                 uint32_t blocks, uint32_t *sink, hipStream_t stream);
 
 // S = sum of R (exact, uint64) into *sum (caller zeroes it).
-hipError_t launch_sum_u32(const uint32_t *x, int32_t n, unsigned long long *sum,
-                          hipStream_t stream);
-
 // diag / farness / closeness from R and S (any output may be null).
 hipError_t launch_estimate(const uint32_t *R, int32_t n, uint32_t tau, int literal,
-                           const unsigned long long *sum, double *diag, double *farness,
-                           double *closeness, hipStream_t stream);
+                           const Totals *totals, const GraphCheck *check, double *diag,
+                           double *farness, double *closeness, hipStream_t stream);
 
 // Block CG on (alpha L + I) X = B, row-major n x k, k <= 64.
 // Rows of more than kCgLongRow neighbours are summed in segments of kCgSegment

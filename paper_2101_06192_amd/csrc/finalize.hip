@@ -3,7 +3,8 @@
 //   diag[v]      = R[v] / tau                      estimates Omega_vv
 //   farness[v]   = (n R[v] + S) / tau - 2          n Omega_vv + tr(Omega) - 2
 //   closeness[v] = n / farness[v]
-// with S = sum_w R[w] an exact 64-bit integer, so every output is one or two
+// with S = sum_w R[w] an exact 64-bit integer (the roots that the sampler has
+// counted over its trees), so every output is one or two
 // correctly rounded binary64 operations and is bit-reproducible.
 #include "fc_kernels.hpp"
 
@@ -13,39 +14,15 @@ namespace fc {
 
 namespace {
 
-// HBM streaming; the blocks are few and each adds once to the total (an atomic
-// per wave of 2048 blocks was 8192 atomics on one address, 40 us for 200 K
-// counts and 101 us for 10^6; now 5.7 us and 6.1 us).
-constexpr uint32_t kSumThreads = 256, kSumBlocks = 256;
-
-__global__ __launch_bounds__(kSumThreads) void sum_u32_kernel(const uint32_t *__restrict__ x,
-                                                              int32_t n, unsigned long long *sum) {
-    __shared__ unsigned long long s_sum[kSumThreads / 64u];
-    unsigned long long acc = 0;
-    const int64_t step = static_cast<int64_t>(gridDim.x) * kSumThreads;
-    int64_t i = static_cast<int64_t>(blockIdx.x) * kSumThreads + threadIdx.x;
-    for (; i + 7 * step < n; i += 8 * step) {  // eight loads in flight
-        uint32_t r[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) r[q] = x[i + q * step];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) acc += r[q];
-    }
-    for (; i < n; i += step) acc += x[i];
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-    if ((threadIdx.x & 63u) == 0) s_sum[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    for (uint32_t w = 1; w < kSumThreads / 64u; ++w) acc += s_sum[w];
-    if (acc) atomicAdd(sum, acc);
-}
-
 __global__ __launch_bounds__(256) void estimate_kernel(const uint32_t *__restrict__ R, int32_t n,
                                                        uint32_t tau, int literal,
-                                                       const unsigned long long *__restrict__ sum,
+                                                       const Totals *__restrict__ totals,
+                                                       const GraphCheck *__restrict__ check,
                                                        double *__restrict__ diag,
                                                        double *__restrict__ farness,
                                                        double *__restrict__ closeness) {
+    // (a call that failed leaves its outputs alone)
+    if (failed(check) || totals->error) return;
     const int32_t v = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
     if (v >= n) return;
     const double dt = static_cast<double>(tau);
@@ -63,7 +40,7 @@ __global__ __launch_bounds__(256) void estimate_kernel(const uint32_t *__restric
     }
     if (farness || closeness) {
         const unsigned long long num =
-            static_cast<unsigned long long>(n) * r + *sum;
+            static_cast<unsigned long long>(n) * r + totals->roots;
         const double f = static_cast<double>(num) / dt - 2.0;
         if (farness) farness[v] = f;
         if (closeness) closeness[v] = static_cast<double>(n) / f;
@@ -89,20 +66,12 @@ hipError_t launch_fill_u64(unsigned long long *p, size_t count, unsigned long lo
     return hipGetLastError();
 }
 
-hipError_t launch_sum_u32(const uint32_t *x, int32_t n, unsigned long long *sum,
-                          hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    const uint32_t blocks = (static_cast<uint32_t>(n) + kSumThreads - 1u) / kSumThreads;
-    sum_u32_kernel<<<blocks < kSumBlocks ? blocks : kSumBlocks, kSumThreads, 0, stream>>>(x, n, sum);
-    return hipGetLastError();
-}
-
 hipError_t launch_estimate(const uint32_t *R, int32_t n, uint32_t tau, int literal,
-                           const unsigned long long *sum, double *diag, double *farness,
-                           double *closeness, hipStream_t stream) {
+                           const Totals *totals, const GraphCheck *check, double *diag,
+                           double *farness, double *closeness, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    estimate_kernel<<<(n + 255) / 256, 256, 0, stream>>>(R, n, tau, literal, sum, diag, farness,
-                                                         closeness);
+    estimate_kernel<<<(n + 255) / 256, 256, 0, stream>>>(R, n, tau, literal, totals, check, diag,
+                                                         farness, closeness);
     return hipGetLastError();
 }
 

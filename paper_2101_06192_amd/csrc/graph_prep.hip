@@ -196,7 +196,9 @@ constexpr uint32_t kVrecThreads = 1024, kVrecBlocks = 256;
 
 __global__ __launch_bounds__(kVrecThreads) void build_vrec_kernel(
     const int32_t *__restrict__ row_ptr, const double *__restrict__ S, int32_t n, double alpha,
-    VRec *__restrict__ vrec, unsigned int *dmax, uint32_t *__restrict__ iso, double *wtotal) {
+    VRec *__restrict__ vrec, unsigned int *dmax, uint32_t *__restrict__ iso, double *wtotal,
+    const GraphCheck *check, uint32_t *__restrict__ zero) {
+    if (failed(check)) return;
     __shared__ uint32_t s_max[kVrecThreads / 64u];
     __shared__ double s_sum[kVrecThreads / 64u];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
@@ -224,6 +226,7 @@ __global__ __launch_bounds__(kVrecThreads) void build_vrec_kernel(
         const double W = S && d ? S[a + static_cast<int32_t>(d) - 1] : 0.0;
         sw += W;
         if (!live) continue;
+        if (zero) zero[v] = 0u;
         const unsigned long long t = S ? root_threshold_w(alpha, W) : root_threshold(alpha, d);
         VRec r;
         r.start = a;
@@ -306,11 +309,11 @@ hipError_t launch_row_wdeg(const int32_t *row_ptr, const double *weights, int32_
 
 hipError_t launch_build_vrec(const int32_t *row_ptr, const double *S, int32_t n, double alpha,
                              VRec *vrec, unsigned int *dmax, uint32_t *iso, double *wtotal,
-                             hipStream_t stream) {
+                             const GraphCheck *check, uint32_t *zero, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     const unsigned int blocks = blocks_for(n, kVrecThreads);
     build_vrec_kernel<<<blocks < kVrecBlocks ? blocks : kVrecBlocks, kVrecThreads, 0, stream>>>(
-        row_ptr, S, n, alpha, vrec, dmax, iso, wtotal);
+        row_ptr, S, n, alpha, vrec, dmax, iso, wtotal, check, zero);
     return hipGetLastError();
 }
 

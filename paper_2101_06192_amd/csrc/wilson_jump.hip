@@ -77,6 +77,7 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
     __shared__ uint32_t s_item, s_cnt, s_flags[4];
     __shared__ unsigned long long s_digest, s_roots;
 
+    if (failed(a.check)) return;
     const uint32_t T = blockDim.x, tid = threadIdx.x, lane = tid & 63u;
     unsigned int err = 0;
     // The totals and the queue are one line of memory for all workgroups, 12 ns an
