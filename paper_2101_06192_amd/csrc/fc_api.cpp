@@ -432,11 +432,14 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         // tile sampler: when the LDS-counter variant does not fit and most edges join
         // ids of the same tile (graphs with local ids: grids, road networks)
         if (!use_lds && (mode == 5 || (mode == 0 && ctx->coop_lds_counts)) && g.n >= 1) {
-            uint32_t B = ctx->tile_size;
-            if (B == 0) {  // the widest tile whose arrays fit in LDS
-                B = fc::kTileMax;
-                while (B > 64u && fc::tile_lds_bytes(B) + kLdsStaticBytes > ctx->max_lds) B -= 64u;
-            }
+            // the widest tile whose arrays fit in LDS and whose vertices the threads
+            // can own; a wider one that is asked for is cut to that (up to kTileAsk)
+            uint32_t widest = std::min<uint32_t>(fc::kTileMax, fc::kTileOwn * ctx->tile_threads);
+            while (widest > 64u && fc::tile_lds_bytes(widest) + kLdsStaticBytes > ctx->max_lds)
+                widest -= 64u;
+            uint32_t B = widest;
+            if (ctx->tile_size)
+                B = ctx->tile_size <= kTileAsk ? std::min(widest, ctx->tile_size) : ctx->tile_size;
             const uint32_t ntiles = static_cast<uint32_t>((static_cast<uint64_t>(g.n) + B - 1u) / B);
             bool fits = fc::tile_lds_bytes(B) + kLdsStaticBytes <= ctx->max_lds;
             bool local = mode == 5;
@@ -677,25 +680,17 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         const bool bits_lds = ctx->tile_bits_lds && 4u * bw + kLdsStaticBytes <= ctx->max_lds;
         tile_lds = std::max(fc::tile_lds_bytes(ta.B), bits_lds ? 4u * bw : 0u);
         const int fit = fc::tile_max_active(tile_threads, tile_lds, weighted);
-        // first arrows of all trees drawn ahead when their targets fit the budget
-        const size_t pre_bytes = 4u * n * static_cast<size_t>(tree_count);
-        bool predraw = ctx->predraw_mib != 0 &&
-                       pre_bytes <= (static_cast<size_t>(ctx->predraw_mib) << 20);
-        if (predraw && ensure(ctx, ctx->cpre, pre_bytes, "pre-drawn targets") != FC_OK) {
-            predraw = false;
-            ctx->last_error.clear();
-        }
-        const size_t per_slot = (predraw ? 0u : 4u * n) + 8u * n + 2u * n + 4u * n * 3u + 12u * n +
-                                4u * (n + 2u) + 4u * ta.ntiles + (bits_lds ? 4u : 8u) * bw +
-                                10u * 256u;
+        const size_t per_slot = (4u + 4u + 2u + 2u) * n + 4u * n * 3u + 12u * n + 4u * (n + 2u) +
+                                4u * ta.ntiles + (bits_lds ? 4u : 8u) * bw + 11u * 256u;
         slots = std::max<size_t>(1, state_budget_now(ctx) / per_slot);
         slots = std::min<size_t>(slots, tree_count);
         const uint32_t per_cu = fit > 0 ? static_cast<uint32_t>(fit) : 1u;
         slots = std::min<size_t>(slots, static_cast<size_t>(ctx->cu_count) * per_cu);
         if (ctx->max_slots) slots = std::min<size_t>(slots, ctx->max_slots);
-        if ((!predraw && (rc = ensure(ctx, ctx->cword, 4u * n * slots, "tree targets"))) ||
-            (rc = ensure(ctx, ctx->ckk, 8u * n * slots, "draw counts")) ||
+        if ((rc = ensure(ctx, ctx->cword, 4u * n * slots, "tree targets")) ||
+            (rc = ensure(ctx, ctx->ckk, 4u * n * slots, "draw counts")) ||
             (rc = ensure(ctx, ctx->t_ex, 2u * n * slots, "exits")) ||
+            (rc = ensure(ctx, ctx->t_tl, 2u * n * slots, "tile targets")) ||
             (rc = ensure(ctx, ctx->t_exl, 4u * n * slots, "exit lists")) ||
             (rc = ensure(ctx, ctx->t_pc, 4u * n * slots, "in-counts")) ||
             (rc = ensure(ctx, ctx->t_sc, 4u * n * slots, "exit successors")) ||
@@ -705,8 +700,6 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
             (rc = ensure(ctx, ctx->cbits, 4u * bw * slots, "settled bitmap")) ||
             (!bits_lds && (rc = ensure(ctx, ctx->t_xb, 4u * bw * slots, "exit bitmap"))))
             return rc;
-        FC_HIP(ctx, hipMemsetAsync(ctx->ckk.ptr, 0, 8u * n * slots, ctx->stream), "memset draw counts");
-        FC_HIP(ctx, hipMemsetAsync(ctx->t_pc.ptr, 0, 4u * n * slots, ctx->stream), "memset in-counts");
         ta.vrec = vrec;
         ta.col_idx = g.col_idx;
         ta.wsum = wsum;
@@ -721,9 +714,9 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         ta.k_limit = ctx->max_draws ? ctx->max_draws : 0x7FFFFFFFu;
         ta.max_rounds = 0x40000000u;
         ta.step_cap = step_cap;
-        ta.pre = predraw ? static_cast<uint32_t *>(ctx->cpre.ptr) : nullptr;
-        ta.tw = predraw ? nullptr : static_cast<uint32_t *>(ctx->cword.ptr);
-        ta.kk = static_cast<uint64_t *>(ctx->ckk.ptr);
+        ta.tw = static_cast<uint32_t *>(ctx->cword.ptr);
+        ta.kk = static_cast<uint32_t *>(ctx->ckk.ptr);
+        ta.tl = static_cast<uint16_t *>(ctx->t_tl.ptr);
         ta.ex = static_cast<uint16_t *>(ctx->t_ex.ptr);
         ta.exl = static_cast<uint32_t *>(ctx->t_exl.ptr);
         ta.ecnt = static_cast<uint32_t *>(ctx->t_ecnt.ptr);
@@ -858,10 +851,6 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         FC_HIP(ctx, fc::launch_wilson_jump(c, lds_threads, jump_lds, weighted, ctx->stream),
                "wilson_jump launch");
     } else if (use_tile) {
-        if (ta.pre) {
-            FC_HIP(ctx, fc::launch_tile_predraw(ta, ctx->stream), "tile_predraw launch");
-            FC_HIP(ctx, hipEventRecord(ctx->evm, ctx->stream), "event");
-        }
         FC_HIP(ctx, fc::launch_wilson_tile(ta, tile_threads, tile_lds, ctx->stream),
                "wilson_tile launch");
     } else if (use_hyb) {
@@ -911,7 +900,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         stats->digest_sum = tot.digest_sum;
         stats->ms_sample = ms;
         stats->ms_predraw = 0.0;
-        if ((use_lds && c.pre) || (use_tile && ta.pre)) {
+        if (use_lds && c.pre) {
             float pm = 0.f;
             (void)hipEventElapsedTime(&pm, ctx->ev0, ctx->evm);
             stats->ms_predraw = pm;
@@ -1096,7 +1085,7 @@ int fc_destroy(fc_ctx *ctx) {
                       &ctx->iso, &ctx->corigt, &ctx->cpre, &ctx->weights, &ctx->wsum, &ctx->wthr,
                       &ctx->s_wdeg, &ctx->rk_key0, &ctx->rk_key1, &ctx->rk_val0, &ctx->rk_val1,
                       &ctx->rk_hist, &ctx->rk_thist, &ctx->rk_ra, &ctx->rk_rb, &ctx->rk_s, &ctx->g_mat,
-                      &ctx->g_vec, &ctx->g_part, &ctx->g_taken, &ctx->g_scr, &ctx->t_ex, &ctx->t_exl,
+                      &ctx->g_vec, &ctx->g_part, &ctx->g_taken, &ctx->g_scr, &ctx->t_ex, &ctx->t_tl, &ctx->t_exl,
                       &ctx->t_ecnt, &ctx->t_pc, &ctx->t_sc, &ctx->t_bl, &ctx->t_xb})
         if (b->ptr) (void)hipFree(b->ptr);
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);

@@ -42,7 +42,7 @@ struct fc_ctx {
                                  // step thresholds
     DevBuf rk_key0, rk_key1, rk_val0, rk_val1, rk_hist, rk_thist, rk_ra, rk_rb, rk_s;  // ranking
     DevBuf g_mat, g_vec, g_part, g_taken, g_scr;  // group closeness: matrix, vectors, sums, flags, scratch
-    DevBuf t_ex, t_exl, t_ecnt, t_pc, t_sc, t_bl, t_xb;  // tile sampler (exits, counts, lists)
+    DevBuf t_ex, t_tl, t_exl, t_ecnt, t_pc, t_sc, t_bl, t_xb;  // tile sampler (exits, counts, lists)
     hipEvent_t ev0 = nullptr, ev1 = nullptr, evm = nullptr;
     Small *host_small = nullptr;  // pinned: where a call's counters are read back
     size_t state_budget = 0;      // bytes of per-tree state the sampler may use
@@ -94,6 +94,8 @@ namespace fc_host {
 
 // static LDS of the LDS-counter kernel (item, tails, totals, phase clocks) with margin
 constexpr size_t kLdsStaticBytes = 1024;
+// Largest "tile_size" that the tile sampler takes (6 bytes of LDS a vertex).
+constexpr uint32_t kTileAsk = 26432;
 // fewest non-isolated vertices for which the LDS sampler draws first arrows ahead
 constexpr uint32_t kPredrawMinVertices = 16384;
 

@@ -239,10 +239,11 @@ hipError_t launch_relabel_vrec(const VRec *vrec, const uint32_t *inv, uint32_t n
                                hipStream_t stream);
 
 // Tile sampler (graphs whose ids are local): one workgroup per tree pops the
-// cycles inside each tile of B consecutive ids with LDS counters, finds the
+// cycles inside each tile of B consecutive ids in LDS, finds the
 // cycles that cross tiles on the functional graph of the exit vertices, and
 // finishes the few vertices whose exit does not reach u* with global counters.
 constexpr uint32_t kTileMax = 32704;  // largest tile: local ids and codes fit 15 bits
+constexpr uint32_t kTileOwn = 32;     // vertices of a tile per thread, at most
 struct TileArgs {
     const VRec *vrec;          // records of G* (original ids)
     const int32_t *col_idx;
@@ -257,13 +258,13 @@ struct TileArgs {
     uint32_t k_limit;          // largest per-vertex draw count in one tree
     uint32_t max_rounds;       // bound on popping rounds per tile and in the residual
     unsigned long long step_cap;  // per-tree bound on draws
-    uint32_t *pre;             // tree_count * n first-arrow targets drawn ahead, or null
-    uint32_t *tw;              // slots * n targets (when pre is null)
-    uint64_t *kk;              // slots * n (epoch << 32) | draws; zeroed per launch
+    uint32_t *tw;              // slots * n targets out of the tile, and of the residual
+    uint32_t *kk;              // slots * n draws (of the vertices not settled in their tile)
+    uint16_t *tl;              // slots * n tile-local targets (of the same)
     uint16_t *ex;              // slots * n tile-local exit, or 0x7FFF (reaches u* in the tile)
     uint32_t *exl;             // slots * n per-tile exit lists (tile * B offsets)
     uint32_t *ecnt;            // slots * ntiles exits per tile
-    uint32_t *pc;              // slots * n in-counts; zeroed per launch
+    uint32_t *pc;              // slots * n in-counts
     uint32_t *sc;              // slots * n exit-graph successors
     uint32_t *bl;              // slots * 3 n lists
     uint32_t *lv;              // slots * (n + 2) peel level bounds
@@ -273,8 +274,8 @@ struct TileArgs {
     uint32_t repop;            // 1: pop re-formed 2-cycles within the tile round that re-forms them
     unsigned int *queue;
     Totals *totals;
-    unsigned long long *phase_ticks;  // 8 tick sums: tile loads, counts, peels, pops, exits,
-                                      // exit graph, residual, output
+    unsigned long long *phase_ticks;  // 8 tick sums: first arrows, redraws, jumps, cycles,
+                                      // exits, exit graph, residual, output
     uint32_t *root_counts;
     unsigned long long *visit_counts;
     unsigned long long *tree_digests;
@@ -285,8 +286,6 @@ struct TileArgs {
 // lds: dynamic LDS bytes, at least tile_lds_bytes(B) and, with xb null or
 // bits_lds set, a bitmap of n bits (4 ceil(n / 32)).
 hipError_t launch_wilson_tile(const TileArgs &a, uint32_t threads, size_t lds, hipStream_t stream);
-// First arrow of every vertex in every tree of the call: a.pre[item * n + v].
-hipError_t launch_tile_predraw(const TileArgs &a, hipStream_t stream);
 hipError_t tile_set_limit(size_t bytes);
 int tile_max_active(uint32_t threads, size_t lds, bool weighted);
 size_t tile_lds_bytes(uint32_t B);  // LDS of one tile's arrays

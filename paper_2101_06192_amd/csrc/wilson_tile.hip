@@ -7,14 +7,13 @@
 // lets one workgroup pop a tree's cycles in any grouping.  Here:
 //
 // 1. Tiles.  The ids are cut into tiles of B consecutive vertices, handled
-//    one after another.  A tile's arrows are loaded into LDS as tile-local
-//    targets; an arrow to u* or out of the tile ends a path there.  Round
-//    after round, the cycles that lie inside the tile are found (in-arrow
-//    counts in LDS, Kahn peel, reverse sweep) and popped, until none is
-//    left; after the first round only the vertices still unresolved are
-//    scanned (they are listed each round).  Every vertex of the tile then
-//    has an exit: the last tile vertex on its path (whose arrow leaves the
-//    tile), or "settled" when the path reaches u* inside the tile.
+//    one after another, whole in LDS: draws, 2-cycles, pointer jumping and cycle
+//    pops as in the small-graph sampler (wilson_jump.hip says how, and why it
+//    finds every cycle), where an arrow out of the tile ends a path as one to u*
+//    does.  Every vertex of the tile then has an exit: the last tile vertex on
+//    its path (whose arrow leaves the tile), or "settled" when the path reaches
+//    u* inside the tile.  The tile's part of the outputs is written at once;
+//    what the residual changes later, it corrects.
 // 2. Exit graph.  On the exit vertices the map u -> ex[target(u)] is a
 //    functional graph whose cycles are exactly the arrows' cycles that cross
 //    tiles.  A Kahn peel over the exits (global counters; only exits take
@@ -27,25 +26,27 @@
 //    when it fits), global in-arrow counters and lists, only for them.
 // No global atomic touches a vertex outside the exit graph and the residual.
 //
-// LDS during the tiles:
-//   lt[i]  u16  tile-local target of tile vertex i, or kRoot (u*) / kExt (a
-//               vertex of another tile)
-//   st[i]  u16  resolved: the tile-local id of its exit, or kSettled;
-//               unresolved: kUnres | in-arrow count of the current round
-//   tp     u16  peel order of the current round
-//   lvs    u16  the first kLvLds peel level bounds (the rest in global lv)
+// LDS during the tiles (6.4 bytes a vertex):
+//   mark, hit, spill  bitmaps: marks (or the vertices of the 2-cycle check under
+//             way), marks that a walk ended at, draw counts that left 8 bits
+//   T      u16 tile-local target, or kRoot (u*) / kExt (a vertex of another
+//              tile), | drawn again << 15
+//   J      u16 open: jump; else kDone | the tile-local id of the exit, or kRoot
+//   list   u16 vertices that draw again, for half of the tile's vertices (pairs
+//              and cycles without room there are popped without it)
+//   K      u8  low byte of the draw count (the rest in kk, where spill says so)
 // and, once the tiles are done, the exit bitmap and then the settled bitmap,
-// when n/8 bytes fit.
+// when n/8 bytes fit.  A thread owns the set's vertices tid, tid + T, ...: at most
+// 32, with a bit each in a register for "open".
 // Global, per tree slot:
-//   tw[v]  u32  the top arrow's target (u* = n): the tree's own pre-drawn
-//               array, or the slot's
-//   kk[v]  u64  (epoch << 32) | arrows drawn, written when v draws again
-//   ex[v]  u16  tile-local id of v's exit, or kSettled
+//   tw[v]  u32  the top arrow's target (u* = n), where it leaves its tile and for
+//               the residual
+//   tl[v]  u16  its tile-local form (T), ex[v] u16 tile-local id of v's exit, or
+//               kRoot: of every vertex once its tile is done
+//   kk[v]  u32  arrows drawn, of the vertices not settled within their tile
 //   exl    u32  each tile's exit vertices, at offset tile * B; ecnt[tile]
-//   pc, sc u32  in-counts (exit graph, residual; zero between uses) and exit
-//               successors
-//   bl     u32  lists: exits / residual, next residual, peel order (during
-//               the tiles: each round's unresolved vertices, two lists)
+//   pc, sc u32  in-counts (exit graph, residual) and exit successors
+//   bl     u32  lists: exits / residual, next residual, peel order
 //   lv     u32  peel level bounds
 //   xb          exits whose chain reaches u* (LDS when n/8 bytes fit)
 //   bits        settled bitmap of the residual rounds (copied into LDS when it
@@ -58,17 +59,39 @@ namespace fc {
 
 namespace {
 
-constexpr uint32_t kRoot = 0xFFFFu;     // lt: the arrow goes to u*
-constexpr uint32_t kExt = 0xFFFEu;      // lt: the arrow leaves the tile
-constexpr uint32_t kUnres = 0x8000u;    // st: unresolved (low 15 bits: in-arrow count)
-constexpr uint32_t kSettled = 0x7FFFu;  // st: the path reaches u* inside the tile
-constexpr uint32_t kCountMask = 0x7FFFu;
-constexpr uint32_t kLvLds = 2048;       // peel level bounds kept in LDS per round
+constexpr uint32_t kRoot = 0x7FFFu;   // T: the arrow goes to u*; ex: the path ends there
+constexpr uint32_t kExt = 0x7FFEu;    // T: the arrow leaves the tile
+constexpr uint32_t kAgain = 0x8000u;  // T: drawn more than once
+constexpr uint32_t kDone = 0x8000u;   // J: the exit is known
+constexpr uint32_t kIdMask = 0x7FFFu;
+constexpr uint32_t kMinJumps = 4;   // passes before marks are tried
+constexpr uint32_t kMoreJumps = 3;  // and after some were not on a cycle
+constexpr uint32_t kU = 4, kD = 2;  // vertices a thread keeps in flight: jumping, drawing
+constexpr uint32_t kWalk = 96;      // arrows a walk to the next vertex that drew again may take
+constexpr uint32_t kLowBits = 8;
 
-// Per-phase clock sums (tid 0 of each workgroup): tile loads, in-arrow counts
-// with peel level 0, peel levels with the reverse sweep, cycle pops, the tiles'
-// exits, the exit graph, the residual rounds, the output.
-enum Phase : int { kPhLoad = 0, kPhCount, kPhPeel, kPhPop, kPhExits, kPhExit, kPhResidual,
+// LDS of a set of up to Bp vertices (Bp a multiple of 64), in words from the start.
+struct TileLayout {
+    uint32_t nb;                       // words of a bitmap
+    uint32_t arrow, jump, list, cap;   // cap: entries of the list
+    uint32_t drawn, words;
+};
+__host__ __device__ inline TileLayout tile_layout(uint32_t Bp) {
+    TileLayout L{};
+    L.nb = Bp >> 5;
+    L.arrow = 3u * L.nb;
+    L.jump = L.arrow + (Bp >> 1);
+    L.list = L.jump + (Bp >> 1);
+    L.cap = Bp >> 1;
+    L.drawn = L.list + (Bp >> 2);
+    L.words = L.drawn + (Bp >> 2);
+    return L;
+}
+
+// Per-phase clock sums (tid 0 of each workgroup): first arrows, 2-cycles and all
+// redraws, jumps, cycle marks and walks, the tiles' exits and outputs, the exit
+// graph, the residual, the tree's totals.
+enum Phase : int { kPhDraw = 0, kPhPop, kPhJump, kPhCycle, kPhExits, kPhExit, kPhResidual,
                    kPhOutput, kPhNum };
 
 // One arrow of v in tree t with draw index k (original ids; kWeighted: the
@@ -113,9 +136,8 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
     // s_lc: three rotating tail counters, so that one barrier per peel level
     // suffices (level k appends with counter (k + 1) % 3 while thread 0 clears
     // counter (k + 2) % 3, which everyone read a level ago)
-    __shared__ uint32_t s_item, s_u, s_c, s_over, s_rover, s_nlev, s_pos, s_nc, s_lc[3];
-    __shared__ uint32_t s_tail[64];
-    __shared__ unsigned long long s_digest, s_roots, s_draws;
+    __shared__ uint32_t s_item, s_u, s_c, s_cnt, s_over, s_lc[3], s_flags[4];
+    __shared__ unsigned long long s_digest, s_roots;
     __shared__ unsigned long long s_ph[kPhNum + 1];
 
     const uint32_t T = blockDim.x;
@@ -125,22 +147,25 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
     const size_t slot = blockIdx.x;
     const uint32_t n = a.n;
     const uint32_t B = a.B;
-    const uint32_t Bp = a.Bp;  // B rounded up to a multiple of 64
     const uint32_t ntiles = a.ntiles;
     const size_t nn = n;
     const uint32_t nw = (n + 31u) >> 5;
 
-    uint16_t *__restrict__ lt = reinterpret_cast<uint16_t *>(s_dyn);
-    uint32_t *__restrict__ st32 = s_dyn + (Bp >> 1);
-    uint16_t *__restrict__ st16 = reinterpret_cast<uint16_t *>(st32);
-    uint16_t *__restrict__ tp = reinterpret_cast<uint16_t *>(s_dyn + Bp);
-    uint16_t *__restrict__ lvs = reinterpret_cast<uint16_t *>(s_dyn + Bp + (Bp >> 1));
+    const TileLayout L = tile_layout(a.Bp);
+    uint32_t *__restrict__ mark = s_dyn;
+    uint32_t *__restrict__ hit = s_dyn + L.nb;
+    uint32_t *__restrict__ spill = s_dyn + 2u * L.nb;
+    uint16_t *arrow = reinterpret_cast<uint16_t *>(s_dyn + L.arrow);
+    uint16_t *jump = reinterpret_cast<uint16_t *>(s_dyn + L.jump);
+    uint16_t *__restrict__ list = reinterpret_cast<uint16_t *>(s_dyn + L.list);
+    uint8_t *__restrict__ drawn = reinterpret_cast<uint8_t *>(s_dyn + L.drawn);
     uint32_t *const gbits = a.bits + slot * static_cast<size_t>(nw);
     uint32_t *__restrict__ bits = a.bits_lds ? s_dyn : gbits;
     uint32_t *__restrict__ xb = a.xb ? a.xb + slot * static_cast<size_t>(nw) : s_dyn;
 
-    uint32_t *const slot_tw = a.tw ? a.tw + slot * nn : nullptr;
-    uint64_t *__restrict__ kk = a.kk + slot * nn;
+    uint32_t *__restrict__ tw = a.tw + slot * nn;
+    uint32_t *__restrict__ kk = a.kk + slot * nn;
+    uint16_t *__restrict__ tl = a.tl + slot * nn;
     uint16_t *__restrict__ ex = a.ex + slot * nn;
     uint32_t *__restrict__ exl = a.exl + slot * nn;
     uint32_t *__restrict__ ecnt = a.ecnt + slot * static_cast<size_t>(ntiles);
@@ -152,7 +177,6 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
     uint32_t *__restrict__ lvg = a.lv + slot * (nn + 2u);
 
     unsigned int err = 0;
-    uint32_t epoch = 0;  // per-slot tree sequence number of this launch (kk is zeroed per launch)
     const bool timing = a.phase_ticks != nullptr;
     if (tid == 0) {
         s_over = 0;
@@ -162,26 +186,13 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
         for (int i = 0; i < kPhNum; ++i) s_ph[i] = 0;
         s_ph[kPhNum] = wall_clock64();
     }
-    auto mark = [&](int which) {
+    auto mark_time = [&](int which) {
         if (timing && tid == 0) {
             const unsigned long long now = wall_clock64();
             s_ph[which] += now - s_ph[kPhNum];
             s_ph[kPhNum] = now;
         }
     };
-    auto st_get = [&](uint32_t i) -> uint32_t { return (st32[i >> 1] >> ((i & 1u) << 4)) & 0xFFFFu; };
-    auto st_inc = [&](uint32_t i) { atomicAdd(&st32[i >> 1], 1u << ((i & 1u) << 4)); };
-    // decrement an unresolved count (>= 1); returns the field before
-    auto st_dec = [&](uint32_t i) -> uint32_t {
-        const uint32_t sh = (i & 1u) << 4;
-        return (atomicAdd(&st32[i >> 1], 0u - (1u << sh)) >> sh) & 0xFFFFu;
-    };
-    // tile peel level bounds: LDS first, global beyond
-    auto lv_set = [&](uint32_t i, uint32_t v) {
-        if (i < kLvLds) lvs[i] = static_cast<uint16_t>(v);
-        else lvg[i] = v;
-    };
-    auto lv_get = [&](uint32_t i) -> uint32_t { return i < kLvLds ? lvs[i] : lvg[i]; };
     auto is_settled = [&](uint32_t v) -> bool {
         return v >= n || ((bits[v >> 5] >> (v & 31u)) & 1u);
     };
@@ -194,303 +205,407 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
         const uint32_t item = uniform(s_item);
         if (item >= a.tree_count) break;
         const uint32_t t = a.tree_begin + item;
-        uint32_t *__restrict__ tw = a.pre ? a.pre + static_cast<size_t>(item) * nn : slot_tw;
-        ++epoch;
+        unsigned long long draws = n;  // arrows drawn in this tree
+        unsigned long long my_digest = 0, my_roots = 0;
         if (tid == 0) {
             s_digest = 0;
             s_roots = 0;
-            s_draws = n;
         }
-        // first arrows, when no pre-draw kernel drew them
-        if (!a.pre) {
-            for (uint32_t v = tid; v < n; v += T) tw[v] = tile_draw<kWeighted>(a, v, 0u, t);
-        }
-        auto pop = [&](uint32_t v) -> uint32_t {  // v draws its next arrow
-            const uint64_t kv = kk[v];
-            const uint32_t k = static_cast<uint32_t>(kv >> 32) == epoch ? static_cast<uint32_t>(kv) : 1u;
-            if (k + 1u > a.k_limit) err |= kErrVisitOverflow;
-            const uint32_t tg = tile_draw<kWeighted>(a, v, k, t);
-            kk[v] = (static_cast<uint64_t>(epoch) << 32) | (k + 1u);
+        // A vertex of the residual draws its arrow with index k: the outputs had
+        // the one before.
+        auto redrawn = [&](uint32_t v, uint32_t was, uint32_t tg, uint32_t k) {
+            const unsigned long long hi = static_cast<unsigned long long>(v) << 32;
+            my_digest += mix64(hi | tg) - mix64(hi | was);
+            if (tg == n) {
+                ++my_roots;
+                atomicAdd(&a.root_counts[v], 1u);
+            }
+            if (a.parents) a.parents[static_cast<size_t>(item) * nn + v] = static_cast<int32_t>(tg);
+            if (a.visit_counts) atomicAdd(&a.visit_counts[v], 1ull);
+            if (a.tree_visits) a.tree_visits[static_cast<size_t>(item) * nn + v] = k + 1u;
+            kk[v] = k + 1u;
             tw[v] = tg;
+        };
+        auto pop_global = [&](uint32_t v) -> uint32_t {  // the residual's global rounds
+            const uint32_t k = kk[v], was = tw[v];
+            if (k >= a.k_limit) err |= kErrVisitOverflow;
+            const uint32_t tg = tile_draw<kWeighted>(a, v, k, t);
+            redrawn(v, was, tg, k);
             return tg;
         };
 
-        // Cycle popping inside a vertex set held in LDS (a tile, or the
-        // residual): set vertex i is global id vid(i); an arrow's target becomes
-        // a set-local code: kRoot when it reaches u* (u* itself, or a vertex
-        // settled before), kExt for a vertex of another tile, else its local id.
-        // Rounds until every vertex of the set is resolved (settled, or its
-        // exit known).
-        // (the residual set: its id list and a list buffer apart from it and bP)
-        uint32_t *res_list = bU, *res_l0 = bN;
-        auto pop_rounds = [&](uint32_t b, uint32_t lo, bool res, int ph_count, int ph_peel,
-                              int ph_pop) {
-            auto vid = [&](uint32_t i) -> uint32_t { return res ? res_list[i] : lo + i; };
+        // Cycle popping inside a vertex set held in LDS: the tile of the b ids from
+        // lo on, which draw their first arrows, or (res) the residual, b ids in
+        // res_list.  Ends with every vertex's exit in J (a tile), or with nobody
+        // left to pop (the residual).
+        uint32_t *res_list = bU;
+        auto pop_set = [&](uint32_t b, uint32_t lo, bool res, int ph_pop, int ph_jump, int ph_cycle) {
+            auto marked = [&](uint32_t i) { return (mark[i >> 5] >> (i & 31u)) & 1u; };
             auto code_of = [&](uint32_t tg) -> uint32_t {
                 if (tg == n) return kRoot;
                 if (res) return ((gbits[tg >> 5] >> (tg & 31u)) & 1u) ? kRoot : sc[tg];
                 return tg - lo < b ? tg - lo : kExt;
             };
-            // After the first round (which scans the whole set) only the vertices
-            // left hanging off a cycle by the sweep and the cycle vertices
-            // themselves can be unresolved: each round lists them (global, per
-            // slot, in lists the tiles do not use otherwise), and later rounds
-            // scan that list instead of the set.
-            uint32_t *Lcur = res ? res_l0 : bN + lo;
-            uint32_t *Lnext = res ? bP : bP + lo;
-            uint32_t lcount = 0;
-            bool full = true;
+            // Arrow of set vertex i from its next draw; the draw count goes up by one.
+            auto redraw = [&](uint32_t i) {
+                const uint32_t v = res ? res_list[i] : lo + i;
+                uint32_t k, was = 0;
+                if (res) {
+                    k = kk[v];
+                    was = tw[v];
+                } else {
+                    k = drawn[i];
+                    if ((spill[i >> 5] >> (i & 31u)) & 1u) k |= kk[v] << kLowBits;
+                }
+                VRec r = load_vrec(a.vrec, v);  // on its way during the Philox rounds
+                const Philox4 x = philox4x32_10(v, k, t, a.stream_id, a.key0, a.key1);
+                hold_vrec(r);
+                if (k >= a.k_limit) {  // the error ends the tree here: as if v were a root
+                    err |= kErrVisitOverflow;
+                    arrow[i] = static_cast<uint16_t>(kRoot | kAgain);
+                    jump[i] = static_cast<uint16_t>(kDone | kRoot);
+                    return;
+                }
+                const uint32_t tg = arrow_target<kWeighted>(r, x.x0, x.x1, a.col_idx, a.wsum, a.wthr, n);
+                if (res) redrawn(v, was, tg, k);
+                const uint32_t code = code_of(tg);
+                arrow[i] = static_cast<uint16_t>(code | kAgain);
+                if (code == kRoot) {
+                    jump[i] = static_cast<uint16_t>(kDone | kRoot);
+                } else if (code == kExt) {
+                    jump[i] = static_cast<uint16_t>(kDone | i);
+                    tw[v] = tg;
+                } else {  // a target whose exit is known: its path is final
+                    const uint32_t j = jump[code];
+                    if (j & kDone) jump[i] = static_cast<uint16_t>(j);
+                }
+                if (!res) {
+                    drawn[i] = static_cast<uint8_t>(k + 1u);
+                    if (((k + 1u) & ((1u << kLowBits) - 1u)) == 0u) {
+                        kk[v] = (k + 1u) >> kLowBits;
+                        atomicOr(&spill[i >> 5], 1u << (i & 31u));
+                    }
+                }
+            };
+            // Appends the pair (u, w) at list[base + ...], of which cap entries are free
+            // (all lanes of the wave call it); without room there it is left alone.
+            auto append_pair = [&](uint32_t base, uint32_t cap, uint32_t u, uint32_t w, bool pred) {
+                const uint64_t m = __ballot(pred);
+                if (m == 0ull) return;
+                uint32_t off = 0;
+                if (lane == 0) off = atomicAdd(&s_cnt, 2u * static_cast<uint32_t>(__popcll(m)));
+                off = uniform(off) + 2u * static_cast<uint32_t>(__popcll(m & ((1ull << lane) - 1ull)));
+                if (pred && off + 2u <= cap) {
+                    list[base + off] = static_cast<uint16_t>(u);
+                    list[base + off + 1u] = static_cast<uint16_t>(w);
+                }
+            };
+
+            for (uint32_t i = tid; i < 3u * L.nb; i += T) s_dyn[i] = 0u;
+            if (tid == 0) s_cnt = 0;
+            if (tid < 4u) s_flags[tid] = 0;
+            uint32_t open = 0;  // bit q: the exit of vertex q T + tid is not known
+            if (res) {
+                for (uint32_t q = 0; q * T + tid < b; ++q) {
+                    const uint32_t i = q * T + tid;
+                    const uint32_t code = code_of(tw[res_list[i]]);
+                    arrow[i] = static_cast<uint16_t>(code);
+                    jump[i] = static_cast<uint16_t>(code == kRoot ? kDone | kRoot : 0u);
+                    if (code != kRoot) open |= 1u << q;
+                }
+            } else {
+                for (uint32_t i0 = 0; i0 * T < b; i0 += kD) {
+                    VRec r[kD] = {};
+                    uint32_t tg[kD];
+#pragma unroll
+                    for (uint32_t q = 0; q < kD; ++q) {
+                        const uint32_t i = (i0 + q) * T + tid;
+                        if (i < b) r[q] = load_vrec(a.vrec, lo + i);
+                    }
+#pragma unroll
+                    for (uint32_t q = 0; q < kD; ++q) {
+                        const uint32_t i = (i0 + q) * T + tid;
+                        tg[q] = n;
+                        if (i < b) {
+                            const Philox4 x = philox4x32_10(lo + i, 0u, t, a.stream_id, a.key0, a.key1);
+                            tg[q] = arrow_target<kWeighted>(r[q], x.x0, x.x1, a.col_idx, a.wsum, a.wthr, n);
+                        }
+                    }
+#pragma unroll
+                    for (uint32_t q = 0; q < kD; ++q) {
+                        const uint32_t i = (i0 + q) * T + tid;
+                        if (i >= b) continue;
+                        const uint32_t code = code_of(tg[q]);
+                        arrow[i] = static_cast<uint16_t>(code);
+                        drawn[i] = 1;
+                        jump[i] = static_cast<uint16_t>(code == kRoot ? kDone | kRoot
+                                                        : code == kExt ? kDone | i : 0u);
+                        if (code == kExt) tw[lo + i] = tg[q];
+                        if (code < kExt) open |= 1u << (i0 + q);
+                    }
+                }
+            }
+            __syncthreads();
+            if (!res) mark_time(kPhDraw);
+            // 2-cycles of the first arrows, each listed by its smaller end
+            {
+                uint32_t pop = 0;
+                for (uint32_t todo = open; todo; todo &= todo - 1u) {
+                    const uint32_t q = static_cast<uint32_t>(__builtin_ctz(todo));
+                    const uint32_t i = q * T + tid, w = arrow[i];
+                    if (i < w && arrow[w] == i) pop |= 1u << q;
+                }
+                while (__ballot(pop != 0u)) {
+                    const bool have = pop != 0u;
+                    const uint32_t u = have ? static_cast<uint32_t>(__builtin_ctz(pop)) * T + tid : 0u;
+                    append_pair(0u, L.cap, u, have ? arrow[u] : 0u, have);
+                    pop &= pop - 1u;
+                }
+            }
+            __syncthreads();
             uint32_t rounds = 0;
+            bool wide = true;  // this round's jumps go over all open vertices
+            uint32_t cur = 0, ccur = min(uniform(s_cnt), L.cap);  // list entries that draw
+            bool done = false;
+            __syncthreads();
             for (;;) {
-                if (++rounds > a.max_rounds || s_over) {
+                // pop what is listed, then the 2-cycles that the new arrows close
+                while (ccur > 0u) {
+                    for (uint32_t j = tid; j < ccur; j += T) {
+                        const uint32_t i = list[cur + j];
+                        redraw(i);
+                        atomicOr(&mark[i >> 5], 1u << (i & 31u));
+                    }
+                    draws += ccur;
+                    if (tid == 0) s_cnt = 0;
+                    __syncthreads();
+                    if (draws > a.step_cap) break;
+                    // pairs go to the larger part of the list that is free; pairs that
+                    // find no room there wait for the cycle search
+                    const uint32_t after = L.cap - (cur + ccur);
+                    const uint32_t nxt = after >= cur ? cur + ccur : 0u;
+                    const uint32_t room = a.repop ? (after >= cur ? after : cur) & ~1u : 0u;
+                    for (uint32_t j0 = wave_base; j0 < ccur; j0 += T) {
+                        uint32_t u = 0, w = 0;
+                        bool pair = false;
+                        if (j0 + lane < ccur) {
+                            u = list[cur + j0 + lane];
+                            w = arrow[u] & kIdMask;
+                            // the pair belongs to its smaller end if both drew
+                            if (w < kExt)
+                                pair = (arrow[w] & kIdMask) == u && (!marked(w) || u < w);
+                        }
+                        append_pair(nxt, room, u, w, pair);
+                    }
+                    __syncthreads();
+                    for (uint32_t j = tid; j < ccur; j += T) {
+                        const uint32_t i = list[cur + j];
+                        atomicAnd(&mark[i >> 5], ~(1u << (i & 31u)));
+                    }
+                    ccur = min(uniform(s_cnt), room);
+                    cur = nxt;
+                    __syncthreads();  // s_cnt is read, the marks are gone
+                }
+                mark_time(ph_pop);
+                if (++rounds > a.max_rounds || draws > a.step_cap) {
                     err |= kErrStepCap;
-                    break;
+                    return;
                 }
-                // in-arrows between unresolved vertices (every unresolved vertex
-                // has an internal target and a zero count here); count them
-                if (tid == 0) {
-                    s_u = 0;
-                    s_c = 0;
-                    s_nc = 0;
-                    s_lc[0] = 0;
-                    s_lc[1] = 0;
-                }
-                __syncthreads();
-                const uint32_t scan = full ? b : lcount;  // candidates: the set, or the list
-                uint32_t mine = 0;
-                for (uint32_t j = tid; j < scan; j += T) {
-                    const uint32_t i = full ? j : Lcur[j];
-                    if (st_get(i) & kUnres) {
-                        ++mine;
-                        const uint32_t tg = lt[i];
-                        if (st_get(tg) & kUnres) st_inc(tg);
-                    }
-                }
-                wave_count(&s_u, mine);
-                __syncthreads();
-                const uint32_t ucount = uniform(s_u);
-                if (ucount == 0) break;  // every vertex of the set resolved
-                // peel level 0: unresolved with no in-arrow (level k appends
-                // with counter (k + 1) % 3)
-                for (uint32_t j = wave_base; j < scan; j += T) {
-                    const uint32_t lj = j + lane;
-                    uint32_t li = 0;
-                    bool leaf = false;
-                    if (lj < scan) {
-                        li = full ? lj : Lcur[lj];
-                        leaf = st_get(li) == kUnres;
-                    }
-                    wave_push<uint16_t>(tp, 0u, &s_lc[0], Bp, &s_over, static_cast<uint16_t>(li), leaf);
-                }
-                __syncthreads();
-                mark(ph_count);
-                uint32_t plo = 0, phi = min(uniform(s_lc[0]), b), nlev = 0;
-                if (tid == 0) lv_set(0, 0);
-                while (phi - plo > 64u) {
-                    const uint32_t cn = (nlev + 1u) % 3u, cz = (nlev + 2u) % 3u;
-                    if (tid == 0) {
-                        lv_set(nlev + 1, phi);
-                        s_lc[cz] = 0;
-                    }
-                    for (uint32_t i = plo + wave_base; i < phi; i += T) {
-                        const uint32_t li = i + lane;
-                        uint32_t tg = 0;
-                        bool push = false;
-                        if (li < phi) {
-                            tg = lt[tp[li]];
-                            if (st_get(tg) & kUnres) push = (st_dec(tg) & kCountMask) == 1u;
+                // where each vertex's jumps start
+                uint32_t work;  // the vertices of this round
+                for (;;) {
+                    work = open;
+                    bool deep = false;
+                    for (uint32_t todo = open; todo; todo &= todo - 1u) {
+                        const uint32_t bit = todo & (0u - todo);
+                        const uint32_t i = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                        const uint32_t c = arrow[i];
+                        if (!wide && !(c & kAgain)) {
+                            work &= ~bit;
+                            continue;
                         }
-                        wave_push<uint16_t>(tp, phi, &s_lc[cn], Bp, &s_over, static_cast<uint16_t>(tg), push);
-                    }
-                    __syncthreads();
-                    ++nlev;
-                    plo = phi;
-                    phi = min(phi + uniform(s_lc[cn]), b);
-                }
-                const uint32_t tail0 = nlev;
-                if (plo < phi) {  // narrow levels: wave 0 alone, frontier in registers
-                    if (wave_base == 0) {
-                        uint32_t cnt = phi - plo, pos = phi, nl = nlev;
-                        uint32_t x = lane < cnt ? tp[plo + lane] : 0u;
-                        while (cnt > 0) {
-                            if (lane == 0) lv_set(nl + 1, pos);
-                            bool push = false;
-                            uint32_t tg = 0;
-                            if (lane < cnt) {
-                                tg = lt[x];
-                                if (st_get(tg) & kUnres) push = (st_dec(tg) & kCountMask) == 1u;
+                        uint32_t x = jump[i];
+                        if (!(x & kDone)) {
+                            uint32_t to = c & kIdMask;
+                            x = jump[to];
+                            if (!wide) {
+                                uint32_t steps = 0;
+                                for (uint32_t y = arrow[to]; !(x & kDone) && !(y & kAgain);) {
+                                    if (++steps > kWalk) break;
+                                    to = y;
+                                    x = jump[to];
+                                    y = arrow[to];
+                                }
+                                deep |= steps > kWalk;
                             }
-                            const uint64_t mask = __ballot(push);
-                            const uint32_t m = static_cast<uint32_t>(__popcll(mask));
-                            if (pos + m > b) {
-                                if (lane == 0) s_over = 1u;
-                                break;
-                            }
-                            if (push) {
-                                const uint32_t r = static_cast<uint32_t>(
-                                    __popcll(mask & ((1ull << lane) - 1ull)));
-                                s_tail[r] = tg;
-                                tp[pos + r] = static_cast<uint16_t>(tg);
-                            }
-                            wave_sync();
-                            x = lane < m ? s_tail[lane] : 0u;
-                            wave_sync();
-                            pos += m;
-                            cnt = m;
-                            ++nl;
+                            jump[i] = static_cast<uint16_t>(x & kDone ? x : to);
                         }
-                        if (lane == 0) {
-                            s_pos = pos;
-                            s_nlev = nl;
+                        if (x & kDone) {
+                            open &= ~bit;
+                            work &= ~bit;
                         }
                     }
+                    if (wide) break;
+                    if (__ballot(deep) && lane == 0) s_flags[3] = 1u;
                     __syncthreads();
-                    phi = min(uniform(s_pos), b);
-                    nlev = uniform(s_nlev);
-                }
-                const uint32_t peeled = phi;
-                // reverse sweep: a peeled vertex takes its target's exit when the
-                // target is resolved; otherwise it hangs off a cycle and stays
-                // unresolved (count 0) for the next round
-                if (wave_base == 0 && nlev > tail0) {
-                    for (uint32_t L = nlev; L > tail0; --L) {
-                        const uint32_t a0 = lv_get(L - 1), a1 = L == nlev ? peeled : lv_get(L);
-                        if (lane < a1 - a0) {
-                            const uint32_t x = tp[a0 + lane];
-                            const uint32_t s = st_get(lt[x]);
-                            if (!(s & kUnres)) st16[x] = static_cast<uint16_t>(s);
-                        }
-                        wave_sync();
-                    }
+                    wide = uniform(s_flags[3]) != 0u;
+                    if (!wide) break;
+                    __syncthreads();
+                    if (tid == 0) s_flags[3] = 0;
                 }
                 __syncthreads();
-                for (uint32_t L = tail0; L > 0; --L) {
-                    const uint32_t a0 = lv_get(L - 1), a1 = lv_get(L);
-                    for (uint32_t i = a0 + tid; i < a1; i += T) {
-                        const uint32_t x = tp[i];
-                        const uint32_t s = st_get(lt[x]);
-                        if (!(s & kUnres)) st16[x] = static_cast<uint16_t>(s);
-                    }
-                    __syncthreads();
-                }
-                mark(ph_peel);
-                if (peeled == ucount) break;  // no cycle: every unresolved vertex resolved
-                // pop the set's cycles: unresolved vertices with an in-arrow left
-                // (exactly one, from the cycle) draw their next arrow.  They are
-                // listed first (the peel order is spent), so that the draws'
-                // global loads go out together.
-                // The same scan lists every vertex still unresolved (hanging off a
-                // cycle, or on one) for the next round: no other can be then.
-                // When every thread scans at most one entry, a cycle vertex is
-                // popped right there (the cycles are disjoint: popping them all at
-                // once is popping them one after another), saving a barrier and
-                // overlapping the draws with the scan.
-                const uint32_t half = Bp >> 1;
-                const bool inline_pop = scan <= T && scan <= half;
-                if (tid == 0) s_lc[0] = 0;  // the first re-pop pass's tail (the peel's counters are spent)
-                for (uint32_t j = wave_base; j < scan; j += T) {
-                    const uint32_t lj = j + lane;
-                    uint32_t li = 0;
-                    bool cyc = false, unres = false;
-                    if (lj < scan) {
-                        li = full ? lj : Lcur[lj];
-                        const uint32_t s = st_get(li);
-                        unres = (s & kUnres) != 0u;
-                        cyc = unres && (s & kCountMask);
-                    }
-                    wave_push<uint16_t>(tp, 0u, &s_c, Bp, &s_over, static_cast<uint16_t>(li), cyc);
-                    wave_push<uint32_t>(Lnext, 0u, &s_nc, b, &s_over, li, unres);
-                    if (inline_pop && cyc) {  // (npop <= half here: the re-pops run when enabled)
-                        const uint32_t tg = pop(vid(li));
-                        const uint32_t code = code_of(tg);
-                        lt[li] = static_cast<uint16_t>(code);
-                        st16[li] = static_cast<uint16_t>(code == kRoot ? kSettled
-                                                         : code == kExt ? li
-                                                         : a.repop ? kUnres | 1u : kUnres);
-                    }
-                }
-                __syncthreads();
-                const uint32_t npop = min(uniform(s_c), b);
-                const uint32_t next_count = min(uniform(s_nc), b);
-                // with the re-pops, vertices redrawn to an unresolved target carry
-                // the mark "redrawn in this pass" (count 1) into the first pass
-                const bool repop = a.repop && npop <= half;
-                const uint32_t fresh = repop ? kUnres | 1u : kUnres;
-                if (!inline_pop) {
-                    for (uint32_t j = tid; j < npop; j += T) {
-                        const uint32_t i = tp[j];
-                        const uint32_t tg = pop(vid(i));
-                        const uint32_t code = code_of(tg);
-                        lt[i] = static_cast<uint16_t>(code);
-                        st16[i] = static_cast<uint16_t>(code == kRoot ? kSettled : code == kExt ? i : fresh);
-                    }
-                    __syncthreads();
-                }
-                if (tid == 0) s_draws += npop;
-                // Re-formed 2-cycles: a redrawn vertex u whose new arrow goes to an
-                // unresolved t whose arrow comes back to u closes a cycle of the
-                // current arrows, popped at once (any cycle may be popped at any
-                // time) instead of a round later.  The pair is popped by u's lane,
-                // or by the smaller id's when both were redrawn in this pass
-                // (both marked).  Passes alternate between the halves of the peel
-                // list; one that would overflow its half pops nothing and ends them.
-                if (repop) {
-                    uint32_t cur = 0, ncur = npop;
-                    for (uint32_t pass = 0; ncur > 0; ++pass) {
-                        const uint32_t nxt = cur ? 0u : half;
-                        const uint32_t cp = pass % 2u;  // tail counter of this pass
-                        if (tid == 0) s_lc[cp ^ 1u] = 0;
-                        for (uint32_t j = wave_base; j < ncur; j += T) {
-                            const uint32_t lj = j + lane;
-                            uint32_t u = 0, tg = 0;
-                            bool lead = false;
-                            if (lj < ncur && pass < 32u) {
-                                u = tp[cur + lj];
-                                if (st_get(u) & kUnres) {
-                                    tg = lt[u];
-                                    if (tg < b) {
-                                        const uint32_t sv = st_get(tg);
-                                        lead = (sv & kUnres) && lt[tg] == u &&
-                                               ((sv & kCountMask) == 0u || u < tg);
-                                    }
+                // jumps until a pass settles nobody, marks, walks to the next mark; where
+                // some mark turns out not to be on a cycle, a few more jumps
+                uint32_t least = kMinJumps;
+                uint32_t total = 0;  // vertices on cycles
+                for (;;) {
+                    for (uint32_t p = 0;; ++p) {
+                        bool settled = false;
+                        for (uint32_t todo = work; todo;) {
+                            uint32_t q[kU], j[kU];
+#pragma unroll
+                            for (uint32_t h = 0; h < kU; ++h) {
+                                q[h] = 32u;
+                                j[h] = 0;
+                                if (todo) {
+                                    q[h] = static_cast<uint32_t>(__builtin_ctz(todo));
+                                    todo &= todo - 1u;
+                                    j[h] = jump[q[h] * T + tid];
                                 }
                             }
-                            wave_push<uint16_t>(tp, nxt, &s_lc[cp], nxt + half, &s_rover,
-                                                static_cast<uint16_t>(u), lead);
-                            wave_push<uint16_t>(tp, nxt, &s_lc[cp], nxt + half, &s_rover,
-                                                static_cast<uint16_t>(tg), lead);
+#pragma unroll
+                            for (uint32_t h = 0; h < kU; ++h)
+                                if (q[h] < 32u) j[h] = jump[j[h]];
+#pragma unroll
+                            for (uint32_t h = 0; h < kU; ++h)
+                                if (q[h] < 32u) {
+                                    jump[q[h] * T + tid] = static_cast<uint16_t>(j[h]);
+                                    if (j[h] & kDone) {
+                                        open &= ~(1u << q[h]);
+                                        work &= ~(1u << q[h]);
+                                        settled = true;
+                                    }
+                                }
                         }
+                        // bit 0: somebody is left, bit 1: somebody was settled in this pass
+                        const uint32_t f = (__ballot(work != 0u) ? 1u : 0u) | (__ballot(settled) ? 2u : 0u);
+                        if (lane == 0 && f) atomicOr(&s_flags[p & 3u], f);
                         __syncthreads();
-                        for (uint32_t j = tid; j < ncur; j += T) {  // clear the marks
-                            const uint32_t u = tp[cur + j];
-                            if (st_get(u) == (kUnres | 1u)) st16[u] = static_cast<uint16_t>(kUnres);
+                        const uint32_t all = uniform(s_flags[p & 3u]);
+                        if (tid == 0) s_flags[(p + 2u) & 3u] = 0;
+                        if (!(all & 1u)) {
+                            done = true;
+                            break;
                         }
-                        const uint32_t nn = uniform(s_lc[cp]);
-                        __syncthreads();
-                        // no pair, or the half overflowed (then nothing is popped: the next
-                        // round finds those cycles)
-                        if (nn == 0u || nn > half) break;
-                        for (uint32_t j = tid; j < nn; j += T) {
-                            const uint32_t i = tp[nxt + j];
-                            const uint32_t tg = pop(vid(i));
-                            const uint32_t code = code_of(tg);
-                            lt[i] = static_cast<uint16_t>(code);
-                            st16[i] = static_cast<uint16_t>(code == kRoot ? kSettled
-                                                            : code == kExt ? i : kUnres | 1u);
-                        }
-                        __syncthreads();
-                        if (tid == 0) s_draws += nn;
-                        cur = nxt;
-                        ncur = nn;
+                        if (!(all & 2u) && p + 1u >= least) break;
                     }
+                    __syncthreads();
+                    if (tid < 4u) s_flags[tid] = 0;
+                    mark_time(ph_jump);
+                    if (done) break;
+                    for (uint32_t todo = work; todo; todo &= todo - 1u) {
+                        const uint32_t c = jump[static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid];
+                        atomicOr(&mark[c >> 5], 1u << (c & 31u));
+                    }
+                    __syncthreads();
+                    uint32_t mine = 0;  // the vertices of this thread that are marked
+                    for (uint32_t todo = work; todo; todo &= todo - 1u) {
+                        const uint32_t q = static_cast<uint32_t>(__builtin_ctz(todo));
+                        if (marked(q * T + tid)) mine |= 1u << q;
+                    }
+                    for (uint32_t todo = mine; todo; todo &= todo - 1u) {
+                        uint32_t x = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                        do {  // ends: the arrows lead to a cycle, which holds a mark
+                            x = arrow[x] & kIdMask;
+                        } while (!marked(x));
+                        atomicOr(&hit[x >> 5], 1u << (x & 31u));
+                    }
+                    __syncthreads();
+                    bool stray = false;
+                    for (uint32_t todo = mine; todo; todo &= todo - 1u) {
+                        const uint32_t c = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                        stray |= !((hit[c >> 5] >> (c & 31u)) & 1u);
+                    }
+                    if (__ballot(stray) && lane == 0) s_flags[3] = 1u;
+                    if (tid == 0) s_cnt = 0;
+                    __syncthreads();
+                    const bool again = uniform(s_flags[3]) != 0u;
+                    if (!again) {  // list the cycles
+                        for (uint32_t todo = mine; todo; todo &= todo - 1u) {
+                            const uint32_t c = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                            uint32_t x = c, len = 0;
+                            do {
+                                x = arrow[x] & kIdMask;
+                                ++len;
+                            } while (!marked(x));
+                            uint32_t at = atomicAdd(&s_cnt, len);
+                            if (at + len > L.cap) continue;
+                            x = c;
+                            do {
+                                list[at++] = static_cast<uint16_t>(x);
+                                x = arrow[x] & kIdMask;
+                            } while (--len);
+                        }
+                        __syncthreads();
+                        total = uniform(s_cnt);
+                        if (total > L.cap) {
+                            // no room for all of them: each thread pops the stretches from
+                            // its marks on as it walks (the marks stay until all are done)
+                            for (uint32_t todo = mine; todo; todo &= todo - 1u) {
+                                uint32_t x = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                                do {
+                                    const uint32_t y = arrow[x] & kIdMask;
+                                    redraw(x);
+                                    x = y;
+                                } while (!marked(x));
+                            }
+                        }
+                    }
+                    __syncthreads();
+                    for (uint32_t i = tid; i < 2u * L.nb; i += T) mark[i] = 0u;  // and hit
+                    if (tid == 0) s_flags[3] = 0;
+                    if (!again) break;
+                    least = kMoreJumps;
+                    __syncthreads();
                 }
-                mark(ph_pop);
-                uint32_t *const spent = Lcur;
-                Lcur = Lnext;
-                Lnext = spent;
-                lcount = next_count;
-                full = false;
+                if (done) break;
+                if (total == 0u) {  // cannot be: somebody is left, so is a cycle
+                    err |= kErrStepCap;
+                    return;
+                }
+                cur = 0;
+                ccur = total;
+                if (total > L.cap) {
+                    ccur = 0;
+                    draws += total;
+                }
+                __syncthreads();
+                mark_time(ph_cycle);
+                wide = false;
             }
+            __syncthreads();
+            if (res) return;
+            // the exits of the vertices that hang off those the last rounds settled
+            for (uint32_t todo = open; todo; todo &= todo - 1u) {
+                const uint32_t i = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                if (jump[i] & kDone) open &= ~(todo & (0u - todo));
+                else jump[i] = static_cast<uint16_t>(arrow[i] & kIdMask);
+            }
+            __syncthreads();
+            for (uint32_t p = 0;; ++p) {  // ends: every path leads to a known exit
+                for (uint32_t todo = open; todo; todo &= todo - 1u) {
+                    const uint32_t i = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
+                    const uint32_t x = jump[jump[i]];
+                    jump[i] = static_cast<uint16_t>(x);
+                    if (x & kDone) open &= ~(todo & (0u - todo));
+                }
+                if (__ballot(open != 0u) && lane == 0) s_flags[p & 3u] = 1u;
+                __syncthreads();
+                const bool more = uniform(s_flags[p & 3u]) != 0u;
+                if (tid == 0) s_flags[(p + 2u) & 3u] = 0;
+                if (!more) break;
+            }
+            mark_time(ph_jump);
         };
 
         // -------------------------------------------------------------------
@@ -500,45 +615,45 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
             const uint32_t lo = tile * B;
             const uint32_t b = min(B, n - lo);
             __syncthreads();
-            {
-                constexpr int kL = 8;  // loads in flight per thread
-                for (uint32_t i0 = tid; i0 < b; i0 += kL * T) {
-                    uint32_t tg[kL];
-#pragma unroll
-                    for (int q = 0; q < kL; ++q) {
-                        const uint32_t i = i0 + q * T;
-                        tg[q] = i < b ? tw[lo + i] : n;
-                    }
-#pragma unroll
-                    for (int q = 0; q < kL; ++q) {
-                        const uint32_t i = i0 + q * T;
-                        if (i < b) {
-                            const uint32_t code = tg[q] == n ? kRoot : (tg[q] - lo < b ? tg[q] - lo : kExt);
-                            lt[i] = static_cast<uint16_t>(code);
-                            st16[i] = static_cast<uint16_t>(code == kRoot ? kSettled
-                                                            : code == kExt ? i : kUnres);
-                        }
-                    }
-                }
-            }
-            mark(kPhLoad);
-            pop_rounds(b, lo, false, kPhCount, kPhPeel, kPhPop);
+            pop_set(b, lo, false, kPhPop, kPhJump, kPhCycle);
             if (err & kErrStepCap) break;
-            // every vertex's exit, and the tile's exit list
+            // the tile's exits, and its part of the outputs
             if (tid == 0) s_c = 0;
             __syncthreads();
-            for (uint32_t i = wave_base; i < b; i += T) {
-                const uint32_t li = i + lane;
+            for (uint32_t i0 = wave_base; i0 < b; i0 += T) {
+                const uint32_t i = i0 + lane, v = lo + i;
                 bool isx = false;
-                if (li < b) {
-                    ex[lo + li] = static_cast<uint16_t>(st_get(li));
-                    isx = lt[li] == kExt;
+                if (i < b) {
+                    const uint32_t c = arrow[i] & kIdMask, e = jump[i] & kIdMask;
+                    isx = c == kExt;
+                    ex[v] = static_cast<uint16_t>(e);
+                    uint32_t k = drawn[i];
+                    if ((spill[i >> 5] >> (i & 31u)) & 1u) k |= kk[v] << kLowBits;
+                    if (e != kRoot) {
+                        tl[v] = static_cast<uint16_t>(c);
+                        kk[v] = k;
+                    }
+                    uint32_t tg = lo + c;
+                    if (c == kRoot) {
+                        tg = n;
+                        ++my_roots;
+                        atomicAdd(&a.root_counts[v], 1u);
+                    } else if (isx) {
+                        tg = tw[v];
+                        pc[v] = 0u;
+                    }
+                    my_digest += mix64((static_cast<unsigned long long>(v) << 32) | tg);
+                    const size_t at = static_cast<size_t>(item) * nn + v;
+                    if (a.parents) a.parents[at] = static_cast<int32_t>(tg);
+                    if (a.visit_counts)
+                        atomicAdd(&a.visit_counts[v], static_cast<unsigned long long>(k));
+                    if (a.tree_visits) a.tree_visits[at] = k;
                 }
-                wave_push<uint32_t>(exl, lo, &s_c, lo + b, &s_over, lo + li, isx);
+                wave_push<uint32_t>(exl, lo, &s_c, lo + b, &s_over, v, isx);
             }
             __syncthreads();
             if (tid == 0) ecnt[tile] = min(s_c, b);
-            mark(kPhExits);
+            mark_time(kPhExits);
         }
         __syncthreads();
         if (err & kErrStepCap) break;
@@ -568,7 +683,7 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
                 const uint32_t u = bU[i];
                 const uint32_t x = tw[u];
                 const uint32_t e = ex[x];
-                const uint32_t s = e == kSettled ? n : x - x % B + e;
+                const uint32_t s = e == kRoot ? n : x - x % B + e;
                 sc[u] = s;
                 if (s < n) atomicAdd(&pc[s], 1u);
             }
@@ -619,7 +734,7 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
             }
             residual = plo < m;  // exits left unpeeled lie on crossing cycles
         }
-        mark(kPhExit);
+        mark_time(kPhExit);
 
         // -------------------------------------------------------------------
         // 3. the residual: vertices whose exit does not reach u*
@@ -630,7 +745,8 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
             for (uint32_t i = tid; i < m; i += T) pc[bU[i]] = 0u;
             __syncthreads();
             // settled bitmap (global first) and the residual list: v is settled iff
-            // its path reaches u* inside its tile or its exit's chain does
+            // its path reaches u* inside its tile or its exit's chain does.  The
+            // residual works on global targets and counters of its own.
             {
                 constexpr int kS = 4;  // vertices per lane in flight
                 for (uint32_t base0 = wave_base; base0 < n; base0 += kS * T) {
@@ -638,14 +754,14 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
 #pragma unroll
                     for (int q = 0; q < kS; ++q) {
                         const uint32_t v = base0 + q * T + lane;
-                        e[q] = v < n ? ex[v] : kSettled;
+                        e[q] = v < n ? ex[v] : kRoot;
                     }
 #pragma unroll
                     for (int q = 0; q < kS; ++q) {
                         const uint32_t base = base0 + q * T;
                         const uint32_t v = base + lane;
                         bool done = true;
-                        if (v < n && e[q] != kSettled) {
+                        if (v < n && e[q] != kRoot) {
                             const uint32_t x = v - v % B + e[q];
                             done = (xb[x >> 5] >> (x & 31u)) & 1u;
                         }
@@ -654,6 +770,11 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
                             if (lane == 0) gbits[base >> 5] = static_cast<uint32_t>(mask);
                             if (lane == 32 && (base >> 5) + 1u < nw)
                                 gbits[(base >> 5) + 1u] = static_cast<uint32_t>(mask >> 32);
+                        }
+                        if (!done) {
+                            const uint32_t c = tl[v];
+                            if (c != kExt) tw[v] = v - v % B + c;
+                            pc[v] = 0u;
                         }
                         wave_push<uint32_t>(bU, 0u, &s_u, n, &s_over, v, !done);
                     }
@@ -679,16 +800,8 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
                     }
                     for (uint32_t i = tid; i < ucount; i += T) sc[U[i]] = i;
                     __syncthreads();
-                    for (uint32_t i = tid; i < ucount; i += T) {
-                        const uint32_t tg = tw[U[i]];
-                        const uint32_t code =
-                            tg == n || ((gbits[tg >> 5] >> (tg & 31u)) & 1u) ? kRoot : sc[tg];
-                        lt[i] = static_cast<uint16_t>(code);
-                        st16[i] = static_cast<uint16_t>(code == kRoot ? kSettled : kUnres);
-                    }
                     res_list = U;
-                    res_l0 = U == bU ? bN : bU;
-                    pop_rounds(ucount, 0u, true, kPhResidual, kPhResidual, kPhResidual);
+                    pop_set(ucount, 0u, true, kPhResidual, kPhResidual, kPhResidual);
                     break;
                 }
                 if (++rounds > a.max_rounds || s_over) {
@@ -768,7 +881,7 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
                         x = U[li];
                         if (!is_settled(x) && pc[x] != 0u) {
                             pc[x] = 0u;
-                            const uint32_t tg = pop(x);
+                            const uint32_t tg = pop_global(x);
                             if (tg == n) set_settled(x);
                             else live = true;
                             ++pops;
@@ -778,7 +891,7 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
                 }
                 wave_count(&s_c, pops);
                 __syncthreads();
-                if (tid == 0) s_draws += s_c;
+                draws += uniform(s_c);
                 ucount = min(uniform(s_u), n);
                 uint32_t *tmp = U;
                 U = Un;
@@ -787,46 +900,12 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
             __syncthreads();
             if (err & kErrStepCap) break;
         }
-        mark(kPhResidual);
-        {
-            const unsigned long long drawn = s_draws;  // final since the last barrier
-            if (drawn > a.step_cap) {
-                err |= kErrStepCap;
-                break;
-            }
+        mark_time(kPhResidual);
+        if (draws > a.step_cap) {
+            err |= kErrStepCap;
+            break;
         }
 
-        // the tree: top arrows; R, digest, optional per-tree dumps
-        unsigned long long my_digest = 0, my_roots = 0;
-        const bool want_k = a.visit_counts || a.tree_visits;
-        constexpr int kO = 16;  // targets whose loads each thread keeps in flight
-        for (uint32_t base = tid; base < n; base += kO * T) {
-            uint32_t tgs[kO];
-#pragma unroll
-            for (int q = 0; q < kO; ++q) {
-                const uint32_t v = base + q * T;
-                tgs[q] = v < n ? tw[v] : 0u;
-            }
-#pragma unroll
-            for (int q = 0; q < kO; ++q) {
-                const uint32_t v = base + q * T;
-                if (v >= n) continue;
-                const uint32_t tg = tgs[q];
-                my_digest += mix64((static_cast<unsigned long long>(v) << 32) | tg);
-                if (tg == n) {
-                    ++my_roots;
-                    atomicAdd(&a.root_counts[v], 1u);
-                }
-                if (a.parents) a.parents[static_cast<size_t>(item) * nn + v] = static_cast<int32_t>(tg);
-                if (want_k) {
-                    const uint64_t kv = kk[v];
-                    const uint32_t k =
-                        static_cast<uint32_t>(kv >> 32) == epoch ? static_cast<uint32_t>(kv) : 1u;
-                    if (a.visit_counts) atomicAdd(&a.visit_counts[v], static_cast<unsigned long long>(k));
-                    if (a.tree_visits) a.tree_visits[static_cast<size_t>(item) * nn + v] = k;
-                }
-            }
-        }
         for (int off = 32; off > 0; off >>= 1) {
             my_digest += __shfl_down(my_digest, off, 64);
             my_roots += __shfl_down(my_roots, off, 64);
@@ -838,12 +917,12 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
         __syncthreads();
         if (tid == 0) {
             if (a.tree_digests) a.tree_digests[item] = s_digest;
-            if (a.tree_steps) a.tree_steps[item] = s_draws;
-            atomicAdd(&a.totals->walk_steps, s_draws);
+            if (a.tree_steps) a.tree_steps[item] = draws;
+            atomicAdd(&a.totals->walk_steps, draws);
             atomicAdd(&a.totals->roots, s_roots);
             atomicAdd(&a.totals->digest_sum, s_digest);
         }
-        mark(kPhOutput);
+        mark_time(kPhOutput);
     }
     if (timing && tid == 0)
         for (int i = 0; i < kPhNum; ++i) atomicAdd(&a.phase_ticks[i], s_ph[i]);
@@ -851,34 +930,6 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
     if (err) atomicOr(&a.totals->error, err);
 }
 
-// Trees per workgroup of the pre-draw kernel (each thread owns one vertex and
-// draws its first arrow in that many trees).
-constexpr uint32_t kPreTrees = 16;
-constexpr uint32_t kPreThreads = 256;
-
-template <bool kWeighted>
-__global__ __launch_bounds__(kPreThreads) void tile_predraw_kernel(TileArgs a, uint32_t groups) {
-    const uint32_t v = blockIdx.x * kPreThreads + threadIdx.x;
-    if (v >= a.n) return;
-    const VRec r = load_vrec(a.vrec, v);
-    for (uint32_t g = blockIdx.y; g < groups; g += gridDim.y) {
-        const uint32_t i0 = g * kPreTrees;
-#pragma unroll 4
-        for (uint32_t q = 0; q < kPreTrees; ++q) {
-            const uint32_t item = i0 + q;
-            if (item >= a.tree_count) break;
-            uint32_t tg = a.n;
-            if (!r.always_root) {
-                const Philox4 x = philox4x32_10(v, 0u, a.tree_begin + item, a.stream_id, a.key0, a.key1);
-                tg = arrow_target<kWeighted>(r, x.x0, x.x1, a.col_idx, a.wsum, a.wthr, a.n);
-            }
-            a.pre[static_cast<size_t>(item) * a.n + v] = tg;
-        }
-    }
-}
-
-// Entries of the CSR whose two ends lie in different tiles of B ids (one
-// atomic per block).
 // Entries that join ids of different tiles, one CSR entry per lane and step.
 // (One row per thread left the hub rows to one lane each: 10.8 ms on R-MAT
 // with 2^22 vertices, 65 M entries; now 0.19 ms.)
@@ -923,22 +974,8 @@ hipError_t launch_count_cross(const int32_t *row_ptr, const int32_t *col_idx, ui
     return hipGetLastError();
 }
 
-hipError_t launch_tile_predraw(const TileArgs &a, hipStream_t stream) {
-    if (!a.pre || a.n == 0 || a.tree_count == 0) return hipSuccess;
-    // vertex tiles a multiple of 8 wide: block b of every tree group then runs on
-    // XCD b mod 8, whose L2 keeps that tile's records and adjacency rows
-    uint32_t tiles = (a.n + kPreThreads - 1) / kPreThreads;
-    tiles = (tiles + 7u) & ~7u;
-    const uint32_t groups = (a.tree_count + kPreTrees - 1) / kPreTrees;
-    const dim3 grid(tiles, groups < 65535u ? groups : 65535u);
-    if (a.wsum) tile_predraw_kernel<true><<<grid, kPreThreads, 0, stream>>>(a, groups);
-    else tile_predraw_kernel<false><<<grid, kPreThreads, 0, stream>>>(a, groups);
-    return hipGetLastError();
-}
-
 size_t tile_lds_bytes(uint32_t B) {
-    const size_t Bp = (static_cast<size_t>(B) + 63u) & ~static_cast<size_t>(63u);
-    return 6u * Bp + 2u * kLvLds;
+    return 4u * static_cast<size_t>(tile_layout((B + 63u) & ~63u).words);
 }
 
 hipError_t tile_set_limit(size_t bytes) {
@@ -963,7 +1000,7 @@ int tile_max_active(uint32_t threads, size_t lds, bool weighted) {
 hipError_t launch_wilson_tile(const TileArgs &a, uint32_t threads, size_t lds, hipStream_t stream) {
     if (a.n == 0 || a.tree_count == 0 || a.slots == 0) return hipSuccess;
     if (a.B == 0 || a.B > kTileMax || a.Bp % 64u || a.Bp < a.B) return hipErrorInvalidValue;
-    if (lds < tile_lds_bytes(a.B)) return hipErrorInvalidValue;
+    if (a.B > kTileOwn * threads || lds < tile_lds_bytes(a.Bp)) return hipErrorInvalidValue;
     const size_t bw = 4u * static_cast<size_t>((a.n + 31u) >> 5);
     if ((a.bits_lds || !a.xb) && bw > lds) return hipErrorInvalidValue;
     if (a.wsum) wilson_tile_kernel<true><<<a.slots, threads, lds, stream>>>(a);
