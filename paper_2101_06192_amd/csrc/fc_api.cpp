@@ -689,7 +689,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         if (ctx->max_slots) slots = std::min<size_t>(slots, ctx->max_slots);
         if ((rc = ensure(ctx, ctx->cword, 4u * n * slots, "tree targets")) ||
             (rc = ensure(ctx, ctx->ckk, 4u * n * slots, "draw counts")) ||
-            (rc = ensure(ctx, ctx->t_ex, 2u * n * slots, "exits")) ||
+            (rc = ensure(ctx, ctx->t_ex, 2u * (n + 7u) * slots, "exits")) ||
             (rc = ensure(ctx, ctx->t_tl, 2u * n * slots, "tile targets")) ||
             (rc = ensure(ctx, ctx->t_exl, 4u * n * slots, "exit lists")) ||
             (rc = ensure(ctx, ctx->t_pc, 4u * n * slots, "in-counts")) ||

@@ -261,7 +261,8 @@ struct TileArgs {
     uint32_t *tw;              // slots * n targets out of the tile, and of the residual
     uint32_t *kk;              // slots * n draws (of the vertices not settled in their tile)
     uint16_t *tl;              // slots * n tile-local targets (of the same)
-    uint16_t *ex;              // slots * n tile-local exit, or 0x7FFF (reaches u* in the tile)
+    uint16_t *ex;              // slots * (n up to a multiple of 8) tile-local exit, or 0x7FFF
+                               // (reaches u* in the tile)
     uint32_t *exl;             // slots * n per-tile exit lists (tile * B offsets)
     uint32_t *ecnt;            // slots * ntiles exits per tile
     uint32_t *pc;              // slots * n in-counts

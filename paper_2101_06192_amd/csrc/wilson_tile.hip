@@ -26,6 +26,16 @@
 //    when it fits), global in-arrow counters and lists, only for them.
 // No global atomic touches a vertex outside the exit graph and the residual.
 //
+// What bounds it (grid of 1000 x 1000, 12% of the edges removed, alpha 1, 1024 trees
+// on 256 CUs, 40 tiles a tree; 32.1 ms when the tiles were peeled level by level and
+// the first arrows drawn ahead by a kernel of their own, 19.6 ms now): first arrows
+// 3.5 ms, all of it Philox and so the arithmetic units; redraws 5.0 ms, a chain of 13
+// passes a tile that each wait for the loads of one draw (record, then neighbour);
+// jumps 3.9 ms and cycles 1.4 ms, LDS; outputs 2.7 ms, the digest's products and the
+// root counts' atomics (0.8 ms); exit graph 0.7 ms, residual 2.4 ms.  One workgroup a
+// CU with the widest tile: two with tiles half as wide wait as long on each, and cut
+// twice as many paths (29.1 ms).
+//
 // LDS during the tiles (6.4 bytes a vertex):
 //   mark, hit, spill  bitmaps: marks (or the vertices of the 2-cycle check under
 //             way), marks that a walk ended at, draw counts that left 8 bits
@@ -68,6 +78,7 @@ constexpr uint32_t kMinJumps = 4;   // passes before marks are tried
 constexpr uint32_t kMoreJumps = 3;  // and after some were not on a cycle
 constexpr uint32_t kU = 4, kD = 2;  // vertices a thread keeps in flight: jumping, drawing
 constexpr uint32_t kWalk = 96;      // arrows a walk to the next vertex that drew again may take
+constexpr uint32_t kFewPairs = 64;  // 2-cycles of the first arrows: fewer vertices wait for the cycles
 constexpr uint32_t kLowBits = 8;
 
 // LDS of a set of up to Bp vertices (Bp a multiple of 64), in words from the start.
@@ -166,7 +177,7 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
     uint32_t *__restrict__ tw = a.tw + slot * nn;
     uint32_t *__restrict__ kk = a.kk + slot * nn;
     uint16_t *__restrict__ tl = a.tl + slot * nn;
-    uint16_t *__restrict__ ex = a.ex + slot * nn;
+    uint16_t *__restrict__ ex = a.ex + slot * ((nn + 7u) & ~static_cast<size_t>(7u));
     uint32_t *__restrict__ exl = a.exl + slot * nn;
     uint32_t *__restrict__ ecnt = a.ecnt + slot * static_cast<size_t>(ntiles);
     uint32_t *__restrict__ pc = a.pc + slot * nn;
@@ -243,47 +254,69 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
             auto marked = [&](uint32_t i) { return (mark[i >> 5] >> (i & 31u)) & 1u; };
             auto code_of = [&](uint32_t tg) -> uint32_t {
                 if (tg == n) return kRoot;
-                if (res) return ((gbits[tg >> 5] >> (tg & 31u)) & 1u) ? kRoot : sc[tg];
+                if (res) {
+                    const uint32_t at = sc[tg];  // (both loads at once)
+                    return ((gbits[tg >> 5] >> (tg & 31u)) & 1u) ? kRoot : at;
+                }
                 return tg - lo < b ? tg - lo : kExt;
             };
-            // Arrow of set vertex i from its next draw; the draw count goes up by one.
-            auto redraw = [&](uint32_t i) {
-                const uint32_t v = res ? res_list[i] : lo + i;
-                uint32_t k, was = 0;
-                if (res) {
-                    k = kk[v];
-                    was = tw[v];
-                } else {
-                    k = drawn[i];
-                    if ((spill[i >> 5] >> (i & 31u)) & 1u) k |= kk[v] << kLowBits;
+            // Arrows of set vertices at[0..m) from their next draws; the draw counts go
+            // up by one.  The loads of kD draws are in flight together.
+            auto redraw = [&](const uint32_t (&at)[kD], uint32_t m) {
+                uint32_t k[kD], was[kD], tg[kD];
+                VRec r[kD];
+#pragma unroll
+                for (uint32_t q = 0; q < kD; ++q) {
+                    k[q] = was[q] = 0;
+                    r[q] = {};
+                    if (q >= m) continue;
+                    const uint32_t i = at[q], v = res ? res_list[i] : lo + i;
+                    if (res) {
+                        k[q] = kk[v];
+                        was[q] = tw[v];
+                    } else {
+                        k[q] = drawn[i];
+                        if ((spill[i >> 5] >> (i & 31u)) & 1u) k[q] |= kk[v] << kLowBits;
+                    }
+                    r[q] = load_vrec(a.vrec, v);  // on its way during the Philox rounds
                 }
-                VRec r = load_vrec(a.vrec, v);  // on its way during the Philox rounds
-                const Philox4 x = philox4x32_10(v, k, t, a.stream_id, a.key0, a.key1);
-                hold_vrec(r);
-                if (k >= a.k_limit) {  // the error ends the tree here: as if v were a root
-                    err |= kErrVisitOverflow;
-                    arrow[i] = static_cast<uint16_t>(kRoot | kAgain);
-                    jump[i] = static_cast<uint16_t>(kDone | kRoot);
-                    return;
+#pragma unroll
+                for (uint32_t q = 0; q < kD; ++q) {
+                    tg[q] = n;
+                    if (q >= m) continue;
+                    const uint32_t v = res ? res_list[at[q]] : lo + at[q];
+                    const Philox4 x = philox4x32_10(v, k[q], t, a.stream_id, a.key0, a.key1);
+                    hold_vrec(r[q]);
+                    tg[q] = arrow_target<kWeighted>(r[q], x.x0, x.x1, a.col_idx, a.wsum, a.wthr, n);
                 }
-                const uint32_t tg = arrow_target<kWeighted>(r, x.x0, x.x1, a.col_idx, a.wsum, a.wthr, n);
-                if (res) redrawn(v, was, tg, k);
-                const uint32_t code = code_of(tg);
-                arrow[i] = static_cast<uint16_t>(code | kAgain);
-                if (code == kRoot) {
-                    jump[i] = static_cast<uint16_t>(kDone | kRoot);
-                } else if (code == kExt) {
-                    jump[i] = static_cast<uint16_t>(kDone | i);
-                    tw[v] = tg;
-                } else {  // a target whose exit is known: its path is final
-                    const uint32_t j = jump[code];
-                    if (j & kDone) jump[i] = static_cast<uint16_t>(j);
-                }
-                if (!res) {
-                    drawn[i] = static_cast<uint8_t>(k + 1u);
-                    if (((k + 1u) & ((1u << kLowBits) - 1u)) == 0u) {
-                        kk[v] = (k + 1u) >> kLowBits;
-                        atomicOr(&spill[i >> 5], 1u << (i & 31u));
+#pragma unroll
+                for (uint32_t q = 0; q < kD; ++q) {
+                    if (q >= m) continue;
+                    const uint32_t i = at[q], v = res ? res_list[i] : lo + i;
+                    if (k[q] >= a.k_limit) {  // the error ends the tree here: as if v were a root
+                        err |= kErrVisitOverflow;
+                        arrow[i] = static_cast<uint16_t>(kRoot | kAgain);
+                        jump[i] = static_cast<uint16_t>(kDone | kRoot);
+                        continue;
+                    }
+                    if (res) redrawn(v, was[q], tg[q], k[q]);
+                    const uint32_t code = code_of(tg[q]);
+                    arrow[i] = static_cast<uint16_t>(code | kAgain);
+                    if (code == kRoot) {
+                        jump[i] = static_cast<uint16_t>(kDone | kRoot);
+                    } else if (code == kExt) {
+                        jump[i] = static_cast<uint16_t>(kDone | i);
+                        tw[v] = tg[q];
+                    } else {  // a target whose exit is known: its path is final
+                        const uint32_t j = jump[code];
+                        if (j & kDone) jump[i] = static_cast<uint16_t>(j);
+                    }
+                    if (!res) {
+                        drawn[i] = static_cast<uint8_t>(k[q] + 1u);
+                        if (((k[q] + 1u) & ((1u << kLowBits) - 1u)) == 0u) {
+                            kk[v] = (k[q] + 1u) >> kLowBits;
+                            atomicOr(&spill[i >> 5], 1u << (i & 31u));
+                        }
                     }
                 }
             };
@@ -369,12 +402,26 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
             bool done = false;
             __syncthreads();
             for (;;) {
-                // pop what is listed, then the 2-cycles that the new arrows close
-                while (ccur > 0u) {
-                    for (uint32_t j = tid; j < ccur; j += T) {
-                        const uint32_t i = list[cur + j];
-                        redraw(i);
-                        atomicOr(&mark[i >> 5], 1u << (i & 31u));
+                // pop what is listed, then the 2-cycles that the new arrows close.  A
+                // pass takes 2 us, nearly all of it the loads of one draw after the
+                // other: the few pairs that are left of the first arrows' are as well
+                // popped with the first cycles (grid of 1e6 vertices, alpha 1, 1024
+                // trees: 20.8 ms with every pass, 20.4 without those below kFewPairs).
+                while (ccur > (wide ? kFewPairs : 0u)) {
+                    for (uint32_t j = tid; j < ccur; j += kD * T) {
+                        uint32_t at[kD], m = 0;
+#pragma unroll
+                        for (uint32_t q = 0; q < kD; ++q) {
+                            at[q] = 0;
+                            if (j + q * T < ccur) {
+                                at[q] = list[cur + j + q * T];
+                                m = q + 1u;
+                            }
+                        }
+                        redraw(at, m);
+#pragma unroll
+                        for (uint32_t q = 0; q < kD; ++q)
+                            if (q < m) atomicOr(&mark[at[q] >> 5], 1u << (at[q] & 31u));
                     }
                     draws += ccur;
                     if (tid == 0) s_cnt = 0;
@@ -555,7 +602,8 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
                                 uint32_t x = static_cast<uint32_t>(__builtin_ctz(todo)) * T + tid;
                                 do {
                                     const uint32_t y = arrow[x] & kIdMask;
-                                    redraw(x);
+                                    uint32_t at[kD] = {x};
+                                    redraw(at, 1u);
                                     x = y;
                                 } while (!marked(x));
                             }
@@ -747,41 +795,57 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
             // settled bitmap (global first) and the residual list: v is settled iff
             // its path reaches u* inside its tile or its exit's chain does.  The
             // residual works on global targets and counters of its own.
-            {
-                constexpr int kS = 4;  // vertices per lane in flight
-                for (uint32_t base0 = wave_base; base0 < n; base0 += kS * T) {
-                    uint32_t e[kS];
+            // Eight vertices a lane: one 16-byte load of exits (kS in flight), one byte
+            // of the bitmap.
+            constexpr uint32_t kS = 4;
+            for (uint32_t base0 = wave_base * 8u; base0 < n; base0 += kS * 8u * T) {
+                uint4 e4[kS];
 #pragma unroll
-                    for (int q = 0; q < kS; ++q) {
-                        const uint32_t v = base0 + q * T + lane;
-                        e[q] = v < n ? ex[v] : kRoot;
-                    }
-#pragma unroll
-                    for (int q = 0; q < kS; ++q) {
-                        const uint32_t base = base0 + q * T;
-                        const uint32_t v = base + lane;
-                        bool done = true;
-                        if (v < n && e[q] != kRoot) {
-                            const uint32_t x = v - v % B + e[q];
-                            done = (xb[x >> 5] >> (x & 31u)) & 1u;
-                        }
-                        const uint64_t mask = __ballot(done);
-                        if (base < n) {
-                            if (lane == 0) gbits[base >> 5] = static_cast<uint32_t>(mask);
-                            if (lane == 32 && (base >> 5) + 1u < nw)
-                                gbits[(base >> 5) + 1u] = static_cast<uint32_t>(mask >> 32);
-                        }
-                        if (!done) {
-                            const uint32_t c = tl[v];
-                            if (c != kExt) tw[v] = v - v % B + c;
-                            pc[v] = 0u;
-                        }
-                        wave_push<uint32_t>(bU, 0u, &s_u, n, &s_over, v, !done);
-                    }
+                for (uint32_t p = 0; p < kS; ++p) {
+                    const uint32_t v0 = base0 + (p * T + lane) * 8u;
+                    e4[p] = v0 < n ? *reinterpret_cast<const uint4 *>(ex + v0) : uint4{};
                 }
+                uint32_t left[kS], mine = 0;  // bit q: v0 + q is not settled
+#pragma unroll
+                for (uint32_t p = 0; p < kS; ++p) {
+                    left[p] = 0;
+                    const uint32_t v0 = base0 + (p * T + lane) * 8u;
+                    if (v0 >= n) continue;
+                    const uint32_t e2[4] = {e4[p].x, e4[p].y, e4[p].z, e4[p].w};
+                    const uint32_t lo = v0 - v0 % B;  // (tiles are multiples of 64 ids)
+#pragma unroll
+                    for (uint32_t q = 0; q < 8u; ++q) {
+                        const uint32_t e = (e2[q >> 1] >> ((q & 1u) << 4)) & 0xFFFFu;
+                        if (v0 + q < n && e != kRoot) {
+                            const uint32_t x = lo + e;
+                            if (!((xb[x >> 5] >> (x & 31u)) & 1u)) left[p] |= 1u << q;
+                        }
+                    }
+                    reinterpret_cast<uint8_t *>(gbits)[v0 >> 3] = static_cast<uint8_t>(~left[p]);
+                    mine += static_cast<uint32_t>(__popc(left[p]));
+                }
+                if (!__ballot(mine != 0u)) continue;
+                uint32_t at = mine;  // running sum over the wave
+                for (uint32_t off = 1; off < 64u; off <<= 1) {
+                    const uint32_t y = __shfl_up(at, off, 64);
+                    if (lane >= off) at += y;
+                }
+                uint32_t first = 0;
+                if (lane == 63u) first = atomicAdd(&s_u, at);
+                at += __shfl(first, 63, 64) - mine;
+#pragma unroll
+                for (uint32_t p = 0; p < kS; ++p)
+                    for (uint32_t todo = left[p]; todo; todo &= todo - 1u)
+                        bU[at++] = base0 + (p * T + lane) * 8u + static_cast<uint32_t>(__builtin_ctz(todo));
             }
             __syncthreads();
             uint32_t ucount = min(uniform(s_u), n);
+            for (uint32_t i = tid; i < ucount; i += T) {
+                const uint32_t v = bU[i], c = tl[v];
+                if (c != kExt) tw[v] = v - v % B + c;
+                pc[v] = 0u;
+            }
+            __syncthreads();
             if (ucount > B && a.bits_lds) {  // the global rounds test the bitmap in LDS
                 for (uint32_t i = tid; i < nw; i += T) s_dyn[i] = gbits[i];
                 __syncthreads();
