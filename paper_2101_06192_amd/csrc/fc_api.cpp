@@ -263,7 +263,7 @@ uint32_t sampler_mode(const fc_ctx *ctx, const fc_params *p) {
 // Faster than the LDS-counter one wherever it fits: 1.4 to 3 times over BA, R-MAT
 // and grid graphs of 1000 to 25900 vertices, alpha 1 to 10, 64 to 4096 trees.
 bool jump_applies(const fc_ctx *ctx, const fc_params *p, int32_t n) {
-    return sampler_mode(ctx, p) == 0 && ctx->coop_lds_counts && !ctx->phase_timing && n > 0 &&
+    return sampler_mode(ctx, p) == 0 && ctx->coop_lds_counts && ctx->hub < 2 && !ctx->phase_timing && n > 0 &&
            static_cast<uint32_t>(n) <= fc::kJumpMax &&
            fc::jump_lds_bytes(static_cast<uint32_t>(n)) + kLdsStaticBytes <= ctx->max_lds;
 }
@@ -273,6 +273,91 @@ bool jump_applies(const fc_ctx *ctx, const fc_params *p, int32_t n) {
 // sums of weights and the other samplers do not).
 bool deferrable(const fc_ctx *ctx, const fc_params *p, const fc_graph *g) {
     return g && !(g->weights && g->nnz) && jump_applies(ctx, p, g->n);
+}
+
+// Scratch, relabelled graph and launch shape of the hubs-first sampler: *c but for the
+// outputs.  nl vertices are not isolated.
+int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::VRec *vrec, uint32_t nl,
+                uint32_t tree_begin, uint32_t tree_count, bool weighted, uint32_t nb, fc::CoopArgs *c,
+                uint32_t *threads, size_t *lds) {
+    int rc;
+    const uint32_t un = static_cast<uint32_t>(g.n);
+    const size_t n = un, stride = std::max<uint32_t>(nl, 1u);
+    if ((rc = ensure(ctx, ctx->rl_blk, 4u * fc::kRelabelClasses * nb, "class counts")) ||
+        (rc = ensure(ctx, ctx->rl_base, 4u * fc::kRelabelClasses * nb, "class offsets")) ||
+        (rc = ensure(ctx, ctx->rl_inv, 4u * n, "relabel inverse")) ||
+        (rc = ensure(ctx, ctx->rl_orig, 4u * n, "relabel ids")) ||
+        (rc = ensure(ctx, ctx->rl_vrec, sizeof(fc::VRec) * n, "relabelled records")) ||
+        (rc = ensure(ctx, ctx->rl_adj, 8u * static_cast<size_t>(g.nnz), "relabelled adjacency")))
+        return rc;
+    Small *sm = static_cast<Small *>(ctx->small.ptr);
+    FC_HIP(ctx, fc::launch_class_bounds(g.row_ptr, un, fc::kHubsFirst, static_cast<uint32_t *>(ctx->rl_blk.ptr),
+                                        static_cast<uint32_t *>(ctx->rl_base.ptr), sm->class_bounds,
+                                        nullptr, ctx->stream), "class bounds");
+    FC_HIP(ctx, fc::launch_relabel_graph(g.row_ptr, g.col_idx, un, g.nnz, fc::kHubsFirst,
+                                         static_cast<const uint32_t *>(ctx->rl_base.ptr), 32u,
+                                         static_cast<uint32_t *>(ctx->rl_inv.ptr),
+                                         static_cast<uint32_t *>(ctx->rl_orig.ptr),
+                                         static_cast<unsigned long long *>(ctx->rl_adj.ptr), ctx->stream),
+           "relabel");
+    FC_HIP(ctx, fc::launch_relabel_vrec(vrec, static_cast<const uint32_t *>(ctx->rl_inv.ptr), un,
+                                        static_cast<fc::VRec *>(ctx->rl_vrec.ptr), ctx->stream),
+           "relabel records");
+    const HubShape s = hub_shape(ctx, nl);
+    *threads = s.threads;
+    *lds = s.lds;
+    const int fit = fc::hub_max_active(s.threads, s.lds, weighted);
+    const size_t nw = (stride + 31u) / 32u;
+    const size_t pre_bytes = 8u * stride * static_cast<size_t>(tree_count);
+    bool predraw = ctx->predraw_mib != 0 && pre_bytes <= (static_cast<size_t>(ctx->predraw_mib) << 20);
+    if (predraw && ensure(ctx, ctx->cpre, pre_bytes, "pre-drawn arrows") != FC_OK) {
+        predraw = false;  // not enough device memory: each tree draws its own
+        ctx->last_error.clear();
+    }
+    const size_t per_slot = ((predraw ? 0u : 8u) + 8u + 24u + 4u) * stride + 8u * s.set + 4u * nw;
+    size_t slots = std::max<size_t>(1, state_budget_now(ctx) / per_slot);
+    slots = std::min<size_t>(slots, tree_count);
+    slots = std::min<size_t>(slots, static_cast<size_t>(ctx->cu_count) * static_cast<size_t>(std::max(1, fit)));
+    if (ctx->max_slots) slots = std::min<size_t>(slots, ctx->max_slots);
+    if ((!predraw && (rc = ensure(ctx, ctx->cword, 8u * stride * slots, "arrows"))) ||
+        (rc = ensure(ctx, ctx->ckk, 8u * stride * slots, "set ids and draw counts")) ||
+        (rc = ensure(ctx, ctx->clists, 24u * stride * slots, "lists")) ||
+        (rc = ensure(ctx, ctx->clevels, 4u * stride * slots, "in-arrow counts")) ||
+        (rc = ensure(ctx, ctx->corigt, 8u * s.set * slots, "set members")) ||
+        (rc = ensure(ctx, ctx->cbits, 4u * nw * slots, "settled bitmap")))
+        return rc;
+    FC_HIP(ctx, hipMemsetAsync(ctx->ckk.ptr, 0, 8u * stride * slots, ctx->stream), "memset draw counts");
+    c->word = predraw ? nullptr : ctx->cword.ptr;
+    c->pre = predraw ? static_cast<uint64_t *>(ctx->cpre.ptr) : nullptr;
+    c->kk = static_cast<uint64_t *>(ctx->ckk.ptr);
+    c->lists = static_cast<uint64_t *>(ctx->clists.ptr);
+    c->levels = static_cast<uint32_t *>(ctx->clevels.ptr);
+    c->origt = static_cast<uint32_t *>(ctx->corigt.ptr);
+    c->bits = static_cast<uint32_t *>(ctx->cbits.ptr);
+    c->n_max = static_cast<uint32_t>(stride);
+    c->set = s.set;
+    c->lds_bits = s.lds_bits;
+    c->slots = static_cast<uint32_t>(slots);
+    c->item_count = tree_count;
+    c->key0 = static_cast<uint32_t>(p->seed);
+    c->key1 = static_cast<uint32_t>(p->seed >> 32);
+    c->max_rounds = 0x40000000u;
+    c->k_limit = ctx->max_draws ? ctx->max_draws : 0x7FFFFFFFu;
+    c->jobs = nullptr;
+    c->item_job = nullptr;
+    fc::CoopJob &j = c->single;
+    j.vrec = static_cast<const fc::VRec *>(ctx->rl_vrec.ptr);
+    j.adj = static_cast<const unsigned long long *>(ctx->rl_adj.ptr);
+    j.orig = static_cast<const uint32_t *>(ctx->rl_orig.ptr);
+    j.n = un;
+    j.n3 = nl;
+    j.hot = s.hot;
+    j.tree_count = tree_count;
+    j.tshift = 32;
+    j.stream_id = p->stream_id;
+    j.tree_begin = tree_begin;
+    j.first_item = 0;
+    return FC_OK;
 }
 
 // Estimators to compute from the root counts once the trees are sampled.
@@ -346,7 +431,8 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     fc::CoopArgs c{};
     bool lds_bits = false, in_bits = false, word32 = false;
     uint32_t repop_words = 0;  // global-counter sampler: re-pop filter words (0: off)
-    bool use_lds = false, use_hyb = false, use_tile = false;
+    bool use_lds = false, use_hyb = false, use_tile = false, use_hub = false;
+    size_t hub_lds = 0;
     size_t jump_lds = 0;  // LDS of one tree of the small-graph variant (0: not used)
     fc::TileArgs ta{};
     uint32_t tile_threads = 1024;
@@ -401,24 +487,26 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         // (isolated vertices need no LDS, so only the id width bounds n here)
         const bool try_lds = (mode == 3 || (mode == 0 && ctx->coop_lds_counts)) &&
                              g.n < (1 << fc::kRelabelIdBits);
+        const bool try_hub = mode == 0 && ctx->hub && ctx->coop_lds_counts && g.n >= 1;
         const uint32_t nb = fc::relabel_blocks(static_cast<uint32_t>(g.n));
-        if (try_lds) {
+        if (try_lds || try_hub) {
             if ((rc = ensure(ctx, ctx->rl_blk, 4u * fc::kRelabelClasses * nb, "class counts")) ||
                 (rc = ensure(ctx, ctx->rl_base, 4u * fc::kRelabelClasses * nb, "class offsets")))
                 return rc;
-            FC_HIP(ctx, fc::launch_class_bounds(g.row_ptr, static_cast<uint32_t>(g.n), false,
+            FC_HIP(ctx, fc::launch_class_bounds(g.row_ptr, static_cast<uint32_t>(g.n), fc::kNarrowFirst,
                                                 static_cast<uint32_t *>(ctx->rl_blk.ptr),
                                                 static_cast<uint32_t *>(ctx->rl_base.ptr),
-                                                sm->class_bounds, ctx->stream),
+                                                sm->class_bounds, &sm->square, ctx->stream),
                    "class bounds");
         }
-        unsigned int cb[4] = {0, 0, 0, 0};
-        FC_HIP(ctx, hipMemcpyAsync(&dmax, &sm->dmax, sizeof(dmax), hipMemcpyDeviceToHost, ctx->stream),
-               "copy dmax");
-        if (try_lds)
-            FC_HIP(ctx, hipMemcpyAsync(cb, sm->class_bounds, sizeof(cb), hipMemcpyDeviceToHost,
-                                       ctx->stream), "copy class bounds");
+        FC_HIP(ctx, hipMemcpyAsync(ctx->host_small, sm, sizeof(Small), hipMemcpyDeviceToHost, ctx->stream),
+               "copy degrees");
         FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "build_vrec");
+        unsigned int cb[4];
+        std::copy(ctx->host_small->class_bounds, ctx->host_small->class_bounds + 4, cb);
+        dmax = ctx->host_small->dmax;
+        const unsigned long long square = ctx->host_small->square;
+        const uint32_t nl = cb[3];  // vertices that are not isolated (with try_hub or try_lds)
         if (try_lds) {
             const fc::CountLayout L = fc::count_layout(cb[3], cb[0], cb[1], cb[2]);
             if (4u * static_cast<size_t>(L.words) + kLdsStaticBytes <= ctx->max_lds) {
@@ -469,15 +557,44 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         // Automatically only where the global-counter variant cannot keep its
         // settled bitmap in LDS either (beyond that size the hybrid wins).
         const bool coop_bits_fit = fc::coop_lds_bytes(static_cast<uint32_t>(g.n)) + 1024u <= ctx->max_lds;
-        if (!use_lds && !use_tile &&
+        // hubs first, reported as the sampler whose place it takes: always where a tree's
+        // counters do not fit LDS (ms of 512 trees, global counters or hybrid against
+        // hubs first: BA of 400000 vertices 28.4 / 8.4, of 1.5 million 131 / 40,
+        // Erdos-Renyi of 300000 19.8 / 8.0, R-MAT of 1 million 43.2 / 5.7, of 2^22 108 / 28)
+        if (try_hub && !use_tile &&
+            (ctx->hub == 2 || !use_lds ||
+             hub_applies(nl, static_cast<uint64_t>(g.nnz), square, p->alpha, vol))) {
+            use_hub = true;
+            kname = use_lds ? "wilson_lds" : coop_bits_fit ? "wilson_coop" : "wilson_hyb";
+            use_lds = false;
+            if ((rc = hub_prepare(ctx, g, p, vrec, nl, tree_begin, tree_count, weighted, nb, &c, &lds_threads,
+                                  &hub_lds)))
+                return rc;
+            slots = c.slots;
+            fc::CoopJob &j = c.single;
+            j.col_idx = g.col_idx;
+            j.wsum = wsum;
+            j.wthr = wthr;
+            j.step_cap = step_cap;
+            j.root_counts = root_counts;
+            j.visit_counts = reinterpret_cast<unsigned long long *>(visit_counts);
+            j.tree_digests = reinterpret_cast<unsigned long long *>(tree_digests);
+            j.tree_steps = reinterpret_cast<unsigned long long *>(tree_steps);
+            j.parents = parents;
+            j.tree_visits = tree_visits;
+            c.queue = &sm->queue;
+            c.totals = &sm->totals;
+            c.phase_ticks = ctx->phase_timing ? sm->phase_ticks : nullptr;
+        }
+        if (!use_lds && !use_tile && !use_hub &&
             (mode == 4 || (mode == 0 && ctx->coop_lds_counts && !coop_bits_fit)) && g.n >= 1) {
             if ((rc = ensure(ctx, ctx->rl_blk, 4u * fc::kRelabelClasses * nb, "class counts")) ||
                 (rc = ensure(ctx, ctx->rl_base, 4u * fc::kRelabelClasses * nb, "class offsets")))
                 return rc;
-            FC_HIP(ctx, fc::launch_class_bounds(g.row_ptr, static_cast<uint32_t>(g.n), true,
+            FC_HIP(ctx, fc::launch_class_bounds(g.row_ptr, static_cast<uint32_t>(g.n), fc::kWidestFirst,
                                                 static_cast<uint32_t *>(ctx->rl_blk.ptr),
                                                 static_cast<uint32_t *>(ctx->rl_base.ptr),
-                                                sm->class_bounds, ctx->stream),
+                                                sm->class_bounds, nullptr, ctx->stream),
                    "class bounds");
             FC_HIP(ctx, hipMemcpyAsync(cb, sm->class_bounds, sizeof(cb), hipMemcpyDeviceToHost,
                                        ctx->stream), "copy class bounds");
@@ -510,7 +627,8 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
                 (rc = ensure(ctx, ctx->rl_adj, 8u * static_cast<size_t>(g.nnz), "relabelled adjacency")))
                 return rc;
             FC_HIP(ctx, fc::launch_relabel_graph(g.row_ptr, g.col_idx, static_cast<uint32_t>(g.n),
-                                                 g.nnz, static_cast<const uint32_t *>(ctx->rl_base.ptr),
+                                                 g.nnz, fc::kWidestFirst,
+                                                 static_cast<const uint32_t *>(ctx->rl_base.ptr),
                                                  32u, static_cast<uint32_t *>(ctx->rl_inv.ptr),
                                                  static_cast<uint32_t *>(ctx->rl_orig.ptr),
                                                  static_cast<unsigned long long *>(ctx->rl_adj.ptr),
@@ -590,7 +708,8 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
                 (rc = ensure(ctx, ctx->rl_adj, 8u * static_cast<size_t>(g.nnz), "relabelled adjacency")))
                 return rc;
             FC_HIP(ctx, fc::launch_relabel_graph(g.row_ptr, g.col_idx, static_cast<uint32_t>(g.n),
-                                                 g.nnz, static_cast<const uint32_t *>(ctx->rl_base.ptr),
+                                                 g.nnz, fc::kNarrowFirst,
+                                                 static_cast<const uint32_t *>(ctx->rl_base.ptr),
                                                  fc::kRelabelIdBits,
                                                  static_cast<uint32_t *>(ctx->rl_inv.ptr),
                                                  static_cast<uint32_t *>(ctx->rl_orig.ptr),
@@ -738,7 +857,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         ta.parents = parents;
         ta.tree_visits = tree_visits;
     }
-    if (use_coop && !jump_lds && !use_lds && !use_hyb && !use_tile) {
+    if (use_coop && !jump_lds && !use_lds && !use_hyb && !use_tile && !use_hub) {
         // 32-bit tree words when target and in-arrow count both fit (the count of
         // a vertex never exceeds its degree)
         word_layout(static_cast<uint32_t>(g.n), dmax, ctx->coop_word32, &tshift, &word32);
@@ -853,6 +972,13 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     } else if (use_tile) {
         FC_HIP(ctx, fc::launch_wilson_tile(ta, tile_threads, tile_lds, ctx->stream),
                "wilson_tile launch");
+    } else if (use_hub) {
+        if (c.pre) {
+            FC_HIP(ctx, fc::launch_hub_predraw(c, ctx->stream), "hub_predraw launch");
+            FC_HIP(ctx, hipEventRecord(ctx->evm, ctx->stream), "event");
+        }
+        FC_HIP(ctx, fc::launch_wilson_hub(c, lds_threads, hub_lds, weighted, ctx->stream),
+               "wilson_hub launch");
     } else if (use_hyb) {
         FC_HIP(ctx, fc::launch_wilson_hyb(c, lds_threads, lds_words, ctx->stream),
                "wilson_hyb launch");
@@ -900,7 +1026,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         stats->digest_sum = tot.digest_sum;
         stats->ms_sample = ms;
         stats->ms_predraw = 0.0;
-        if (use_lds && c.pre) {
+        if ((use_lds || use_hub) && c.pre) {
             float pm = 0.f;
             (void)hipEventElapsedTime(&pm, ctx->ev0, ctx->evm);
             stats->ms_predraw = pm;
@@ -963,6 +1089,36 @@ uint32_t lds_threads_for(const fc_ctx *ctx, uint64_t trees, uint32_t lds_words) 
     uint32_t t = 1024u;
     while (t > 256u && 2048u / t < per_cu) t /= 2;
     return t;
+}
+
+// Whether the hubs-first sampler takes the place of the one with LDS counters: where
+// arrows gather at few vertices (the mean degree of an edge's end is at least ten
+// times that of a vertex) and are followed far (vol: the sum of the degrees).  ms of 512
+// trees, LDS counters against hubs first: R-MAT of 30000 to 250000 vertices (skew 14 to
+// 28) at alpha 10 3.8 / 1.5 to 12.6 / 2.6, at alpha 1 0.76 / 0.39 to 2.48 / 1.71, at
+// alpha 0.1 0.24 / 0.23 to 1.33 / 1.36, with edge factor 3 there 0.86 / 0.94; BA (skew
+// 3 to 4) and Erdos-Renyi (1.1) of 30000 to 110000 at alpha 1 0.49 / 0.68 to 1.75 /
+// 2.50, at alpha 10 1.29 / 1.08 to 3.21 / 3.79.
+bool hub_applies(uint32_t nl, uint64_t nnz, uint64_t square, double alpha, double vol) {
+    return static_cast<double>(square) * nl >= 10.0 * static_cast<double>(nnz) * static_cast<double>(nnz) &&
+           alpha * vol >= 2.0 * nl;
+}
+
+// Launch shape of the hubs-first sampler for nl vertices that are not isolated.
+HubShape hub_shape(const fc_ctx *ctx, uint32_t nl) {
+    HubShape s{};
+    s.threads = ctx->hub_threads;
+    const size_t most = ctx->max_lds - kLdsStaticBytes;
+    uint32_t set = std::min(fc::kHubMax, fc::kHubOwn * s.threads) & ~63u;
+    if (ctx->hub_set) set = std::min(set, ctx->hub_set);
+    set = std::min(set, std::max(64u, (nl + 63u) & ~63u));
+    while (set > 64u && fc::hub_lds_bytes(set) > most) set -= 64u;
+    s.set = set;
+    s.hot = nl <= set ? nl : static_cast<uint32_t>(static_cast<uint64_t>(set) * ctx->hub_hot / 1000u);
+    const size_t words = (static_cast<size_t>(nl) + 31u) / 32u;
+    s.lds = std::max(fc::hub_lds_bytes(set), std::min(4u * words, most & ~size_t{3}));
+    s.lds_bits = static_cast<uint32_t>(std::min<size_t>(words, s.lds / 4u)) * 32u;
+    return s;
 }
 
 uint32_t jump_threads_for(const fc_ctx *ctx, uint32_t n, uint64_t trees) {
@@ -1046,6 +1202,7 @@ int fc_create(fc_ctx **out, int hip_device, void *hip_stream) {
         fc::lds_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess ||
         fc::hyb_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess ||
         fc::tile_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess ||
+        fc::hub_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess ||
         fc::jump_set_limit(ctx->max_lds - kLdsStaticBytes) != hipSuccess) {
         (void)hipGetLastError();
         fc_destroy(ctx);
@@ -1159,6 +1316,19 @@ int fc_set_option(fc_ctx *ctx, const char *key, int64_t value) {
     } else if (k == "max_slots") {
         if (value < 0 || value > 0x7FFFFFFF) return set_err(ctx, FC_ERR_ARG, "max_slots");
         ctx->max_slots = static_cast<uint32_t>(value);
+    } else if (k == "hub") {
+        if (value < 0 || value > 2) return set_err(ctx, FC_ERR_ARG, "hub must be 0, 1 or 2");
+        ctx->hub = static_cast<uint32_t>(value);
+    } else if (k == "hub_set") {
+        if (value < 0 || value > fc::kHubMax || value % 64)
+            return set_err(ctx, FC_ERR_ARG, "hub_set must be 0 or a multiple of 64 up to 32704");
+        ctx->hub_set = static_cast<uint32_t>(value);
+    } else if (k == "hub_hot") {
+        if (value < 0 || value > 1000) return set_err(ctx, FC_ERR_ARG, "hub_hot");
+        ctx->hub_hot = static_cast<uint32_t>(value);
+    } else if (k == "hub_threads") {
+        if (value < 64 || value > 1024 || value % 64) return set_err(ctx, FC_ERR_ARG, "hub_threads");
+        ctx->hub_threads = static_cast<uint32_t>(value);
     } else if (k == "tile_size") {
         if (value < 0 || value > fc::kTileMax || value % 64)
             return set_err(ctx, FC_ERR_ARG, "tile_size must be 0 or a multiple of 64 up to 32704");
@@ -1283,6 +1453,10 @@ int fc_sample_noalloc(fc_ctx *ctx, const fc_graph *g, const fc_params *params,
     sh.lds_repop = ctx->lds_repop;
     sh.lds_lean = ctx->lds_lean;
     sh.coop_repop = ctx->coop_repop;
+    sh.hub = ctx->hub;
+    sh.hub_set = ctx->hub_set;
+    sh.hub_hot = ctx->hub_hot;
+    sh.hub_threads = ctx->hub_threads;
     sh.tile_size = ctx->tile_size;
     sh.tile_cross_permille = ctx->tile_cross_permille;
     sh.tile_threads = ctx->tile_threads;

@@ -532,10 +532,10 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         uint32_t *bnd = static_cast<uint32_t *>(b->rl_bounds.ptr);
         for (size_t f = 0; f < gs.size(); ++f)
             if (!small(gs[f].n))
-                FB_HIP(fc::launch_class_bounds(gs[f].rp, gs[f].n, false,
+                FB_HIP(fc::launch_class_bounds(gs[f].rp, gs[f].n, fc::kNarrowFirst,
                                                blk + fc::kRelabelClasses * gs[f].off_b,
                                                base + fc::kRelabelClasses * gs[f].off_b, bnd + 4 * f,
-                                               b->stream),
+                                               nullptr, b->stream),
                        "class bounds");
         FB_HIP(hipMemcpyAsync(bounds.data(), bnd, 16 * gs.size(), hipMemcpyDeviceToHost, b->stream),
                "copy class bounds");
@@ -571,7 +571,7 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         unsigned long long *adj = static_cast<unsigned long long *>(b->rl_adj.ptr);
         for (const GInfo &gi : gs)
             if (!small(gi.n))
-                FB_HIP(fc::launch_relabel_graph(gi.rp, gi.ci, gi.n, gi.nnz,
+                FB_HIP(fc::launch_relabel_graph(gi.rp, gi.ci, gi.n, gi.nnz, fc::kNarrowFirst,
                                                 base + fc::kRelabelClasses * gi.off_b,
                                                 fc::kRelabelIdBits, inv + gi.off_n, orig + gi.off_n,
                                                 adj + gi.off_e, b->stream), "relabel");

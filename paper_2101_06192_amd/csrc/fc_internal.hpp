@@ -24,6 +24,7 @@ struct Small {  // device-side counters of one call
     unsigned int pad;
     unsigned long long phase_ticks[8];
     unsigned int class_bounds[4];  // n0, n1, n2, n3 of the degree-class relabelling
+    unsigned long long square;     // sum of the squared degrees
     double wtotal;                 // sum of the weighted degrees (weighted graphs)
 };
 
@@ -69,6 +70,11 @@ struct fc_ctx {
     uint32_t coop_repop = 2;      // the same for the global-counter sampler
     uint32_t lds_lean = 0;        // LDS-counter sampler: the lean register shape for workgroups
                                   // of at most 512 threads (batch autotuning times both)
+    uint32_t hub = 1;             // hubs-first sampler: 0 never, 1 where a tree does not fit LDS
+                                  // whole, 2 also where it does
+    uint32_t hub_set = 0;         // its LDS set's vertices (0: the most that fit)
+    uint32_t hub_hot = 130;       // of these, per mille, hubs at the start; the rest join later
+    uint32_t hub_threads = 1024;  // its threads per workgroup
     uint32_t tile_size = 0;       // tile sampler: vertices per tile (0: the widest that fits LDS)
     uint32_t tile_cross_permille = 100;  // picked automatically when at most this share (per
                                          // mille) of the CSR entries cross tiles
@@ -136,6 +142,12 @@ int begin(fc_ctx *ctx);
 // Threads per workgroup of the LDS-counter sampler for `trees` trees whose
 // counters and bitmap take lds_words words of LDS.
 uint32_t lds_threads_for(const fc_ctx *ctx, uint64_t trees, uint32_t lds_words);
+struct HubShape {
+    uint32_t threads, set, hot, lds_bits;
+    size_t lds;
+};
+bool hub_applies(uint32_t nl, uint64_t nnz, uint64_t square, double alpha, double vol);
+HubShape hub_shape(const fc_ctx *ctx, uint32_t nl);
 // Threads per workgroup of the small-graph sampler for `trees` trees of n vertices.
 uint32_t jump_threads_for(const fc_ctx *ctx, uint32_t n, uint64_t trees);
 // Bits of the target field so that n < 2^tshift, and whether a 32-bit tree

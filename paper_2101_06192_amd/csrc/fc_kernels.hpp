@@ -121,6 +121,8 @@ struct CoopArgs {
                               // first arrows are drawn already (launch_lds_predraw), used in
                               // place of the slot's word array; or null
     uint32_t n_max;           // largest n of any job (per-slot stride)
+    uint32_t set;             // hubs-first variant: vertices of a set in LDS
+    uint32_t lds_bits;        // hubs-first variant: settled bits kept in LDS
     uint32_t slots;           // workgroups (trees in flight)
     uint32_t item_count;      // trees over all jobs
     uint32_t key0, key1;
@@ -224,19 +226,38 @@ constexpr uint32_t kRelabelIdBits = 18;
 // into base, and bounds[0..3] = n0, n1, n2, n3.
 constexpr uint32_t kRelabelClasses = 5;
 uint32_t relabel_blocks(uint32_t n);
-// widest_first orders the classes 32-, 16-, 8-, 4-bit (hybrid sampler) instead
-// of 4-, 8-, 16-, 32-bit; isolated vertices come last either way.
-hipError_t launch_class_bounds(const int32_t *row_ptr, uint32_t n, bool widest_first, uint32_t *blk,
-                               uint32_t *base, uint32_t *bounds, hipStream_t stream);
+// The classes in the order 4-, 8-, 16-, 32-bit (kNarrowFirst), 32-, 16-, 8-, 4-bit
+// (kWidestFirst, hybrid sampler), or by degree, from 256 down (kHubsFirst); isolated
+// vertices come last in each.  *square (or null) += the squared degrees.
+enum ClassOrder : int { kNarrowFirst = 0, kWidestFirst, kHubsFirst };
+hipError_t launch_class_bounds(const int32_t *row_ptr, uint32_t n, ClassOrder order, uint32_t *blk,
+                               uint32_t *base, uint32_t *bounds, unsigned long long *square,
+                               hipStream_t stream);
 // inv/orig permutations and relabelled adjacency of one graph (base from
 // launch_class_bounds).
 hipError_t launch_relabel_graph(const int32_t *row_ptr, const int32_t *col_idx, uint32_t n,
-                                int64_t nnz, const uint32_t *base, uint32_t orig_shift,
-                                uint32_t *inv, uint32_t *orig, unsigned long long *adj,
+                                int64_t nnz, ClassOrder order, const uint32_t *base,
+                                uint32_t orig_shift, uint32_t *inv, uint32_t *orig,
+                                unsigned long long *adj,
                                 hipStream_t stream);
 // Relabelled records of one G* (from the original-id records vrec).
 hipError_t launch_relabel_vrec(const VRec *vrec, const uint32_t *inv, uint32_t n, VRec *vrec_r,
                                hipStream_t stream);
+
+// Hubs-first variant: relabelled as for the hybrid one but by launch_class_bounds with
+// kHubsFirst.  Arrays per slot: word (u64 arrows; not with pre, the first arrows
+// of all trees drawn ahead), kk (u64, zero at launch), lists, levels (n_max in-arrow
+// counts), origt (2 * set ids), bits.
+constexpr uint32_t kHubMax = 32704;  // largest set: local ids and codes fit 15 bits
+constexpr uint32_t kHubOwn = 32;     // vertices of a set per thread, at most
+// lds: dynamic LDS bytes, at least hub_lds_bytes(a.set) and a.lds_bits / 8
+hipError_t launch_wilson_hub(const CoopArgs &a, uint32_t threads, size_t lds, bool weighted,
+                             hipStream_t stream);
+// First arrow of every vertex that is not isolated in every tree of a single-job launch.
+hipError_t launch_hub_predraw(const CoopArgs &a, hipStream_t stream);
+hipError_t hub_set_limit(size_t bytes);
+int hub_max_active(uint32_t threads, size_t lds, bool weighted);
+size_t hub_lds_bytes(uint32_t set);  // LDS of a set (a multiple of 64)
 
 // Tile sampler (graphs whose ids are local): one workgroup per tree pops the
 // cycles inside each tile of B consecutive ids in LDS, finds the

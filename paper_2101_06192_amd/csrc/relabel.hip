@@ -3,7 +3,8 @@
 // That sampler keeps the in-arrow count of every vertex of a tree in LDS.  A
 // count never exceeds the vertex degree, so a vertex of degree d gets a field
 // of 4 << c bits, c = class(d): 4 bits up to degree 15, 8 up to 255, 16 up to
-// 65535, else 32.  Isolated vertices form a fifth class with no field: they
+// 65535, else 32 (the hubs-first sampler keeps no counts: its classes end at 15, 63
+// and 255, to tell the hubs apart).  Isolated vertices form a fifth class with no field: they
 // are never a target, and in every tree they are roots after one draw.
 // Vertices are renumbered so that each class is a contiguous range of
 // internal ids (class 0 first, isolated vertices last; original order kept
@@ -12,7 +13,7 @@
 // vertex record carries the original id, and the relabelled adjacency holds
 // (internal, original) pairs of each neighbour at the same CSR positions
 // (internal id in the low bits, original id shifted by 18 for the LDS sampler
-// or 32 for the hybrid one), so the neighbour chosen by a draw is the one the
+// or 32 for the others), so the neighbour chosen by a draw is the one the
 // original CSR gives.
 #include "fc_kernels.hpp"
 
@@ -23,32 +24,43 @@ namespace {
 constexpr int kPlaceThreads = 1024;
 constexpr uint32_t kClasses = kRelabelClasses;  // four field widths, then isolated vertices
 
-__device__ __forceinline__ uint32_t deg_class(uint32_t d) {
-    return d == 0u ? 4u : d <= 15u ? 0u : d <= 255u ? 1u : d <= 65535u ? 2u : 3u;
+__device__ __forceinline__ uint32_t deg_class(uint32_t d, ClassOrder order) {
+    const uint32_t top1 = order == kHubsFirst ? 63u : 255u, top2 = order == kHubsFirst ? 255u : 65535u;
+    return d == 0u ? 4u : d <= 15u ? 0u : d <= top1 ? 1u : d <= top2 ? 2u : 3u;
 }
 
-// Per block of kPlaceThreads vertices: how many fall in each class.
+// Per block of kPlaceThreads vertices: how many fall in each class; with square, the
+// sum of the squared degrees.
 __global__ __launch_bounds__(kPlaceThreads) void class_count_kernel(
-    const int32_t *__restrict__ row_ptr, uint32_t n, uint32_t *__restrict__ blk) {
+    const int32_t *__restrict__ row_ptr, uint32_t n, ClassOrder order, uint32_t *__restrict__ blk,
+    unsigned long long *square) {
     __shared__ uint32_t s[kClasses];
+    __shared__ unsigned long long s_square;
+    if (threadIdx.x == 0) s_square = 0;
     if (threadIdx.x < kClasses) s[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t v = blockIdx.x * kPlaceThreads + threadIdx.x;
-    const uint32_t c =
-        v < n ? deg_class(static_cast<uint32_t>(row_ptr[v + 1] - row_ptr[v])) : kClasses;
+    const uint32_t d = v < n ? static_cast<uint32_t>(row_ptr[v + 1] - row_ptr[v]) : 0u;
+    const uint32_t c = v < n ? deg_class(d, order) : kClasses;
+    if (square) {
+        unsigned long long sq = static_cast<unsigned long long>(d) * d;
+        for (int off = 32; off > 0; off >>= 1) sq += __shfl_down(sq, off, 64);
+        if ((threadIdx.x & 63u) == 0 && sq) atomicAdd(&s_square, sq);
+    }
     for (uint32_t k = 0; k < kClasses; ++k) {
         const uint64_t m = __ballot(c == k);
         if ((threadIdx.x & 63u) == 0 && m) atomicAdd(&s[k], static_cast<uint32_t>(__popcll(m)));
     }
     __syncthreads();
     if (threadIdx.x < kClasses) blk[blockIdx.x * kClasses + threadIdx.x] = s[threadIdx.x];
+    if (threadIdx.x == 0 && s_square) atomicAdd(square, s_square);
 }
 
 // Rank of class c in the id order: narrowest field first (LDS sampler) or
-// widest first (hybrid sampler, whose LDS holds a prefix of the ids: the
-// highest-degree vertices, which receive most arrows); isolated vertices last.
-__device__ __forceinline__ uint32_t class_rank(uint32_t c, bool widest_first) {
-    return c == 4u || !widest_first ? c : 3u - c;
+// widest first (hybrid and hubs-first samplers, whose LDS holds a prefix of the ids:
+// the highest-degree vertices, which receive most arrows); isolated vertices last.
+__device__ __forceinline__ uint32_t class_rank(uint32_t c, ClassOrder order) {
+    return c == 4u || order == kNarrowFirst ? c : 3u - c;
 }
 
 // One block: base[b][k] = first internal id of class k in block b; bounds[r] =
@@ -60,7 +72,7 @@ __device__ __forceinline__ uint32_t class_rank(uint32_t c, bool widest_first) {
 constexpr uint32_t kScanThreads = 1024;
 
 __global__ __launch_bounds__(kScanThreads) void class_scan_kernel(
-    const uint32_t *__restrict__ blk, uint32_t nb, int widest_first, uint32_t *__restrict__ base,
+    const uint32_t *__restrict__ blk, uint32_t nb, ClassOrder order, uint32_t *__restrict__ base,
     uint32_t *__restrict__ bounds) {
     constexpr uint32_t kWaves = kScanThreads / 64u;
     __shared__ uint32_t s_wave[kClasses][kWaves];
@@ -91,10 +103,10 @@ __global__ __launch_bounds__(kScanThreads) void class_scan_kernel(
         total[k] = t;
     }
     for (uint32_t k = 0; k < kClasses; ++k) {  // classes of a lower rank come first
-        const uint32_t r = class_rank(k, widest_first);
+        const uint32_t r = class_rank(k, order);
         uint32_t start = 0;
         for (uint32_t j = 0; j < kClasses; ++j)
-            if (class_rank(j, widest_first) < r) start += total[j];
+            if (class_rank(j, order) < r) start += total[j];
         if (threadIdx.x == 0 && r + 1 < kClasses) bounds[r] = start + total[k];
         before[k] += start;
     }
@@ -108,14 +120,14 @@ __global__ __launch_bounds__(kScanThreads) void class_scan_kernel(
 // inv[v] = internal id of v, orig[internal] = v: rank inside the block from
 // per-wave ballots, waves in order.
 __global__ __launch_bounds__(kPlaceThreads) void class_place_kernel(
-    const int32_t *__restrict__ row_ptr, uint32_t n, const uint32_t *__restrict__ base,
-    uint32_t *__restrict__ inv, uint32_t *__restrict__ orig) {
+    const int32_t *__restrict__ row_ptr, uint32_t n, ClassOrder order,
+    const uint32_t *__restrict__ base, uint32_t *__restrict__ inv, uint32_t *__restrict__ orig) {
     constexpr uint32_t kWaves = kPlaceThreads / 64;
     __shared__ uint32_t s_wave[kWaves][kClasses];
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
     const uint32_t v = blockIdx.x * kPlaceThreads + threadIdx.x;
     const uint32_t c =
-        v < n ? deg_class(static_cast<uint32_t>(row_ptr[v + 1] - row_ptr[v])) : kClasses;
+        v < n ? deg_class(static_cast<uint32_t>(row_ptr[v + 1] - row_ptr[v]), order) : kClasses;
     uint64_t mine = 0;
     for (uint32_t k = 0; k < kClasses; ++k) {
         const uint64_t m = __ballot(c == k);
@@ -156,12 +168,13 @@ __global__ void relabel_adj_kernel(const int32_t *__restrict__ col_idx, int64_t 
 
 uint32_t relabel_blocks(uint32_t n) { return (n + kPlaceThreads - 1) / kPlaceThreads; }
 
-hipError_t launch_class_bounds(const int32_t *row_ptr, uint32_t n, bool widest_first, uint32_t *blk,
-                               uint32_t *base, uint32_t *bounds, hipStream_t stream) {
+hipError_t launch_class_bounds(const int32_t *row_ptr, uint32_t n, ClassOrder order, uint32_t *blk,
+                               uint32_t *base, uint32_t *bounds, unsigned long long *square,
+                               hipStream_t stream) {
     const uint32_t nb = relabel_blocks(n);
     if (nb == 0) return hipSuccess;
-    class_count_kernel<<<nb, kPlaceThreads, 0, stream>>>(row_ptr, n, blk);
-    class_scan_kernel<<<1, kScanThreads, 0, stream>>>(blk, nb, widest_first ? 1 : 0, base, bounds);
+    class_count_kernel<<<nb, kPlaceThreads, 0, stream>>>(row_ptr, n, order, blk, square);
+    class_scan_kernel<<<1, kScanThreads, 0, stream>>>(blk, nb, order, base, bounds);
     return hipGetLastError();
 }
 
@@ -173,12 +186,13 @@ hipError_t launch_relabel_vrec(const VRec *vrec, const uint32_t *inv, uint32_t n
 }
 
 hipError_t launch_relabel_graph(const int32_t *row_ptr, const int32_t *col_idx, uint32_t n,
-                                int64_t nnz, const uint32_t *base, uint32_t orig_shift,
+                                int64_t nnz, ClassOrder order, const uint32_t *base,
+                                uint32_t orig_shift,
                                 uint32_t *inv, uint32_t *orig, unsigned long long *adj,
                                 hipStream_t stream) {
     const uint32_t nb = relabel_blocks(n);
     if (nb == 0) return hipSuccess;
-    class_place_kernel<<<nb, kPlaceThreads, 0, stream>>>(row_ptr, n, base, inv, orig);
+    class_place_kernel<<<nb, kPlaceThreads, 0, stream>>>(row_ptr, n, order, base, inv, orig);
     if (nnz > 0) {
         int64_t blocks = (nnz + 255) / 256;
         if (blocks > 16384) blocks = 16384;
