@@ -303,10 +303,10 @@ int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::V
     FC_HIP(ctx, fc::launch_relabel_vrec(vrec, static_cast<const uint32_t *>(ctx->rl_inv.ptr), un,
                                         static_cast<fc::VRec *>(ctx->rl_vrec.ptr), ctx->stream),
            "relabel records");
-    const HubShape s = hub_shape(ctx, nl);
-    *threads = s.threads;
+    const HubShape s = hub_shape(ctx, nl, ctx->hub_threads, 1u);
+    *threads = ctx->hub_threads;
     *lds = s.lds;
-    const int fit = fc::hub_max_active(s.threads, s.lds, weighted);
+    const int fit = fc::hub_max_active(*threads, s.lds, weighted);
     const size_t nw = (stride + 31u) / 32u;
     const size_t pre_bytes = 8u * stride * static_cast<size_t>(tree_count);
     bool predraw = ctx->predraw_mib != 0 && pre_bytes <= (static_cast<size_t>(ctx->predraw_mib) << 20);
@@ -337,6 +337,7 @@ int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::V
     c->n_max = static_cast<uint32_t>(stride);
     c->set = s.set;
     c->lds_bits = s.lds_bits;
+    c->hub_hot = ctx->hub_hot;
     c->slots = static_cast<uint32_t>(slots);
     c->item_count = tree_count;
     c->key0 = static_cast<uint32_t>(p->seed);
@@ -351,7 +352,6 @@ int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::V
     j.orig = static_cast<const uint32_t *>(ctx->rl_orig.ptr);
     j.n = un;
     j.n3 = nl;
-    j.hot = s.hot;
     j.tree_count = tree_count;
     j.tshift = 32;
     j.stream_id = p->stream_id;
@@ -1104,17 +1104,16 @@ bool hub_applies(uint32_t nl, uint64_t nnz, uint64_t square, double alpha, doubl
            alpha * vol >= 2.0 * nl;
 }
 
-// Launch shape of the hubs-first sampler for nl vertices that are not isolated.
-HubShape hub_shape(const fc_ctx *ctx, uint32_t nl) {
+// Launch shape of the hubs-first sampler for at most nl vertices that are not isolated,
+// with per_cu workgroups on a CU.
+HubShape hub_shape(const fc_ctx *ctx, uint32_t nl, uint32_t threads, uint32_t per_cu) {
     HubShape s{};
-    s.threads = ctx->hub_threads;
-    const size_t most = ctx->max_lds - kLdsStaticBytes;
-    uint32_t set = std::min(fc::kHubMax, fc::kHubOwn * s.threads) & ~63u;
+    const size_t most = ((ctx->max_lds / per_cu) & ~size_t{511}) - kLdsStaticBytes;
+    uint32_t set = std::min(fc::kHubMax, fc::kHubOwn * threads) & ~63u;
     if (ctx->hub_set) set = std::min(set, ctx->hub_set);
     set = std::min(set, std::max(64u, (nl + 63u) & ~63u));
     while (set > 64u && fc::hub_lds_bytes(set) > most) set -= 64u;
     s.set = set;
-    s.hot = nl <= set ? nl : static_cast<uint32_t>(static_cast<uint64_t>(set) * ctx->hub_hot / 1000u);
     const size_t words = (static_cast<size_t>(nl) + 31u) / 32u;
     s.lds = std::max(fc::hub_lds_bytes(set), std::min(4u * words, most & ~size_t{3}));
     s.lds_bits = static_cast<uint32_t>(std::min<size_t>(words, s.lds / 4u)) * 32u;

@@ -37,9 +37,11 @@ namespace {
 // device job table and item map, scratch, counters and launch shape.
 struct Group {
     std::vector<int32_t> jobs;
-    DevBuf jobtab, item_job, word, kk, lists, levels, bits, small, scratch_r;
+    DevBuf jobtab, item_job, word, kk, lists, levels, bits, members, small, scratch_r;
     fc::CoopArgs args{};
-    uint32_t n_max = 0, item_count = 0, slots = 0, threads = 512, wg_per_cu = 4;
+    uint32_t n_max = 0;      // slot stride: the most vertices (hubs first: not isolated ones)
+    uint32_t n_out = 0;      // the most vertices of a job
+    uint32_t item_count = 0, slots = 0, threads = 512, wg_per_cu = 4;
     size_t ntab = 0, kk_words = 0;
     bool use_lds = false, lds_bits = false, in_bits = false, word32 = true;
     bool weighted = false;   // some job's graph carries edge weights
@@ -47,13 +49,15 @@ struct Group {
     bool lean = false;       // LDS kernel: the lean register shape (at most 512 threads)
     bool jump = false;       // small-graph kernel (whole trees in LDS); use_lds is false
     size_t jump_lds = 0;     // its dynamic LDS (largest graph)
+    bool hub = false;        // hubs-first kernel; use_lds is false
+    HubShape hub_shape{};    // (set with the shape)
     uint32_t repop_words = 0;  // the same, global-counter kernel: its LDS filter (set with the shape)
     uint32_t lds_words = 0;  // dynamic LDS of the LDS-counter kernel (largest graph)
 };
 
-// wide, narrow, and the small graphs by the trees of the largest that a CU holds:
-// up to three, up to eight, more
-constexpr int kMaxGroups = 5;
+// hubs first, wide, narrow, and the small graphs by the trees of the largest that a CU
+// holds: up to three, up to eight, more
+enum Part : int { kHubs = 0, kWide, kNarrow, kFew, kSome, kMany, kMaxGroups };
 
 }  // namespace
 
@@ -64,7 +68,7 @@ struct fc_batch {
     int32_t flags = 0;
     DevBuf vrec, dmax, iso, wsum, wthr, wtot;  // weighted graphs' running row sums and step
                                                // thresholds, each job's weighted volume
-    DevBuf rl_blk, rl_base, rl_bounds, rl_inv, rl_orig, rl_adj, rl_vrec;  // degree-class relabelling
+    DevBuf rl_blk, rl_base, rl_bounds, rl_square, rl_inv, rl_orig, rl_adj, rl_vrec;  // degree-class relabelling
     Group grp[kMaxGroups];
     int ngroups = 0;
     uint32_t item_count = 0;
@@ -81,11 +85,11 @@ int free_batch(fc_batch *b) {
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
-    for (DevBuf *d : {&b->vrec, &b->dmax, &b->iso, &b->wsum, &b->wthr, &b->wtot, &b->rl_blk, &b->rl_base, &b->rl_bounds, &b->rl_inv,
+    for (DevBuf *d : {&b->vrec, &b->dmax, &b->iso, &b->wsum, &b->wthr, &b->wtot, &b->rl_blk, &b->rl_base, &b->rl_bounds, &b->rl_square, &b->rl_inv,
                       &b->rl_orig, &b->rl_adj, &b->rl_vrec})
         if (d->ptr) (void)hipFree(d->ptr);
     for (Group &g : b->grp)
-        for (DevBuf *d : {&g.jobtab, &g.item_job, &g.word, &g.kk, &g.lists, &g.levels, &g.bits,
+        for (DevBuf *d : {&g.jobtab, &g.item_job, &g.word, &g.kk, &g.lists, &g.levels, &g.bits, &g.members,
                           &g.small, &g.scratch_r})
             if (d->ptr) (void)hipFree(d->ptr);
     for (hipEvent_t e : {b->ev_in, b->ev0, b->ev1})
@@ -107,6 +111,7 @@ hipError_t enqueue_group(const Group &g, const fc::CoopArgs &a, uint32_t threads
         return fc::launch_wilson_lds(a, threads, g.lds_words, g.weighted, g.repop, g.lean, stream);
     e = fc::launch_fill_u64(static_cast<unsigned long long *>(g.kk.ptr), g.kk_words, 0ull, stream);
     if (e != hipSuccess) return e;
+    if (g.hub) return fc::launch_wilson_hub(a, threads, g.hub_shape.lds, g.weighted, stream);
     return fc::launch_wilson_coop(a, threads, g.lds_bits, g.in_bits, g.word32, g.weighted,
                                   g.repop_words, stream);
 }
@@ -120,6 +125,30 @@ int size_scratch(fc_ctx *ctx, Group &g, uint32_t slots) {
         g.slots = slots;
         g.args.word = g.word.ptr;
         g.args.slots = slots;
+        return FC_OK;
+    }
+    if (g.hub) {
+        const HubShape &s = g.hub_shape;
+        if ((rc = ensure(ctx, g.word, 8 * n * slots, "batch arrows")) ||
+            (rc = ensure(ctx, g.kk, 8 * n * slots, "batch set ids")) ||
+            (rc = ensure(ctx, g.lists, 24 * n * slots, "batch lists")) ||
+            (rc = ensure(ctx, g.levels, 4 * n * slots, "batch in-arrow counts")) ||
+            (rc = ensure(ctx, g.members, 8 * static_cast<size_t>(s.set) * slots, "batch set members")) ||
+            (rc = ensure(ctx, g.bits, 4 * nwords * slots, "batch bitmap")))
+            return rc;
+        g.kk_words = n * slots;
+        g.slots = slots;
+        fc::CoopArgs &a = g.args;
+        a.word = g.word.ptr;
+        a.kk = static_cast<uint64_t *>(g.kk.ptr);
+        a.lists = static_cast<uint64_t *>(g.lists.ptr);
+        a.levels = static_cast<uint32_t *>(g.levels.ptr);
+        a.origt = static_cast<uint32_t *>(g.members.ptr);
+        a.bits = static_cast<uint32_t *>(g.bits.ptr);
+        a.set = s.set;
+        a.lds_bits = s.lds_bits;
+        a.hub_hot = ctx->hub_hot;
+        a.slots = slots;
         return FC_OK;
     }
     const size_t wbytes = g.word32 && !g.use_lds ? 4 : 8;
@@ -141,19 +170,23 @@ int size_scratch(fc_ctx *ctx, Group &g, uint32_t slots) {
     return FC_OK;
 }
 
-// (also picks the re-pop filter of a global-counter group for this shape)
+// (also picks the re-pop filter of a global-counter group and the set of a hubs-first
+// group for this shape)
 uint32_t slots_for(const fc_ctx *ctx, Group &g, uint32_t threads, uint32_t wg_per_cu) {
     const size_t n = g.n_max;
-    const int fit = g.jump      ? fc::jump_max_active(threads, g.jump_lds, g.weighted)
+    if (g.hub) g.hub_shape = hub_shape(ctx, g.n_max, threads, wg_per_cu);
+    const int fit = g.hub       ? fc::hub_max_active(threads, g.hub_shape.lds, g.weighted)
+                    : g.jump      ? fc::jump_max_active(threads, g.jump_lds, g.weighted)
                     : g.use_lds ? fc::lds_max_active(threads, g.lds_words, g.weighted, g.repop, g.lean)
                               : fc::coop_max_active(threads, g.lds_bits, g.in_bits, g.word32,
                                                     g.n_max, g.weighted, 0u);
     if (fit > 0) wg_per_cu = std::min<uint32_t>(wg_per_cu, static_cast<uint32_t>(fit));
-    g.repop_words = g.use_lds || g.jump
+    g.repop_words = g.use_lds || g.jump || g.hub
                         ? 0u
                         : coop_repop_words(ctx, threads, wg_per_cu, g.lds_bits, g.in_bits,
                                                  g.word32, g.n_max, g.weighted);
-    const size_t per_slot = g.jump      ? 4 * n
+    const size_t per_slot = g.hub       ? (8 + 8 + 24 + 4) * n + 8 * size_t{g.hub_shape.set} + 4 * ((n + 31) / 32)
+                            : g.jump    ? 4 * n
                             : g.use_lds ? (8 + 24 + 4) * n + 8
                                       : ((g.word32 ? 4 : 8) + 8 + 24 + 4) * n + 8 +
                                             (g.lds_bits ? 0 : 4 * ((n + 31) / 32));
@@ -211,9 +244,10 @@ void disk_store(const fc_ctx *ctx, const TuneKey &k, const std::array<uint32_t, 
 
 TuneKey tune_key(const fc_batch *b, const Group &g) {
     const fc_ctx *ctx = b->ctx;
-    TuneKey k = {static_cast<uint64_t>(ctx->device), g.jump ? 2u : g.use_lds ? 1u : 0u, g.n_max, g.lds_words, g.weighted,
+    TuneKey k = {static_cast<uint64_t>(ctx->device), g.hub ? 3u : g.jump ? 2u : g.use_lds ? 1u : 0u, g.n_max, g.lds_words, g.weighted,
                  g.word32, g.lds_bits, g.in_bits, ctx->lds_repop, ctx->coop_repop,
                  ctx->state_budget, ctx->max_draws};
+    if (g.hub) k.insert(k.end(), {ctx->hub_set, ctx->hub_hot});
     for (int32_t j : g.jobs) {
         const fc_job &jb = b->jobs[j];
         uint64_t abits;
@@ -260,7 +294,9 @@ int autotune(fc_batch *b, Group &g) {
     // R-MAT batches); 0, 1 and 2 keep the re-pops as the option says
     std::vector<std::array<uint32_t, 4>> cand;
     const bool tune_repop = g.use_lds && ctx->lds_repop == 3;
-    if (g.jump) {
+    if (g.hub) {
+        for (uint32_t w : {1u, 2u, 3u}) cand.push_back({w == 1u ? 1024u : 512u, w, g.repop ? 1u : 0u, 0u});
+    } else if (g.jump) {
         for (uint32_t t : {128u, 256u, 512u, 1024u})
             if (t * fc::kJumpOwn >= g.n_max) cand.push_back({t, 64u, g.repop ? 1u : 0u, 0u});
     } else if (g.use_lds) {
@@ -275,7 +311,7 @@ int autotune(fc_batch *b, Group &g) {
     std::vector<fc::CoopJob> tab(g.ntab);
     FC_HIP(ctx, hipMemcpy(tab.data(), g.jobtab.ptr, sizeof(fc::CoopJob) * tab.size(),
                           hipMemcpyDeviceToHost), "read job table");
-    if ((rc = ensure(ctx, g.scratch_r, 4 * static_cast<size_t>(g.n_max), "tuning outputs"))) return rc;
+    if ((rc = ensure(ctx, g.scratch_r, 4 * static_cast<size_t>(g.n_out), "tuning outputs"))) return rc;
     // the tuning sample: a thirty-second of every job's trees (at least one), so
     // that every graph and alpha of the group is in it, not only the largest
     // first jobs
@@ -514,31 +550,38 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
     }
     // graphs whose trees fit LDS whole need no relabelling
     auto small = [&](uint32_t n) {
-        return ctx->coop_lds_counts && n <= fc::kJumpMax &&
+        return ctx->coop_lds_counts && ctx->hub < 2 && n <= fc::kJumpMax &&
                fc::jump_lds_bytes(n) + kLdsStaticBytes <= ctx->max_lds;
     };
     uint32_t n_rest = 0;  // the largest of the others
     for (const GInfo &gi : gs)
         if (!small(gi.n)) n_rest = std::max(n_rest, gi.n);
-    const bool try_lds = ctx->coop_lds_counts && n_rest > 0 && n_rest < (1u << fc::kRelabelIdBits);
+    const bool try_hub = ctx->coop_lds_counts && ctx->hub && n_rest > 0;
+    const bool try_lds = ctx->coop_lds_counts && n_rest > 0 && (try_hub || n_rest < (1u << fc::kRelabelIdBits));
     std::vector<unsigned int> bounds(4 * gs.size(), 0u);
+    std::vector<unsigned long long> square(gs.size(), 0ull);
     if (try_lds) {
         if ((rc = ensure(ctx, b->rl_blk, 4 * fc::kRelabelClasses * tb, "class counts")) ||
             (rc = ensure(ctx, b->rl_base, 4 * fc::kRelabelClasses * tb, "class offsets")) ||
-            (rc = ensure(ctx, b->rl_bounds, 16 * gs.size(), "class bounds")))
+            (rc = ensure(ctx, b->rl_bounds, 16 * gs.size(), "class bounds")) ||
+            (rc = ensure(ctx, b->rl_square, 8 * gs.size(), "squared degrees")))
             return fail(rc);
         uint32_t *blk = static_cast<uint32_t *>(b->rl_blk.ptr);
         uint32_t *base = static_cast<uint32_t *>(b->rl_base.ptr);
         uint32_t *bnd = static_cast<uint32_t *>(b->rl_bounds.ptr);
+        unsigned long long *sq = static_cast<unsigned long long *>(b->rl_square.ptr);
+        FB_HIP(hipMemsetAsync(sq, 0, 8 * gs.size(), b->stream), "memset squared degrees");
         for (size_t f = 0; f < gs.size(); ++f)
             if (!small(gs[f].n))
                 FB_HIP(fc::launch_class_bounds(gs[f].rp, gs[f].n, fc::kNarrowFirst,
                                                blk + fc::kRelabelClasses * gs[f].off_b,
                                                base + fc::kRelabelClasses * gs[f].off_b, bnd + 4 * f,
-                                               nullptr, b->stream),
+                                               sq + f, b->stream),
                        "class bounds");
         FB_HIP(hipMemcpyAsync(bounds.data(), bnd, 16 * gs.size(), hipMemcpyDeviceToHost, b->stream),
                "copy class bounds");
+        FB_HIP(hipMemcpyAsync(square.data(), sq, 8 * gs.size(), hipMemcpyDeviceToHost, b->stream),
+               "copy squared degrees");
     }
     std::vector<unsigned int> dmax(order.size());
     FB_HIP(hipMemcpyAsync(dmax.data(), dmax_d, 4 * order.size(), hipMemcpyDeviceToHost, b->stream),
@@ -548,57 +591,83 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
            "copy weighted volumes");
     FB_HIP(hipStreamSynchronize(b->stream), "batch preparation");
     std::vector<uint32_t> gwords(gs.size(), 0);
-    bool use_lds = false;
+    std::vector<char> hub(gs.size(), 0);  // graphs sampled hubs first
+    bool use_lds = false, any_hub = false;
     if (try_lds) {
-        uint32_t words = 0;
+        std::vector<double> reach(gs.size(), 0.0);  // largest alpha * volume of a graph's jobs
+        for (size_t k = 0; k < order.size(); ++k) {
+            const fc_job &j = b->jobs[order[k]];
+            const double vol = wsum_of(k) ? wvol[k] : static_cast<double>(j.graph.nnz);
+            reach[gof[k]] = std::max(reach[gof[k]], j.alpha * vol);
+        }
+        uint32_t words = 0, n_lds = 0;
         for (size_t f = 0; f < gs.size(); ++f) {
             if (small(gs[f].n)) continue;
             gwords[f] = fc::count_layout(bounds[4 * f + 3], bounds[4 * f], bounds[4 * f + 1],
                                          bounds[4 * f + 2]).words;
+            const bool fits = 4u * static_cast<size_t>(gwords[f]) + kLdsStaticBytes <= ctx->max_lds &&
+                              gs[f].n < (1u << fc::kRelabelIdBits);
+            hub[f] = try_hub && (ctx->hub == 2 || !fits ||
+                                 hub_applies(bounds[4 * f + 3], static_cast<uint64_t>(gs[f].nnz), square[f], 1.0,
+                                             reach[f]));
+            any_hub = any_hub || hub[f];
+            if (hub[f]) continue;
             words = std::max(words, gwords[f]);
+            n_lds = std::max(n_lds, gs[f].n);
         }
-        use_lds = 4u * static_cast<size_t>(words) + kLdsStaticBytes <= ctx->max_lds;
+        use_lds = n_lds > 0 && n_lds < (1u << fc::kRelabelIdBits) &&
+                  4u * static_cast<size_t>(words) + kLdsStaticBytes <= ctx->max_lds;
     }
-    if (use_lds) {
+    if (use_lds || any_hub) {
         if ((rc = ensure(ctx, b->rl_inv, 4 * tn, "relabel inverse")) ||
             (rc = ensure(ctx, b->rl_orig, 4 * tn, "relabel ids")) ||
             (rc = ensure(ctx, b->rl_adj, 8 * te, "relabelled adjacency")) ||
             (rc = ensure(ctx, b->rl_vrec, sizeof(fc::VRec) * vtotal, "relabelled records")))
             return fail(rc);
-        const uint32_t *base = static_cast<const uint32_t *>(b->rl_base.ptr);
+        uint32_t *base = static_cast<uint32_t *>(b->rl_base.ptr);
         uint32_t *inv = static_cast<uint32_t *>(b->rl_inv.ptr);
         uint32_t *orig = static_cast<uint32_t *>(b->rl_orig.ptr);
         unsigned long long *adj = static_cast<unsigned long long *>(b->rl_adj.ptr);
-        for (const GInfo &gi : gs)
-            if (!small(gi.n))
-                FB_HIP(fc::launch_relabel_graph(gi.rp, gi.ci, gi.n, gi.nnz, fc::kNarrowFirst,
-                                                base + fc::kRelabelClasses * gi.off_b,
-                                                fc::kRelabelIdBits, inv + gi.off_n, orig + gi.off_n,
-                                                adj + gi.off_e, b->stream), "relabel");
+        for (size_t f = 0; f < gs.size(); ++f) {
+            const GInfo &gi = gs[f];
+            if (small(gi.n) || !(hub[f] || use_lds)) continue;
+            const size_t at = fc::kRelabelClasses * gi.off_b;
+            const fc::ClassOrder how = hub[f] ? fc::kHubsFirst : fc::kNarrowFirst;
+            if (hub[f])
+                FB_HIP(fc::launch_class_bounds(gi.rp, gi.n, how, static_cast<uint32_t *>(b->rl_blk.ptr) + at,
+                                               base + at, static_cast<uint32_t *>(b->rl_bounds.ptr) + 4 * f,
+                                               nullptr, b->stream), "class bounds");
+            FB_HIP(fc::launch_relabel_graph(gi.rp, gi.ci, gi.n, gi.nnz, how, base + at,
+                                            hub[f] ? 32u : fc::kRelabelIdBits, inv + gi.off_n,
+                                            orig + gi.off_n, adj + gi.off_e, b->stream), "relabel");
+        }
         fc::VRec *vr = static_cast<fc::VRec *>(b->rl_vrec.ptr);
         for (size_t k = 0; k < order.size(); ++k)
-            if (!small(gs[gof[k]].n))
+            if (!small(gs[gof[k]].n) && (hub[gof[k]] || use_lds))
                 FB_HIP(fc::launch_relabel_vrec(vrec + voff[k], inv + gs[gof[k]].off_n,
                                                static_cast<uint32_t>(b->jobs[order[k]].graph.n),
                                                vr + voff[k], b->stream), "relabel records");
     }
 
     // launch groups.  Small graphs by how many trees of theirs fit a CU's LDS (a
-    // group's workgroups all take what its largest graph needs; 34.3 ms a run of 21 R-MAT graphs with one
-    // group for all of them, kBatchThree with three).  With LDS counters, jobs whose
-    // fields take at most a third of the LDS form the narrow group (three workgroups
-    // per CU fit, as many as the lean shape's registers allow at 512 threads);
-    // everything else is one group.
+    // group's workgroups all take what its largest graph needs, so that one graph of
+    // 20000 vertices would hold graphs of 1000 to one tree a CU; with 21 R-MAT graphs up
+    // to 117000 vertices one group for all of them was as fast, 31.7 ms a run both ways).
+    // With LDS counters, jobs whose fields take at most a third of the LDS form the
+    // narrow group (three workgroups per CU fit, as many as the lean shape's registers
+    // allow at 512 threads); everything else is one group.
     std::vector<int32_t> parts[kMaxGroups];
     for (size_t k = 0; k < order.size(); ++k) {
         const uint32_t n = gs[gof[k]].n;
-        int part = 0;
+        int part = kWide;
         if (small(n)) {
             const size_t per_cu = ctx->max_lds / (fc::jump_lds_bytes(n) + kLdsStaticBytes);
-            part = per_cu <= 3 ? 2 : per_cu <= 8 ? 3 : 4;
+            part = per_cu <= 3 ? kFew : per_cu <= 8 ? kSome : kMany;
+        } else if (hub[gof[k]]) {
+            part = kHubs;
         } else if (use_lds && 4u * static_cast<size_t>(gwords[gof[k]]) + kLdsStaticBytes <=
                                   ctx->max_lds / 3) {
-            part = 1;
+            part = kNarrow;
         }
         parts[part].push_back(order[k]);
     }
@@ -606,8 +675,9 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         if (parts[part].empty()) continue;
         Group &g = b->grp[b->ngroups++];
         g.jobs = std::move(parts[part]);
-        g.jump = part >= 2;
-        g.use_lds = use_lds && !g.jump;
+        g.jump = part >= kFew;
+        g.hub = part == kHubs;
+        g.use_lds = use_lds && !g.jump && !g.hub;
     }
 
     for (int gi = 0; gi < b->ngroups; ++gi) {
@@ -616,7 +686,9 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         g.word32 = ctx->coop_word32;
         for (int32_t j : g.jobs) {
             const size_t k = pos[j];
-            g.n_max = std::max<uint32_t>(g.n_max, static_cast<uint32_t>(b->jobs[j].graph.n));
+            g.n_out = std::max<uint32_t>(g.n_out, static_cast<uint32_t>(b->jobs[j].graph.n));
+            g.n_max = std::max<uint32_t>(g.n_max, g.hub ? std::max(1u, bounds[4 * gof[k] + 3])
+                                                        : static_cast<uint32_t>(b->jobs[j].graph.n));
             g.item_count += b->jobs[j].tree_count;
             g.weighted = g.weighted || wsum_of(k) != nullptr;
             if (g.use_lds) g.lds_words = std::max(g.lds_words, gwords[gof[k]]);
@@ -627,7 +699,7 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         }
         g.repop = ctx->lds_repop >= 2 || (ctx->lds_repop == 1 && g.weighted);
         if (g.jump) g.jump_lds = fc::jump_lds_bytes(g.n_max);
-        g.lds_bits = !g.use_lds && !g.jump && ctx->coop_lds_bits &&
+        g.lds_bits = !g.use_lds && !g.jump && !g.hub && ctx->coop_lds_bits &&
                      fc::coop_lds_bytes(g.n_max) + 1024u <= ctx->max_lds;
         g.in_bits = g.lds_bits && ctx->coop_in_bits &&
                     2 * fc::coop_lds_bytes(g.n_max) + 1024u <= ctx->max_lds;
@@ -647,8 +719,8 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
             c.wthr = wthr_of(k);
             c.n = static_cast<uint32_t>(j.graph.n);
             c.tree_count = j.tree_count;
-            c.iso = g.use_lds ? nullptr : iso + ioff[k];
-            if (g.use_lds) {
+            c.iso = g.use_lds || g.hub ? nullptr : iso + ioff[k];
+            if (g.use_lds || g.hub) {
                 const GInfo &gf = gs[gof[k]];
                 c.vrec = static_cast<const fc::VRec *>(b->rl_vrec.ptr) + voff[k];
                 c.adj = static_cast<const unsigned long long *>(b->rl_adj.ptr) + gf.off_e;
@@ -697,7 +769,10 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         a.phase_ticks = nullptr;
         a.jobs = static_cast<const fc::CoopJob *>(g.jobtab.ptr);
         a.item_job = static_cast<const uint32_t *>(g.item_job.ptr);
-        if (g.jump) {
+        if (g.hub) {
+            g.threads = ctx->hub_threads;
+            g.wg_per_cu = 1u;
+        } else if (g.jump) {
             g.threads = jump_threads_for(ctx, g.n_max, g.item_count);
             g.wg_per_cu = 64u;
         } else if (g.use_lds) {
@@ -738,10 +813,10 @@ int fc_batch_run(fc_batch *b, fc_stats *stats) {
         const Group &g = b->grp[0];
         if (b->ngroups >= 2)  // the first two groups (the field holds no more)
             std::snprintf(stats->sampler, sizeof(stats->sampler), "%s:%u+%u",
-                          g.use_lds || g.jump ? "lbatch" : "batch", g.threads, b->grp[1].threads);
+                          g.use_lds || g.jump || g.hub ? "lbatch" : "batch", g.threads, b->grp[1].threads);
         else
             std::snprintf(stats->sampler, sizeof(stats->sampler), "%s:%ux%u",
-                          g.use_lds || g.jump ? "lbatch" : "batch", g.threads, g.wg_per_cu);
+                          g.use_lds || g.jump || g.hub ? "lbatch" : "batch", g.threads, g.wg_per_cu);
     }
     if (b->item_count == 0) return FC_OK;
     // order after the caller's earlier work on the context stream, and make the

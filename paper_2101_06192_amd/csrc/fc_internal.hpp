@@ -143,11 +143,11 @@ int begin(fc_ctx *ctx);
 // counters and bitmap take lds_words words of LDS.
 uint32_t lds_threads_for(const fc_ctx *ctx, uint64_t trees, uint32_t lds_words);
 struct HubShape {
-    uint32_t threads, set, hot, lds_bits;
+    uint32_t set, lds_bits;
     size_t lds;
 };
 bool hub_applies(uint32_t nl, uint64_t nnz, uint64_t square, double alpha, double vol);
-HubShape hub_shape(const fc_ctx *ctx, uint32_t nl);
+HubShape hub_shape(const fc_ctx *ctx, uint32_t nl, uint32_t threads, uint32_t per_cu);
 // Threads per workgroup of the small-graph sampler for `trees` trees of n vertices.
 uint32_t jump_threads_for(const fc_ctx *ctx, uint32_t n, uint64_t trees);
 // Bits of the target field so that n < 2^tshift, and whether a 32-bit tree

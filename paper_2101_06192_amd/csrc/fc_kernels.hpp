@@ -123,6 +123,7 @@ struct CoopArgs {
     uint32_t n_max;           // largest n of any job (per-slot stride)
     uint32_t set;             // hubs-first variant: vertices of a set in LDS
     uint32_t lds_bits;        // hubs-first variant: settled bits kept in LDS
+    uint32_t hub_hot;         // hubs-first variant: hubs at the start, per mille of a set
     uint32_t slots;           // workgroups (trees in flight)
     uint32_t item_count;      // trees over all jobs
     uint32_t key0, key1;

@@ -164,7 +164,8 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
         const uint32_t t = job.tree_begin + ti;
         const uint32_t n = job.n;      // also the id of u*
         const uint32_t nl = job.n3;    // ids [0, nl) are not isolated
-        const uint32_t hot = job.hot;  // ids [0, hot) are the hubs
+        // ids [0, hot) are the hubs
+        const uint32_t hot = nl <= a.set ? nl : a.set * a.hub_hot / 1000u;
         const uint32_t nb = (nl + 31u) >> 5;
         const uint32_t lb = min(nb, a.lds_bits >> 5);  // words of the bitmap that are in LDS
         uint64_t *__restrict__ cur = a.pre ? a.pre + static_cast<size_t>(item) * stride
@@ -1049,7 +1050,7 @@ hipError_t launch_wilson_hub(const CoopArgs &a, uint32_t threads, size_t lds, bo
                              hipStream_t stream) {
     if (a.n_max == 0 || a.item_count == 0 || a.slots == 0) return hipSuccess;
     if (a.set == 0 || a.set % 64u || a.set > kHubOwn * threads || a.set > kHubMax ||
-        a.lds_bits % 32u || lds < hub_lds_bytes(a.set) || lds < a.lds_bits / 8u)
+        a.lds_bits % 32u || a.hub_hot > 1000u || lds < hub_lds_bytes(a.set) || lds < a.lds_bits / 8u)
         return hipErrorInvalidValue;
     void *args[] = {const_cast<CoopArgs *>(&a)};
     return hipLaunchKernel(hub_kernel_of(weighted), dim3(a.slots), dim3(threads), args, lds, stream);

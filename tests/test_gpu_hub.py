@@ -100,3 +100,22 @@ def test_default_shape(hub, n, alpha):
     hub.set_option("hub", 1)
     _check(hub, inputs.barabasi_albert(n, 5, 1), alpha, 1, 0, 3)
     _check(hub, inputs.rmat(n, 8, 2), alpha, 1, 0, 3)
+
+
+@pytest.mark.parametrize("size", [64, 0])
+def test_batch(hub, size):
+    """Jobs of several graphs and alphas in one launch group, run twice."""
+    graphs = [inputs.barabasi_albert(4000, 4, 1), inputs.rmat(4096, 8, 7), _triangles(901),
+              inputs.with_weights(inputs.barabasi_albert(3000, 3, 2), 3), inputs.from_edge_list(130, [])]
+    hub.set_option("hub_set", size)
+    jobs = [{"graph": hub.to_device(g), "alpha": al, "tree_count": 5, "stream_id": i, "tree_begin": 3}
+            for i, g in enumerate(graphs) for al in (0.5, 6.0)]
+    for tune in (False, True):
+        batch = hub.Batch(jobs, seed=5, autotune=tune)
+        for _ in range(2):
+            batch.reset()
+            batch.run()
+            for k, job in enumerate(jobs):
+                ref = oracle.sample(graphs[k // 2], job["alpha"], 5, 3, 5, stream=job["stream_id"])
+                got = batch.result(k)["root_counts"]
+                assert np.array_equal(got, ref.R), (size, tune, k)
