@@ -151,6 +151,24 @@ int check_outcome(fc_ctx *ctx, const fc::GraphCheck &found) {
     return set_err(ctx, FC_ERR_GRAPH, m);
 }
 
+// The checks of a graph, before anything else is enqueued for it.
+int check_graph(fc_ctx *ctx, GraphView *v) {
+    // both passes are enqueued together (the second does nothing once the
+    // first has found bad row offsets) and read back once
+    fc::GraphCheck *gc = &static_cast<Small *>(ctx->small.ptr)->check;
+    FC_HIP(ctx, hipMemsetAsync(gc, 0, sizeof(*gc), ctx->stream), "memset");
+    FC_HIP(ctx, fc::launch_validate_rows(v->row_ptr, v->n, v->nnz, &gc->err, ctx->stream),
+           "validate_rows launch");
+    FC_HIP(ctx, fc::launch_validate_cols(v->row_ptr, v->col_idx, v->weights, v->n, v->nnz, &gc->err,
+                                         &gc->sym_diff, ctx->stream),
+           "validate_cols launch");
+    FC_HIP(ctx, hipMemcpyAsync(&ctx->host_small->check, gc, sizeof(*gc), hipMemcpyDeviceToHost,
+                               ctx->stream), "copy error word");
+    FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "graph checks");
+    v->pending = false;
+    return check_outcome(ctx, ctx->host_small->check);
+}
+
 int prepare_graph(fc_ctx *ctx, const fc_graph *g, bool trusted, GraphView *out, bool defer) {
     int rc = check_graph_args(ctx, g);
     if (rc) return rc;
@@ -186,26 +204,8 @@ int prepare_graph(fc_ctx *ctx, const fc_graph *g, bool trusted, GraphView *out, 
         v.weights = g->nnz ? g->weights : nullptr;
     }
     if (!trusted) {
-        // both passes are enqueued together (the second does nothing once the
-        // first has found bad row offsets) and read back once
-        Small *sm = static_cast<Small *>(ctx->small.ptr);
-        fc::GraphCheck *gc = &sm->check;
-        if (defer) FC_HIP(ctx, hipMemsetAsync(sm, 0, sizeof(Small), ctx->stream), "memset counters");
-        else FC_HIP(ctx, hipMemsetAsync(gc, 0, sizeof(*gc), ctx->stream), "memset");
-        FC_HIP(ctx, fc::launch_validate_rows(v.row_ptr, v.n, v.nnz, &gc->err, ctx->stream),
-               "validate_rows launch");
-        FC_HIP(ctx, fc::launch_validate_cols(v.row_ptr, v.col_idx, v.weights, v.n, v.nnz, &gc->err,
-                                             &gc->sym_diff, ctx->stream),
-               "validate_cols launch");
-        if (defer) {
-            v.pending = true;
-        } else {
-            FC_HIP(ctx, hipMemcpyAsync(&ctx->host_small->check, gc, sizeof(*gc),
-                                       hipMemcpyDeviceToHost, ctx->stream),
-                   "copy error word");
-            FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "graph checks");
-            if ((rc = check_outcome(ctx, ctx->host_small->check))) return rc;
-        }
+        v.pending = true;
+        if (!defer && (rc = check_graph(ctx, &v))) return rc;
     }
     *out = v;
     return FC_OK;
@@ -375,8 +375,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     int rc;
     Small *sm = static_cast<Small *>(ctx->small.ptr);
     const fc::GraphCheck *check = g.pending ? &sm->check : nullptr;
-    if (!g.pending)
-        FC_HIP(ctx, hipMemsetAsync(sm, 0, sizeof(Small), ctx->stream), "memset counters");
+    FC_HIP(ctx, hipMemsetAsync(sm, 0, sizeof(Small), ctx->stream), "memset counters");
     if (stats) {
         stats->tau = tree_count;
         stats->trees_in_flight = 0;
@@ -385,11 +384,8 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         stats->sampler[0] = 0;
     }
     if (g.n == 0 || tree_count == 0) {
-        if (!g.pending) return FC_OK;
-        FC_HIP(ctx, hipMemcpyAsync(&ctx->host_small->check, check, sizeof(*check),
-                                   hipMemcpyDeviceToHost, ctx->stream), "copy error word");
-        FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "graph checks");
-        return check_outcome(ctx, ctx->host_small->check);
+        GraphView only = g;
+        return g.pending ? check_graph(ctx, &only) : FC_OK;
     }
     if ((rc = ensure(ctx, ctx->vrec, sizeof(fc::VRec) * static_cast<size_t>(g.n), "vertex records")))
         return rc;
@@ -401,10 +397,25 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     if ((rc = weight_tables(ctx, g, ctx->wsum, ctx->wthr, &wsum, &wthr))) return rc;
     const bool weighted = wsum != nullptr;
     const bool repop = ctx->lds_repop >= 2 || (ctx->lds_repop == 1 && weighted);
-    FC_HIP(ctx, fc::launch_build_vrec(g.row_ptr, wsum, g.n, p->alpha, vrec, &sm->dmax,
-                                      static_cast<uint32_t *>(ctx->iso.ptr), &sm->wtotal, check,
-                                      est ? root_counts : nullptr, ctx->stream),
-           "build_vrec");
+    uint32_t *counts_out = nullptr;
+    if (g.pending) {
+        // the caller's counts are written once the checks are known to have passed
+        if (est) {
+            if ((rc = ensure(ctx, ctx->rtmp, sizeof(uint32_t) * static_cast<size_t>(g.n), "root counts")))
+                return rc;
+            uint32_t *own = static_cast<uint32_t *>(ctx->rtmp.ptr);
+            if (root_counts != own) counts_out = root_counts;
+            root_counts = own;
+        }
+        FC_HIP(ctx, fc::launch_prepare_small(g.row_ptr, g.col_idx, g.n, g.nnz, p->alpha, vrec, &sm->check,
+                                             est ? root_counts : nullptr, ctx->stream),
+               "prepare_small launch");
+    } else {
+        FC_HIP(ctx, fc::launch_build_vrec(g.row_ptr, wsum, g.n, p->alpha, vrec, &sm->dmax,
+                                          static_cast<uint32_t *>(ctx->iso.ptr), &sm->wtotal,
+                                          est ? root_counts : nullptr, ctx->stream),
+               "build_vrec");
+    }
     double vol = static_cast<double>(g.nnz);  // sum of the (weighted) degrees
     if (weighted) {
         FC_HIP(ctx, hipMemcpyAsync(&vol, &sm->wtotal, sizeof(vol), hipMemcpyDeviceToHost,
@@ -999,7 +1010,8 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     FC_HIP(ctx, hipEventRecord(ctx->ev1, ctx->stream), "event");
     if (est)
         FC_HIP(ctx, fc::launch_estimate(root_counts, g.n, tree_count, est->literal, &sm->totals, check,
-                                        est->diag, est->farness, est->closeness, ctx->stream),
+                                        est->diag, est->farness, est->closeness, counts_out,
+                                        ctx->stream),
                "estimate launch");
     // everything the host wants to know, read back once
     FC_HIP(ctx, hipMemcpyAsync(ctx->host_small, sm, sizeof(Small), hipMemcpyDeviceToHost, ctx->stream),

@@ -544,8 +544,7 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
     for (size_t k = 0; k < order.size(); ++k) {
         const fc_job &j = b->jobs[order[k]];
         FB_HIP(fc::launch_build_vrec(j.graph.row_ptr, wsum_of(k), j.graph.n, j.alpha, vrec + voff[k],
-                                     dmax_d + k, iso + ioff[k], wtot_d + k, nullptr, nullptr,
-                                     b->stream),
+                                     dmax_d + k, iso + ioff[k], wtot_d + k, nullptr, b->stream),
                "build_vrec");
     }
     // graphs whose trees fit LDS whole need no relabelling

@@ -19,6 +19,11 @@ hipError_t launch_validate_rows(const int32_t *row_ptr, int32_t n, int64_t nnz,
                                 unsigned int *err, hipStream_t stream);
 // With weights (not null) it also checks every weight's range and that it
 // equals the weight of the reverse entry.
+// Both checks and the vertex records of a graph without weights, in one launch
+// (*check is zero before; zero: n words to clear, or null).
+hipError_t launch_prepare_small(const int32_t *row_ptr, const int32_t *col_idx, int32_t n, int64_t nnz,
+                                double alpha, VRec *vrec, GraphCheck *check, uint32_t *zero,
+                                hipStream_t stream);
 hipError_t launch_validate_cols(const int32_t *row_ptr, const int32_t *col_idx,
                                 const double *weights, int32_t n, int64_t nnz, unsigned int *err,
                                 unsigned long long *sym_diff, hipStream_t stream);
@@ -44,7 +49,7 @@ hipError_t launch_row_wdeg(const int32_t *row_ptr, const double *weights, int32_
 // and the W_v are added into *wtotal (when not null; any order).
 hipError_t launch_build_vrec(const int32_t *row_ptr, const double *S, int32_t n, double alpha,
                              VRec *vrec, unsigned int *dmax, uint32_t *iso, double *wtotal,
-                             const GraphCheck *check, uint32_t *zero, hipStream_t stream);
+                             uint32_t *zero, hipStream_t stream);
 
 // thr(d), d = 0..d_max, as the device computes it (uint64, 2^32 for "always").
 hipError_t launch_thresholds(double alpha, int32_t d_max, unsigned long long *out,
@@ -326,11 +331,12 @@ hipError_t launch_fill_u64(unsigned long long *p, size_t count, unsigned long lo
 hipError_t launch_random_access(uint32_t *data, uint32_t words_pow2, uint32_t iters, bool atomics,
                                 uint32_t blocks, uint32_t *sink, hipStream_t stream);
 
-// S = sum of R (exact, uint64) into *sum (caller zeroes it).
-// diag / farness / closeness from R and S (any output may be null).
+// diag / farness / closeness from R and the sum of R in *totals (any output may be
+// null); counts: a copy of R, or null.
 hipError_t launch_estimate(const uint32_t *R, int32_t n, uint32_t tau, int literal,
                            const Totals *totals, const GraphCheck *check, double *diag,
-                           double *farness, double *closeness, hipStream_t stream);
+                           double *farness, double *closeness, uint32_t *counts,
+                           hipStream_t stream);
 
 // Block CG on (alpha L + I) X = B, row-major n x k, k <= 64.
 // Rows of more than kCgLongRow neighbours are summed in segments of kCgSegment

@@ -20,13 +20,15 @@ __global__ __launch_bounds__(256) void estimate_kernel(const uint32_t *__restric
                                                        const GraphCheck *__restrict__ check,
                                                        double *__restrict__ diag,
                                                        double *__restrict__ farness,
-                                                       double *__restrict__ closeness) {
+                                                       double *__restrict__ closeness,
+                                                       uint32_t *__restrict__ counts) {
     // (a call that failed leaves its outputs alone)
     if (failed(check) || totals->error) return;
     const int32_t v = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
     if (v >= n) return;
     const double dt = static_cast<double>(tau);
     const uint32_t r = R[v];
+    if (counts) counts[v] = r;
     if (diag) {
         double d = static_cast<double>(r) / dt;
         if (literal) {
@@ -68,10 +70,11 @@ hipError_t launch_fill_u64(unsigned long long *p, size_t count, unsigned long lo
 
 hipError_t launch_estimate(const uint32_t *R, int32_t n, uint32_t tau, int literal,
                            const Totals *totals, const GraphCheck *check, double *diag,
-                           double *farness, double *closeness, hipStream_t stream) {
+                           double *farness, double *closeness, uint32_t *counts,
+                           hipStream_t stream) {
     if (n == 0) return hipSuccess;
     estimate_kernel<<<(n + 255) / 256, 256, 0, stream>>>(R, n, tau, literal, totals, check, diag,
-                                                         farness, closeness);
+                                                         farness, closeness, counts);
     return hipGetLastError();
 }
 

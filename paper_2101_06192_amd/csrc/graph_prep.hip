@@ -12,16 +12,22 @@ namespace fc {
 
 namespace {
 
-__global__ void validate_rows_kernel(const int32_t *__restrict__ row_ptr, int32_t n, int64_t nnz,
-                                     unsigned int *err) {
-    const int64_t v = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (v > n) return;
+// Whether row offset v (of n + 1) is wrong.
+__device__ __forceinline__ bool bad_offset(const int32_t *__restrict__ row_ptr, int64_t v, int32_t n,
+                                           int64_t nnz) {
     const int64_t a = row_ptr[v];
     bool bad = a < 0 || a > nnz;
     if (v == 0) bad |= (a != 0);
     if (v == n) bad |= (a != nnz);
     if (v < n) bad |= (row_ptr[v + 1] < a);
-    if (bad) atomicOr(err, kErrGraphRowPtr);
+    return bad;
+}
+
+__global__ void validate_rows_kernel(const int32_t *__restrict__ row_ptr, int32_t n, int64_t nnz,
+                                     unsigned int *err) {
+    const int64_t v = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (v > n) return;
+    if (bad_offset(row_ptr, v, n, nnz)) atomicOr(err, kErrGraphRowPtr);
 }
 
 // Column checks, one CSR entry per lane and step (entries of a wave are
@@ -47,11 +53,14 @@ __global__ void validate_rows_kernel(const int32_t *__restrict__ row_ptr, int32_
 // search for nearly every entry, even out.
 constexpr uint32_t kColThreads = 512, kColBlocks = 1024;
 
-__global__ __launch_bounds__(kColThreads) void validate_cols_kernel(
+// kFollow: the row offsets are known to be right.  Otherwise they are cut to the
+// entries before they are followed, and what is found in a graph whose offsets are
+// wrong means nothing.
+template <bool kFollow>
+__device__ __forceinline__ void check_columns(
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx,
     const double *__restrict__ weights, int32_t n, int64_t nnz, uint32_t steps, unsigned int *err,
     unsigned long long *sym_diff) {
-    if (*err & kErrGraphRowPtr) return;  // row offsets that may not be followed
     __shared__ long long s_diff;
     if (threadIdx.x == 0) s_diff = 0;
     __syncthreads();
@@ -74,10 +83,16 @@ __global__ __launch_bounds__(kColThreads) void validate_cols_kernel(
                 e |= kErrGraphColumn;
             } else {
                 if (u == v) e |= kErrGraphSelfLoop;
-                if (j > vb && col_idx[j - 1] >= u) e |= kErrGraphOrder;
+                if (j > vb && j > 0 && col_idx[j - 1] >= u) e |= kErrGraphOrder;
                 int32_t a = row_ptr[u];
-                const int32_t end = row_ptr[u + 1];
-                const int32_t du = end - a, dv = ve - vb;
+                int32_t end = row_ptr[u + 1];
+                if (!kFollow) {
+                    const int32_t most = static_cast<int32_t>(nnz);
+                    a = a < 0 ? 0 : a > most ? most : a;
+                    end = end < a ? a : end > most ? most : end;
+                }
+                const int32_t du = end - a;
+                const int32_t dv = static_cast<int32_t>(static_cast<uint32_t>(ve) - static_cast<uint32_t>(vb));
                 down = du < dv || (du == dv && u < v);
                 up = !down && u != v;
                 double w = 0.0;
@@ -107,6 +122,14 @@ __global__ __launch_bounds__(kColThreads) void validate_cols_kernel(
     __syncthreads();
     if (threadIdx.x == 0 && s_diff)
         atomicAdd(sym_diff, static_cast<unsigned long long>(s_diff));
+}
+
+__global__ __launch_bounds__(kColThreads) void validate_cols_kernel(
+    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx,
+    const double *__restrict__ weights, int32_t n, int64_t nnz, uint32_t steps, unsigned int *err,
+    unsigned long long *sym_diff) {
+    if (*err & kErrGraphRowPtr) return;  // row offsets that may not be followed
+    check_columns<true>(row_ptr, col_idx, weights, n, nnz, steps, err, sym_diff);
 }
 
 // kColChunk consecutive entries per thread (step thresholds).
@@ -197,8 +220,7 @@ constexpr uint32_t kVrecThreads = 1024, kVrecBlocks = 256;
 __global__ __launch_bounds__(kVrecThreads) void build_vrec_kernel(
     const int32_t *__restrict__ row_ptr, const double *__restrict__ S, int32_t n, double alpha,
     VRec *__restrict__ vrec, unsigned int *dmax, uint32_t *__restrict__ iso, double *wtotal,
-    const GraphCheck *check, uint32_t *__restrict__ zero) {
-    if (failed(check)) return;
+    uint32_t *__restrict__ zero) {
     __shared__ uint32_t s_max[kVrecThreads / 64u];
     __shared__ double s_sum[kVrecThreads / 64u];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
@@ -254,6 +276,28 @@ __global__ __launch_bounds__(kVrecThreads) void build_vrec_kernel(
     if (S && wtotal && sw > 0.0) atomicAdd(wtotal, sw);
 }
 
+// The checks and the records of a small graph without weights in one launch: each
+// block takes kColThreads row offsets and vertices, and its share of the entries.
+// Between launches this small a call waits longer than it computes: with three
+// kernels a farness call on 1000 vertices, 10 K entries and 576 trees took 123 us,
+// with this one 97.  zero may be cleared before the checks are over, so it is no
+// output of the call.
+__global__ __launch_bounds__(kColThreads) void prepare_small_kernel(
+    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx, int32_t n, int64_t nnz,
+    uint32_t steps, double alpha, VRec *__restrict__ vrec, GraphCheck *check,
+    uint32_t *__restrict__ zero) {
+    const int64_t v = static_cast<int64_t>(blockIdx.x) * kColThreads + threadIdx.x;
+    if (v <= n && bad_offset(row_ptr, v, n, nnz)) atomicOr(&check->err, kErrGraphRowPtr);
+    if (v < n) {
+        const int32_t a = row_ptr[v];
+        const uint32_t d = static_cast<uint32_t>(row_ptr[v + 1]) - static_cast<uint32_t>(a);
+        const unsigned long long t = root_threshold(alpha, d);
+        vrec[v] = {a, d, static_cast<uint32_t>(t), (t >> 32) ? 1u : 0u};
+        if (zero) zero[v] = 0u;
+    }
+    if (nnz) check_columns<false>(row_ptr, col_idx, nullptr, n, nnz, steps, &check->err, &check->sym_diff);
+}
+
 __global__ void thresholds_kernel(double alpha, int32_t d_max, unsigned long long *out) {
     const int32_t d = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
     if (d > d_max) return;
@@ -273,13 +317,28 @@ hipError_t launch_validate_rows(const int32_t *row_ptr, int32_t n, int64_t nnz,
     return hipGetLastError();
 }
 
+// Up to 8 steps per wave once there are kColBlocks blocks.
+static uint32_t column_steps(int64_t nnz) {
+    const int64_t want = nnz / (static_cast<int64_t>(kColThreads) * kColBlocks);
+    return static_cast<uint32_t>(want < 1 ? 1 : want > 8 ? 8 : want);
+}
+
+hipError_t launch_prepare_small(const int32_t *row_ptr, const int32_t *col_idx, int32_t n, int64_t nnz,
+                                double alpha, VRec *vrec, GraphCheck *check, uint32_t *zero,
+                                hipStream_t stream) {
+    const uint32_t steps = column_steps(nnz);
+    const unsigned int rows = blocks_for(static_cast<int64_t>(n) + 1, kColThreads);
+    const unsigned int cols = blocks_for(nnz, static_cast<int>(kColThreads * steps));
+    prepare_small_kernel<<<rows > cols ? rows : cols, kColThreads, 0, stream>>>(
+        row_ptr, col_idx, n, nnz, steps, alpha, vrec, check, zero);
+    return hipGetLastError();
+}
+
 hipError_t launch_validate_cols(const int32_t *row_ptr, const int32_t *col_idx,
                                 const double *weights, int32_t n, int64_t nnz, unsigned int *err,
                                 unsigned long long *sym_diff, hipStream_t stream) {
     if (n == 0 || nnz == 0) return hipSuccess;
-    // up to 8 steps per wave once there are kColBlocks blocks
-    const int64_t want = nnz / (static_cast<int64_t>(kColThreads) * kColBlocks);
-    const uint32_t steps = static_cast<uint32_t>(want < 1 ? 1 : want > 8 ? 8 : want);
+    const uint32_t steps = column_steps(nnz);
     validate_cols_kernel<<<blocks_for(nnz, static_cast<int>(kColThreads * steps)), kColThreads, 0,
                            stream>>>(row_ptr, col_idx, weights, n, nnz, steps, err, sym_diff);
     return hipGetLastError();
@@ -309,11 +368,11 @@ hipError_t launch_row_wdeg(const int32_t *row_ptr, const double *weights, int32_
 
 hipError_t launch_build_vrec(const int32_t *row_ptr, const double *S, int32_t n, double alpha,
                              VRec *vrec, unsigned int *dmax, uint32_t *iso, double *wtotal,
-                             const GraphCheck *check, uint32_t *zero, hipStream_t stream) {
+                             uint32_t *zero, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     const unsigned int blocks = blocks_for(n, kVrecThreads);
     build_vrec_kernel<<<blocks < kVrecBlocks ? blocks : kVrecBlocks, kVrecThreads, 0, stream>>>(
-        row_ptr, S, n, alpha, vrec, dmax, iso, wtotal, check, zero);
+        row_ptr, S, n, alpha, vrec, dmax, iso, wtotal, zero);
     return hipGetLastError();
 }
 
