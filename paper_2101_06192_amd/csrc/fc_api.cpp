@@ -324,9 +324,11 @@ int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::V
         (rc = ensure(ctx, ctx->clists, 24u * stride * slots, "lists")) ||
         (rc = ensure(ctx, ctx->clevels, 4u * stride * slots, "in-arrow counts")) ||
         (rc = ensure(ctx, ctx->corigt, 8u * s.set * slots, "set members")) ||
-        (rc = ensure(ctx, ctx->cbits, 4u * nw * slots, "settled bitmap")))
+        (rc = ensure(ctx, ctx->cbits, 4u * nw * slots, "settled bitmap")) ||
+        (rc = ensure(ctx, ctx->crint, 4u * stride, "root counts")))
         return rc;
     FC_HIP(ctx, hipMemsetAsync(ctx->ckk.ptr, 0, 8u * stride * slots, ctx->stream), "memset draw counts");
+    FC_HIP(ctx, hipMemsetAsync(ctx->crint.ptr, 0, 4u * stride, ctx->stream), "memset root counts");
     c->word = predraw ? nullptr : ctx->cword.ptr;
     c->pre = predraw ? static_cast<uint64_t *>(ctx->cpre.ptr) : nullptr;
     c->kk = static_cast<uint64_t *>(ctx->ckk.ptr);
@@ -352,6 +354,7 @@ int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::V
     j.orig = static_cast<const uint32_t *>(ctx->rl_orig.ptr);
     j.n = un;
     j.n3 = nl;
+    j.rint = static_cast<uint32_t *>(ctx->crint.ptr);
     j.tree_count = tree_count;
     j.tshift = 32;
     j.stream_id = p->stream_id;
@@ -990,6 +993,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         }
         FC_HIP(ctx, fc::launch_wilson_hub(c, lds_threads, hub_lds, weighted, ctx->stream),
                "wilson_hub launch");
+        FC_HIP(ctx, fc::launch_hub_counts(c, 1u, c.single.n3, ctx->stream), "hub_counts launch");
     } else if (use_hyb) {
         FC_HIP(ctx, fc::launch_wilson_hyb(c, lds_threads, lds_words, ctx->stream),
                "wilson_hyb launch");
@@ -1253,7 +1257,7 @@ int fc_destroy(fc_ctx *ctx) {
                       &ctx->iso, &ctx->corigt, &ctx->cpre, &ctx->weights, &ctx->wsum, &ctx->wthr,
                       &ctx->s_wdeg, &ctx->rk_key0, &ctx->rk_key1, &ctx->rk_val0, &ctx->rk_val1,
                       &ctx->rk_hist, &ctx->rk_thist, &ctx->rk_ra, &ctx->rk_rb, &ctx->rk_s, &ctx->g_mat,
-                      &ctx->g_vec, &ctx->g_part, &ctx->g_taken, &ctx->g_scr, &ctx->t_ex, &ctx->t_tl, &ctx->t_exl,
+                      &ctx->g_vec, &ctx->g_part, &ctx->g_taken, &ctx->g_scr, &ctx->t_ex, &ctx->t_tl, &ctx->crint, &ctx->t_exl,
                       &ctx->t_ecnt, &ctx->t_pc, &ctx->t_sc, &ctx->t_bl, &ctx->t_xb})
         if (b->ptr) (void)hipFree(b->ptr);
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);

@@ -37,12 +37,12 @@ namespace {
 // device job table and item map, scratch, counters and launch shape.
 struct Group {
     std::vector<int32_t> jobs;
-    DevBuf jobtab, item_job, word, kk, lists, levels, bits, members, small, scratch_r;
+    DevBuf jobtab, item_job, word, kk, lists, levels, bits, members, rint, small, scratch_r;
     fc::CoopArgs args{};
     uint32_t n_max = 0;      // slot stride: the most vertices (hubs first: not isolated ones)
     uint32_t n_out = 0;      // the most vertices of a job
     uint32_t item_count = 0, slots = 0, threads = 512, wg_per_cu = 4;
-    size_t ntab = 0, kk_words = 0;
+    size_t ntab = 0, kk_words = 0, rint_words = 0;
     bool use_lds = false, lds_bits = false, in_bits = false, word32 = true;
     bool weighted = false;   // some job's graph carries edge weights
     bool repop = false;      // re-formed 2-cycles popped within their round (LDS kernel)
@@ -89,7 +89,7 @@ int free_batch(fc_batch *b) {
                       &b->rl_orig, &b->rl_adj, &b->rl_vrec})
         if (d->ptr) (void)hipFree(d->ptr);
     for (Group &g : b->grp)
-        for (DevBuf *d : {&g.jobtab, &g.item_job, &g.word, &g.kk, &g.lists, &g.levels, &g.bits, &g.members,
+        for (DevBuf *d : {&g.jobtab, &g.item_job, &g.word, &g.kk, &g.lists, &g.levels, &g.bits, &g.members, &g.rint,
                           &g.small, &g.scratch_r})
             if (d->ptr) (void)hipFree(d->ptr);
     for (hipEvent_t e : {b->ev_in, b->ev0, b->ev1})
@@ -111,7 +111,13 @@ hipError_t enqueue_group(const Group &g, const fc::CoopArgs &a, uint32_t threads
         return fc::launch_wilson_lds(a, threads, g.lds_words, g.weighted, g.repop, g.lean, stream);
     e = fc::launch_fill_u64(static_cast<unsigned long long *>(g.kk.ptr), g.kk_words, 0ull, stream);
     if (e != hipSuccess) return e;
-    if (g.hub) return fc::launch_wilson_hub(a, threads, g.hub_shape.lds, g.weighted, stream);
+    if (g.hub) {
+        e = fc::launch_fill_u64(static_cast<unsigned long long *>(g.rint.ptr), g.rint_words / 2, 0ull, stream);
+        if (e != hipSuccess) return e;
+        e = fc::launch_wilson_hub(a, threads, g.hub_shape.lds, g.weighted, stream);
+        if (e != hipSuccess) return e;
+        return fc::launch_hub_counts(a, static_cast<uint32_t>(g.ntab), g.n_max, stream);
+    }
     return fc::launch_wilson_coop(a, threads, g.lds_bits, g.in_bits, g.word32, g.weighted,
                                   g.repop_words, stream);
 }
@@ -703,6 +709,12 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         g.in_bits = g.lds_bits && ctx->coop_in_bits &&
                     2 * fc::coop_lds_bytes(g.n_max) + 1024u <= ctx->max_lds;
 
+        if (g.hub) {
+            for (int32_t j : g.jobs) g.rint_words += (bounds[4 * gof[pos[j]] + 3] + 1u) & ~1u;
+            g.rint_words = std::max<size_t>(g.rint_words, 2);
+            if ((rc = ensure(ctx, g.rint, 4 * g.rint_words, "batch root counts"))) return fail(rc);
+        }
+        size_t rint_at = 0;
         // job table and item -> job map
         std::vector<fc::CoopJob> tab(g.jobs.size());
         std::vector<uint32_t> item_job(g.item_count);
@@ -738,6 +750,10 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
             const double cap = 256.0 * (static_cast<double>(j.graph.n) + j.alpha * vol) + 1048576.0;
             c.step_cap = cap > 4.0e18 ? 4000000000000000000ull : static_cast<unsigned long long>(cap);
             c.root_counts = j.root_counts;
+            if (g.hub) {
+                c.rint = static_cast<uint32_t *>(g.rint.ptr) + rint_at;
+                rint_at += (c.n3 + 1u) & ~1u;
+            }
             c.tree_digests = reinterpret_cast<unsigned long long *>(j.tree_digests);
             std::fill(item_job.begin() + first, item_job.begin() + first + j.tree_count,
                       static_cast<uint32_t>(t));

@@ -38,6 +38,7 @@ struct fc_ctx {
     DevBuf rl_blk, rl_base, rl_inv, rl_orig, rl_vrec, rl_adj;     // degree-class relabelling
     DevBuf iso;                                                   // isolated-vertex bitmap
     DevBuf corigt;                                                // hybrid: target ids per slot
+    DevBuf crint;                                                 // hubs first: root counts
     DevBuf cpre;                                                  // LDS: pre-drawn tree words
     DevBuf weights, wsum, wthr;  // staged edge weights (host graphs), running row weight sums,
                                  // step thresholds

@@ -108,6 +108,7 @@ struct CoopJob {
     uint32_t pad;
     unsigned long long step_cap;  // per-tree bound on draws; exceeding it is an error
     uint32_t *root_counts;
+    uint32_t *rint;           // hubs-first variant: n3 root counts on internal ids, zero at launch
     unsigned long long *visit_counts;
     unsigned long long *tree_digests;
     unsigned long long *tree_steps;
@@ -259,6 +260,8 @@ constexpr uint32_t kHubOwn = 32;     // vertices of a set per thread, at most
 // lds: dynamic LDS bytes, at least hub_lds_bytes(a.set) and a.lds_bits / 8
 hipError_t launch_wilson_hub(const CoopArgs &a, uint32_t threads, size_t lds, bool weighted,
                              hipStream_t stream);
+// After it: every job's root_counts += rint, back on original ids (count: jobs).
+hipError_t launch_hub_counts(const CoopArgs &a, uint32_t count, uint32_t n_max, hipStream_t stream);
 // First arrow of every vertex that is not isolated in every tree of a single-job launch.
 hipError_t launch_hub_predraw(const CoopArgs &a, hipStream_t stream);
 hipError_t hub_set_limit(size_t bytes);

@@ -21,13 +21,16 @@
 //    A vertex drawn again after the stream corrects the outputs by itself.
 //
 // What bounds it: R-MAT of 2^22 vertices, alpha 1, 512 trees, two on each CU after the
-// other, 28 ms (108 ms with in-arrow counts, and 300 bytes of lists, counts and words
+// other, 25.4 ms (108 ms with in-arrow counts, and 300 bytes of lists, counts and words
 // a vertex and tree moved over memory): first arrows 6.4 ms, Philox and 8 bytes
-// written; hubs 0.9 ms, waits for one draw's loads after the other; stream 8.3 ms and
+// written; hubs 0.9 ms, waits for one draw's loads after the other; stream 5.4 ms
+// (8.3 before its loads went ahead by one step and the root counts to internal ids) and
 // list 9.4 ms, latency and bandwidth of the arrows and pairs read and written; sets
 // 1.9 ms.  130 per mille of a set are hubs at the start: with 100 the list takes longer
-// (28.4 ms), with 160 sets come close to full (26.8 ms; with 300 they are, 56 ms).
-// One workgroup a CU with the widest set: two with half of it 38 ms.
+// (+0.8 ms), with 160 sets come close to full (-0.8 ms; with 300 they are, twice the
+// time).  The list is read in id order, hubs first: backwards every other time it
+// settles less, 17.8 ms.  One workgroup a CU with the widest set: two with half of it
+// +10 ms.
 //
 // LDS in steps 1 and 4 as in wilson_tile.hip (6.4 bytes a vertex of the set); in 2 and
 // 3 the settled bits of the lowest ids, as many as fit.
@@ -40,6 +43,7 @@
 //   pc      u32  in-arrow counts of a peel
 //   vid     u32  ids of a set's members, then the same with their outcome
 //   gbits        settled bits: of the ids beyond those in LDS, and of all in step 4
+// Per job: rint, the root counts on internal ids.
 #include "fc_kernels.hpp"
 #include "fc_wave.hpp"
 
@@ -198,12 +202,12 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
         }
         // Vertex v (original id ov) drew its arrow number k anew after the stream: the
         // outputs had the one before.
-        auto correct = [&](uint32_t ov, uint64_t was, uint64_t now, uint32_t k) {
+        auto correct = [&](uint32_t v, uint32_t ov, uint64_t was, uint64_t now, uint32_t k) {
             const unsigned long long hi = static_cast<unsigned long long>(ov) << 32;
             my_digest += mix64(hi | hi32(now)) - mix64(hi | hi32(was));
             if (lo32(now) == n) {
                 ++my_roots;
-                atomicAdd(&job.root_counts[ov], 1u);
+                atomicAdd(&job.rint[v], 1u);
             }
             const size_t at = static_cast<size_t>(ti) * n + ov;
             if (job.parents) job.parents[at] = static_cast<int32_t>(hi32(now));
@@ -314,7 +318,7 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
                     }
                     const unsigned long long where = tag | (static_cast<unsigned long long>(i) << 31);
                     if (res) {
-                        correct(r[q].always_root & 0x7FFFFFFFu, was[q], now[q], k[q]);
+                        correct(v[q], r[q].always_root & 0x7FFFFFFFu, was[q], now[q], k[q]);
                         st[v[q]] = where | (k[q] + 1u);
                     } else {
                         drawn[i] = static_cast<uint8_t>(k[q] + 1u);
@@ -702,15 +706,25 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
             if (hubs) {
                 // 2. the stream: outputs, and every vertex whose target is settled
                 const bool want_k = job.visit_counts || job.tree_visits;
+                uint64_t w_ahead[kS];  // (loaded one step ahead)
+                uint32_t ov_ahead[kS];
+#pragma unroll
+                for (int q = 0; q < kS; ++q) {
+                    const uint32_t v = wave_base + q * T + lane;
+                    w_ahead[q] = v < nl ? cur[v] : 0ull;
+                    ov_ahead[q] = v < nl ? job.orig[v] : 0u;
+                }
                 for (uint32_t base = wave_base; base < nl; base += kS * T) {
                     uint64_t w[kS];
                     uint32_t ov[kS];
                     bool left[kS];
 #pragma unroll
                     for (int q = 0; q < kS; ++q) {
-                        const uint32_t v = base + q * T + lane;
-                        w[q] = v < nl ? cur[v] : 0ull;
-                        ov[q] = v < nl ? job.orig[v] : 0u;
+                        const uint32_t v = base + (kS + q) * T + lane;
+                        w[q] = w_ahead[q];
+                        ov[q] = ov_ahead[q];
+                        w_ahead[q] = v < nl ? cur[v] : 0ull;
+                        ov_ahead[q] = v < nl ? job.orig[v] : 0u;
                     }
 #pragma unroll
                     for (int q = 0; q < kS; ++q) {
@@ -724,7 +738,7 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
                             my_digest += mix64((static_cast<unsigned long long>(ov[q]) << 32) | hi32(w[q]));
                             if (to == n) {
                                 ++my_roots;
-                                atomicAdd(&job.root_counts[ov[q]], 1u);
+                                atomicAdd(&job.rint[v], 1u);
                             }
                             const size_t at = static_cast<size_t>(ti) * n + ov[q];
                             if (job.parents) job.parents[at] = static_cast<int32_t>(hi32(w[q]));
@@ -912,7 +926,7 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
                             err |= kErrVisitOverflow;
                             e[q] = pair(n, n);
                         }
-                        correct(r[q].always_root & 0x7FFFFFFFu, was[q], e[q], k[q]);
+                        correct(v[q], r[q].always_root & 0x7FFFFFFFu, was[q], e[q], k[q]);
                         cur[v[q]] = e[q];
                         st[v[q]] = tag | (k[q] + 1u);
                         e[q] = pair(v[q], lo32(e[q]));
@@ -1007,6 +1021,17 @@ __global__ __launch_bounds__(kPreThreads) void hub_predraw_kernel(CoopArgs a, ui
     }
 }
 
+// Root counts back on original ids.  The trees count them by internal id, where the
+// stream's 64 lanes add to one or two lines of memory instead of up to 64 (R-MAT of
+// 2^22 vertices, 512 trees: 27.3 ms with the counts on original ids, 25.4 so).
+__global__ __launch_bounds__(256) void hub_counts_kernel(CoopArgs a) {
+    const CoopJob job = a.jobs ? a.jobs[blockIdx.y] : a.single;
+    for (uint32_t v = blockIdx.x * 256u + threadIdx.x; v < job.n3; v += gridDim.x * 256u) {
+        const uint32_t c = job.rint[v];
+        if (c) atomicAdd(&job.root_counts[job.orig[v]], c);
+    }
+}
+
 const void *hub_kernel_of(bool weighted) {
     return weighted ? reinterpret_cast<const void *>(&wilson_hub_kernel<true>)
                     : reinterpret_cast<const void *>(&wilson_hub_kernel<false>);
@@ -1031,6 +1056,19 @@ int hub_max_active(uint32_t threads, size_t lds, bool weighted) {
                                                      static_cast<int>(threads), lds) != hipSuccess)
         return 0;
     return blocks;
+}
+
+hipError_t launch_hub_counts(const CoopArgs &a, uint32_t count, uint32_t n_max, hipStream_t stream) {
+    if (count == 0 || n_max == 0) return hipSuccess;
+    const uint32_t blocks = (n_max + 255u) / 256u;
+    const uint32_t step = 65535u;
+    for (uint32_t j = 0; j < count; j += step) {
+        CoopArgs part = a;
+        if (a.jobs) part.jobs = a.jobs + j;
+        const dim3 grid(blocks < 2048u ? blocks : 2048u, count - j < step ? count - j : step);
+        hub_counts_kernel<<<grid, 256, 0, stream>>>(part);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_hub_predraw(const CoopArgs &a, hipStream_t stream) {
