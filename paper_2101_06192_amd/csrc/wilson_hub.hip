@@ -225,6 +225,28 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
             const uint32_t w = v >> 5;
             return ((w < lb ? s_dyn[w] : gbits[w]) >> (v & 31u)) & 1u;
         };
+        // The same of several vertices, none of them left out: their words on the way
+        // together, without branches where all bits are in LDS.
+        auto settled_all = [&](const auto &v, auto &is) {
+            constexpr int kN = static_cast<int>(sizeof(v) / sizeof(v[0]));
+            uint32_t word[kN];
+            bool far = false;
+#pragma unroll
+            for (int q = 0; q < kN; ++q) {
+                const uint32_t x = min(v[q] >> 5, nb);
+                far |= x >= lb && x < nb;
+                word[q] = s_dyn[min(x, lb - 1u)];
+            }
+            if (__ballot(far)) {
+#pragma unroll
+                for (int q = 0; q < kN; ++q) {
+                    const uint32_t x = v[q] >> 5;
+                    if (x >= lb && x < nb) word[q] = gbits[x];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < kN; ++q) is[q] = v[q] >= nl || ((word[q] >> (v[q] & 31u)) & 1u);
+        };
         auto settle = [&](uint32_t v) {
             const uint32_t w = v >> 5, bit = 1u << (v & 31u);
             if (w < lb) atomicOr(&s_dyn[w], bit);
@@ -716,8 +738,8 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
                 }
                 for (uint32_t base = wave_base; base < nl; base += kS * T) {
                     uint64_t w[kS];
-                    uint32_t ov[kS];
-                    bool left[kS];
+                    uint32_t ov[kS], to[kS];
+                    bool left[kS], ends[kS];
 #pragma unroll
                     for (int q = 0; q < kS; ++q) {
                         const uint32_t v = base + (kS + q) * T + lane;
@@ -727,16 +749,16 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
                         ov_ahead[q] = v < nl ? job.orig[v] : 0u;
                     }
 #pragma unroll
+                    for (int q = 0; q < kS; ++q) to[q] = lo32(w[q]);
+                    settled_all(to, ends);
+#pragma unroll
                     for (int q = 0; q < kS; ++q) {
                         const uint32_t v0 = base + q * T, v = v0 + lane;
                         left[q] = false;
-                        bool ok = false;
                         if (v < nl) {
-                            const uint32_t to = lo32(w[q]);
-                            ok = settled(v);
-                            left[q] = !ok && !settled(to);
+                            left[q] = !ends[q] && !settled(v);
                             my_digest += mix64((static_cast<unsigned long long>(ov[q]) << 32) | hi32(w[q]));
-                            if (to == n) {
+                            if (to[q] == n) {
                                 ++my_roots;
                                 atomicAdd(&job.rint[v], 1u);
                             }
@@ -792,13 +814,19 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
                         e[q] = i < ucount ? U[i] : 0ull;
                     }
 #pragma unroll
+                    for (int q = 0; q < kR; ++q)
+                        if (stale && base + q * T + lane < ucount) e[q] = pair(lo32(e[q]), lo32(cur[lo32(e[q])]));
+                    uint32_t to[kR];
+                    bool ends[kR];
+#pragma unroll
+                    for (int q = 0; q < kR; ++q) to[q] = hi32(e[q]);
+                    settled_all(to, ends);
+#pragma unroll
                     for (int q = 0; q < kR; ++q) {
-                        left[q] = false;
-                        if (base + q * T + lane >= ucount) continue;
-                        if (stale) e[q] = pair(lo32(e[q]), lo32(cur[lo32(e[q])]));
-                        if (stale && settled(lo32(e[q]))) continue;
-                        if (settled(hi32(e[q]))) settle(lo32(e[q]));
-                        else left[q] = true;
+                        const bool in = base + q * T + lane < ucount &&
+                                        !(stale && settled(lo32(e[q])));
+                        left[q] = in && !ends[q];
+                        if (in && ends[q]) settle(lo32(e[q]));
                     }
                     wave_append_many<kR>(Unext, &s_u, nl, &s_over, e, left);
                 }
