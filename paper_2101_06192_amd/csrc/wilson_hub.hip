@@ -21,11 +21,12 @@
 //    A vertex drawn again after the stream corrects the outputs by itself.
 //
 // What bounds it: R-MAT of 2^22 vertices, alpha 1, 512 trees, two on each CU after the
-// other, 25.4 ms (108 ms with in-arrow counts, and 300 bytes of lists, counts and words
-// a vertex and tree moved over memory): first arrows 6.4 ms, Philox and 8 bytes
-// written; hubs 0.9 ms, waits for one draw's loads after the other; stream 5.4 ms
-// (8.3 before its loads went ahead by one step and the root counts to internal ids) and
-// list 9.4 ms, latency and bandwidth of the arrows and pairs read and written; sets
+// other, 20.3 ms (108 ms with in-arrow counts, and 300 bytes of lists, counts and words
+// a vertex and tree moved over memory): first arrows 3.8 ms, Philox and 8 bytes
+// written; hubs 0.9 ms, waits for one draw's loads after the other; stream 4.7 ms
+// (8.3 before its loads went ahead by one step, the root counts to internal ids and the
+// settled bits of a step were read together) and
+// list 8.2 ms (9.4 before), latency and bandwidth of the arrows and pairs read and written; sets
 // 1.9 ms.  130 per mille of a set are hubs at the start: with 100 the list takes longer
 // (+0.8 ms), with 160 sets come close to full (-0.8 ms; with 300 they are, twice the
 // time).  The list is read in id order, hubs first: backwards every other time it
@@ -1027,24 +1028,41 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
     if (err) atomicOr(&a.totals->error, err);
 }
 
-// First arrows of all trees ahead: each thread owns one vertex and draws in kPreTrees
-// trees, so its record and row are read once for them.
-constexpr uint32_t kPreTrees = 16;
+// First arrows of all trees ahead: each thread owns one vertex and draws in `trees`
+// trees, so its record and row are read once for them.  Rows of up to kPreRow entries
+// (without weights) wait in LDS, a column for each thread: drawn from memory, the 64
+// lines of a wave's draw are as many requests to the L2, which held it to 165 G draws/s
+// on R-MAT of 2^22 vertices (6.3 ms for 512 trees; with rows of 8 5.4, of 16 5.0, of 24
+// 4.4, of 32, where too few waves fit, 4.6; with 256 trees instead of 64 after a row is
+// there 3.8).
+constexpr uint32_t kPreTrees = 256, kPreBlocks = 2048;  // trees at most; blocks wanted
 constexpr uint32_t kPreThreads = 256;
+constexpr uint32_t kPreRow = 24;
 
 template <bool kWeighted>
-__global__ __launch_bounds__(kPreThreads) void hub_predraw_kernel(CoopArgs a, uint32_t groups) {
+__global__ __launch_bounds__(kPreThreads) void hub_predraw_kernel(CoopArgs a, uint32_t trees,
+                                                                  uint32_t groups) {
+    __shared__ unsigned long long s_row[kWeighted ? 1 : kPreRow][kPreThreads];
     const CoopJob &j = a.single;
     const uint32_t v = blockIdx.x * kPreThreads + threadIdx.x;
     if (v >= j.n3) return;
     const VRec r = load_vrec(j.vrec, v);
+    const bool near = !kWeighted && r.deg <= kPreRow;
+    if (near)
+        for (uint32_t i = 0; i < r.deg; ++i) s_row[i][threadIdx.x] = j.adj[r.start + static_cast<int32_t>(i)];
     for (uint32_t g = blockIdx.y; g < groups; g += gridDim.y) {
 #pragma unroll 4
-        for (uint32_t q = 0; q < kPreTrees; ++q) {
-            const uint32_t item = g * kPreTrees + q;
+        for (uint32_t q = 0; q < trees; ++q) {
+            const uint32_t item = g * trees + q;
             if (item >= a.item_count) break;
-            a.pre[static_cast<size_t>(item) * a.n_max + v] =
-                hub_draw<kWeighted>(j, r, a.key0, a.key1, 0u, j.tree_begin + item);
+            const uint32_t orig = r.always_root & 0x7FFFFFFFu;
+            const Philox4 x = philox4x32_10(orig, 0u, j.tree_begin + item, j.stream_id, a.key0, a.key1);
+            uint64_t w = pair(j.n, j.n);
+            if (!(r.always_root >> 31) && x.x0 >= r.thr) {
+                const uint32_t idx = neighbour_entry<kWeighted>(r, x.x1, j.wsum, j.wthr);
+                w = near ? s_row[idx][threadIdx.x] : j.adj[r.start + static_cast<int32_t>(idx)];
+            }
+            a.pre[static_cast<size_t>(item) * a.n_max + v] = w;
         }
     }
 }
@@ -1105,10 +1123,13 @@ hipError_t launch_hub_predraw(const CoopArgs &a, hipStream_t stream) {
     // XCD b mod 8, whose L2 keeps that tile's records and adjacency rows
     uint32_t tiles = (a.single.n3 + kPreThreads - 1) / kPreThreads;
     tiles = (tiles + 7u) & ~7u;
-    const uint32_t groups = (a.item_count + kPreTrees - 1) / kPreTrees;
+    // as many trees a block as leave enough blocks (and 16 at least)
+    uint32_t trees = static_cast<uint32_t>(static_cast<uint64_t>(a.item_count) * tiles / kPreBlocks);
+    trees = trees < 16u ? 16u : trees > kPreTrees ? kPreTrees : trees;
+    const uint32_t groups = (a.item_count - 1u) / trees + 1u;
     const dim3 grid(tiles, groups < 65535u ? groups : 65535u);
-    if (a.single.wsum) hub_predraw_kernel<true><<<grid, kPreThreads, 0, stream>>>(a, groups);
-    else hub_predraw_kernel<false><<<grid, kPreThreads, 0, stream>>>(a, groups);
+    if (a.single.wsum) hub_predraw_kernel<true><<<grid, kPreThreads, 0, stream>>>(a, trees, groups);
+    else hub_predraw_kernel<false><<<grid, kPreThreads, 0, stream>>>(a, trees, groups);
     return hipGetLastError();
 }
 
