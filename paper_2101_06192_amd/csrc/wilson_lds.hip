@@ -872,45 +872,67 @@ void wilson_lds_kernel(CoopArgs a) {
     if (err) atomicOr(&a.totals->error, err);
 }
 
-// Trees per workgroup of the pre-draw kernel (each thread owns one vertex and
-// draws its first arrow in that many trees).
-constexpr uint32_t kPreTrees = 16;
+// First arrows ahead: each thread owns one vertex and draws in `trees` trees.  Its row,
+// up to kPreRow entries, waits in LDS (a column for each thread): gathers from memory
+// are a request to the L2 for every lane (BA(200000, 5), 4096 trees: 2.59 ms, 1.98 ms
+// so; 2.07 with 256 trees at most or with 128).  A weighted row's thresholds take the
+// longer (1015 trees: 1.25 ms with 16 trees and rows from memory, 1.28 to 1.45 from LDS).
+constexpr uint32_t kPreTrees = 64, kPreBlocks = 2048;  // trees at most; blocks wanted
+constexpr uint32_t kPreTreesW = 16;                    // trees with weights
 constexpr uint32_t kPreThreads = 256;
+constexpr uint32_t kPreRow = 24;
 
-// First arrow of a weighted graph's vertex in tree t, given the first chunk
-// of its row's step thresholds (loaded once for all of the vertex's trees):
-// the same word as draw<true>(j, r, key0, key1, 0, t).
-__device__ __forceinline__ uint64_t draw_first_w(const CoopJob &j, const VRec &r,
-                                                 const uint32_t (&t0)[kWeightedScan],
-                                                 uint32_t key0, uint32_t key1, uint32_t t) {
+// First arrow of vertex r in tree t: the same word as draw<kWeighted>(j, r, key0,
+// key1, 0, t).  Of a weighted graph's vertex, t0 is the first chunk of its row's step
+// thresholds (loaded once for all of its trees); column: its row in LDS, or null.
+template <bool kWeighted>
+__device__ __forceinline__ uint64_t draw_first(const CoopJob &j, const VRec &r,
+                                               const uint32_t (&t0)[kWeightedScan],
+                                               const unsigned long long *column, uint32_t key0,
+                                               uint32_t key1, uint32_t t) {
     const uint32_t orig = r.always_root & 0x7FFFFFFFu;
     const Philox4 x = philox4x32_10(orig, 0u, t, j.stream_id, key0, key1);
     const uint64_t kbits = 1ull << kKShift;
     if ((r.always_root >> 31) || x.x0 < r.thr) return pack(j.n, j.n, 0u) | kbits;
     const uint32_t m = r.deg - 1;
-    const uint32_t idx = (x.x1 - 1u >= 0xFFFFFFFEu || m > kWeightedScan)
+    const uint32_t idx = !kWeighted ? neighbour_entry<false>(r, x.x1, j.wsum, j.wthr)
+                         : (x.x1 - 1u >= 0xFFFFFFFEu || m > kWeightedScan)
                              ? weighted_entry(j.wsum + r.start, j.wthr + r.start, r.deg, x.x1)
                              : weighted_chunk_count(t0, 0u, m, x.x1);
-    return j.adj[r.start + static_cast<int32_t>(idx)] | kbits;
+    return (column ? column[idx * kPreThreads] : j.adj[r.start + static_cast<int32_t>(idx)]) | kbits;
 }
 
 template <bool kWeighted>
-__global__ __launch_bounds__(kPreThreads) void lds_predraw_kernel(CoopArgs a, uint32_t groups) {
+__global__ __launch_bounds__(kPreThreads) void lds_predraw_kernel(CoopArgs a, uint32_t trees,
+                                                                  uint32_t groups) {
+    __shared__ unsigned long long s_row[kWeighted ? 1 : kPreRow][kPreThreads];
     const CoopJob &job = a.single;
     const uint32_t v = blockIdx.x * kPreThreads + threadIdx.x;
     if (v >= job.n3) return;
     const VRec r = load_vrec(job.vrec, v);
-    uint32_t t0[kWeightedScan];
+    uint32_t t0[kWeightedScan] = {};
     if (kWeighted) load_chunk(job.wthr + r.start, t0);  // padded table: in bounds
+    const unsigned long long *column = !kWeighted && r.deg <= kPreRow ? &s_row[0][threadIdx.x] : nullptr;
+    if (column)
+        for (uint32_t i = 0; i < r.deg; ++i)
+            s_row[i][threadIdx.x] = job.adj[r.start + static_cast<int32_t>(i)];
     for (uint32_t g = blockIdx.y; g < groups; g += gridDim.y) {
-        const uint32_t i0 = g * kPreTrees;
+        if (kWeighted) {
 #pragma unroll
-        for (uint32_t q = 0; q < kPreTrees; ++q) {
-            const uint32_t item = i0 + q;
-            if (item < a.item_count)
+            for (uint32_t q = 0; q < kPreTreesW; ++q) {
+                const uint32_t item = g * kPreTreesW + q;
+                if (item < a.item_count)
+                    a.pre[static_cast<size_t>(item) * a.n_max + v] =
+                        draw_first<kWeighted>(job, r, t0, column, a.key0, a.key1, job.tree_begin + item);
+            }
+        } else {
+#pragma unroll 4
+            for (uint32_t q = 0; q < trees; ++q) {
+                const uint32_t item = g * trees + q;
+                if (item >= a.item_count) break;
                 a.pre[static_cast<size_t>(item) * a.n_max + v] =
-                    kWeighted ? draw_first_w(job, r, t0, a.key0, a.key1, job.tree_begin + item)
-                              : draw<false>(job, r, a.key0, a.key1, 0u, job.tree_begin + item);
+                    draw_first<kWeighted>(job, r, t0, column, a.key0, a.key1, job.tree_begin + item);
+            }
         }
     }
 }
@@ -923,10 +945,13 @@ hipError_t launch_lds_predraw(const CoopArgs &a, hipStream_t stream) {
     // XCD b mod 8, whose L2 keeps that tile's records and adjacency rows
     uint32_t tiles = (a.single.n3 + kPreThreads - 1) / kPreThreads;
     tiles = (tiles + 7u) & ~7u;
-    const uint32_t groups = (a.item_count + kPreTrees - 1) / kPreTrees;
+    // as many trees a block as leave enough blocks (and 16 at least)
+    uint32_t trees = static_cast<uint32_t>(static_cast<uint64_t>(a.item_count) * tiles / kPreBlocks);
+    trees = a.single.wsum ? kPreTreesW : trees < 16u ? 16u : trees > kPreTrees ? kPreTrees : trees;
+    const uint32_t groups = (a.item_count - 1u) / trees + 1u;
     const dim3 grid(tiles, groups < 65535u ? groups : 65535u);
-    if (a.single.wsum) lds_predraw_kernel<true><<<grid, kPreThreads, 0, stream>>>(a, groups);
-    else lds_predraw_kernel<false><<<grid, kPreThreads, 0, stream>>>(a, groups);
+    if (a.single.wsum) lds_predraw_kernel<true><<<grid, kPreThreads, 0, stream>>>(a, trees, groups);
+    else lds_predraw_kernel<false><<<grid, kPreThreads, 0, stream>>>(a, trees, groups);
     return hipGetLastError();
 }
 
