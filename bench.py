@@ -68,18 +68,20 @@ PROFILE_SPECS = {
         "sources": ["wilson_lds.hip"], "labels": ["step"], "counters": True, "timeout": 240,
         "title": "BA(200000, 5) with log-uniform [0.1, 10) edge weights, alpha = 1, 4096 trees"},
     "wilson_tile_grid1000": {
-        "args": ["--config", "grid1000"], "kernels": ["tile_predraw_kernel", "wilson_tile_kernel"],
+        "args": ["--config", "grid1000"], "kernels": ["wilson_tile_kernel"],
         "sources": ["wilson_tile.hip"], "labels": ["alpha0.5", "alpha1.0", "alpha2.0"],
         "counters": True, "timeout": 240,
         "title": "1000 x 1000 grid, 12% of edges removed, alpha = 0.5, 1, 2, 1024 trees each, "
-                 "tile sampler with its pre-draw kernel"},
-    "wilson_hyb_rmat22": {
-        "args": ["--config", "rmat22", "--sampler", "hyb"], "kernels": ["wilson_hyb_kernel"],
-        "sources": ["wilson_hyb.hip"], "labels": ["step"], "counters": True, "timeout": 360,
-        "title": "R-MAT n = 2^22, edge factor 8, alpha = 1, 1024 trees, hybrid sampler"},
+                 "tile sampler"},
+    "wilson_hub_rmat22": {
+        "args": ["--config", "rmat22"], "kernels": ["hub_predraw_kernel", "wilson_hub_kernel"],
+        "sources": ["wilson_hub.hip"], "labels": ["step"], "counters": True, "timeout": 360,
+        "title": "R-MAT n = 2^22, edge factor 8, alpha = 1, 1024 trees, hubs-first sampler "
+                 "with its pre-draw kernel"},
     "wilson_lds_batch_rmat256": {
-        "args": ["--config", "rmat_batch"], "kernels": ["wilson_lds_kernel"],
-        "sources": ["wilson_lds.hip", "fc_batch.cpp"], "labels": ["run"], "counters": True,
+        "args": ["--config", "rmat_batch"], "kernels": ["wilson_hub_kernel", "wilson_jump_kernel"],
+        "sources": ["wilson_hub.hip", "wilson_jump.hip", "fc_batch.cpp"], "labels": ["run"],
+        "counters": True,
         "timeout": 420,
         "title": "256 R-MAT graphs (n log-uniform in [2^10, 2^17], edge factor 8) x alpha "
                  "{0.1, 1, 10} x 512 trees, one autotuned batch run (its launch groups)"},
@@ -289,28 +291,32 @@ def _timed(fn, steps, warmup):
     return (time.perf_counter() - t0) / steps, out
 
 
-def _phases(st):
-    """Per-phase wall time per workgroup of a workgroup sampler's call."""
-    if st["sampler"] == "wilson_lds":
+def _phases(st, hub=False):
+    """Per-phase wall time per workgroup of a workgroup sampler's call (hub: the
+    hubs-first sampler ran in the place of the one that the statistics name)."""
+    if hub:
+        names = ["first_arrows", "hubs_claims", "hubs_redraws", "hubs_jumps", "hubs_cycles",
+                 "stream", "list", "sets"]
+    elif st["sampler"] == "wilson_lds":
         names = ["first_arrows", "count_and_level0", "peel_wide", "peel_tail",
                  "sweep_and_split", "cycle_scan", "cycles", "output"]
     elif st["sampler"] == "wilson_tile":
-        names = ["tile_load", "count_and_level0", "peel_and_sweep", "cycle_pops", "tile_exits",
-                 "exit_graph", "residual", "output"]
+        names = ["first_arrows", "redraws", "jumps", "cycles", "exits_and_output", "exit_graph",
+                 "residual", "totals"]
     else:
         names = ["first_arrows", "in_arrows", "peel_level0", "peel_levels", "sweep", "redraw",
                  "output"]
     return dict(zip(names, st["phase_ms"]))
 
 
-def _kernels_ms(st):
+def _kernels_ms(st, hub=False):
     """The sampling call's kernels and their HIP-event times (the pre-draw kernel,
     when one ran, is inside ms_sample)."""
     ms = st["ms_sample"]
     pre = st.get("ms_predraw", 0.0)
-    name = f"{st['sampler']}_kernel"
+    name = "wilson_hub_kernel" if hub else f"{st['sampler']}_kernel"
     if pre > 0.0:
-        pre_name = "tile_predraw_kernel" if st["sampler"] == "wilson_tile" else "lds_predraw_kernel"
+        pre_name = "hub_predraw_kernel" if hub else "lds_predraw_kernel"
         return {pre_name: pre, name: ms - pre}
     return {name: ms}
 
@@ -319,7 +325,7 @@ def _kernels_ms(st):
 # workloads
 # --------------------------------------------------------------------------
 def leg_sampling(fc, dev, g, dg, trees, alpha, steps, warmup, sampler="auto", weighted=False,
-                 stem=None, label="step", phase=False, seed=0):
+                 stem=None, label="step", phase=False, seed=0, hub=False):
     """`steps` timed calls of farness (sample + estimate) on a resident graph."""
     stats = []
 
@@ -334,7 +340,7 @@ def leg_sampling(fc, dev, g, dg, trees, alpha, steps, warmup, sampler="auto", we
     kms = sum(s["ms_sample"] for s in timed) / len(timed)
     kernels = {}
     for s in timed:
-        for k, v in _kernels_ms(s).items():
+        for k, v in _kernels_ms(s, hub).items():
             kernels[k] = kernels.get(k, 0.0) + v / len(timed)
     alg = wilson_bytes(st["walk_steps"], g.n * trees, st["roots"], weighted)
     traffic = traffic_of(stem, label) if stem else None
@@ -345,7 +351,7 @@ def leg_sampling(fc, dev, g, dg, trees, alpha, steps, warmup, sampler="auto", we
            "roofline": roofline_hbm(alg, kms, traffic, kernels_ms=kernels,
                                     kernel=" + ".join(kernels))}
     if phase:
-        res["phase_ms_per_workgroup"] = _phases(st)
+        res["phase_ms_per_workgroup"] = _phases(st, hub)
     return res
 
 
@@ -363,6 +369,18 @@ def leg_grid(fc, inputs, dev, steps, warmup, sampler="auto", phase=False) -> dic
     return {"value": 3 * 1024 / total, "unit": "trees/s",
             "config": {"workload": "grid_1000x1000_rm0.12_alpha0.5_1_2_trees1024", "n": g.n,
                        "m": g.m}, "per_alpha": per}
+
+
+def _batch_groups(gs) -> int:
+    """Sampling launches of a run over R-MAT graphs: one hubs first, and the small
+    graphs' by how many trees of theirs fit a CU's 160 KiB of LDS."""
+    parts = set()
+    for g in gs:
+        half = (g.n + 2) & ~1
+        lds = 12 * ((g.n + 31) // 32) + 2 * (2 * half + g.n) + 1024
+        per_cu = (160 << 10) // lds
+        parts.add("hubs" if per_cu == 0 else "few" if per_cu <= 3 else "some" if per_cu <= 8 else "many")
+    return len(parts)
 
 
 def leg_batch(fc, inputs, dev, steps, warmup, side=True) -> dict:
@@ -408,10 +426,11 @@ def leg_batch(fc, inputs, dev, steps, warmup, side=True) -> dict:
                        "create_s": create_s, "create_cached_s": create_cached_s,
                        "roofline": roofline_hbm(alg, kms,
                                                 traffic_of("wilson_lds_batch_rmat256", "run"),
-                                                kernel="wilson_lds_kernel (launch groups)")},
+                                                kernel="wilson_hub_kernel + wilson_jump_kernel "
+                                                       "(launch groups)")},
            "generation_s": gen_s,
            # the launch groups of the last run are the batch's last dispatches
-           "profile_last_dispatches": 2 if "+" in st["sampler"] else 1}
+           "profile_last_dispatches": _batch_groups(gs)}
     b.close()
     if side:
         def per_job():
@@ -425,7 +444,7 @@ def leg_batch(fc, inputs, dev, steps, warmup, side=True) -> dict:
     return res
 
 
-def leg_rmat22(fc, inputs, dev, steps, warmup, samplers=("hyb",), eps=True, phase=False) -> dict:
+def leg_rmat22(fc, inputs, dev, steps, warmup, samplers=("auto",), eps=True, phase=False) -> dict:
     """R-MAT n = 2^22, edge factor 8, alpha = 1, 1024 trees; the time to an
     (eps = 0.1, delta = 0.1) estimate of diag(Omega)."""
     import torch
@@ -436,7 +455,8 @@ def leg_rmat22(fc, inputs, dev, steps, warmup, samplers=("hyb",), eps=True, phas
     per = {}
     for smp in samplers:
         per[smp] = leg_sampling(fc, dev, g, dg, 1024, 1.0, steps, warmup, smp,
-                                stem="wilson_hyb_rmat22" if smp == "hyb" else None, phase=phase)
+                                stem="wilson_hub_rmat22" if smp == "auto" else None, phase=phase,
+                                hub=smp == "auto")
     best = max(per, key=lambda k: per[k]["trees_per_s"])
     res = {"value": per[best]["trees_per_s"], "unit": "trees/s",
            "config": {"workload": "rmat_n4194304_ef8_alpha1_trees1024", "n": g.n, "m": g.m,
@@ -1043,7 +1063,7 @@ def main():
         t0 = time.perf_counter()
         extras["grid1000"] = leg_grid(fc, inputs, dev, es, 1)
         extras["rmat_batch"] = leg_batch(fc, inputs, dev, es, 1, side=not args.no_side)
-        extras["rmat22"] = leg_rmat22(fc, inputs, dev, max(1, es - 1), 1, samplers=("hyb",),
+        extras["rmat22"] = leg_rmat22(fc, inputs, dev, max(1, es - 1), 1, samplers=("auto",),
                                       eps=not args.no_eps)
         extras["ba200k_w"] = leg_weighted(fc, inputs, dev, es, 1, eps=not args.no_eps)
         extras["er1000"] = leg_er1000(fc, inputs, dev, es, 1, samplers=("auto",))
@@ -1083,7 +1103,7 @@ def other_config(args, fc, inputs, dev) -> dict:
         smp = ("lane", "coop", "lds") if args.sampler == "auto" else (args.sampler,)
         return leg_er1000(fc, inputs, dev, st, wu, smp, phase=args.phase_timing)
     if c == "rmat22":
-        smp = ("coop", "hyb") if args.sampler == "auto" else (args.sampler,)
+        smp = (args.sampler,)
         return leg_rmat22(fc, inputs, dev, st, wu, smp, eps=not args.no_eps,
                           phase=args.phase_timing)
     if c == "ba200k_w":

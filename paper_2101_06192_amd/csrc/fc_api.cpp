@@ -578,12 +578,17 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         if (try_hub && !use_tile &&
             (ctx->hub == 2 || !use_lds ||
              hub_applies(nl, static_cast<uint64_t>(g.nnz), square, p->alpha, vol))) {
-            use_hub = true;
+            // (what it needs beyond the others may be too much for a full device)
+            rc = hub_prepare(ctx, g, p, vrec, nl, tree_begin, tree_count, weighted, nb, &c, &lds_threads,
+                             &hub_lds);
+            if (rc == FC_OK) use_hub = true;
+            else if (rc != FC_ERR_NOMEM) return rc;
+            else ctx->last_error.clear();
+        }
+        if (use_hub) {
+            // reported as the sampler whose place it takes
             kname = use_lds ? "wilson_lds" : coop_bits_fit ? "wilson_coop" : "wilson_hyb";
             use_lds = false;
-            if ((rc = hub_prepare(ctx, g, p, vrec, nl, tree_begin, tree_count, weighted, nb, &c, &lds_threads,
-                                  &hub_lds)))
-                return rc;
             slots = c.slots;
             fc::CoopJob &j = c.single;
             j.col_idx = g.col_idx;
@@ -1468,10 +1473,7 @@ int fc_sample_noalloc(fc_ctx *ctx, const fc_graph *g, const fc_params *params,
     sh.lds_repop = ctx->lds_repop;
     sh.lds_lean = ctx->lds_lean;
     sh.coop_repop = ctx->coop_repop;
-    sh.hub = ctx->hub;
-    sh.hub_set = ctx->hub_set;
-    sh.hub_hot = ctx->hub_hot;
-    sh.hub_threads = ctx->hub_threads;
+    sh.hub = 0;  // its relabelled graph and sets take more of the array than the others' state
     sh.tile_size = ctx->tile_size;
     sh.tile_cross_permille = ctx->tile_cross_permille;
     sh.tile_threads = ctx->tile_threads;

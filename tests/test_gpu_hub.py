@@ -119,3 +119,17 @@ def test_batch(hub, size):
                 ref = oracle.sample(graphs[k // 2], job["alpha"], 5, 3, 5, stream=job["stream_id"])
                 got = batch.result(k)["root_counts"]
                 assert np.array_equal(got, ref.R), (size, tune, k)
+
+
+def test_noalloc_holds_what_it_held(hub):
+    """A graph whose buffers leave little of the library's static array: the hubs-first
+    sampler's would not fit it, the call takes the sampler that does."""
+    hub.set_option("hub", 1)
+    g = inputs.barabasi_albert(900_000, 1, 3)
+    ref = oracle.sample(g, 1.0, 2, 0, 2)
+    got = hub.sample_noalloc(hub.to_device(g), 1.0, seed=2, tree_count=2, want_digests=True)
+    assert np.array_equal(got["tree_digests"], ref.digests)
+    assert np.array_equal(got["root_counts"], ref.R)
+    got = hub.sample(g, 1.0, seed=2, tree_count=2, want_digests=True)
+    assert np.array_equal(got["tree_digests"], ref.digests)
+    assert np.array_equal(got["root_counts"], ref.R)
