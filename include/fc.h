@@ -102,7 +102,7 @@ extern "C" {
                                    settled bits of the highest-degree vertices in LDS, the
                                    rest in global memory */
 #define FC_FLAG_SAMPLER_TILE 64 /* force the tile sampler: the tree's cycles are popped tile by
-                                   tile (tiles of consecutive ids, counters in LDS), the
+                                   tile (tiles of consecutive ids, each whole in LDS), the
                                    cycles that cross tiles through the graph of the vertices
                                    whose arrow leaves their tile */
 /* No sampler flag: a workgroup-per-tree sampler, with LDS counters whenever
@@ -110,7 +110,11 @@ extern "C" {
  * most a tenth of the CSR entries join ids of different tiles (option
  * "tile_cross_permille"); else with global counters when the settled bitmap
  * alone fits in LDS; else the hybrid (option "coop_lds_counts" = 0: global
- * counters throughout).  The lane sampler runs
+ * counters throughout).  Two variants take the place of these, and are reported
+ * by the name of the one whose place they take: trees of up to about 25500
+ * vertices lie whole in LDS, and where the global counters or the hybrid would
+ * run, or the LDS counters on a graph whose arrows gather at few vertices, the
+ * vertices of highest degree are settled first (option "hub").  The lane sampler runs
  * only on request.  All samplers produce identical results (same trees, same
  * counts). */
 
@@ -161,8 +165,9 @@ typedef struct {
     double ms_total;         /* host wall time of the call */
     char sampler[16];        /* "wilson_lane", "wilson_coop", "wilson_lds" (workgroup sampler,
                                 counters in LDS), "wilson_hyb" (hybrid), or for a batch
-                                "batch:<threads>x<wg per CU>"
-                                ("lbatch:..." with counters in LDS) */
+                                "batch:<threads>x<wg per CU>", of several launch
+                                groups "batch:<threads of the first>+<of the second>"
+                                ("lbatch:..." unless the first has global counters) */
     double phase_ms[8];      /* workgroup sampler with option "phase_timing": average
                                 milliseconds per workgroup spent in
                                 wilson_coop: first arrows, in-arrow counting, peel
@@ -172,10 +177,17 @@ typedef struct {
                                   reverse sweep (which also lists the vertices left
                                   hanging off cycles), scan for the cycle vertices,
                                   cycle popping, output;
-                                else zeros */
+                                wilson_tile: first arrows, redraws, jumps, cycles, the
+                                  tiles' exits and outputs, exit graph, residual, totals;
+                                hubs first: first arrows (when not drawn ahead), then
+                                  of the hubs claims, redraws, jumps and cycles, the
+                                  stream over all vertices, the list of those left, its
+                                  sets;
+                                else zeros (with the option on, trees whole in LDS give
+                                way to the LDS counters) */
     double ms_predraw;       /* part of ms_sample spent drawing every tree's first arrows
-                                ahead of the LDS-counter sampler (option "predraw_mib"),
-                                else 0 */
+                                ahead of the LDS-counter or the hubs-first sampler
+                                (option "predraw_mib"), else 0 */
 } fc_stats;
 
 /* Create a context on HIP device `hip_device` that enqueues its work on
@@ -195,16 +207,18 @@ FC_API int fc_set_stream(fc_ctx *ctx, void *hip_stream);
  *   "coop_lds_counts" 1 (default): the workgroup sampler keeps every in-arrow counter of a
  *                     tree in LDS (degree-sized fields on degree-class relabelled ids) when
  *                     they and the settled bitmap fit; 0: counters in global tree words
- *   "lds_threads"     threads per workgroup of that LDS-counter variant (64..1024, multiple
- *                     of 64; 0, the default: 1024 when LDS holds at most two trees per
- *                     CU, else narrower (down to 256) as the trees per CU grow)
+ *   "lds_threads"     threads per workgroup of that LDS-counter variant, and of trees whole
+ *                     in LDS (64..1024, multiple of 64; 0, the default: 1024 when LDS
+ *                     holds at most two trees per CU, else narrower (down to 256) as the
+ *                     trees per CU grow)
  *   "lds_wg_per_cu"   cap on its resident workgroups per CU (0, the default: as many as fit)
  *   "lanes_per_wave"  active lanes per wave of the lane sampler (1..64)
  *   "max_slots"       cap on trees in flight (0 = memory bound only)
  *   "phase_timing"    1: the workgroup sampler reports per-phase times in fc_stats
  *   "hyb_hot_cap"     cap on how many (highest-degree) vertices the hybrid sampler keeps in
  *                     LDS (default 2^31 - 1: as many as fit; 0: none, all counters global)
- *   "predraw_mib"     the LDS-counter sampler draws every tree's first arrows in one
+ *   "predraw_mib"     the LDS-counter sampler (and the hubs-first one, for graphs of any size)
+ *                     draws every tree's first arrows in one
  *                     vertex-major kernel beforehand (each vertex's record and adjacency
  *                     row read once for many trees) when the graph has at least 16384
  *                     non-isolated vertices and the words of all the call's trees
@@ -229,8 +243,17 @@ FC_API int fc_set_stream(fc_ctx *ctx, void *hip_stream);
  *                     SIMD instead of four); 0 (the default) the full one.  A batch created
  *                     with FC_FLAG_AUTOTUNE times both shapes and keeps the faster (the
  *                     trees are the same either way)
+ *   "hub"             hubs-first sampler in the automatic choice: 0 never, 1 (the default)
+ *                     where a tree does not fit LDS whole, 2 also where it does and on
+ *                     every graph (to compare, and to test it on small graphs)
+ *   "hub_set"         its vertices in LDS at a time, a multiple of 64 up to 32704 (0, the
+ *                     default: as many as fit)
+ *   "hub_hot"         of these, per mille, the vertices of highest degree it starts with
+ *                     (default 130; what their arrows lead to joins them)
+ *   "hub_threads"     its threads per workgroup (64..1024, multiple of 64; default 1024)
  *   "tile_size"       tile sampler: vertices per tile, a multiple of 64 up to 32704 (0, the
- *                     default: the widest tile whose LDS arrays fit)
+ *                     default: the widest tile whose LDS arrays fit; up to 26432 is cut to
+ *                     that, more is refused by calls that force this sampler)
  *   "tile_cross_permille"  the tile sampler is picked automatically when at most this many
  *                     CSR entries per thousand join ids of different tiles (default 100)
  *   "tile_threads"    threads per workgroup of the tile sampler (64..1024, multiple of 64;
