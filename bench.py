@@ -11,7 +11,7 @@ value = trees per second over the timed steps (whole job, one GPU).
 
 The default line also carries, under "extras", the other sampling workloads
 (road-like grid at three alphas, the batch of 256 R-MAT graphs, R-MAT 2^22 on
-the hybrid sampler), each with its Wilson-model fraction of the HBM peak and,
+hubs first), each with its Wilson-model fraction of the HBM peak and,
 where a counter summary taken on the current kernel source exists under
 profiles/, its measured HBM traffic.  --config runs one workload alone;
 --take-profiles runs rocprofv3 over the committed workloads and writes the
