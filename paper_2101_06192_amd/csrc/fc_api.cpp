@@ -13,6 +13,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -106,6 +107,8 @@ int ensure(fc_ctx *ctx, DevBuf &b, size_t bytes, const char *what) {
     b.bytes = bytes;
     return FC_OK;
 }
+
+size_t small_bytes(const fc_ctx *ctx) { return ctx->arena ? offsetof(Small, ends) : sizeof(Small); }
 
 size_t state_budget_now(const fc_ctx *ctx) {
     if (!ctx->arena) return ctx->state_budget;
@@ -378,7 +381,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     int rc;
     Small *sm = static_cast<Small *>(ctx->small.ptr);
     const fc::GraphCheck *check = g.pending ? &sm->check : nullptr;
-    FC_HIP(ctx, hipMemsetAsync(sm, 0, sizeof(Small), ctx->stream), "memset counters");
+    FC_HIP(ctx, hipMemsetAsync(sm, 0, small_bytes(ctx), ctx->stream), "memset counters");
     if (stats) {
         stats->tau = tree_count;
         stats->trees_in_flight = 0;
@@ -510,16 +513,17 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
             FC_HIP(ctx, fc::launch_class_bounds(g.row_ptr, static_cast<uint32_t>(g.n), fc::kNarrowFirst,
                                                 static_cast<uint32_t *>(ctx->rl_blk.ptr),
                                                 static_cast<uint32_t *>(ctx->rl_base.ptr),
-                                                sm->class_bounds, &sm->square, ctx->stream),
+                                                sm->class_bounds, try_hub ? sm->ends : nullptr, ctx->stream),
                    "class bounds");
         }
-        FC_HIP(ctx, hipMemcpyAsync(ctx->host_small, sm, sizeof(Small), hipMemcpyDeviceToHost, ctx->stream),
+        FC_HIP(ctx, hipMemcpyAsync(ctx->host_small, sm, small_bytes(ctx), hipMemcpyDeviceToHost, ctx->stream),
                "copy degrees");
         FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "build_vrec");
         unsigned int cb[4];
         std::copy(ctx->host_small->class_bounds, ctx->host_small->class_bounds + 4, cb);
         dmax = ctx->host_small->dmax;
-        const unsigned long long square = ctx->host_small->square;
+        unsigned long long ends[fc::kDegreeBits];
+        std::copy(ctx->host_small->ends, ctx->host_small->ends + fc::kDegreeBits, ends);
         const uint32_t nl = cb[3];  // vertices that are not isolated (with try_hub or try_lds)
         if (try_lds) {
             const fc::CountLayout L = fc::count_layout(cb[3], cb[0], cb[1], cb[2]);
@@ -571,13 +575,9 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         // Automatically only where the global-counter variant cannot keep its
         // settled bitmap in LDS either (beyond that size the hybrid wins).
         const bool coop_bits_fit = fc::coop_lds_bytes(static_cast<uint32_t>(g.n)) + 1024u <= ctx->max_lds;
-        // hubs first, reported as the sampler whose place it takes: always where a tree's
-        // counters do not fit LDS (ms of 512 trees, global counters or hybrid against
-        // hubs first: BA of 400000 vertices 28.4 / 8.4, of 1.5 million 131 / 40,
-        // Erdos-Renyi of 300000 19.8 / 8.0, R-MAT of 1 million 43.2 / 5.7, of 2^22 108 / 28)
         if (try_hub && !use_tile &&
-            (ctx->hub == 2 || !use_lds ||
-             hub_applies(nl, static_cast<uint64_t>(g.nnz), square, p->alpha, vol))) {
+            (ctx->hub == 2 ||
+             hub_applies(use_lds, nl, static_cast<uint64_t>(g.nnz), ends, p->alpha * vol))) {
             // (what it needs beyond the others may be too much for a full device)
             rc = hub_prepare(ctx, g, p, vrec, nl, tree_begin, tree_count, weighted, nb, &c, &lds_threads,
                              &hub_lds);
@@ -1023,7 +1023,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
                                         ctx->stream),
                "estimate launch");
     // everything the host wants to know, read back once
-    FC_HIP(ctx, hipMemcpyAsync(ctx->host_small, sm, sizeof(Small), hipMemcpyDeviceToHost, ctx->stream),
+    FC_HIP(ctx, hipMemcpyAsync(ctx->host_small, sm, small_bytes(ctx), hipMemcpyDeviceToHost, ctx->stream),
            "copy counters");
     FC_HIP(ctx, hipStreamSynchronize(ctx->stream), "sampler");
     if (g.pending && (rc = check_outcome(ctx, ctx->host_small->check))) return rc;
@@ -1112,17 +1112,31 @@ uint32_t lds_threads_for(const fc_ctx *ctx, uint64_t trees, uint32_t lds_words) 
     return t;
 }
 
-// Whether the hubs-first sampler takes the place of the one with LDS counters: where
-// arrows gather at few vertices (the mean degree of an edge's end is at least ten
-// times that of a vertex) and are followed far (vol: the sum of the degrees).  ms of 512
-// trees, LDS counters against hubs first: R-MAT of 30000 to 250000 vertices (skew 14 to
-// 28) at alpha 10 3.8 / 1.5 to 12.6 / 2.6, at alpha 1 0.76 / 0.39 to 2.48 / 1.71, at
-// alpha 0.1 0.24 / 0.23 to 1.33 / 1.36, with edge factor 3 there 0.86 / 0.94; BA (skew
-// 3 to 4) and Erdos-Renyi (1.1) of 30000 to 110000 at alpha 1 0.49 / 0.68 to 1.75 /
-// 2.50, at alpha 10 1.29 / 1.08 to 3.21 / 3.79.
-bool hub_applies(uint32_t nl, uint64_t nnz, uint64_t square, double alpha, double vol) {
-    return static_cast<double>(square) * nl >= 10.0 * static_cast<double>(nnz) * static_cast<double>(nnz) &&
-           alpha * vol >= 2.0 * nl;
+// Whether the hubs-first sampler takes the place of the others, for a tree whose in-arrow
+// counts fit LDS (fits) or not.  share: the share of the edges' ends at hubs, rows of at
+// least four times the mean (rounded up to a power of two, as ends is); reach: alpha
+// times the sum of the (weighted) degrees, so x = reach / nl is how far arrows are
+// followed.  A walk that is at a hub one step in 1 / share is short once hubs are settled;
+// without hubs the others go over lists of the vertices again and again while arrows
+// meet cycles (ids in no order; ms of 64 trees, the other sampler against hubs first):
+//   fits: R-MAT of 30000 to 250000 vertices (share 0.46 to 0.56) at x 27 and more 0.32 /
+//   0.20 to 5.8 / 1.0, at 1.3 to 3 0.12 / 0.11 to 0.42 / 0.36, with 1.3 also 0.27 / 0.28;
+//   BA (0.09 to 0.12) of 30000 to 150000 at x 6 and Erdos-Renyi (0) 0.23 / 0.36 and so on,
+//   a path with one hub of 4% of its vertices (0.02) 0.72 / 1.22.
+//   Does not fit: lattices, rings, paths and Erdos-Renyi graphs (0) of 400000 to 1.4
+//   million at x up to 4 9.8 / 7.4 to 31 / 17, at x 6 to 8 36 / 50 and 44 / 105, at 40
+//   121 / 295; a lattice of degree 6 where one vertex in two has an edge to a hub as well
+//   (0.07) at x 35 14.9 / 13.0, BA at x 180 78 / 50, R-MAT of 2^22 at x 40 56 / 9.  Trees (BA
+//   with one edge a vertex, 0.2) at x 20 13.8 / 10.2, at 60 19 / 22; a star (0.5) at x 200 158 / 1.7.
+bool hub_applies(bool fits, uint32_t nl, uint64_t nnz, const unsigned long long *ends, double reach) {
+    uint32_t b = 0;
+    while (b + 1 < fc::kDegreeBits && (uint64_t{nl} << b) < 4 * nnz) ++b;
+    uint64_t at_hubs = 0;
+    for (; b < fc::kDegreeBits; ++b) at_hubs += ends[b];
+    const double share = static_cast<double>(at_hubs) / static_cast<double>(std::max<uint64_t>(nnz, 1));
+    const double x = reach / std::max(nl, 1u);
+    if (fits) return share >= 0.3 && x >= 2.0;
+    return x <= 4.0 || share >= 0.3 || (share >= 0.055 && (x <= 20.0 || nnz >= 3 * uint64_t{nl}));
 }
 
 // Launch shape of the hubs-first sampler for at most nl vertices that are not isolated,
@@ -1484,7 +1498,7 @@ int fc_sample_noalloc(fc_ctx *ctx, const fc_graph *g, const fc_params *params,
     sh.arena_size = kStaticScratchBytes;
     sh.arena_off = 0;
     GraphView gv;
-    if ((rc = ensure(&sh, sh.small, sizeof(Small), "counters")) ||
+    if ((rc = ensure(&sh, sh.small, small_bytes(&sh), "counters")) ||
         (rc = prepare_graph(&sh, g, params->flags & FC_FLAG_TRUSTED_GRAPH, &gv,
                             deferrable(&sh, params, g))) ||
         (rc = run_sampler(&sh, gv, params, tree_begin, tree_count, root_counts, visit_counts,

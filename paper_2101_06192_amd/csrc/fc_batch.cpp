@@ -68,7 +68,7 @@ struct fc_batch {
     int32_t flags = 0;
     DevBuf vrec, dmax, iso, wsum, wthr, wtot;  // weighted graphs' running row sums and step
                                                // thresholds, each job's weighted volume
-    DevBuf rl_blk, rl_base, rl_bounds, rl_square, rl_inv, rl_orig, rl_adj, rl_vrec;  // degree-class relabelling
+    DevBuf rl_blk, rl_base, rl_bounds, rl_ends, rl_inv, rl_orig, rl_adj, rl_vrec;  // degree-class relabelling
     Group grp[kMaxGroups];
     int ngroups = 0;
     uint32_t item_count = 0;
@@ -85,7 +85,7 @@ int free_batch(fc_batch *b) {
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
-    for (DevBuf *d : {&b->vrec, &b->dmax, &b->iso, &b->wsum, &b->wthr, &b->wtot, &b->rl_blk, &b->rl_base, &b->rl_bounds, &b->rl_square, &b->rl_inv,
+    for (DevBuf *d : {&b->vrec, &b->dmax, &b->iso, &b->wsum, &b->wthr, &b->wtot, &b->rl_blk, &b->rl_base, &b->rl_bounds, &b->rl_ends, &b->rl_inv,
                       &b->rl_orig, &b->rl_adj, &b->rl_vrec})
         if (d->ptr) (void)hipFree(d->ptr);
     for (Group &g : b->grp)
@@ -564,29 +564,29 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
     const bool try_hub = ctx->coop_lds_counts && ctx->hub && n_rest > 0;
     const bool try_lds = ctx->coop_lds_counts && n_rest > 0 && (try_hub || n_rest < (1u << fc::kRelabelIdBits));
     std::vector<unsigned int> bounds(4 * gs.size(), 0u);
-    std::vector<unsigned long long> square(gs.size(), 0ull);
+    std::vector<unsigned long long> ends(fc::kDegreeBits * gs.size(), 0ull);
     if (try_lds) {
         if ((rc = ensure(ctx, b->rl_blk, 4 * fc::kRelabelClasses * tb, "class counts")) ||
             (rc = ensure(ctx, b->rl_base, 4 * fc::kRelabelClasses * tb, "class offsets")) ||
             (rc = ensure(ctx, b->rl_bounds, 16 * gs.size(), "class bounds")) ||
-            (rc = ensure(ctx, b->rl_square, 8 * gs.size(), "squared degrees")))
+            (rc = ensure(ctx, b->rl_ends, 8 * ends.size(), "degree sums")))
             return fail(rc);
         uint32_t *blk = static_cast<uint32_t *>(b->rl_blk.ptr);
         uint32_t *base = static_cast<uint32_t *>(b->rl_base.ptr);
         uint32_t *bnd = static_cast<uint32_t *>(b->rl_bounds.ptr);
-        unsigned long long *sq = static_cast<unsigned long long *>(b->rl_square.ptr);
-        FB_HIP(hipMemsetAsync(sq, 0, 8 * gs.size(), b->stream), "memset squared degrees");
+        unsigned long long *ends_d = static_cast<unsigned long long *>(b->rl_ends.ptr);
+        FB_HIP(hipMemsetAsync(ends_d, 0, 8 * ends.size(), b->stream), "memset degree sums");
         for (size_t f = 0; f < gs.size(); ++f)
             if (!small(gs[f].n))
                 FB_HIP(fc::launch_class_bounds(gs[f].rp, gs[f].n, fc::kNarrowFirst,
                                                blk + fc::kRelabelClasses * gs[f].off_b,
                                                base + fc::kRelabelClasses * gs[f].off_b, bnd + 4 * f,
-                                               sq + f, b->stream),
+                                               ends_d + fc::kDegreeBits * f, b->stream),
                        "class bounds");
         FB_HIP(hipMemcpyAsync(bounds.data(), bnd, 16 * gs.size(), hipMemcpyDeviceToHost, b->stream),
                "copy class bounds");
-        FB_HIP(hipMemcpyAsync(square.data(), sq, 8 * gs.size(), hipMemcpyDeviceToHost, b->stream),
-               "copy squared degrees");
+        FB_HIP(hipMemcpyAsync(ends.data(), ends_d, 8 * ends.size(), hipMemcpyDeviceToHost, b->stream),
+               "copy degree sums");
     }
     std::vector<unsigned int> dmax(order.size());
     FB_HIP(hipMemcpyAsync(dmax.data(), dmax_d, 4 * order.size(), hipMemcpyDeviceToHost, b->stream),
@@ -612,9 +612,9 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
                                          bounds[4 * f + 2]).words;
             const bool fits = 4u * static_cast<size_t>(gwords[f]) + kLdsStaticBytes <= ctx->max_lds &&
                               gs[f].n < (1u << fc::kRelabelIdBits);
-            hub[f] = try_hub && (ctx->hub == 2 || !fits ||
-                                 hub_applies(bounds[4 * f + 3], static_cast<uint64_t>(gs[f].nnz), square[f], 1.0,
-                                             reach[f]));
+            hub[f] = try_hub &&
+                     (ctx->hub == 2 || hub_applies(fits, bounds[4 * f + 3], static_cast<uint64_t>(gs[f].nnz),
+                                                   &ends[fc::kDegreeBits * f], reach[f]));
             any_hub = any_hub || hub[f];
             if (hub[f]) continue;
             words = std::max(words, gwords[f]);

@@ -24,8 +24,9 @@ struct Small {  // device-side counters of one call
     unsigned int pad;
     unsigned long long phase_ticks[8];
     unsigned int class_bounds[4];  // n0, n1, n2, n3 of the degree-class relabelling
-    unsigned long long square;     // sum of the squared degrees
     double wtotal;                 // sum of the weighted degrees (weighted graphs)
+    // (last: left out of a call on a caller's array, which asks for none of it)
+    unsigned long long ends[fc::kDegreeBits];  // sums of the degrees, by their highest bit
 };
 
 struct fc_ctx {
@@ -111,6 +112,8 @@ int hip_fail(fc_ctx *ctx, hipError_t e, const char *what);
 // Grow-only device buffer: (re)allocates when `bytes` exceeds its size; in
 // arena mode carves it from the context's arena instead (never allocates).
 int ensure(fc_ctx *ctx, DevBuf &b, size_t bytes, const char *what);
+// Bytes of Small that a context's calls use.
+size_t small_bytes(const fc_ctx *ctx);
 // Bytes of per-tree state the sampler may use now: the context's budget, or
 // in arena mode what is left of the arena.
 size_t state_budget_now(const fc_ctx *ctx);
@@ -147,7 +150,7 @@ struct HubShape {
     uint32_t set, lds_bits;
     size_t lds;
 };
-bool hub_applies(uint32_t nl, uint64_t nnz, uint64_t square, double alpha, double vol);
+bool hub_applies(bool fits, uint32_t nl, uint64_t nnz, const unsigned long long *ends, double reach);
 HubShape hub_shape(const fc_ctx *ctx, uint32_t nl, uint32_t threads, uint32_t per_cu);
 // Threads per workgroup of the small-graph sampler for `trees` trees of n vertices.
 uint32_t jump_threads_for(const fc_ctx *ctx, uint32_t n, uint64_t trees);

@@ -235,10 +235,11 @@ constexpr uint32_t kRelabelClasses = 5;
 uint32_t relabel_blocks(uint32_t n);
 // The classes in the order 4-, 8-, 16-, 32-bit (kNarrowFirst), 32-, 16-, 8-, 4-bit
 // (kWidestFirst, hybrid sampler), or by degree, from 256 down (kHubsFirst); isolated
-// vertices come last in each.  *square (or null) += the squared degrees.
+// vertices come last in each.  ends[b] (or null) += the degrees from 2^b to 2^(b+1) - 1.
+constexpr uint32_t kDegreeBits = 32;
 enum ClassOrder : int { kNarrowFirst = 0, kWidestFirst, kHubsFirst };
 hipError_t launch_class_bounds(const int32_t *row_ptr, uint32_t n, ClassOrder order, uint32_t *blk,
-                               uint32_t *base, uint32_t *bounds, unsigned long long *square,
+                               uint32_t *base, uint32_t *bounds, unsigned long long *ends,
                                hipStream_t stream);
 // inv/orig permutations and relabelled adjacency of one graph (base from
 // launch_class_bounds).

@@ -29,31 +29,27 @@ __device__ __forceinline__ uint32_t deg_class(uint32_t d, ClassOrder order) {
     return d == 0u ? 4u : d <= 15u ? 0u : d <= top1 ? 1u : d <= top2 ? 2u : 3u;
 }
 
-// Per block of kPlaceThreads vertices: how many fall in each class; with square, the
-// sum of the squared degrees.
+// Per block of kPlaceThreads vertices: how many fall in each class; with ends, the sums of
+// the degrees from 2^b to 2^(b+1) - 1 (a block's fit 32 bits: row offsets do).
 __global__ __launch_bounds__(kPlaceThreads) void class_count_kernel(
     const int32_t *__restrict__ row_ptr, uint32_t n, ClassOrder order, uint32_t *__restrict__ blk,
-    unsigned long long *square) {
-    __shared__ uint32_t s[kClasses];
-    __shared__ unsigned long long s_square;
-    if (threadIdx.x == 0) s_square = 0;
+    unsigned long long *ends) {
+    __shared__ uint32_t s[kClasses], s_ends[kDegreeBits];
+    if (threadIdx.x < kDegreeBits) s_ends[threadIdx.x] = 0;
     if (threadIdx.x < kClasses) s[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t v = blockIdx.x * kPlaceThreads + threadIdx.x;
     const uint32_t d = v < n ? static_cast<uint32_t>(row_ptr[v + 1] - row_ptr[v]) : 0u;
     const uint32_t c = v < n ? deg_class(d, order) : kClasses;
-    if (square) {
-        unsigned long long sq = static_cast<unsigned long long>(d) * d;
-        for (int off = 32; off > 0; off >>= 1) sq += __shfl_down(sq, off, 64);
-        if ((threadIdx.x & 63u) == 0 && sq) atomicAdd(&s_square, sq);
-    }
+    if (ends && d) atomicAdd(&s_ends[31 - __clz(d)], d);
     for (uint32_t k = 0; k < kClasses; ++k) {
         const uint64_t m = __ballot(c == k);
         if ((threadIdx.x & 63u) == 0 && m) atomicAdd(&s[k], static_cast<uint32_t>(__popcll(m)));
     }
     __syncthreads();
     if (threadIdx.x < kClasses) blk[blockIdx.x * kClasses + threadIdx.x] = s[threadIdx.x];
-    if (threadIdx.x == 0 && s_square) atomicAdd(square, s_square);
+    if (ends && threadIdx.x < kDegreeBits && s_ends[threadIdx.x])
+        atomicAdd(&ends[threadIdx.x], static_cast<unsigned long long>(s_ends[threadIdx.x]));
 }
 
 // Rank of class c in the id order: narrowest field first (LDS sampler) or
@@ -169,11 +165,11 @@ __global__ void relabel_adj_kernel(const int32_t *__restrict__ col_idx, int64_t 
 uint32_t relabel_blocks(uint32_t n) { return (n + kPlaceThreads - 1) / kPlaceThreads; }
 
 hipError_t launch_class_bounds(const int32_t *row_ptr, uint32_t n, ClassOrder order, uint32_t *blk,
-                               uint32_t *base, uint32_t *bounds, unsigned long long *square,
+                               uint32_t *base, uint32_t *bounds, unsigned long long *ends,
                                hipStream_t stream) {
     const uint32_t nb = relabel_blocks(n);
     if (nb == 0) return hipSuccess;
-    class_count_kernel<<<nb, kPlaceThreads, 0, stream>>>(row_ptr, n, order, blk, square);
+    class_count_kernel<<<nb, kPlaceThreads, 0, stream>>>(row_ptr, n, order, blk, ends);
     class_scan_kernel<<<1, kScanThreads, 0, stream>>>(blk, nb, order, base, bounds);
     return hipGetLastError();
 }

@@ -133,3 +133,23 @@ def test_noalloc_holds_what_it_held(hub):
     got = hub.sample(g, 1.0, seed=2, tree_count=2, want_digests=True)
     assert np.array_equal(got["tree_digests"], ref.digests)
     assert np.array_equal(got["root_counts"], ref.R)
+
+
+@pytest.mark.parametrize("name,below,above", [("grid", 1.0, 1.3), ("tree", 9.0, 12.0), ("rmat", 0.05, 5.0)])
+def test_both_sides_of_the_rule(hub, name, below, above):
+    """Graphs whose in-arrow counts do not fit LDS, where the automatic choice changes from
+    hubs first to the other sampler (no hubs; few edges) and where it does not."""
+    hub.set_option("hub", 1)
+    g = {"grid": lambda: inputs.grid_removed(600, 700, 0.12, 3),
+         "tree": lambda: inputs.barabasi_albert(400_000, 1, 1),
+         "rmat": lambda: inputs.rmat(700_000, 8, 2)}[name]()
+    d = hub.to_device(g)
+    for alpha in (below, above):
+        ref = oracle.sample(g, alpha, 6, 0, 2, per_tree=True)
+        got = hub.sample(g, alpha=alpha, seed=6, tree_count=2, want_digests=True)
+        assert np.array_equal(got["tree_digests"], ref.digests)
+        assert np.array_equal(got["root_counts"], ref.R)
+    batch = hub.Batch([{"graph": d, "alpha": al, "tree_count": 2} for al in (below, above)], seed=6)
+    batch.run()
+    for k, alpha in enumerate((below, above)):
+        assert np.array_equal(batch.result(k)["root_counts"], oracle.sample(g, alpha, 6, 0, 2).R)
