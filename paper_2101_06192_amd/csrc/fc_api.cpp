@@ -1004,7 +1004,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
                "wilson_hyb launch");
     } else if (use_lds) {
         if (c.pre) {
-            FC_HIP(ctx, fc::launch_lds_predraw(c, ctx->stream), "lds_predraw launch");
+            FC_HIP(ctx, fc::launch_lds_predraw(c, g.nnz, ctx->stream), "lds_predraw launch");
             FC_HIP(ctx, hipEventRecord(ctx->evm, ctx->stream), "event");
         }
         FC_HIP(ctx, fc::launch_wilson_lds(c, lds_threads, lds_words, weighted, repop, lds_lean,

@@ -175,7 +175,7 @@ hipError_t lds_set_limit(size_t bytes);  // as coop_set_lds_limit, for the LDS-c
 // launch (a.single, items [0, a.item_count)): a.pre[item * a.n_max + v] = the
 // tree word the LDS kernel's first round would write.  Vertex-major, so the
 // relabelled records and adjacency are read once per vertex tile for many trees.
-hipError_t launch_lds_predraw(const CoopArgs &a, hipStream_t stream);
+hipError_t launch_lds_predraw(const CoopArgs &a, int64_t nnz, hipStream_t stream);
 int lds_max_active(uint32_t threads, uint32_t lds_words, bool weighted, bool repop, bool lean);
 
 // Small-graph variant: the whole tree in LDS, paths followed by pointer jumping.

@@ -875,12 +875,19 @@ void wilson_lds_kernel(CoopArgs a) {
 // First arrows ahead: each thread owns one vertex and draws in `trees` trees.  Its row,
 // up to kPreRow entries, waits in LDS (a column for each thread): gathers from memory
 // are a request to the L2 for every lane (BA(200000, 5), 4096 trees: 2.59 ms, 1.98 ms
-// so; 2.07 with 256 trees at most or with 128).  A weighted row's thresholds take the
+// so; 2.07 with 256 trees at most or with 128).  A weighted row's thresholds take
 // longer (1015 trees: 1.25 ms with 16 trees and rows from memory, 1.28 to 1.45 from LDS).
+// Below kPreRowNnz entries the rows stay in the L2s (a tile's in its XCD's, see below),
+// and loading them anew for more trees is what costs: 16 trees, rows from memory (512
+// trees of a path with a hub, 100000 vertices: 0.092 ms, from LDS 0.109; Erdos-Renyi of
+// 70000, degree 8, 0.073 and 0.083; BA(110000, 5), 1.1 million entries, 0.131 and 0.135,
+// 4096 trees 1.10 and 0.97).  Rows of up to 24 entries in LDS leave a CU fewer blocks:
+// there 0.145 and 1.01 ms.
 constexpr uint32_t kPreTrees = 64, kPreBlocks = 2048;  // trees at most; blocks wanted
-constexpr uint32_t kPreTreesW = 16;                    // trees with weights
+constexpr uint32_t kPreFew = 16;                       // trees with rows from memory
 constexpr uint32_t kPreThreads = 256;
-constexpr uint32_t kPreRow = 24;
+constexpr uint32_t kPreRow = 12;
+constexpr uint64_t kPreRowNnz = 1u << 20;
 
 // First arrow of vertex r in tree t: the same word as draw<kWeighted>(j, r, key0,
 // key1, 0, t).  Of a weighted graph's vertex, t0 is the first chunk of its row's step
@@ -902,25 +909,25 @@ __device__ __forceinline__ uint64_t draw_first(const CoopJob &j, const VRec &r,
     return (column ? column[idx * kPreThreads] : j.adj[r.start + static_cast<int32_t>(idx)]) | kbits;
 }
 
-template <bool kWeighted>
+template <bool kWeighted, bool kRows>
 __global__ __launch_bounds__(kPreThreads) void lds_predraw_kernel(CoopArgs a, uint32_t trees,
                                                                   uint32_t groups) {
-    __shared__ unsigned long long s_row[kWeighted ? 1 : kPreRow][kPreThreads];
+    __shared__ unsigned long long s_row[kRows ? kPreRow : 1u][kRows ? kPreThreads : 1u];
     const CoopJob &job = a.single;
     const uint32_t v = blockIdx.x * kPreThreads + threadIdx.x;
     if (v >= job.n3) return;
     const VRec r = load_vrec(job.vrec, v);
     uint32_t t0[kWeightedScan] = {};
     if (kWeighted) load_chunk(job.wthr + r.start, t0);  // padded table: in bounds
-    const unsigned long long *column = !kWeighted && r.deg <= kPreRow ? &s_row[0][threadIdx.x] : nullptr;
+    const unsigned long long *column = kRows && r.deg <= kPreRow ? &s_row[0][threadIdx.x] : nullptr;
     if (column)
         for (uint32_t i = 0; i < r.deg; ++i)
             s_row[i][threadIdx.x] = job.adj[r.start + static_cast<int32_t>(i)];
     for (uint32_t g = blockIdx.y; g < groups; g += gridDim.y) {
-        if (kWeighted) {
+        if (!kRows) {
 #pragma unroll
-            for (uint32_t q = 0; q < kPreTreesW; ++q) {
-                const uint32_t item = g * kPreTreesW + q;
+            for (uint32_t q = 0; q < kPreFew; ++q) {
+                const uint32_t item = g * kPreFew + q;
                 if (item < a.item_count)
                     a.pre[static_cast<size_t>(item) * a.n_max + v] =
                         draw_first<kWeighted>(job, r, t0, column, a.key0, a.key1, job.tree_begin + item);
@@ -939,19 +946,21 @@ __global__ __launch_bounds__(kPreThreads) void lds_predraw_kernel(CoopArgs a, ui
 
 }  // namespace
 
-hipError_t launch_lds_predraw(const CoopArgs &a, hipStream_t stream) {
+hipError_t launch_lds_predraw(const CoopArgs &a, int64_t nnz, hipStream_t stream) {
     if (!a.pre || a.single.n3 == 0 || a.item_count == 0) return hipSuccess;
     // vertex tiles a multiple of 8 wide: block b of every tree group then runs on
     // XCD b mod 8, whose L2 keeps that tile's records and adjacency rows
     uint32_t tiles = (a.single.n3 + kPreThreads - 1) / kPreThreads;
     tiles = (tiles + 7u) & ~7u;
-    // as many trees a block as leave enough blocks (and 16 at least)
+    const bool rows = !a.single.wsum && static_cast<uint64_t>(nnz) >= kPreRowNnz;
+    // with rows in LDS, as many trees a block as leave enough blocks (and 16 at least)
     uint32_t trees = static_cast<uint32_t>(static_cast<uint64_t>(a.item_count) * tiles / kPreBlocks);
-    trees = a.single.wsum ? kPreTreesW : trees < 16u ? 16u : trees > kPreTrees ? kPreTrees : trees;
+    trees = !rows || trees < kPreFew ? kPreFew : trees > kPreTrees ? kPreTrees : trees;
     const uint32_t groups = (a.item_count - 1u) / trees + 1u;
     const dim3 grid(tiles, groups < 65535u ? groups : 65535u);
-    if (a.single.wsum) lds_predraw_kernel<true><<<grid, kPreThreads, 0, stream>>>(a, trees, groups);
-    else lds_predraw_kernel<false><<<grid, kPreThreads, 0, stream>>>(a, trees, groups);
+    if (a.single.wsum) lds_predraw_kernel<true, false><<<grid, kPreThreads, 0, stream>>>(a, trees, groups);
+    else if (rows) lds_predraw_kernel<false, true><<<grid, kPreThreads, 0, stream>>>(a, trees, groups);
+    else lds_predraw_kernel<false, false><<<grid, kPreThreads, 0, stream>>>(a, trees, groups);
     return hipGetLastError();
 }
 
