@@ -112,9 +112,9 @@ extern "C" {
  * alone fits in LDS; else the hybrid (option "coop_lds_counts" = 0: global
  * counters throughout).  Two variants take the place of these, and are reported
  * by the name of the one whose place they take: trees of up to about 25500
- * vertices lie whole in LDS, and where the global counters or the hybrid would
- * run, or the LDS counters on a graph whose arrows gather at few vertices, the
- * vertices of highest degree are settled first (option "hub").  The lane sampler runs
+ * vertices lie whole in LDS, and where arrows gather at few vertices, or (in place of
+ * the global counters and the hybrid) are not followed far, the vertices of highest
+ * degree are settled first (option "hub").  The lane sampler runs
  * only on request.  All samplers produce identical results (same trees, same
  * counts). */
 
@@ -244,8 +244,8 @@ FC_API int fc_set_stream(fc_ctx *ctx, void *hip_stream);
  *                     with FC_FLAG_AUTOTUNE times both shapes and keeps the faster (the
  *                     trees are the same either way)
  *   "hub"             hubs-first sampler in the automatic choice: 0 never, 1 (the default)
- *                     where a tree does not fit LDS whole, 2 also where it does and on
- *                     every graph (to compare, and to test it on small graphs)
+ *                     where a tree does not fit LDS whole and the graph has hubs or small
+ *                     alpha, 2 on every graph (to compare, and to test it on small ones)
  *   "hub_set"         its vertices in LDS at a time, a multiple of 64 up to 32704 (0, the
  *                     default: as many as fit)
  *   "hub_hot"         of these, per mille, the vertices of highest degree it starts with

@@ -1127,7 +1127,8 @@ uint32_t lds_threads_for(const fc_ctx *ctx, uint64_t trees, uint32_t lds_words) 
 //   million at x up to 4 9.8 / 7.4 to 31 / 17, at x 6 to 8 36 / 50 and 44 / 105, at 40
 //   121 / 295; a lattice of degree 6 where one vertex in two has an edge to a hub as well
 //   (0.07) at x 35 14.9 / 13.0, BA at x 180 78 / 50, R-MAT of 2^22 at x 40 56 / 9.  Trees (BA
-//   with one edge a vertex, 0.2) at x 20 13.8 / 10.2, at 60 19 / 22; a star (0.5) at x 200 158 / 1.7.
+//   with one edge a vertex, 0.2) at x 20 13.8 / 10.2, at 60 19 / 22; a star (0.5) at x 200
+//   158 / 1.7.
 bool hub_applies(bool fits, uint32_t nl, uint64_t nnz, const unsigned long long *ends, double reach) {
     uint32_t b = 0;
     while (b + 1 < fc::kDegreeBits && (uint64_t{nl} << b) < 4 * nnz) ++b;
