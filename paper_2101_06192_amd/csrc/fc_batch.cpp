@@ -802,12 +802,45 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
         if ((rc = size_scratch(ctx, g, slots_for(ctx, g, g.threads, g.wg_per_cu)))) return fail(rc);
     }
 
-    // capture the run: per group, counter resets and the sampling kernel
-    FB_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal), "begin capture");
+    // capture the run: per group, counter resets and the sampling kernel.  The hubs-first
+    // group goes ahead; the others are branches of the graph, so that a group's last trees
+    // leave no CU idle while another waits (4 weighted graphs of 2000 to 60000 vertices,
+    // alpha 10, 256 trees: 3.41 ms one after the other, 2.45 so; 9 small graphs at three
+    // alphas 1.84 and 1.57).  A hubs-first tree takes a CU's whole LDS, and waits for one
+    // that is empty of the others': as a branch too, 256 R-MAT graphs at three alphas
+    // 211 ms, ahead 176.
+    hipStream_t side[kMaxGroups] = {};
+    hipEvent_t forked = nullptr, joined[kMaxGroups] = {};
     hipError_t ce = hipSuccess;
-    for (int gi = 0; gi < b->ngroups && ce == hipSuccess; ++gi)
-        ce = enqueue_group(b->grp[gi], b->grp[gi].args, b->grp[gi].threads, b->stream);
-    hipError_t ee = hipStreamEndCapture(b->stream, &b->graph);
+    for (int gi = 1; gi < b->ngroups && ce == hipSuccess; ++gi) {
+        if (!forked) ce = hipEventCreateWithFlags(&forked, hipEventDisableTiming);
+        if (ce == hipSuccess) ce = hipStreamCreateWithFlags(&side[gi], hipStreamNonBlocking);
+        if (ce == hipSuccess) ce = hipEventCreateWithFlags(&joined[gi], hipEventDisableTiming);
+    }
+    hipError_t ee = hipSuccess;
+    if (ce == hipSuccess) {
+        ee = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);
+        if (ee == hipSuccess) {
+            const int first = b->grp[0].hub && b->ngroups > 1 ? 1 : 0;
+            if (first) ce = enqueue_group(b->grp[0], b->grp[0].args, b->grp[0].threads, b->stream);
+            if (forked && ce == hipSuccess) ce = hipEventRecord(forked, b->stream);
+            for (int gi = first; gi < b->ngroups && ce == hipSuccess; ++gi) {
+                hipStream_t to = gi > first ? side[gi] : b->stream;
+                if (gi > first) ce = hipStreamWaitEvent(to, forked, 0);
+                if (ce == hipSuccess)
+                    ce = enqueue_group(b->grp[gi], b->grp[gi].args, b->grp[gi].threads, to);
+                if (gi > first && ce == hipSuccess) ce = hipEventRecord(joined[gi], to);
+            }
+            for (int gi = first + 1; gi < b->ngroups && ce == hipSuccess; ++gi)
+                ce = hipStreamWaitEvent(b->stream, joined[gi], 0);
+            ee = hipStreamEndCapture(b->stream, &b->graph);
+        }
+    }
+    for (hipStream_t q : side)
+        if (q) (void)hipStreamDestroy(q);
+    for (hipEvent_t e : joined)
+        if (e) (void)hipEventDestroy(e);
+    if (forked) (void)hipEventDestroy(forked);
     if (ce != hipSuccess) return fail(hip_fail(ctx, ce, "capturing the batch launch"));
     if (ee != hipSuccess) return fail(hip_fail(ctx, ee, "end capture"));
     FB_HIP(hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0), "instantiate graph");
