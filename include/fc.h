@@ -214,6 +214,10 @@ FC_API int fc_set_stream(fc_ctx *ctx, void *hip_stream);
  *   "lds_wg_per_cu"   cap on its resident workgroups per CU (0, the default: as many as fit)
  *   "lanes_per_wave"  active lanes per wave of the lane sampler (1..64)
  *   "max_slots"       cap on trees in flight (0 = memory bound only)
+ *   "scratch_limit"   most bytes of device memory that the context's scratch and its batches
+ *                     may hold together (0, the default: what the device has); what goes
+ *                     beyond is refused as on a full device: a sampler that can do
+ *                     without does, else the call returns FC_ERR_NOMEM
  *   "phase_timing"    1: the workgroup sampler reports per-phase times in fc_stats
  *   "hyb_hot_cap"     cap on how many (highest-degree) vertices the hybrid sampler keeps in
  *                     LDS (default 2^31 - 1: as many as fit; 0: none, all counters global)

@@ -93,19 +93,27 @@ int ensure(fc_ctx *ctx, DevBuf &b, size_t bytes, const char *what) {
     }
     if (b.ptr) {
         (void)hipStreamSynchronize(ctx->stream);
-        (void)hipFree(b.ptr);
-        b.ptr = nullptr;
-        b.bytes = 0;
+        release(*ctx->held, b);
     }
-    hipError_t e = hipMalloc(&b.ptr, bytes);
-    if (e != hipSuccess) {
+    const size_t held = *ctx->held;
+    const bool refused =
+        ctx->scratch_limit && (held > ctx->scratch_limit || bytes > ctx->scratch_limit - held);
+    if (refused || hipMalloc(&b.ptr, bytes) != hipSuccess) {
         (void)hipGetLastError();
         b.ptr = nullptr;
         return set_err(ctx, FC_ERR_NOMEM, std::string("allocating ") + what + " (" +
                                               std::to_string(bytes) + " bytes) failed");
     }
     b.bytes = bytes;
+    *ctx->held += bytes;
     return FC_OK;
+}
+
+void release(std::atomic<size_t> &held, DevBuf &b) {
+    if (!b.ptr) return;
+    (void)hipFree(b.ptr);
+    held -= b.bytes;
+    b = DevBuf{};
 }
 
 size_t small_bytes(const fc_ctx *ctx) { return ctx->arena ? offsetof(Small, ends) : sizeof(Small); }
@@ -279,7 +287,9 @@ bool deferrable(const fc_ctx *ctx, const fc_params *p, const fc_graph *g) {
 }
 
 // Scratch, relabelled graph and launch shape of the hubs-first sampler: *c but for the
-// outputs.  nl vertices are not isolated.
+// outputs.  nl vertices are not isolated.  All that may be refused (FC_ERR_NOMEM) is
+// allocated before the first launch: the class offsets and bounds that the caller
+// computed are those of the sampler that then takes over, until nothing can fail.
 int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::VRec *vrec, uint32_t nl,
                 uint32_t tree_begin, uint32_t tree_count, bool weighted, uint32_t nb, fc::CoopArgs *c,
                 uint32_t *threads, size_t *lds) {
@@ -293,23 +303,8 @@ int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::V
         (rc = ensure(ctx, ctx->rl_vrec, sizeof(fc::VRec) * n, "relabelled records")) ||
         (rc = ensure(ctx, ctx->rl_adj, 8u * static_cast<size_t>(g.nnz), "relabelled adjacency")))
         return rc;
-    Small *sm = static_cast<Small *>(ctx->small.ptr);
-    FC_HIP(ctx, fc::launch_class_bounds(g.row_ptr, un, fc::kHubsFirst, static_cast<uint32_t *>(ctx->rl_blk.ptr),
-                                        static_cast<uint32_t *>(ctx->rl_base.ptr), sm->class_bounds,
-                                        nullptr, ctx->stream), "class bounds");
-    FC_HIP(ctx, fc::launch_relabel_graph(g.row_ptr, g.col_idx, un, g.nnz, fc::kHubsFirst,
-                                         static_cast<const uint32_t *>(ctx->rl_base.ptr), 32u,
-                                         static_cast<uint32_t *>(ctx->rl_inv.ptr),
-                                         static_cast<uint32_t *>(ctx->rl_orig.ptr),
-                                         static_cast<unsigned long long *>(ctx->rl_adj.ptr), ctx->stream),
-           "relabel");
-    FC_HIP(ctx, fc::launch_relabel_vrec(vrec, static_cast<const uint32_t *>(ctx->rl_inv.ptr), un,
-                                        static_cast<fc::VRec *>(ctx->rl_vrec.ptr), ctx->stream),
-           "relabel records");
     const HubShape s = hub_shape(ctx, nl, ctx->hub_threads, 1u);
-    *threads = ctx->hub_threads;
-    *lds = s.lds;
-    const int fit = fc::hub_max_active(*threads, s.lds, weighted);
+    const int fit = fc::hub_max_active(ctx->hub_threads, s.lds, weighted);
     const size_t nw = (stride + 31u) / 32u;
     const size_t pre_bytes = 8u * stride * static_cast<size_t>(tree_count);
     bool predraw = ctx->predraw_mib != 0 && pre_bytes <= (static_cast<size_t>(ctx->predraw_mib) << 20);
@@ -330,6 +325,21 @@ int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::V
         (rc = ensure(ctx, ctx->cbits, 4u * nw * slots, "settled bitmap")) ||
         (rc = ensure(ctx, ctx->crint, 4u * stride, "root counts")))
         return rc;
+    *threads = ctx->hub_threads;
+    *lds = s.lds;
+    Small *sm = static_cast<Small *>(ctx->small.ptr);
+    FC_HIP(ctx, fc::launch_class_bounds(g.row_ptr, un, fc::kHubsFirst, static_cast<uint32_t *>(ctx->rl_blk.ptr),
+                                        static_cast<uint32_t *>(ctx->rl_base.ptr), sm->class_bounds,
+                                        nullptr, ctx->stream), "class bounds");
+    FC_HIP(ctx, fc::launch_relabel_graph(g.row_ptr, g.col_idx, un, g.nnz, fc::kHubsFirst,
+                                         static_cast<const uint32_t *>(ctx->rl_base.ptr), 32u,
+                                         static_cast<uint32_t *>(ctx->rl_inv.ptr),
+                                         static_cast<uint32_t *>(ctx->rl_orig.ptr),
+                                         static_cast<unsigned long long *>(ctx->rl_adj.ptr), ctx->stream),
+           "relabel");
+    FC_HIP(ctx, fc::launch_relabel_vrec(vrec, static_cast<const uint32_t *>(ctx->rl_inv.ptr), un,
+                                        static_cast<fc::VRec *>(ctx->rl_vrec.ptr), ctx->stream),
+           "relabel records");
     FC_HIP(ctx, hipMemsetAsync(ctx->ckk.ptr, 0, 8u * stride * slots, ctx->stream), "memset draw counts");
     FC_HIP(ctx, hipMemsetAsync(ctx->crint.ptr, 0, 4u * stride, ctx->stream), "memset root counts");
     c->word = predraw ? nullptr : ctx->cword.ptr;
@@ -1351,6 +1361,9 @@ int fc_set_option(fc_ctx *ctx, const char *key, int64_t value) {
     } else if (k == "max_slots") {
         if (value < 0 || value > 0x7FFFFFFF) return set_err(ctx, FC_ERR_ARG, "max_slots");
         ctx->max_slots = static_cast<uint32_t>(value);
+    } else if (k == "scratch_limit") {
+        if (value < 0) return set_err(ctx, FC_ERR_ARG, "scratch_limit");
+        ctx->scratch_limit = static_cast<size_t>(value);
     } else if (k == "hub") {
         if (value < 0 || value > 2) return set_err(ctx, FC_ERR_ARG, "hub must be 0, 1 or 2");
         ctx->hub = static_cast<uint32_t>(value);
@@ -1576,7 +1589,7 @@ int fc_probe_random_access(fc_ctx *ctx, uint64_t footprint_bytes, int32_t atomic
     if ((rc = ensure(ctx, buf, 4 * words + 64, "probe footprint"))) return rc;
     uint32_t *data = static_cast<uint32_t *>(buf.ptr);
     auto done = [&](int code) {
-        (void)hipFree(buf.ptr);
+        release(*ctx->held, buf);
         return code;
     };
     if (hipMemsetAsync(data, 0, 4 * words + 64, ctx->stream) != hipSuccess)

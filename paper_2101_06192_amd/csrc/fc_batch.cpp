@@ -63,6 +63,7 @@ enum Part : int { kHubs = 0, kWide, kNarrow, kFew, kSome, kMany, kMaxGroups };
 
 struct fc_batch {
     fc_ctx *ctx = nullptr;
+    std::shared_ptr<std::atomic<size_t>> held;  // the context's
     std::vector<fc_job> jobs;
     uint64_t seed = 0;
     int32_t flags = 0;
@@ -87,11 +88,11 @@ int free_batch(fc_batch *b) {
     if (b->graph) (void)hipGraphDestroy(b->graph);
     for (DevBuf *d : {&b->vrec, &b->dmax, &b->iso, &b->wsum, &b->wthr, &b->wtot, &b->rl_blk, &b->rl_base, &b->rl_bounds, &b->rl_ends, &b->rl_inv,
                       &b->rl_orig, &b->rl_adj, &b->rl_vrec})
-        if (d->ptr) (void)hipFree(d->ptr);
+        release(*b->held, *d);
     for (Group &g : b->grp)
         for (DevBuf *d : {&g.jobtab, &g.item_job, &g.word, &g.kk, &g.lists, &g.levels, &g.bits, &g.members, &g.rint,
                           &g.small, &g.scratch_r})
-            if (d->ptr) (void)hipFree(d->ptr);
+            release(*b->held, *d);
     for (hipEvent_t e : {b->ev_in, b->ev0, b->ev1})
         if (e) (void)hipEventDestroy(e);
     if (b->stream) (void)hipStreamDestroy(b->stream);
@@ -339,7 +340,7 @@ int autotune(fc_batch *b, Group &g) {
     DevBuf tmp_tab, tmp_map;
     if ((rc = ensure(ctx, tmp_tab, sizeof(fc::CoopJob) * tab.size(), "tuning job table")) ||
         (rc = ensure(ctx, tmp_map, 4 * tmap.size(), "tuning item map"))) {
-        if (tmp_tab.ptr) (void)hipFree(tmp_tab.ptr);
+        release(*ctx->held, tmp_tab);
         return rc;
     }
     const uint32_t prefix = static_cast<uint32_t>(tmap.size());
@@ -391,8 +392,8 @@ int autotune(fc_batch *b, Group &g) {
             best_l = cand[c][3] != 0u;
         }
     }
-    if (tmp_tab.ptr) (void)hipFree(tmp_tab.ptr);
-    if (tmp_map.ptr) (void)hipFree(tmp_map.ptr);
+    release(*ctx->held, tmp_tab);
+    release(*ctx->held, tmp_map);
     g.repop = best_r;
     g.lean = best_l;
     if (rc) return rc;
@@ -432,6 +433,7 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
 
     fc_batch *b = new fc_batch();
     b->ctx = ctx;
+    b->held = ctx->held;
     b->jobs.assign(jobs, jobs + n_jobs);
     b->seed = seed;
     b->flags = flags;

@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <memory>
 #include <string>
 
 #include "fc.h"
@@ -49,6 +51,9 @@ struct fc_ctx {
     hipEvent_t ev0 = nullptr, ev1 = nullptr, evm = nullptr;
     Small *host_small = nullptr;  // pinned: where a call's counters are read back
     size_t state_budget = 0;      // bytes of per-tree state the sampler may use
+    size_t scratch_limit = 0;     // most bytes of device memory to hold (0: what the device has)
+    // what this context's buffers and its batches' take now (a batch may outlive its context)
+    std::shared_ptr<std::atomic<size_t>> held = std::make_shared<std::atomic<size_t>>(0);
     uint32_t lanes_per_wave = 64; // active lanes per wave in the lane sampler
     uint32_t max_slots = 0;       // 0 = as many trees in flight as memory allows
     uint32_t cu_count = 256;
@@ -112,6 +117,8 @@ int hip_fail(fc_ctx *ctx, hipError_t e, const char *what);
 // Grow-only device buffer: (re)allocates when `bytes` exceeds its size; in
 // arena mode carves it from the context's arena instead (never allocates).
 int ensure(fc_ctx *ctx, DevBuf &b, size_t bytes, const char *what);
+// Frees a buffer that ensure() allocated (held: its context's).
+void release(std::atomic<size_t> &held, DevBuf &b);
 // Bytes of Small that a context's calls use.
 size_t small_bytes(const fc_ctx *ctx);
 // Bytes of per-tree state the sampler may use now: the context's budget, or
