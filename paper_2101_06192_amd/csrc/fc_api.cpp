@@ -15,6 +15,7 @@
 #include <cstdlib>
 #include <cstddef>
 #include <cstring>
+#include <iterator>
 #include <mutex>
 #include <string>
 
@@ -286,45 +287,69 @@ bool deferrable(const fc_ctx *ctx, const fc_params *p, const fc_graph *g) {
     return g && !(g->weights && g->nnz) && jump_applies(ctx, p, g->n);
 }
 
+// Pre-drawn words or arrows of a call, `bytes` of them: whether they fit the budget
+// and the device.
+bool predraw_fits(fc_ctx *ctx, size_t bytes, const char *what) {
+    if (ctx->predraw_mib == 0 || bytes > (static_cast<size_t>(ctx->predraw_mib) << 20)) return false;
+    if (ensure(ctx, ctx->cpre, bytes, what) == FC_OK) return true;
+    ctx->last_error.clear();  // not enough device memory: each tree draws its own
+    return false;
+}
+
 // Scratch, relabelled graph and launch shape of the hubs-first sampler: *c but for the
-// outputs.  nl vertices are not isolated.  All that may be refused (FC_ERR_NOMEM) is
+// outputs.  nl vertices are not isolated; rl_blk and rl_base are there.  All that may be refused (FC_ERR_NOMEM) is
 // allocated before the first launch: the class offsets and bounds that the caller
 // computed are those of the sampler that then takes over, until nothing can fail.
+// When its state does not fit beside pre-drawn arrows allocated here, these go first;
+// when it does not fit at all, what was allocated here goes back, so that the other
+// sampler finds the memory it would have found.
 int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::VRec *vrec, uint32_t nl,
                 uint32_t tree_begin, uint32_t tree_count, bool weighted, uint32_t nb, fc::CoopArgs *c,
                 uint32_t *threads, size_t *lds) {
-    int rc;
     const uint32_t un = static_cast<uint32_t>(g.n);
     const size_t n = un, stride = std::max<uint32_t>(nl, 1u);
-    if ((rc = ensure(ctx, ctx->rl_blk, 4u * fc::kRelabelClasses * nb, "class counts")) ||
-        (rc = ensure(ctx, ctx->rl_base, 4u * fc::kRelabelClasses * nb, "class offsets")) ||
-        (rc = ensure(ctx, ctx->rl_inv, 4u * n, "relabel inverse")) ||
-        (rc = ensure(ctx, ctx->rl_orig, 4u * n, "relabel ids")) ||
-        (rc = ensure(ctx, ctx->rl_vrec, sizeof(fc::VRec) * n, "relabelled records")) ||
-        (rc = ensure(ctx, ctx->rl_adj, 8u * static_cast<size_t>(g.nnz), "relabelled adjacency")))
-        return rc;
     const HubShape s = hub_shape(ctx, nl, ctx->hub_threads, 1u);
     const int fit = fc::hub_max_active(ctx->hub_threads, s.lds, weighted);
     const size_t nw = (stride + 31u) / 32u;
-    const size_t pre_bytes = 8u * stride * static_cast<size_t>(tree_count);
-    bool predraw = ctx->predraw_mib != 0 && pre_bytes <= (static_cast<size_t>(ctx->predraw_mib) << 20);
-    if (predraw && ensure(ctx, ctx->cpre, pre_bytes, "pre-drawn arrows") != FC_OK) {
-        predraw = false;  // not enough device memory: each tree draws its own
-        ctx->last_error.clear();
+    size_t slots = 0;
+    auto allocate = [&](bool predraw) {
+        const size_t per_slot = ((predraw ? 0u : 8u) + 8u + 24u + 4u) * stride + 8u * s.set + 4u * nw;
+        slots = std::max<size_t>(1, state_budget_now(ctx) / per_slot);
+        slots = std::min<size_t>(slots, tree_count);
+        slots = std::min<size_t>(slots, static_cast<size_t>(ctx->cu_count) * static_cast<size_t>(std::max(1, fit)));
+        if (ctx->max_slots) slots = std::min<size_t>(slots, ctx->max_slots);
+        int rc;
+        if ((rc = ensure(ctx, ctx->rl_inv, 4u * n, "relabel inverse")) ||
+            (rc = ensure(ctx, ctx->rl_orig, 4u * n, "relabel ids")) ||
+            (rc = ensure(ctx, ctx->rl_vrec, sizeof(fc::VRec) * n, "relabelled records")) ||
+            (rc = ensure(ctx, ctx->rl_adj, 8u * static_cast<size_t>(g.nnz), "relabelled adjacency")) ||
+            (!predraw && (rc = ensure(ctx, ctx->cword, 8u * stride * slots, "arrows"))) ||
+            (rc = ensure(ctx, ctx->ckk, 8u * stride * slots, "set ids and draw counts")) ||
+            (rc = ensure(ctx, ctx->clists, 24u * stride * slots, "lists")) ||
+            (rc = ensure(ctx, ctx->clevels, 4u * stride * slots, "in-arrow counts")) ||
+            (rc = ensure(ctx, ctx->corigt, 8u * s.set * slots, "set members")) ||
+            (rc = ensure(ctx, ctx->cbits, 4u * nw * slots, "settled bitmap")) ||
+            (rc = ensure(ctx, ctx->crint, 4u * stride, "root counts")))
+            return rc;
+        return FC_OK;
+    };
+    DevBuf *const taken[] = {&ctx->rl_inv, &ctx->rl_orig, &ctx->rl_vrec, &ctx->rl_adj, &ctx->cpre,
+                             &ctx->cword, &ctx->ckk, &ctx->clists, &ctx->clevels, &ctx->corigt,
+                             &ctx->cbits, &ctx->crint};
+    size_t before[std::size(taken)];
+    for (size_t i = 0; i < std::size(taken); ++i) before[i] = taken[i]->bytes;
+    const size_t pre_before = ctx->cpre.bytes;
+    bool predraw = predraw_fits(ctx, 8u * stride * static_cast<size_t>(tree_count), "pre-drawn arrows");
+    int rc = allocate(predraw);
+    if (rc == FC_ERR_NOMEM && predraw && ctx->cpre.bytes > pre_before) {
+        predraw = false;
+        release(*ctx->held, ctx->cpre);
+        rc = allocate(false);
     }
-    const size_t per_slot = ((predraw ? 0u : 8u) + 8u + 24u + 4u) * stride + 8u * s.set + 4u * nw;
-    size_t slots = std::max<size_t>(1, state_budget_now(ctx) / per_slot);
-    slots = std::min<size_t>(slots, tree_count);
-    slots = std::min<size_t>(slots, static_cast<size_t>(ctx->cu_count) * static_cast<size_t>(std::max(1, fit)));
-    if (ctx->max_slots) slots = std::min<size_t>(slots, ctx->max_slots);
-    if ((!predraw && (rc = ensure(ctx, ctx->cword, 8u * stride * slots, "arrows"))) ||
-        (rc = ensure(ctx, ctx->ckk, 8u * stride * slots, "set ids and draw counts")) ||
-        (rc = ensure(ctx, ctx->clists, 24u * stride * slots, "lists")) ||
-        (rc = ensure(ctx, ctx->clevels, 4u * stride * slots, "in-arrow counts")) ||
-        (rc = ensure(ctx, ctx->corigt, 8u * s.set * slots, "set members")) ||
-        (rc = ensure(ctx, ctx->cbits, 4u * nw * slots, "settled bitmap")) ||
-        (rc = ensure(ctx, ctx->crint, 4u * stride, "root counts")))
-        return rc;
+    if (rc == FC_ERR_NOMEM)
+        for (size_t i = 0; i < std::size(taken); ++i)
+            if (taken[i]->bytes > before[i]) release(*ctx->held, *taken[i]);
+    if (rc) return rc;
     *threads = ctx->hub_threads;
     *lds = s.lds;
     Small *sm = static_cast<Small *>(ctx->small.ptr);
@@ -514,12 +539,17 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         // (isolated vertices need no LDS, so only the id width bounds n here)
         const bool try_lds = (mode == 3 || (mode == 0 && ctx->coop_lds_counts)) &&
                              g.n < (1 << fc::kRelabelIdBits);
-        const bool try_hub = mode == 0 && ctx->hub && ctx->coop_lds_counts && g.n >= 1;
+        bool try_hub = mode == 0 && ctx->hub && ctx->coop_lds_counts && g.n >= 1;
         const uint32_t nb = fc::relabel_blocks(static_cast<uint32_t>(g.n));
         if (try_lds || try_hub) {
             if ((rc = ensure(ctx, ctx->rl_blk, 4u * fc::kRelabelClasses * nb, "class counts")) ||
-                (rc = ensure(ctx, ctx->rl_base, 4u * fc::kRelabelClasses * nb, "class offsets")))
-                return rc;
+                (rc = ensure(ctx, ctx->rl_base, 4u * fc::kRelabelClasses * nb, "class offsets"))) {
+                if (try_lds || rc != FC_ERR_NOMEM) return rc;
+                ctx->last_error.clear();
+                try_hub = false;
+            }
+        }
+        if (try_lds || try_hub) {
             FC_HIP(ctx, fc::launch_class_bounds(g.row_ptr, static_cast<uint32_t>(g.n), fc::kNarrowFirst,
                                                 static_cast<uint32_t *>(ctx->rl_blk.ptr),
                                                 static_cast<uint32_t *>(ctx->rl_base.ptr),
@@ -763,13 +793,9 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
             // first arrows of all trees drawn ahead by one vertex-major kernel when
             // every tree's words fit the budget (the trees then work in place);
             // below 16384 vertices a tree's own first pass is too short to gain
-            const size_t pre_bytes = 8u * n * static_cast<size_t>(tree_count);
-            bool predraw = ctx->predraw_mib != 0 && cb[3] >= kPredrawMinVertices &&
-                           pre_bytes <= (static_cast<size_t>(ctx->predraw_mib) << 20);
-            if (predraw && ensure(ctx, ctx->cpre, pre_bytes, "pre-drawn tree words") != FC_OK) {
-                predraw = false;  // not enough device memory: each tree draws its own
-                ctx->last_error.clear();
-            }
+            const bool predraw = cb[3] >= kPredrawMinVertices &&
+                                 predraw_fits(ctx, 8u * n * static_cast<size_t>(tree_count),
+                                              "pre-drawn tree words");
             if ((!predraw && (rc = ensure(ctx, ctx->cword, 8u * n * slots, "tree words"))) ||
                 (rc = ensure(ctx, ctx->clists, 24u * n * slots, "lists")) ||
                 (rc = ensure(ctx, ctx->clevels, 4u * (n + 2u) * slots, "levels")))

@@ -42,7 +42,7 @@ struct fc_ctx {
     DevBuf iso;                                                   // isolated-vertex bitmap
     DevBuf corigt;                                                // hybrid: target ids per slot
     DevBuf crint;                                                 // hubs first: root counts
-    DevBuf cpre;                                                  // LDS: pre-drawn tree words
+    DevBuf cpre;                                                  // pre-drawn tree words or arrows
     DevBuf weights, wsum, wthr;  // staged edge weights (host graphs), running row weight sums,
                                  // step thresholds
     DevBuf rk_key0, rk_key1, rk_val0, rk_val1, rk_hist, rk_thist, rk_ra, rk_rb, rk_s;  // ranking

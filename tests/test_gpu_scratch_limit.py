@@ -46,3 +46,51 @@ def test_lds_counters_take_over_on_their_own_ids(fresh, ahead):
         fresh.set_option("scratch_limit", limit)
         _same(fresh, g, dg, 1.0, trees, refs)
     _same(fresh, g, dg, 0.05, trees, refs)
+
+
+def _runs(fc, limit, calls):
+    """Whether a context that may hold `limit` bytes serves `calls`; they are checked."""
+    for ctx in fc._contexts.values():
+        ctx.close()
+    fc._contexts.clear()
+    fc.set_option("scratch_limit", limit)
+    try:
+        calls()
+    except fc.FCError as e:
+        assert e.code == fc.FC_ERR_NOMEM
+        return False
+    return True
+
+
+def _least(fc, calls, upto, step=1 << 16):
+    """The least limit (to `step` bytes) at which `calls` are served."""
+    lo, hi = 0, upto // step
+    assert _runs(fc, upto, calls)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        if _runs(fc, mid * step, calls):
+            hi = mid
+        else:
+            lo = mid
+    return hi * step
+
+
+@pytest.mark.parametrize("n,trees", [(30000, 64), (400_000, 8), (1_500_000, 2)])
+def test_hubs_first_needs_no_more_than_the_sampler_it_replaces(fresh, n, trees):
+    """R-MAT graphs for which hubs first takes the place of the LDS counters, the global
+    counters and the hybrid: what these fit is served, with the right trees, and so is
+    everything above (where hubs first gets some of its buffers, then all of them)."""
+    g = inputs.rmat(n, 8, 2)
+    dg = fresh.to_device(g)
+    refs = {}
+
+    def replaced():
+        fresh.set_option("hub", 0)
+        fresh.sample(dg, alpha=1.0, seed=5, tree_count=trees)
+
+    least = _least(fresh, replaced, 8 << 30)
+    print(f"n={n} least {least}", flush=True)
+    for percent in range(100, 200, 6):
+        # (64 KiB: the counts by which the choice is made)
+        limit = least * percent // 100 + (1 << 16)
+        assert _runs(fresh, limit, lambda: _same(fresh, g, dg, 1.0, trees, refs)), (least, percent)
