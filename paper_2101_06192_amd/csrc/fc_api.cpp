@@ -96,15 +96,24 @@ int ensure(fc_ctx *ctx, DevBuf &b, size_t bytes, const char *what) {
         (void)hipStreamSynchronize(ctx->stream);
         release(*ctx->held, b);
     }
-    const size_t held = *ctx->held;
-    const bool refused =
-        ctx->scratch_limit && (held > ctx->scratch_limit || bytes > ctx->scratch_limit - held);
-    if (refused || hipMalloc(&b.ptr, bytes) != hipSuccess) {
+    auto allocate = [&]() -> bool {
+        const size_t held = *ctx->held;
+        const bool refused =
+            ctx->scratch_limit && (held > ctx->scratch_limit || bytes > ctx->scratch_limit - held);
+        if (!refused && hipMalloc(&b.ptr, bytes) == hipSuccess) return true;
         (void)hipGetLastError();
         b.ptr = nullptr;
+        return false;
+    };
+    bool got = allocate();
+    if (!got && ctx->cpre.ptr && !ctx->pre_used) {
+        (void)hipStreamSynchronize(ctx->stream);
+        release(*ctx->held, ctx->cpre);
+        got = allocate();
+    }
+    if (!got)
         return set_err(ctx, FC_ERR_NOMEM, std::string("allocating ") + what + " (" +
                                               std::to_string(bytes) + " bytes) failed");
-    }
     b.bytes = bytes;
     *ctx->held += bytes;
     return FC_OK;
@@ -291,6 +300,7 @@ bool deferrable(const fc_ctx *ctx, const fc_params *p, const fc_graph *g) {
 // and the device.
 bool predraw_fits(fc_ctx *ctx, size_t bytes, const char *what) {
     if (ctx->predraw_mib == 0 || bytes > (static_cast<size_t>(ctx->predraw_mib) << 20)) return false;
+    ctx->pre_used = true;
     if (ensure(ctx, ctx->cpre, bytes, what) == FC_OK) return true;
     ctx->last_error.clear();  // not enough device memory: each tree draws its own
     return false;
@@ -346,9 +356,11 @@ int hub_prepare(fc_ctx *ctx, const GraphView &g, const fc_params *p, const fc::V
         release(*ctx->held, ctx->cpre);
         rc = allocate(false);
     }
-    if (rc == FC_ERR_NOMEM)
+    if (rc == FC_ERR_NOMEM) {
         for (size_t i = 0; i < std::size(taken); ++i)
             if (taken[i]->bytes > before[i]) release(*ctx->held, *taken[i]);
+        ctx->pre_used = false;
+    }
     if (rc) return rc;
     *threads = ctx->hub_threads;
     *lds = s.lds;
@@ -1211,6 +1223,7 @@ uint32_t jump_threads_for(const fc_ctx *ctx, uint32_t n, uint64_t trees) {
 int begin(fc_ctx *ctx) {
     if (!ctx) return FC_ERR_ARG;
     ctx->last_error.clear();
+    ctx->pre_used = false;
     FC_HIP(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     return FC_OK;
 }

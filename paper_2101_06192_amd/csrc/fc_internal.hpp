@@ -43,6 +43,7 @@ struct fc_ctx {
     DevBuf corigt;                                                // hybrid: target ids per slot
     DevBuf crint;                                                 // hubs first: root counts
     DevBuf cpre;                                                  // pre-drawn tree words or arrows
+    bool pre_used = false;                                        // (by the call under way)
     DevBuf weights, wsum, wthr;  // staged edge weights (host graphs), running row weight sums,
                                  // step thresholds
     DevBuf rk_key0, rk_key1, rk_val0, rk_val1, rk_hist, rk_thist, rk_ra, rk_rb, rk_s;  // ranking
@@ -115,7 +116,8 @@ constexpr uint32_t kPredrawMinVertices = 16384;
 int set_err(fc_ctx *ctx, int code, const std::string &msg);
 int hip_fail(fc_ctx *ctx, hipError_t e, const char *what);
 // Grow-only device buffer: (re)allocates when `bytes` exceeds its size; in
-// arena mode carves it from the context's arena instead (never allocates).
+// arena mode carves it from the context's arena instead (never allocates).  Pre-drawn
+// arrows that an earlier call left are given back before an allocation is refused.
 int ensure(fc_ctx *ctx, DevBuf &b, size_t bytes, const char *what);
 // Frees a buffer that ensure() allocated (held: its context's).
 void release(std::atomic<size_t> &held, DevBuf &b);

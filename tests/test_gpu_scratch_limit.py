@@ -94,3 +94,20 @@ def test_hubs_first_needs_no_more_than_the_sampler_it_replaces(fresh, n, trees):
         # (64 KiB: the counts by which the choice is made)
         limit = least * percent // 100 + (1 << 16)
         assert _runs(fresh, limit, lambda: _same(fresh, g, dg, 1.0, trees, refs)), (least, percent)
+
+
+def test_earlier_arrows_give_way(fresh):
+    """Pre-drawn arrows that an earlier call left do not stand in a later call's way."""
+    small, large = inputs.rmat(30000, 8, 2), inputs.rmat(400_000, 8, 2)
+    ds, dl = fresh.to_device(small), fresh.to_device(large)
+
+    def calls(mib):
+        fresh.set_option("hub", 1)
+        fresh.set_option("predraw_mib", mib)
+        fresh.sample(ds, alpha=1.0, seed=5, tree_count=512)
+        fresh.set_option("hub", 0)
+        fresh.sample(dl, alpha=1.0, seed=5, tree_count=8)
+
+    # without arrows ahead the first call keeps them in its slots
+    least = _least(fresh, lambda: calls(0), 8 << 30)
+    assert _runs(fresh, least + (1 << 16), lambda: calls(32768))
