@@ -210,6 +210,7 @@ __global__ __launch_bounds__(1024) void wilson_jump_kernel(CoopArgs a) {
         bool wide = true;  // this round's jumps go over all unsettled vertices
         uint32_t cur = 0, ccur = uniform(s_cnt);  // the list's vertices that draw: [cur, cur + ccur)
         bool done = false;
+        __syncthreads();  // s_cnt is read
         for (;;) {
             // pop what is listed, then the 2-cycles that the new arrows close
             while (ccur > 0u) {
