@@ -892,6 +892,7 @@ __global__ __launch_bounds__(1024) void wilson_hub_kernel(CoopArgs a) {
                     }
                     __syncthreads();
                     uint32_t lo = 0, hi = min(uniform(s_c), nl);
+                    __syncthreads();  // s_c is read
                     while (lo < hi) {
                         for (uint32_t base = lo + wave_base; base < hi; base += T) {
                             uint64_t e[1] = {0ull};
