@@ -736,6 +736,7 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
                 if (s < n) atomicAdd(&pc[s], 1u);
             }
             __syncthreads();
+            if (tid == 0) s_u = 0;  // everybody has read it; the residual counts with it
             for (uint32_t i = wave_base; i < m; i += T) {
                 const uint32_t li = i + lane;
                 uint32_t u = 0;
@@ -788,7 +789,6 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
         // 3. the residual: vertices whose exit does not reach u*
         // -------------------------------------------------------------------
         if (residual) {
-            if (tid == 0) s_u = 0;
             // exits on crossing cycles keep one in-arrow count: clear it
             for (uint32_t i = tid; i < m; i += T) pc[bU[i]] = 0u;
             __syncthreads();
@@ -872,15 +872,16 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
                     err |= kErrStepCap;
                     break;
                 }
-                if (tid == 0) {
-                    s_lc[0] = s_lc[1] = s_lc[2] = 0;
-                    s_c = 0;
-                }
+                if (tid == 0) s_lc[0] = s_lc[1] = s_lc[2] = 0;
                 for (uint32_t i = tid; i < ucount; i += T) {
                     const uint32_t tg = tw[U[i]];
                     if (!is_settled(tg)) atomicAdd(&pc[tg], 1u);
                 }
                 __syncthreads();
+                if (tid == 0) {  // the last round's are read, the next barrier is before this one's
+                    s_u = 0;
+                    s_c = 0;
+                }
                 for (uint32_t i = wave_base; i < ucount; i += T) {
                     const uint32_t li = i + lane;
                     uint32_t x = 0;
@@ -916,7 +917,6 @@ __global__ __launch_bounds__(1024) void wilson_tile_kernel(TileArgs a) {
                     phi = min(phi + uniform(s_lc[cn]), n);
                 }
                 const uint32_t peeled = phi;
-                if (tid == 0) s_u = 0;  // every thread read it before the level-0 barrier
                 // reverse sweep: settled when the target is; the others hang off a
                 // cycle and stay listed
                 for (uint32_t L = nlev; L > 0; --L) {

@@ -210,6 +210,7 @@ def test_the_check_finds_what_it_is_for():
         assert bool(clashes(kernel % body)) == bad, body
 
 
-@pytest.mark.parametrize("source", ["wilson_jump.hip", "wilson_hub.hip", "wilson_hyb.hip"])
+@pytest.mark.parametrize("source", ["wilson_jump.hip", "wilson_tile.hip", "wilson_hub.hip",
+                                    "wilson_hyb.hip"])
 def test_barriers_between_uses_of_a_counter(source):
     assert clashes(_source(source)) == []
