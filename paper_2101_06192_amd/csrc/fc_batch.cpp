@@ -405,12 +405,9 @@ int autotune(fc_batch *b, Group &g) {
     return FC_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t seed, int32_t flags,
-                    fc_batch **out) {
+// The batch itself.  hub_mode: option "hub", or 0 for a batch without hubs-first groups.
+int build(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t seed, int32_t flags, uint32_t hub_mode,
+          fc_batch **out) {
     int rc = begin(ctx);
     if (rc) return rc;
     if (!out || n_jobs < 0 || (n_jobs > 0 && !jobs))
@@ -557,13 +554,13 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
     }
     // graphs whose trees fit LDS whole need no relabelling
     auto small = [&](uint32_t n) {
-        return ctx->coop_lds_counts && ctx->hub < 2 && n <= fc::kJumpMax &&
+        return ctx->coop_lds_counts && hub_mode < 2 && n <= fc::kJumpMax &&
                fc::jump_lds_bytes(n) + kLdsStaticBytes <= ctx->max_lds;
     };
     uint32_t n_rest = 0;  // the largest of the others
     for (const GInfo &gi : gs)
         if (!small(gi.n)) n_rest = std::max(n_rest, gi.n);
-    const bool try_hub = ctx->coop_lds_counts && ctx->hub && n_rest > 0;
+    const bool try_hub = ctx->coop_lds_counts && hub_mode && n_rest > 0;
     const bool try_lds = ctx->coop_lds_counts && n_rest > 0 && (try_hub || n_rest < (1u << fc::kRelabelIdBits));
     std::vector<unsigned int> bounds(4 * gs.size(), 0u);
     std::vector<unsigned long long> ends(fc::kDegreeBits * gs.size(), 0ull);
@@ -615,7 +612,7 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
             const bool fits = 4u * static_cast<size_t>(gwords[f]) + kLdsStaticBytes <= ctx->max_lds &&
                               gs[f].n < (1u << fc::kRelabelIdBits);
             hub[f] = try_hub &&
-                     (ctx->hub == 2 || hub_applies(fits, bounds[4 * f + 3], static_cast<uint64_t>(gs[f].nnz),
+                     (hub_mode == 2 || hub_applies(fits, bounds[4 * f + 3], static_cast<uint64_t>(gs[f].nnz),
                                                    &ends[fc::kDegreeBits * f], reach[f]));
             any_hub = any_hub || hub[f];
             if (hub[f]) continue;
@@ -849,6 +846,19 @@ int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t se
 #undef FB_HIP
     *out = b;
     return FC_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int fc_batch_create(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t seed, int32_t flags,
+                    fc_batch **out) {
+    if (!ctx) return FC_ERR_ARG;
+    int rc = build(ctx, jobs, n_jobs, seed, flags, ctx->hub, out);
+    // hubs first takes more memory than the samplers that it replaces
+    if (rc == FC_ERR_NOMEM && ctx->hub) rc = build(ctx, jobs, n_jobs, seed, flags, 0u, out);
+    return rc;
 }
 
 int fc_batch_run(fc_batch *b, fc_stats *stats) {

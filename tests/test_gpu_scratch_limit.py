@@ -111,3 +111,26 @@ def test_earlier_arrows_give_way(fresh):
     # without arrows ahead the first call keeps them in its slots
     least = _least(fresh, lambda: calls(0), 8 << 30)
     assert _runs(fresh, least + (1 << 16), lambda: calls(32768))
+
+
+@pytest.mark.parametrize("tune", [False, True])
+def test_batches_need_no_more_than_without_hubs_first(fresh, tune):
+    """Jobs on graphs for which hubs first takes the place of the LDS and of the global
+    counters, and a small one beside them."""
+    graphs = [inputs.rmat(400_000, 8, 2), inputs.rmat(30000, 8, 2), inputs.barabasi_albert(3000, 3, 1)]
+    on_device = [fresh.to_device(g) for g in graphs]
+    refs = [oracle.sample(g, 1.0, 5, 0, 2).R for g in graphs]
+
+    def create(hub):
+        fresh.set_option("hub", hub)
+        batch = fresh.Batch([{"graph": d, "alpha": 1.0, "tree_count": 2} for d in on_device], seed=5,
+                            autotune=tune)
+        batch.run()
+        got = [batch.result(k)["root_counts"] for k in range(len(graphs))]
+        batch.close()
+        assert all(np.array_equal(a, b) for a, b in zip(got, refs))
+
+    least = _least(fresh, lambda: create(0), 8 << 30)
+    print(f"least {least}", flush=True)
+    for percent in range(100, 200, 9):
+        assert _runs(fresh, least * percent // 100 + (1 << 16), lambda: create(1)), (least, percent)
