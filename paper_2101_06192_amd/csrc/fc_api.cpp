@@ -429,16 +429,19 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     Small *sm = static_cast<Small *>(ctx->small.ptr);
     const fc::GraphCheck *check = g.pending ? &sm->check : nullptr;
     FC_HIP(ctx, hipMemsetAsync(sm, 0, small_bytes(ctx), ctx->stream), "memset counters");
-    if (stats) {
+    auto clear_stats = [&]() {
         stats->tau = tree_count;
         stats->trees_in_flight = 0;
         stats->walk_steps = stats->roots = stats->digest_sum = 0;
         stats->ms_sample = 0.0;
         stats->sampler[0] = 0;
-    }
+    };
+    if (stats && !g.pending) clear_stats();  // else once the graph is known to be sound
     if (g.n == 0 || tree_count == 0) {
         GraphView only = g;
-        return g.pending ? check_graph(ctx, &only) : FC_OK;
+        if (g.pending && (rc = check_graph(ctx, &only))) return rc;
+        if (stats) clear_stats();
+        return FC_OK;
     }
     if ((rc = ensure(ctx, ctx->vrec, sizeof(fc::VRec) * static_cast<size_t>(g.n), "vertex records")))
         return rc;
@@ -1088,6 +1091,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     if (stats) {
         float ms = 0.f;
         (void)hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1);
+        stats->tau = tree_count;
         stats->trees_in_flight = static_cast<uint32_t>(slots);
         std::snprintf(stats->sampler, sizeof(stats->sampler), "%s", kname);
         stats->walk_steps = tot.walk_steps;
@@ -1486,7 +1490,7 @@ int fc_sample(fc_ctx *ctx, const fc_graph *g, const fc_params *params, uint32_t 
         return rc;
     rc = run_sampler(ctx, gv, params, tree_begin, tree_count, root_counts, visit_counts,
                      tree_digests, tree_steps, parents, tree_visits, stats, nullptr);
-    if (stats) stats->ms_total = now_ms() - t0;
+    if (stats && !(rc && gv.pending)) stats->ms_total = now_ms() - t0;
     return rc;
 }
 
