@@ -902,11 +902,12 @@ int fc_batch_run(fc_batch *b, fc_stats *stats) {
     }
     if (error & fc::kErrStepCap)
         return set_err(ctx, FC_ERR_HIP, "a tree exceeded the step bound (internal fault)");
-    if (error & fc::kErrVisitOverflow)
-        return set_err(ctx, FC_ERR_OVERFLOW,
-                       b->grp[0].use_lds || b->grp[0].jump
-                           ? "a per-vertex draw count exceeded 2^28 - 1 (LDS counters)"
-                                         : "a per-vertex visit counter exceeded 2^31 - 1");
+    for (int gi = 0; gi < b->ngroups; ++gi)
+        if (sm[gi].totals.error & fc::kErrVisitOverflow)
+            return set_err(ctx, FC_ERR_OVERFLOW,
+                           b->grp[gi].use_lds || b->grp[gi].jump
+                               ? "a per-vertex draw count exceeded 2^28 - 1 (LDS counters)"
+                               : "a per-vertex visit counter exceeded 2^31 - 1");
     if (stats) {
         float ms = 0.f;
         (void)hipEventElapsedTime(&ms, b->ev0, b->ev1);

@@ -45,3 +45,24 @@ def test_statistics_of_an_unsound_graph_stay_as_they_were(gpu_lib, entry, n, tre
     rc, raw, _ = _call(fc, entry, bad, trees)
     assert rc == fc.FC_ERR_GRAPH
     assert raw == b"\xab" * len(raw)
+
+
+def test_a_batch_names_the_limit_of_the_group_that_met_it(gpu_lib):
+    """A large graph sampled hubs first (31-bit draw counts) ahead of a small one whose
+    whole tree lies in LDS (28 bits): the draw limit is met in the small one alone."""
+    fc = gpu_lib
+    large = inputs.rmat(400_000, 8, 2)
+    small = inputs.from_edge_list(400, [(0, i) for i in range(1, 400)])
+    limit = int(oracle.sample(large, 0.05, 5, 0, 2, per_tree=True).tree_visits.max())
+    assert int(oracle.sample(small, 1e4, 5, 0, 2, per_tree=True).tree_visits.max()) > limit
+    jobs = [{"graph": fc.to_device(large), "alpha": 0.05, "tree_count": 2},
+            {"graph": fc.to_device(small), "alpha": 1e4, "tree_count": 2}]
+    fc.set_option("max_draws", limit)
+    try:
+        batch = fc.Batch(jobs, seed=5)
+        with pytest.raises(fc.FCError) as e:
+            batch.run()
+    finally:
+        fc.set_option("max_draws", 0)
+    assert e.value.code == fc.FC_ERR_OVERFLOW
+    assert "2^28 - 1" in str(e.value)
