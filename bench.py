@@ -291,16 +291,15 @@ def _timed(fn, steps, warmup):
     return (time.perf_counter() - t0) / steps, out
 
 
-def _phases(st, hub=False):
-    """Per-phase wall time per workgroup of a workgroup sampler's call (hub: the
-    hubs-first sampler ran in the place of the one that the statistics name)."""
-    if hub:
+def _phases(st):
+    """Per-phase wall time per workgroup of a workgroup sampler's call."""
+    if st["kernels"] == "wilson_hub":
         names = ["first_arrows", "hubs_claims", "hubs_redraws", "hubs_jumps", "hubs_cycles",
                  "stream", "list", "sets"]
-    elif st["sampler"] == "wilson_lds":
+    elif st["kernels"] == "wilson_lds":
         names = ["first_arrows", "count_and_level0", "peel_wide", "peel_tail",
                  "sweep_and_split", "cycle_scan", "cycles", "output"]
-    elif st["sampler"] == "wilson_tile":
+    elif st["kernels"] == "wilson_tile":
         names = ["first_arrows", "redraws", "jumps", "cycles", "exits_and_output", "exit_graph",
                  "residual", "totals"]
     else:
@@ -309,14 +308,14 @@ def _phases(st, hub=False):
     return dict(zip(names, st["phase_ms"]))
 
 
-def _kernels_ms(st, hub=False):
+def _kernels_ms(st):
     """The sampling call's kernels and their HIP-event times (the pre-draw kernel,
     when one ran, is inside ms_sample)."""
     ms = st["ms_sample"]
     pre = st.get("ms_predraw", 0.0)
-    name = "wilson_hub_kernel" if hub else f"{st['sampler']}_kernel"
+    name = f"{st['kernels']}_kernel"
     if pre > 0.0:
-        pre_name = "hub_predraw_kernel" if hub else "lds_predraw_kernel"
+        pre_name = "hub_predraw_kernel" if st["kernels"] == "wilson_hub" else "lds_predraw_kernel"
         return {pre_name: pre, name: ms - pre}
     return {name: ms}
 
@@ -325,7 +324,7 @@ def _kernels_ms(st, hub=False):
 # workloads
 # --------------------------------------------------------------------------
 def leg_sampling(fc, dev, g, dg, trees, alpha, steps, warmup, sampler="auto", weighted=False,
-                 stem=None, label="step", phase=False, seed=0, hub=False):
+                 stem=None, label="step", phase=False, seed=0):
     """`steps` timed calls of farness (sample + estimate) on a resident graph."""
     stats = []
 
@@ -340,7 +339,7 @@ def leg_sampling(fc, dev, g, dg, trees, alpha, steps, warmup, sampler="auto", we
     kms = sum(s["ms_sample"] for s in timed) / len(timed)
     kernels = {}
     for s in timed:
-        for k, v in _kernels_ms(s, hub).items():
+        for k, v in _kernels_ms(s).items():
             kernels[k] = kernels.get(k, 0.0) + v / len(timed)
     alg = wilson_bytes(st["walk_steps"], g.n * trees, st["roots"], weighted)
     traffic = traffic_of(stem, label) if stem else None
@@ -351,7 +350,7 @@ def leg_sampling(fc, dev, g, dg, trees, alpha, steps, warmup, sampler="auto", we
            "roofline": roofline_hbm(alg, kms, traffic, kernels_ms=kernels,
                                     kernel=" + ".join(kernels))}
     if phase:
-        res["phase_ms_per_workgroup"] = _phases(st, hub)
+        res["phase_ms_per_workgroup"] = _phases(st)
     return res
 
 
@@ -369,18 +368,6 @@ def leg_grid(fc, inputs, dev, steps, warmup, sampler="auto", phase=False) -> dic
     return {"value": 3 * 1024 / total, "unit": "trees/s",
             "config": {"workload": "grid_1000x1000_rm0.12_alpha0.5_1_2_trees1024", "n": g.n,
                        "m": g.m}, "per_alpha": per}
-
-
-def _batch_groups(gs) -> int:
-    """Sampling launches of a run over R-MAT graphs: one hubs first, and the small
-    graphs' by how many trees of theirs fit a CU's 160 KiB of LDS."""
-    parts = set()
-    for g in gs:
-        half = (g.n + 2) & ~1
-        lds = 12 * ((g.n + 31) // 32) + 2 * (2 * half + g.n) + 1024
-        per_cu = (160 << 10) // lds
-        parts.add("hubs" if per_cu == 0 else "few" if per_cu <= 3 else "some" if per_cu <= 8 else "many")
-    return len(parts)
 
 
 def leg_batch(fc, inputs, dev, steps, warmup, side=True) -> dict:
@@ -430,7 +417,7 @@ def leg_batch(fc, inputs, dev, steps, warmup, side=True) -> dict:
                                                        "(launch groups)")},
            "generation_s": gen_s,
            # the launch groups of the last run are the batch's last dispatches
-           "profile_last_dispatches": _batch_groups(gs)}
+           "profile_last_dispatches": len(st["kernels"].split("+"))}
     b.close()
     if side:
         def per_job():
@@ -455,8 +442,7 @@ def leg_rmat22(fc, inputs, dev, steps, warmup, samplers=("auto",), eps=True, pha
     per = {}
     for smp in samplers:
         per[smp] = leg_sampling(fc, dev, g, dg, 1024, 1.0, steps, warmup, smp,
-                                stem="wilson_hub_rmat22" if smp == "auto" else None, phase=phase,
-                                hub=smp == "auto")
+                                stem="wilson_hub_rmat22" if smp == "auto" else None, phase=phase)
     best = max(per, key=lambda k: per[k]["trees_per_s"])
     res = {"value": per[best]["trees_per_s"], "unit": "trees/s",
            "config": {"workload": "rmat_n4194304_ef8_alpha1_trees1024", "n": g.n, "m": g.m,
@@ -1006,7 +992,7 @@ def main():
         for k, v in _kernels_ms(s).items():
             kernels[k] = kernels.get(k, 0.0) + v / len(stats)
     alg_bytes = wilson_bytes(walk_steps, g.n * trees, st["roots"])
-    stem = "wilson_lds_ba200k" if st["sampler"] == "wilson_lds" else None
+    stem = "wilson_lds_ba200k" if st["kernels"] == "wilson_lds" else None
     traffic = traffic_of(stem) if stem else None
 
     eps_leg = None

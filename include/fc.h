@@ -167,9 +167,11 @@ typedef struct {
                                 counters in LDS), "wilson_hyb" (hybrid), or for a batch
                                 "batch:<threads>x<wg per CU>", of several launch
                                 groups "batch:<threads of the first>+<of the second>"
-                                ("lbatch:..." unless the first has global counters) */
+                                ("lbatch:..." unless the first has global counters);
+                                fc_sampler_kernels() tells the variants apart */
     double phase_ms[8];      /* workgroup sampler with option "phase_timing": average
-                                milliseconds per workgroup spent in
+                                milliseconds per workgroup spent in (by the kernel,
+                                fc_sampler_kernels())
                                 wilson_coop: first arrows, in-arrow counting, peel
                                   level 0, peel levels, reverse sweep, redraw, output;
                                 wilson_lds: first arrows, in-arrow counting with peel
@@ -179,7 +181,7 @@ typedef struct {
                                   cycle popping, output;
                                 wilson_tile: first arrows, redraws, jumps, cycles, the
                                   tiles' exits and outputs, exit graph, residual, totals;
-                                hubs first: first arrows (when not drawn ahead), then
+                                wilson_hub: first arrows (when not drawn ahead), then
                                   of the hubs claims, redraws, jumps and cycles, the
                                   stream over all vertices, the list of those left, its
                                   sets;
@@ -484,6 +486,13 @@ FC_API int fc_group_closeness(fc_ctx *ctx, const fc_graph *g, double alpha, int3
  * atomics are bounded by these rates. */
 FC_API int fc_probe_random_access(fc_ctx *ctx, uint64_t footprint_bytes, int32_t atomics,
                                   double *rate_out);
+
+/* The kernels that sampled the trees of the context's last call or batch run:
+ * "wilson_lane", "wilson_coop", "wilson_lds", "wilson_hyb", "wilson_tile",
+ * "wilson_hub" (hubs first), "wilson_jump" (trees whole in LDS), of a batch one
+ * for each launch group, joined by "+"; "" when it sampled none or failed.  Valid
+ * until the next call on the context. */
+FC_API const char *fc_sampler_kernels(fc_ctx *ctx);
 
 /* Message for an error code / for the last failing call on a context. */
 FC_API const char *fc_error_string(int code);

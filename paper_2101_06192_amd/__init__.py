@@ -129,6 +129,7 @@ def lib() -> ctypes.CDLL:
                                                   ctypes.POINTER(f64)]),
             "fc_error_string": (ctypes.c_char_p, [ctypes.c_int]),
             "fc_last_error": (ctypes.c_char_p, [vp]),
+            "fc_sampler_kernels": (ctypes.c_char_p, [vp]),
         }
         for name, (res, args) in sig.items():
             f = getattr(L, name)
@@ -172,6 +173,10 @@ class Context:
     def check(self, rc: int):
         if rc != FC_OK:
             raise FCError(rc, lib().fc_last_error(self.handle).decode() or error_string(rc))
+
+    def stats(self, st: fc_stats) -> dict:
+        """The statistics of the call just made, and the kernels that sampled."""
+        return {**st.as_dict(), "kernels": lib().fc_sampler_kernels(self.handle).decode()}
 
     def sync_stream(self):
         import torch
@@ -324,7 +329,7 @@ def _sample(entry, g, alpha, seed, tree_begin, tree_count, stream_id, device, wa
     ctx.check(getattr(lib(), entry)(ctx.handle, ctypes.byref(gs), ctypes.byref(ps),
                                     int(tree_begin), int(tree_count), _ptr(R), _ptr(V), _ptr(D),
                                     _ptr(S), _ptr(P), _ptr(TV), ctypes.byref(st)))
-    res = {"stats": st.as_dict()}
+    res = {"stats": ctx.stats(st)}
     res["root_counts"] = _out(R[:n], as_torch)
     if not as_torch:
         res["root_counts"] = res["root_counts"].view(np.uint32)
@@ -375,7 +380,7 @@ def _estimate(entry: str, g, alpha, eps, delta, seed, kappa, tau_, literal, devi
     out["diag"] = _out(diag[:n], as_torch)
     rc = _out(R[:n], as_torch)
     out["root_counts"] = rc if as_torch else rc.view(np.uint32)
-    out["stats"] = st.as_dict()
+    out["stats"] = ctx.stats(st)
     out["tau"] = int(st.tau)
     return out
 
@@ -435,7 +440,7 @@ class Batch:
         self.ctx.sync_stream()
         st = fc_stats()
         self.ctx.check(lib().fc_batch_run(self.handle, ctypes.byref(st)))
-        return st.as_dict()
+        return self.ctx.stats(st)
 
     def reset(self):
         for r in self.root_counts:

@@ -428,6 +428,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
     int rc;
     Small *sm = static_cast<Small *>(ctx->small.ptr);
     const fc::GraphCheck *check = g.pending ? &sm->check : nullptr;
+    ctx->kernels.clear();
     FC_HIP(ctx, hipMemsetAsync(sm, 0, small_bytes(ctx), ctx->stream), "memset counters");
     auto clear_stats = [&]() {
         stats->tau = tree_count;
@@ -1088,6 +1089,7 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
                            ? "a per-vertex draw count exceeded 2^28 - 1 (the LDS-counter "
                                    "sampler's limit; option coop_lds_counts = 0 allows 2^31 - 1)"
                                  : "a per-vertex visit counter exceeded 2^31 - 1");
+    ctx->kernels = jump_lds ? "wilson_jump" : use_hub ? "wilson_hub" : kname;
     if (stats) {
         float ms = 0.f;
         (void)hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1);
@@ -1563,6 +1565,7 @@ int fc_sample_noalloc(fc_ctx *ctx, const fc_graph *g, const fc_params *params,
         ctx->last_error = "fc_sample_noalloc: " + sh.last_error;
         return rc;
     }
+    ctx->kernels = sh.kernels;
     if (stats) stats->ms_total = now_ms() - t0;
     return FC_OK;
 }
@@ -1667,6 +1670,8 @@ const char *fc_error_string(int code) {
         default: return "unknown error code";
     }
 }
+
+const char *fc_sampler_kernels(fc_ctx *ctx) { return ctx ? ctx->kernels.c_str() : ""; }
 
 const char *fc_last_error(fc_ctx *ctx) {
     if (!ctx) return "no context";

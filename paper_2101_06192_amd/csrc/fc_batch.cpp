@@ -878,6 +878,7 @@ int fc_batch_run(fc_batch *b, fc_stats *stats) {
             std::snprintf(stats->sampler, sizeof(stats->sampler), "%s:%ux%u",
                           g.use_lds || g.jump || g.hub ? "lbatch" : "batch", g.threads, g.wg_per_cu);
     }
+    ctx->kernels.clear();
     if (b->item_count == 0) return FC_OK;
     // order after the caller's earlier work on the context stream, and make the
     // context stream wait for the batch
@@ -908,6 +909,11 @@ int fc_batch_run(fc_batch *b, fc_stats *stats) {
                            b->grp[gi].use_lds || b->grp[gi].jump
                                ? "a per-vertex draw count exceeded 2^28 - 1 (LDS counters)"
                                : "a per-vertex visit counter exceeded 2^31 - 1");
+    for (int gi = 0; gi < b->ngroups; ++gi) {
+        const Group &g = b->grp[gi];
+        ctx->kernels += gi ? "+" : "";
+        ctx->kernels += g.hub ? "wilson_hub" : g.jump ? "wilson_jump" : g.use_lds ? "wilson_lds" : "wilson_coop";
+    }
     if (stats) {
         float ms = 0.f;
         (void)hipEventElapsedTime(&ms, b->ev0, b->ev1);

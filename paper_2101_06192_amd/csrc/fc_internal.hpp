@@ -35,6 +35,7 @@ struct fc_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     std::string last_error;
+    std::string kernels;  // the sampling kernels of the last call
     DevBuf state, vrec, row_ptr, col_idx, small, rtmp, thr, cword, ckk, clists, clevels, cbits;
     DevBuf s_r64, s_r, s_p, s_q, s_d, s_pa, s_pb, s_small, s_wdeg;  // solver workspace
     DevBuf s_minv, s_segbase, s_seg, s_segsum;  // solver: preconditioner, long rows' segments
