@@ -213,7 +213,7 @@ FC_API int fc_set_stream(fc_ctx *ctx, void *hip_stream);
  *                     in LDS (64..1024, multiple of 64; 0, the default: 1024 when LDS
  *                     holds at most two trees per CU, else narrower (down to 256) as the
  *                     trees per CU grow)
- *   "lds_wg_per_cu"   cap on its resident workgroups per CU (0, the default: as many as fit)
+ *   "lds_wg_per_cu"   cap on their resident workgroups per CU (0, the default: as many as fit)
  *   "lanes_per_wave"  active lanes per wave of the lane sampler (1..64)
  *   "max_slots"       cap on trees in flight (0 = memory bound only)
  *   "scratch_limit"   most bytes of device memory that the context's scratch and its batches

@@ -513,11 +513,11 @@ int run_sampler(fc_ctx *ctx, const GraphView &g, const fc_params *p, uint32_t tr
         kname = "wilson_lds";
         const uint32_t n = static_cast<uint32_t>(g.n);
         lds_threads = jump_threads_for(ctx, n, tree_count);
-        const int fit = fc::jump_max_active(lds_threads, jump_lds, weighted);
+        size_t per_cu = static_cast<size_t>(std::max(1, fc::jump_max_active(lds_threads, jump_lds, weighted)));
+        if (ctx->lds_wg_per_cu) per_cu = std::min<size_t>(per_cu, ctx->lds_wg_per_cu);
         slots = std::max<size_t>(1, state_budget_now(ctx) / (4u * static_cast<size_t>(n)));
         slots = std::min<size_t>(slots, tree_count);
-        slots = std::min<size_t>(slots, static_cast<size_t>(ctx->cu_count) *
-                                            static_cast<size_t>(std::max(1, fit)));
+        slots = std::min<size_t>(slots, static_cast<size_t>(ctx->cu_count) * per_cu);
         if (ctx->max_slots) slots = std::min<size_t>(slots, ctx->max_slots);
         if ((rc = ensure(ctx, ctx->cword, 4u * static_cast<size_t>(n) * slots, "draw counts"))) return rc;
         c.word = ctx->cword.ptr;

@@ -788,7 +788,7 @@ int build(fc_ctx *ctx, const fc_job *jobs, int32_t n_jobs, uint64_t seed, int32_
             g.wg_per_cu = 1u;
         } else if (g.jump) {
             g.threads = jump_threads_for(ctx, g.n_max, g.item_count);
-            g.wg_per_cu = 64u;
+            g.wg_per_cu = ctx->lds_wg_per_cu ? ctx->lds_wg_per_cu : 64u;
         } else if (g.use_lds) {
             g.threads = lds_threads_for(ctx, g.item_count, g.lds_words);
             g.wg_per_cu = ctx->lds_wg_per_cu ? ctx->lds_wg_per_cu : 64u;
