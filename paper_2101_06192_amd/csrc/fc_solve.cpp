@@ -36,8 +36,7 @@ extern "C" int fc_solve(fc_ctx *ctx, const fc_graph *g, double alpha, const doub
     const size_t nk = static_cast<size_t>(n) * k;
     const size_t tb = fp32 ? 4 : 8;
     const uint32_t max_blocks = std::max<uint32_t>(64, ctx->cu_count * 8);
-    const uint32_t kp = fc::cg_padded(k, fp32);
-    const size_t nkp = static_cast<size_t>(n) * kp;
+    uint32_t kp = fc::cg_padded(k, fp32);
     // no more segments than this: every long row adds at most one that is not full
     const size_t seg_bound = static_cast<size_t>(gv.nnz) / fc::kCgSegment +
                              static_cast<size_t>(gv.nnz) / fc::kCgLongRow + 1;
@@ -46,16 +45,28 @@ extern "C" int fc_solve(fc_ctx *ctx, const fc_graph *g, double alpha, const doub
         DevBuf &r64, &r, &p, &q, &d, &pa, &pb, &small;
     } sb{ctx->s_r64, ctx->s_r, ctx->s_p, ctx->s_q, ctx->s_d, ctx->s_pa, ctx->s_pb, ctx->s_small};
     auto fail = [&](int code) { return code; };
-    if ((rc = ensure(ctx, sb.r64, 8 * nk, "residual")) || (rc = ensure(ctx, sb.r, tb * nkp, "r")) ||
-        (rc = ensure(ctx, sb.p, tb * nkp, "p")) || (rc = ensure(ctx, sb.q, tb * nkp, "q")) ||
-        (rc = ensure(ctx, sb.d, tb * nkp, "d")) ||
-        (rc = ensure(ctx, ctx->s_minv, tb * static_cast<size_t>(n), "preconditioner")) ||
-        (rc = ensure(ctx, ctx->s_segbase, 4 * static_cast<size_t>(n), "long rows")) ||
-        (rc = ensure(ctx, ctx->s_seg, 8 * seg_bound, "row segments")) ||
-        (rc = ensure(ctx, sb.pa, 8 * 64 * static_cast<size_t>(max_blocks), "partials")) ||
-        (rc = ensure(ctx, sb.pb, 8 * 64 * static_cast<size_t>(max_blocks), "partials")) ||
-        (rc = ensure(ctx, sb.small, 8 * (576 + 64 + 64 + 64) + 64, "solver scalars")))
-        return fail(rc);
+    auto allocate = [&]() {
+        const size_t nkp = static_cast<size_t>(n) * kp;
+        if ((rc = ensure(ctx, sb.r64, 8 * nk, "residual")) || (rc = ensure(ctx, sb.r, tb * nkp, "r")) ||
+            (rc = ensure(ctx, sb.p, tb * nkp, "p")) || (rc = ensure(ctx, sb.q, tb * nkp, "q")) ||
+            (rc = ensure(ctx, sb.d, tb * nkp, "d")) ||
+            (rc = ensure(ctx, ctx->s_minv, tb * static_cast<size_t>(n), "preconditioner")) ||
+            (rc = ensure(ctx, ctx->s_segbase, 4 * static_cast<size_t>(n), "long rows")) ||
+            (rc = ensure(ctx, ctx->s_seg, 8 * seg_bound, "row segments")) ||
+            (rc = ensure(ctx, sb.pa, 8 * 64 * static_cast<size_t>(max_blocks), "partials")) ||
+            (rc = ensure(ctx, sb.pb, 8 * 64 * static_cast<size_t>(max_blocks), "partials")) ||
+            (rc = ensure(ctx, sb.small, 8 * (576 + 64 + 64 + 64) + 64, "solver scalars")))
+            return rc;
+        return FC_OK;
+    };
+    rc = allocate();
+    if (rc == FC_ERR_NOMEM && kp > k) {  // no room for the padding: single values a lane
+        for (DevBuf *b : {&sb.r, &sb.p, &sb.q, &sb.d}) release(*ctx->held, *b);
+        kp = k;
+        rc = allocate();
+        if (rc == FC_OK) ctx->last_error.clear();
+    }
+    if (rc) return fail(rc);
     double *small = static_cast<double *>(sb.small.ptr);
     fc::CgWork w{};
     w.row_ptr = gv.row_ptr;

@@ -3,6 +3,7 @@
 that are its own.  Trees and root counts are integers: they equal the oracle's."""
 import numpy as np
 import pytest
+import torch
 
 import inputs
 import oracle
@@ -134,3 +135,29 @@ def test_batches_need_no_more_than_without_hubs_first(fresh, tune):
     print(f"least {least}", flush=True)
     for percent in range(100, 200, 9):
         assert _runs(fresh, least * percent // 100 + (1 << 16), lambda: create(1)), (least, percent)
+
+
+@pytest.mark.parametrize("precision,size,k", [("fp32_refined", 4, 5), ("fp32_refined", 4, 3), ("fp64", 8, 3)])
+def test_solver_needs_no_more_than_six_vectors(fresh, precision, size, k):
+    """Columns are padded to whole 16-byte loads where there is room.  Without it the inner
+    vectors have k columns: the least limit is that of the residual, five vectors in the
+    inner precision and the partial sums, and the solution the same to the tolerance."""
+    g = inputs.grid_removed(300, 300, 0.12, 3)
+    dg = fresh.to_device(g)
+    B = np.random.default_rng(1).standard_normal((g.n, k))
+    got = {}
+
+    def call():
+        got["x"] = fresh.solve(dg, 1.0, B, rtol=1e-9, precision=precision)
+
+    assert _runs(fresh, 1 << 30, call)
+    full = got["x"]
+    least = _least(fresh, call, 1 << 30)
+    print(f"least {least}", flush=True)
+    partials = 2 * 8 * 64 * max(64, 8 * torch.cuda.get_device_properties(0).multi_processor_count)
+    assert least <= 8 * g.n * k + 5 * size * g.n * k + partials + (1 << 17)
+    assert _runs(fresh, least, call)
+    assert float(got["x"]["relres"].max()) <= 1e-9
+    # both solve a system whose smallest eigenvalue is 1: they are as close as their residuals
+    norm = np.linalg.norm(B, axis=0)
+    assert np.all(np.linalg.norm(got["x"]["X"] - full["X"], axis=0) <= 2e-9 * norm)
