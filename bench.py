@@ -85,14 +85,19 @@ PROFILE_SPECS = {
         "timeout": 420,
         "title": "256 R-MAT graphs (n log-uniform in [2^10, 2^17], edge factor 8) x alpha "
                  "{0.1, 1, 10} x 512 trees, one autotuned batch run (its launch groups)"},
+    "wilson_jump_er1000": {
+        "args": ["--config", "er1000", "--sampler", "auto"], "kernels": ["wilson_jump_kernel"],
+        "sources": ["wilson_jump.hip"], "labels": ["step"], "counters": True, "timeout": 180,
+        "title": "Erdos-Renyi n = 1000, p = 0.01, alpha = 1, 2000 trees, trees whole in LDS"},
     "wilson_lane_er1000": {
         "args": ["--config", "er1000", "--sampler", "lane"], "kernels": ["wilson_lane_kernel"],
         "sources": ["wilson_lane.hip"], "labels": ["step"], "counters": False, "timeout": 180,
         "title": "Erdos-Renyi n = 1000, p = 0.01, alpha = 1, 2000 trees, lane-per-tree sampler"},
     "cg_ba2m_rhs64": {
         "args": ["--config", "solve"],
-        "kernels": ["apply_kernel", "residual_kernel", "update_kernel", "direction_kernel",
-                    "correct_kernel", "reduce_kernel", "scalars_kernel", "start_kernel"],
+        "kernels": ["apply_kernel", "segment_sum_kernel", "residual_kernel", "update_kernel",
+                    "direction_kernel", "correct_kernel", "column_sum_kernel", "scalars_kernel",
+                    "start_kernel", "segments_kernel", "minv_kernel", "nonzero_kernel"],
         "sources": ["cg.hip", "fc_solve.cpp"], "labels": None, "counters": True, "timeout": 300,
         "title": "(alpha L + I) X = B on BA(2000000, 8), 64 right-hand sides, rtol 1e-9, "
                  "binary64 then binary32 with binary64 refinement"},
@@ -457,8 +462,7 @@ def leg_rmat22(fc, inputs, dev, steps, warmup, samplers=("auto",), eps=True, pha
     return res
 
 
-def leg_er1000(fc, inputs, dev, steps, warmup, samplers=("lane", "coop", "lds"),
-               phase=False) -> dict:
+def leg_er1000(fc, inputs, dev, steps, warmup, samplers=("auto",), phase=False) -> dict:
     g = inputs.erdos_renyi(1000, 0.01, 0)
     dg = fc.to_device(g, dev)
     per = {smp: leg_sampling(fc, dev, g, dg, 2000, 1.0, steps, warmup, smp, phase=phase)
@@ -1086,7 +1090,7 @@ def other_config(args, fc, inputs, dev) -> dict:
     """The non-headline workloads, alone."""
     c, st, wu = args.config, args.steps, args.warmup
     if c == "er1000":
-        smp = ("lane", "coop", "lds") if args.sampler == "auto" else (args.sampler,)
+        smp = (args.sampler,)
         return leg_er1000(fc, inputs, dev, st, wu, smp, phase=args.phase_timing)
     if c == "rmat22":
         smp = (args.sampler,)

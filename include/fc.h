@@ -251,7 +251,8 @@ FC_API int fc_set_stream(fc_ctx *ctx, void *hip_stream);
  *                     trees are the same either way)
  *   "hub"             hubs-first sampler in the automatic choice: 0 never, 1 (the default)
  *                     where a tree does not fit LDS whole and the graph has hubs or small
- *                     alpha, 2 on every graph (to compare, and to test it on small ones).
+ *                     alpha, 2 on every graph but those that the tile sampler takes (to
+ *                     compare, and to test it on small ones).
  *                     Where its buffers do not fit the device, the call or the batch goes
  *                     on with the samplers that it replaces
  *   "hub_set"         its vertices in LDS at a time, a multiple of 64 up to 32704 (0, the

@@ -62,7 +62,7 @@ struct fc_ctx {
     size_t max_lds = 65536;       // dynamic LDS a workgroup may use
     uint32_t coop_threads = 512;  // threads per workgroup in the workgroup sampler
     uint32_t coop_wg_per_cu = 3;  // resident workgroups per CU in the workgroup sampler
-    uint32_t force_sampler = 0;   // 0 auto, 1 lane, 2 coop, 3 lds, 4 hyb (environment override)
+    uint32_t force_sampler = 0;   // 0 auto, 1 lane, 2 coop, 3 lds, 4 hyb, 5 tile (environment override)
     bool coop_lds_bits = true;    // settled bitmap in LDS when it fits
     bool coop_word32 = true;      // 32-bit tree words when target and count fit
     bool coop_in_bits = true;     // in-arrow bitmap in LDS when both bitmaps fit
@@ -79,8 +79,8 @@ struct fc_ctx {
     uint32_t coop_repop = 2;      // the same for the global-counter sampler
     uint32_t lds_lean = 0;        // LDS-counter sampler: the lean register shape for workgroups
                                   // of at most 512 threads (batch autotuning times both)
-    uint32_t hub = 1;             // hubs-first sampler: 0 never, 1 where a tree does not fit LDS
-                                  // whole, 2 also where it does
+    uint32_t hub = 1;             // hubs-first sampler: 0 never, 1 by hub_applies where a tree does
+                                  // not fit LDS whole, 2 wherever the tile sampler does not go ahead
     uint32_t hub_set = 0;         // its LDS set's vertices (0: the most that fit)
     uint32_t hub_hot = 130;       // of these, per mille, hubs at the start; the rest join later
     uint32_t hub_threads = 1024;  // its threads per workgroup

