@@ -138,9 +138,12 @@ extern "C" int fc_solve(fc_ctx *ctx, const fc_graph *g, double alpha, const doub
             scale[j] = done ? 0.0 : std::sqrt(rr[j]);
             // inner target: binary32 gains about five digits per sweep (its
             // recurrence stays trustworthy down to ~1e-6 on a unit residual);
-            // binary64 aims straight at the outer tolerance (with a safety factor)
+            // binary64 aims straight at the outer tolerance (with a safety factor), but
+            // not at what no residual reaches (that of a zero right-hand side): below
+            // the floor the recurrence changes nothing any more, and where its scalars
+            // underflow it divides by what is left of them
             const double target = fp32 ? 1e-5
-                                       : std::max(1e-300, 0.5 * rtol * std::sqrt(bb[j]) / std::sqrt(rr[j]));
+                                       : std::max(1e-100, 0.5 * rtol * std::sqrt(bb[j]) / std::sqrt(rr[j]));
             tol2[j] = done ? 0.0 : target * target;
         }
         if (converged || total >= static_cast<uint32_t>(max_iters)) break;
