@@ -1263,6 +1263,8 @@ int fc_create(fc_ctx **out, int hip_device, void *hip_stream) {
         hipEventCreate(&ctx->evm) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void **>(&ctx->host_small), sizeof(Small),
                       hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void **>(&ctx->host_bytes), 2 * sizeof(unsigned int),
+                      hipHostMallocCoherent) != hipSuccess ||
         ensure(ctx, ctx->small, sizeof(Small), "counters") != FC_OK) {
         fc_destroy(ctx);
         return FC_ERR_HIP;
@@ -1339,6 +1341,7 @@ int fc_destroy(fc_ctx *ctx) {
     if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
     if (ctx->evm) (void)hipEventDestroy(ctx->evm);
     if (ctx->host_small) (void)hipHostFree(ctx->host_small);
+    if (ctx->host_bytes) (void)hipHostFree(ctx->host_bytes);
     delete ctx;
     return FC_OK;
 }

@@ -52,6 +52,8 @@ struct fc_ctx {
     DevBuf t_ex, t_tl, t_exl, t_ecnt, t_pc, t_sc, t_bl, t_xb;  // tile sampler (exits, counts, lists)
     hipEvent_t ev0 = nullptr, ev1 = nullptr, evm = nullptr;
     Small *host_small = nullptr;  // pinned: where a call's counters are read back
+    unsigned int *host_bytes = nullptr;  // pinned, coherent: the bytes that two sorts have to look at
+    unsigned int sorts = 0;              // the last one's number
     size_t state_budget = 0;      // bytes of per-tree state the sampler may use
     size_t scratch_limit = 0;     // most bytes of device memory to hold (0: what the device has)
     // what this context's buffers and its batches' take now (a batch may outlive its context)

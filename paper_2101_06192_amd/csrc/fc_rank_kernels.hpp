@@ -28,10 +28,12 @@ hipError_t launch_rank_keys(const double *score, uint32_t n, bool descending, co
                             SortInfo *info, hipStream_t stream);
 // Tiles of the radix sort (thist holds 256 * rank_tiles(n) counters).
 uint32_t rank_tiles(uint32_t n);
-// Stable sort by the low `bytes` bytes of the keys (those that vary); totals:
-// bytes x 256 zeroed counters.
-hipError_t launch_sort(const SortBufs &b, uint32_t n, uint32_t bytes, const SortInfo *info,
-                       unsigned int *thist, unsigned int *totals, hipStream_t stream);
+// Stable sort by byte p of the keys, after the bytes below (nothing where the keys do not
+// differ in it); total: 256 zeroed counters; tell (or null): a word of coherent host
+// memory that gets a bit for every byte in which the keys differ, and number << 8.
+hipError_t launch_sort_pass(const SortBufs &b, uint32_t n, uint32_t p, const SortInfo *info,
+                            unsigned int *thist, unsigned int *total, unsigned int *tell,
+                            unsigned int number, hipStream_t stream);
 // The sorted values into order and their inverse into rank (either may be
 // null); nothing when info->bad.
 hipError_t launch_order(const SortBufs &b, uint32_t n, const SortInfo *info, int32_t *order,

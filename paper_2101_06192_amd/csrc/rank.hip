@@ -7,10 +7,11 @@
 // the vertices by the estimate and reports Kendall's rank correlation against
 // the ground truth (Section 6, "Vertex Ranking").
 //
-// Everything of one call is enqueued without a look at the device: which bytes
+// Everything of one call is enqueued without waiting for the device: which bytes
 // of the keys differ at all (the others need no pass), whether a score was NaN
 // and whether a vector has ties is left in a small record that the later
-// kernels read, returning at once where there is nothing to do.
+// kernels read, returning at once where there is nothing to do.  (The host reads
+// the bytes when they are there, and enqueues no more passes of the others.)
 //
 // At these sizes (n = 1000 .. a few million) a pass is launches and dependent
 // loads, not bytes: n = 200 000, per byte pass 40 us (histogram 6, one
@@ -89,8 +90,14 @@ __global__ __launch_bounds__(kRankThreads) void tile_hist_kernel(SortBufs b, uin
                                                                  uint32_t ntiles,
                                                                  const SortInfo *info,
                                                                  unsigned int *__restrict__ thist,
-                                                                 unsigned int *total) {
+                                                                 unsigned int *total, unsigned int *tell,
+                                                                 unsigned int number) {
     const unsigned long long vary = info->vary;
+    if (tell && blockIdx.x == 0 && threadIdx.x == 0) {
+        unsigned int bytes = number << 8;
+        for (uint32_t q = 0; q < 8u; ++q) bytes |= byte_active(vary, q) ? 1u << q : 0u;
+        __hip_atomic_store(tell, bytes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     if (!byte_active(vary, p)) return;
     const uint64_t *key = b.key[passes_below(vary, p) & 1u];
     __shared__ unsigned int h[256];
@@ -540,27 +547,23 @@ hipError_t launch_rank_keys(const double *score, uint32_t n, bool descending, co
     return hipGetLastError();
 }
 
-hipError_t launch_sort(const SortBufs &b, uint32_t n, uint32_t bytes, const SortInfo *info,
-                       unsigned int *thist, unsigned int *totals, hipStream_t stream) {
+hipError_t launch_sort_pass(const SortBufs &b, uint32_t n, uint32_t p, const SortInfo *info,
+                            unsigned int *thist, unsigned int *total, unsigned int *tell,
+                            unsigned int number, hipStream_t stream) {
     if (n < 2) return hipSuccess;
     const uint32_t ntiles = rank_tiles(n);
     const bool shorts = tile_rounds(n) == kShortTile;
-    for (uint32_t p = 0; p < bytes; ++p) {
-        unsigned int *total = totals + 256u * p;
-        if (shorts)
-            tile_hist_kernel<kShortTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles, info,
-                                                                             thist, total);
-        else
-            tile_hist_kernel<kLongTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles, info,
-                                                                            thist, total);
-        tile_scan_kernel<<<256, 64, 0, stream>>>(thist, ntiles, p, info, total);
-        if (shorts)
-            tile_scatter_kernel<kShortTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles,
-                                                                                info, thist);
-        else
-            tile_scatter_kernel<kLongTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles,
-                                                                               info, thist);
-    }
+    if (shorts)
+        tile_hist_kernel<kShortTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles, info, thist,
+                                                                          total, tell, number);
+    else
+        tile_hist_kernel<kLongTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles, info, thist,
+                                                                         total, tell, number);
+    tile_scan_kernel<<<256, 64, 0, stream>>>(thist, ntiles, p, info, total);
+    if (shorts)
+        tile_scatter_kernel<kShortTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles, info, thist);
+    else
+        tile_scatter_kernel<kLongTile><<<ntiles, kRankThreads, 0, stream>>>(b, n, p, ntiles, info, thist);
     return hipGetLastError();
 }
 
@@ -587,8 +590,11 @@ hipError_t launch_discordant(const SortBufs &b, uint32_t n, const SortInfo *info
                                                                               out + 1, pair, s);
     uint32_t bytes = 1;
     while (bytes < 4u && (static_cast<uint64_t>(n - 1u) >> (8u * bytes))) ++bytes;
-    hipError_t e = launch_sort(b, n, bytes, pair, thist, totals, stream);
-    if (e != hipSuccess) return e;
+    for (uint32_t p = 0; p < bytes; ++p) {
+        const hipError_t e = launch_sort_pass(b, n, p, pair, thist, totals + 256u * p, nullptr, 0u,
+                                              stream);
+        if (e != hipSuccess) return e;
+    }
     pair_order_kernel<<<blocks_for(n, kRankThreads), kRankThreads, 0, stream>>>(b, n, pair, rb, s);
     joint_ties_kernel<<<wide_blocks(n), kWideThreads, 0, stream>>>(b, n, pair, s, out + 3);
     merge_tile_kernel<<<wide_blocks(n), kWideThreads, 0, stream>>>(s, n, out);
