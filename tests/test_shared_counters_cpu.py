@@ -17,6 +17,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2101_06192_amd", "csrc")
 COUNTERS = ("s_item", "s_u", "s_c", "s_cnt", "s_set", "s_ext")
+BARRIERS = ("__syncthreads", "lds_barrier")
 
 
 def _source(name):
@@ -130,10 +131,10 @@ class _Walk:
         """One expression or simple statement, its parts in order."""
         if state is None or "__shared__" in text:
             return state
-        names = "|".join(map(re.escape, (*COUNTERS, *self.lambdas, "__syncthreads")))
+        names = "|".join(map(re.escape, (*COUNTERS, *self.lambdas, *BARRIERS)))
         for m in re.finditer(rf"(&?)\b({names})\b(\s*=(?!=))?", text):
             ref, name, assigned = m.groups()
-            if name == "__syncthreads":
+            if name in BARRIERS:
                 state = {}
             elif name in self.lambdas:
                 if text[m.end():m.end() + 1] == "(" and name not in self.calling:
@@ -211,6 +212,6 @@ def test_the_check_finds_what_it_is_for():
 
 
 @pytest.mark.parametrize("source", ["wilson_jump.hip", "wilson_tile.hip", "wilson_hub.hip",
-                                    "wilson_hyb.hip"])
+                                    "wilson_lds.hip", "wilson_hyb.hip"])
 def test_barriers_between_uses_of_a_counter(source):
     assert clashes(_source(source)) == []
